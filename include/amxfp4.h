@@ -139,7 +139,8 @@ int amxfp4_dequantize(const amx_format_t* fmt, const uint8_t* codes, const uint8
  *   other group sizes are multiplied as exact BF16 operands (element * scale has at most 6 significant bits). With
  *   M <= 256 (M <= 768 for batch == 1 and N * K >= 2^27), groups of 32 and K a multiple of 256, B is read as packed
  *   codes and dequantized in registers to exact 16-bit floats (the weights-bound case of a few tokens against a
- *   weight matrix); results do not depend on the kernel beyond the FP32 summation order.
+ *   weight matrix); with M <= 64 and groups of 32 or 16, any K, mostly both operands are, in one launch that leaves the
+ *   workspace alone; results do not depend on the kernel beyond the FP32 summation order.
  *   workspace          device scratch of at least amxfp4_gemm_workspace_bytes() bytes, 256-byte aligned;
  *                      contents are undefined afterwards. May be NULL when the required size is 0.
  */
@@ -226,7 +227,7 @@ int mxfp4_gemm(const amx_format_t* fmt, int64_t M, int64_t N, int64_t K, const u
  *   aligned base; the maximum does not depend on which axis is later grouped).
  * amxfp4_quantize_scaled / amxfp4_dequantize_scaled (FP32 output only: the product is rounded once) /
  *   amxfp4_gemm_scaled: as the calls without the suffix, plus the scale pair(s). The scaled GEMM always multiplies
- *   exact BF16 operands and needs a workspace of amxfp4_gemm_scaled_workspace_bytes().
+ *   exact 16-bit operands and needs a workspace of amxfp4_gemm_scaled_workspace_bytes().
  */
 int amxfp4_tensor_scale(const void* x_bf16, int64_t rows, int64_t K, int64_t row_stride, float* scale_pair,
                         void* stream);

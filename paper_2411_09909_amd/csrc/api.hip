@@ -210,6 +210,14 @@ GemmPlan plan_gemm(const amx_format_t& f, const amx_gemm_options_t* o, bool scal
   return p;
 }
 
+// At most 64 rows and no kernel asked for by the options: the kernel that reads both operands as packed codes, in one
+// launch. It needs no workspace, but the call still asks for the one of the kernel that plan_gemm() names (what a caller
+// sized for these shapes keeps its meaning, and so does what is refused).
+bool uses_stream(const amx_format_t& f, const amx_gemm_options_t* o, int64_t M, int64_t N, int64_t K) {
+  if (o && (o->e5m2_kernel != 0 || o->pot_kernel != 0 || o->tile != 0 || o->few_rows != 0)) return false;
+  return amx::stream_path_preferred(f.group_size, M, N, K);
+}
+
 size_t plan_workspace_bytes(const GemmPlan& p, bool asym, int64_t M, int64_t N, int64_t K, int64_t batch) {
   switch (p.kernel) {
     case kGemmSkinny: return amx::skinny_path_workspace_bytes(M, N, K, batch, p.skinny_slices);
@@ -257,6 +265,11 @@ int gemm_impl(amx_format_t f, const amx_gemm_options_t* opts, int64_t M, int64_t
   hipStream_t hs = reinterpret_cast<hipStream_t>(stream);
   const bool asym = f.asymmetric != 0;
   hipError_t e;
+  if (uses_stream(f, opts, M, N, K)) {
+    e = amx::launch_gemm_stream(f.scale, asym, f.group_size, M, N, K, A_codes, A_scales, B_codes, B_scales, A_pair, B_pair,
+                                C, ldc, batch, hs, timer);
+    return e == hipSuccess ? AMX_OK : hip_fail(e, "gemm launch");
+  }
   switch (plan.kernel) {
     case kGemmSkinny:
       e = amx::launch_gemm_skinny_path(f.scale, asym, M, N, K, A_codes, A_scales, B_codes, B_scales, C, ldc, batch,

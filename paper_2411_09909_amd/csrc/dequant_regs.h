@@ -26,10 +26,11 @@ __device__ __forceinline__ uint32_t pk_sign_mask(uint32_t v) {
 // Eight FP4 codes (one word, first code in the lowest nibble) -> eight dequantized 16-bit floats, two per register.
 // The scale pair (s_pos, s_neg) comes as bit patterns whose meaning depends on the format (skinny_scales()).
 //
-// FP8-E5M2 scales, FP16 result biased by 2^-3: the pair holds each scale twice, as packed FP16.
+// FP8-E5M2 scales, FP16 result biased by 2^-3 (or by the given power of two): the pair holds each scale twice, as packed
+// FP16.
 template <bool ASYM, int SEL>
-__device__ __forceinline__ uint32_t dequant2_f16(uint32_t word, uint32_t s_pos, uint32_t s_neg) {
-  const f16x2 e = __builtin_amdgcn_cvt_scalef32_pk_f16_fp4(word, 0.125f, SEL);
+__device__ __forceinline__ uint32_t dequant2_f16(uint32_t word, uint32_t s_pos, uint32_t s_neg, float bias = 0.125f) {
+  const f16x2 e = __builtin_amdgcn_cvt_scalef32_pk_f16_fp4(word, bias, SEL);
   uint32_t sc = s_pos;
   if constexpr (ASYM) {
     const uint32_t m = pk_sign_mask(__builtin_bit_cast(uint32_t, e));

@@ -85,6 +85,14 @@ hipError_t launch_gemm_skinny_path(int scale_kind, bool asym, int64_t M, int64_t
                                    int64_t ldc, int64_t batch, void* workspace, int forced_slices, hipStream_t s,
                                    const KernelTimer& timer);
 
+// gemm_stream.hip: M <= 64, groups of 32 or 16, any K the format takes: one launch that reads both operands as packed
+// codes (no workspace; tensor pairs: both or neither)
+bool stream_path_preferred(int64_t group_size, int64_t M, int64_t N, int64_t K);
+hipError_t launch_gemm_stream(int scale_kind, bool asym, int64_t group_size, int64_t M, int64_t N, int64_t K,
+                              const uint8_t* A_codes, const uint8_t* A_scales, const uint8_t* B_codes,
+                              const uint8_t* B_scales, const float* A_tensor_pair, const float* B_tensor_pair, float* C,
+                              int64_t ldc, int64_t batch, hipStream_t s, const KernelTimer& timer);
+
 // attention.hip: fused quantized attention, head dimension 128 or 64, groups of 32 (workspace: the three BF16 panels).
 // merged_bf16: out is BF16 [Sq][Hq * head_dim] (token-major) instead of FP32 [Hq][Sq][head_dim]
 size_t attention_workspace_bytes(int64_t Hq, int64_t Hkv, int64_t Sq, int64_t Sk, int64_t head_dim);

@@ -1,0 +1,94 @@
+"""The GEMM for at most 64 rows that reads both operands as packed codes in one launch (gemm_stream.hip), against the
+oracle: every workgroup shape of its rule, partial row and column tiles, K tails, groups of 16, batches, tensor-wise
+scales, and nothing written outside the product."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import ref
+from paper_2411_09909_amd import binding, synth
+from tests import gpu_util as G
+
+pytestmark = pytest.mark.gpu
+
+FORMATS = [(ref.FP8_E5M2, 1, 32), (ref.FP8_E5M2, 0, 32), (ref.E8M0_FLOOR, 1, 32), (ref.E8M0_ROUND, 0, 32),
+           (ref.FP8_E4M3, 1, 32), (ref.FP8_E4M3, 0, 16), (ref.FP8_E4M3, 1, 16), (ref.FP8_E5M2, 1, 16),
+           (ref.E8M0_FLOOR, 0, 16)]
+
+# M: both sides of 16, 32 and 64 rows. N: one column, partial tiles, each tile count at which the rule changes shape (256
+# tiles of 16 / 32 columns and one more). K: one block, one block per wave and one more, tails of one to seven groups.
+SHAPES = [(1, 1, 32), (16, 17, 256), (5, 100, 2304), (13, 33, 2272), (16, 4097, 256), (3, 8193, 288), (2, 16400, 256),
+          (17, 31, 512), (32, 65, 2048), (20, 4097, 512), (32, 8193, 256), (25, 16385, 256), (31, 50, 4544),
+          (33, 64, 256), (64, 45, 2560), (40, 8193, 256), (64, 33, 96), (50, 70, 4448)]
+
+
+def bound(a, b, K):
+    """Largest error an FP32 sum of K exact products can have in any order: K roundings of partial sums, none above the
+    sum of the products' magnitudes (and one factor of two for the accumulation inside a matrix instruction)."""
+    return 2.0 * (K + 2) * 2.0 ** -24 * (np.abs(a) @ np.abs(b).T) + 1e-30
+
+
+@pytest.mark.parametrize("scale,asym,gs", FORMATS)
+@pytest.mark.parametrize("M,N,K", SHAPES)
+def test_against_the_oracle(M, N, K, scale, asym, gs):
+    a = synth.activations(M, K, seed=M + K, n_outlier=1, outlier_gain=60.0)
+    b = synth.weights(N, K, seed=N)
+    ac, as_ = ref.quantize(a, gs, scale, asym)
+    bc, bs = ref.quantize(b, gs, scale, asym)
+    fmt = binding.make_format(scale, asym, gs)
+    ops = [G.to_dev_u8(t) for t in (ac, as_, bc, bs)]
+    # a window of a larger buffer, pattern around it
+    pad = torch.full((M + 2, N + 5), -7.0, device="cuda")
+    out = pad[1:M + 1, :N]
+    binding.gemm(fmt, *ops, out=out)
+    torch.cuda.synchronize()
+    C = out.cpu().numpy().astype(np.float64)
+    ad, bd = (ref.dequantize(c, s, gs, scale, asym).astype(np.float64) for c, s in ((ac, as_), (bc, bs)))
+    assert (np.abs(C - ad @ bd.T) <= bound(ad, bd, K)).all()
+    full = pad.cpu().numpy()
+    assert (full[0] == -7).all() and (full[M + 1] == -7).all() and (full[:, N:] == -7).all()
+    # the tiled kernels on the same operands (options keep them)
+    other = binding.gemm(fmt, *ops, options=binding.gemm_options(few_rows=-1)).cpu().numpy().astype(np.float64)
+    assert (np.abs(other - ad @ bd.T) <= bound(ad, bd, K)).all()
+
+
+@pytest.mark.parametrize("scale,gs", [(ref.FP8_E5M2, 32), (ref.FP8_E4M3, 32), (ref.FP8_E4M3, 16), (ref.E8M0_FLOOR, 32)])
+@pytest.mark.parametrize("M", [7, 24, 48])
+def test_every_scale_byte(M, scale, gs):
+    """Operands made of random codes and of every scale byte of the format in turn (subnormal scales, zero, the largest),
+    the two signs of a group different ones; batch of two, K with a tail."""
+    rng = np.random.default_rng(M)
+    N, K, batch = 70, 544, 2
+    top = {ref.FP8_E5M2: 0x7C, ref.FP8_E4M3: 0x7F, ref.E8M0_FLOOR: 140}[scale]
+    low = 110 if scale == ref.E8M0_FLOOR else 0
+
+    def operand(rows, first):
+        codes = rng.integers(0, 256, (batch, rows, K // 2), dtype=np.uint8)
+        n = batch * rows * (K // gs) * 2
+        scales = (low + (first + 7 * np.arange(n)) % (top - low)).astype(np.uint8).reshape(batch, rows, K // gs, 2)
+        return codes, scales
+
+    (ac, as_), (bc, bs) = operand(M, 0), operand(N, 3)
+    C = G.gpu_gemm(ac, as_, bc, bs, scale, 1, group_size=gs).astype(np.float64)
+    for i in range(batch):
+        ad, bd = (ref.dequantize(c[i], s[i], gs, scale, 1).astype(np.float64) for c, s in ((ac, as_), (bc, bs)))
+        assert (np.abs(C[i] - ad @ bd.T) <= bound(ad, bd, K)).all()
+
+
+@pytest.mark.parametrize("M,N,K,asym", [(1, 300, 1024, 0), (24, 4100, 512, 1), (64, 130, 4512, 0)])
+def test_tensor_scaled(M, N, K, asym):
+    """Double scaling on the few-rows shapes: the product of the dequantized operands times the two tensor-wise scales."""
+    fmt = binding.make_format(ref.FP8_E4M3, asym, 16)
+    x = G.to_dev_bf16(synth.activations(M, K, seed=M, n_outlier=1, outlier_gain=60.0))
+    w = G.to_dev_bf16(synth.weights(N, K, seed=N))
+    xp, wp = binding.tensor_scale(x), binding.tensor_scale(w)
+    xc, xs = binding.quantize(fmt, x, tensor_pair=xp)
+    wc, ws = binding.quantize(fmt, w, tensor_pair=wp)
+    C = binding.gemm(fmt, xc, xs, wc, ws, a_pair=xp, b_pair=wp).double()
+    xd = binding.dequantize(fmt, xc, xs, torch.float32).double()
+    wd = binding.dequantize(fmt, wc, ws, torch.float32).double()
+    alpha = float(xp[0]) * float(wp[0])
+    err = (C - (xd @ wd.T) * alpha).abs()
+    # the sum's bound, and two more roundings: the product of the two scales and the product with it
+    limit = (2.0 * (K + 4) * 2.0 ** -24) * (xd.abs() @ wd.abs().T) * alpha
+    assert bool((err <= limit + 1e-30).all())
