@@ -139,8 +139,9 @@ int amxfp4_dequantize(const amx_format_t* fmt, const uint8_t* codes, const uint8
  *   other group sizes are multiplied as exact BF16 operands (element * scale has at most 6 significant bits). With
  *   M <= 256 (M <= 768 for batch == 1 and N * K >= 2^27), groups of 32 and K a multiple of 256, B is read as packed
  *   codes and dequantized in registers to exact 16-bit floats (the weights-bound case of a few tokens against a
- *   weight matrix); with M <= 64 and groups of 32 or 16, any K, mostly both operands are, in one launch that leaves the
- *   workspace alone; results do not depend on the kernel beyond the FP32 summation order.
+ *   weight matrix); with few rows (M <= 64) and for small problems (M <= 768), groups of 32 or 16 and any K, mostly both
+ *   operands are, in one launch that leaves the workspace alone; results do not depend on the kernel beyond the FP32
+ *   summation order.
  *   workspace          device scratch of at least amxfp4_gemm_workspace_bytes() bytes, 256-byte aligned;
  *                      contents are undefined afterwards. May be NULL when the required size is 0.
  */
@@ -160,8 +161,8 @@ int amxfp4_gemm(const amx_format_t* fmt, int64_t M, int64_t N, int64_t K, const 
  *   amxfp4_prepare_weights          writes it: `prepared` device out, 256-byte aligned, at least that many bytes
  *                                   (AMX_ERR_WORKSPACE otherwise). Depends on fmt, N, K and B only.
  *   amxfp4_gemm_prepared            C = A . B^T with B's prepared form. B_codes / B_scales are still passed: shapes
- *                                   with few rows (M <= 256, see amxfp4_gemm) read B as packed codes and ignore
- *                                   `prepared`. One problem per call (no batch). workspace: at least
+ *                                   with few rows and small problems (M <= 768, see amxfp4_gemm) read B as packed codes
+ *                                   and ignore `prepared`. One problem per call (no batch). workspace: at least
  *                                   amxfp4_gemm_prepared_workspace_bytes(), 256-byte aligned (A's expansion only).
  * `prepared` is opaque, valid for this library build, fmt, N and K; the caller owns it and keeps it unchanged while
  * calls that read it are in flight. Other arguments and status codes as amxfp4_gemm.

@@ -173,6 +173,7 @@ struct GemmPlan {
   GemmKernel kernel;
   int tile;           // BF16-panel kernel: AMX_TILE_*
   int skinny_slices;  // few-rows kernel: forced outer K slices, 0 = cost model
+  bool for_skinny;    // the FP4 kernel in the place of the few-rows kernel: a workspace good for either is asked for
 };
 
 int check_options(const amx_gemm_options_t* o) {
@@ -188,14 +189,28 @@ int check_options(const amx_gemm_options_t* o) {
   return AMX_OK;
 }
 
+// the options leave every choice to the library
+bool default_options(const amx_gemm_options_t* o) {
+  return !o || (o->e5m2_kernel == 0 && o->pot_kernel == 0 && o->tile == 0 && o->few_rows == 0);
+}
+
 // scaled: the tensor-wise double scaling (Sec. 5.3), which only the BF16-panel kernel's epilogue applies.
 GemmPlan plan_gemm(const amx_format_t& f, const amx_gemm_options_t* o, bool scaled, int64_t M, int64_t N, int64_t K,
                    int64_t batch) {
   static const amx_gemm_options_t kDefaults = {0, 0, 0, 0};
   const amx_gemm_options_t& opt = o ? *o : kDefaults;
-  GemmPlan p = {kGemmPanel, opt.tile, opt.few_rows > 0 ? opt.few_rows : 0};
+  GemmPlan p = {kGemmPanel, opt.tile, opt.few_rows > 0 ? opt.few_rows : 0, false};
   if (scaled) return p;
-  if (opt.few_rows >= 0 && uses_skinny(f, M, N, K, batch)) return p.kernel = kGemmSkinny, p;
+  // (symmetric power-of-two scales from some 80 rows on: the FP4 kernel, unless the options ask otherwise; its scratch, a
+  // byte for 32 elements, stays within what amxfp4_gemm_static has)
+  const bool fp4_first = default_options(o) && !f.asymmetric && batch == 1 && uses_fp4_mfma(f, M, N, K) &&
+                         amx::fp4_beats_stream(M, N, K) &&
+                         amx::fp4_path_workspace_bytes(false, M, N, K, 1) <= kStaticScratchBytes;
+  if (opt.few_rows >= 0 && uses_skinny(f, M, N, K, batch)) {
+    p.kernel = fp4_first ? kGemmFp4 : kGemmSkinny;
+    p.for_skinny = fp4_first;
+    return p;
+  }
   const bool pot32 = f.group_size == 32 && (f.scale == AMX_SCALE_E8M0_FLOOR || f.scale == AMX_SCALE_E8M0_ROUND);
   if (pot32 && f.asymmetric) {
     if (opt.pot_kernel == AMX_POT_SPLIT_FP4 && amx::fp4_path_supported(M, N, K)) return p.kernel = kGemmFp4, p;
@@ -210,12 +225,11 @@ GemmPlan plan_gemm(const amx_format_t& f, const amx_gemm_options_t* o, bool scal
   return p;
 }
 
-// At most 64 rows and no kernel asked for by the options: the kernel that reads both operands as packed codes, in one
-// launch. It needs no workspace, but the call still asks for the one of the kernel that plan_gemm() names (what a caller
-// sized for these shapes keeps its meaning, and so does what is refused).
-bool uses_stream(const amx_format_t& f, const amx_gemm_options_t* o, int64_t M, int64_t N, int64_t K) {
-  if (o && (o->e5m2_kernel != 0 || o->pot_kernel != 0 || o->tile != 0 || o->few_rows != 0)) return false;
-  return amx::stream_path_preferred(f.group_size, M, N, K);
+// No kernel asked for by the options, and few rows or a small problem: the kernel that reads both operands as packed codes,
+// in one launch. It needs no workspace, but the call still asks for the one of the kernel that plan_gemm() names (what a
+// caller sized for these shapes keeps its meaning, and so does what is refused).
+bool uses_stream(const amx_format_t& f, const amx_gemm_options_t* o, int64_t M, int64_t N, int64_t K, int64_t batch) {
+  return default_options(o) && amx::stream_path_preferred(f.scale, f.asymmetric != 0, f.group_size, M, N, K, batch);
 }
 
 size_t plan_workspace_bytes(const GemmPlan& p, bool asym, int64_t M, int64_t N, int64_t K, int64_t batch) {
@@ -223,7 +237,11 @@ size_t plan_workspace_bytes(const GemmPlan& p, bool asym, int64_t M, int64_t N, 
     case kGemmSkinny: return amx::skinny_path_workspace_bytes(M, N, K, batch, p.skinny_slices);
     case kGemmFp8Merged: return amx::fp8m_path_workspace_bytes(M, N, K, batch);
     case kGemmFp6Merged: return amx::fp6m_path_workspace_bytes(M, N, K, batch);
-    case kGemmFp4: return amx::fp4_path_workspace_bytes(asym, M, N, K, batch);
+    case kGemmFp4: {
+      const size_t own = amx::fp4_path_workspace_bytes(asym, M, N, K, batch);
+      const size_t few = p.for_skinny ? amx::skinny_path_workspace_bytes(M, N, K, batch, p.skinny_slices) : 0;
+      return own > few ? own : few;
+    }
     case kGemmE5m2Fused: return 0;
     case kGemmE5m2Hybrid: return amx::e5m2_hybrid_workspace_bytes(M, K, batch);
     default: return amx::bf16_path_workspace_bytes(M, N, K, batch);
@@ -265,7 +283,7 @@ int gemm_impl(amx_format_t f, const amx_gemm_options_t* opts, int64_t M, int64_t
   hipStream_t hs = reinterpret_cast<hipStream_t>(stream);
   const bool asym = f.asymmetric != 0;
   hipError_t e;
-  if (uses_stream(f, opts, M, N, K)) {
+  if (uses_stream(f, opts, M, N, K, batch)) {
     e = amx::launch_gemm_stream(f.scale, asym, f.group_size, M, N, K, A_codes, A_scales, B_codes, B_scales, A_pair, B_pair,
                                 C, ldc, batch, hs, timer);
     return e == hipSuccess ? AMX_OK : hip_fail(e, "gemm launch");

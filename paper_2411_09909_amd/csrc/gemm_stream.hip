@@ -1,11 +1,18 @@
-// Fully quantized GEMM (Sec. 4.3) for at most 64 rows on the A side: one launch, both operands read as packed codes.
+// Fully quantized GEMM (Sec. 4.3) for few rows on the A side and for small problems: one launch, both operands read as
+// packed codes.
 //
-// What bounds such a product is reading the weights (B) once, or, for small weights, the chain of launches and memory
-// latencies. So nothing is prepared in memory and nothing is shared between waves while they run: a wave owns NT column
-// tiles of C and every WAVES-th block of 256 along K, streams its rows' codes and scales into registers one block ahead
-// (buffer loads; no LDS, no barrier, no expansion pass), dequantizes both operands to exact 16-bit floats and
-// multiplies them on the 16-bit MFMA. The waves of a workgroup share the columns and split K between them; their sums
-// meet in LDS at the end, in a fixed order, so there are no partial tiles in memory and no reduction launch.
+// What bounds a product with few rows is reading the weights (B) once, or, for small weights, the chain of launches and
+// memory latencies. So nothing is prepared in memory and nothing is shared between waves while they run: a wave owns MT x
+// NT tiles of C and every WAVES-th block of 256 along K, dequantizes both operands to exact 16-bit floats in registers and
+// multiplies them on the 16-bit MFMA. The waves of a workgroup share the tiles and split K between them; their sums meet in
+// LDS at the end, in a fixed order, so there are no barriers while K is walked, no partial tiles in memory and no reduction
+// launch. With more rows the vector arithmetic of the dequantization is the bound (MT + NT dequantized fragments of 16 + 3
+// instructions for MT NT MFMAs), until, from about 512 rows on, expanding the weights once pays.
+//
+// Access: a vector cache has a limited number of line requests in flight, so a block's codes are fetched in whole cache
+// lines, 8 lanes to the 128 bytes of a row, straight into LDS of the wave's own, and read back from there in the MFMA's
+// row-per-lane order. (Loading the fragments' 16-byte pieces straight into registers asks for every line four to eight
+// times: 16 x 28672 x 8192 39 us, 512 x 4096 x 4096 40 us; as it is 35 us = 3.8 TB/s and 28 us.)
 //
 // MFMA shape R x R (R = 32: v_mfma_f32_32x32x16, R = 16: v_mfma_f32_16x16x32, for up to 16 rows: half the work on rows
 // that do not exist). Of a block of 256 elements of its row, a lane owns the contiguous piece lane / R (R / 2 words of
@@ -17,7 +24,7 @@
 // elements are converted times 2^8, no bias left), power-of-two scales through the conversion's own scale operand to
 // BF16. A value has at most 6 significant bits: exact in all of them.
 //
-// Groups of 32 and 16, any K the formats take (a last block shorter than 256 is read chunk by chunk), an optional factor
+// Groups of 32 and 16, any K the formats take (chunks of 32 past K in the last block read as zero), an optional factor
 // alpha (the product of two tensor-wise scales).
 
 #include "dequant_regs.h"
@@ -31,7 +38,6 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
 constexpr int kStreamBlockK = 256;  // 128 bytes of codes per row: one cache line
-constexpr int64_t kStreamMaxM = 64;
 
 // One lane's share of one row of one K block: W words of codes and their scale bytes.
 template <bool ASYM, int GS_LOG2, int R>
@@ -39,9 +45,8 @@ struct StreamPiece {
   static constexpr int kWords = R / 2;                           // 8 codes each
   static constexpr int kEntries = (kWords * 8) >> GS_LOG2;       // scale entries
   static constexpr int kScaleBytes = kEntries * (ASYM ? 2 : 1);  // 2, 4, 8 or 16
+  static constexpr int kScaleWords = kScaleBytes < 4 ? 1 : kScaleBytes / 4;
   static constexpr int kWordsPerEntry = kWords / kEntries;
-  u32x4 w[kWords / 4];
-  uint32_t s[kScaleBytes < 4 ? 1 : kScaleBytes / 4];
 };
 
 // Entry e's scale pair in the form the dequantization takes (see dequant_regs.h).
@@ -74,22 +79,27 @@ __device__ __forceinline__ u32x4 stream_dequant(uint32_t word, uint32_t s_pos, u
     return dequant_word<SCALE_KIND, ASYM>(word, s_pos, s_neg);
 }
 
-// grid: (ceil(N / (NT R)), 1, batch); block: WAVES waves. M <= MT R. WHOLE: K is a multiple of 256 (so every row's scale
+// grid: (ceil(N / (NT R)), ceil(M / (MT R)), batch); block: WAVES waves. WHOLE: K is a multiple of 256 (so every row's scale
 // bytes start on a multiple of four, as their vector loads need); otherwise scale entries are loaded byte by byte.
 template <int SCALE_KIND, bool ASYM, int GS_LOG2, int R, int MT, int NT, int WAVES, bool WHOLE>
 __global__ __launch_bounds__(64 * WAVES) void gemm_stream_kernel(
     const uint8_t* A_codes, const uint8_t* A_scales, const uint8_t* B_codes, const uint8_t* B_scales, float* C,
-    int M, int64_t N, int64_t K, int64_t ldc, const float* alpha_a, const float* alpha_b) {
+    int64_t M, int64_t N, int64_t K, int64_t ldc, const float* alpha_a, const float* alpha_b) {
   using Piece = StreamPiece<ASYM, GS_LOG2, R>;
   constexpr int kAcc = R * R / 64;  // accumulator registers per tile: 16 or 4
+  constexpr int kTiles = MT + NT;   // row tiles of A, then column tiles (rows of B)
   constexpr bool kF16 = SCALE_KIND == kScaleE5M2 || SCALE_KIND == kScaleE4M3;
+  constexpr int kRowBytes = kStreamBlockK / 2, kWaveBytes = kTiles * R * kRowBytes;  // one block of a wave's codes
+  constexpr int kSumBytes = WAVES * MT * NT * kAcc * 64 * 4;
   typedef float acc_t __attribute__((ext_vector_type(kAcc)));
-  __shared__ float sums[WAVES * MT * NT * kAcc * 64];
+  // the waves' blocks of codes; their sums at the end
+  __shared__ __attribute__((aligned(1024))) uint8_t lds[WAVES * kWaveBytes > kSumBytes ? WAVES * kWaveBytes : kSumBytes];
 
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int r = lane % R, piece = lane / R;
-  const int64_t b = blockIdx.z, n0 = (int64_t)blockIdx.x * (NT * R);
+  const int64_t b = blockIdx.z, n0 = (int64_t)blockIdx.x * (NT * R), m0 = (int64_t)blockIdx.y * (MT * R);
+  const int rows_a = M - m0 < MT * R ? (int)(M - m0) : MT * R;
   const int rows_b = N - n0 < NT * R ? (int)(N - n0) : NT * R;
   const int row_codes = (int)(K >> 1), row_scales = (int)((K >> GS_LOG2) * (ASYM ? 2 : 1));
 
@@ -97,18 +107,23 @@ __global__ __launch_bounds__(64 * WAVES) void gemm_stream_kernel(
   auto buffer = [](const uint8_t* p, int bytes) {
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t*>(p), 0, bytes, 0x00020000);
   };
-  const uint8_t* ac = A_codes + b * M * row_codes;
-  const uint8_t* as = A_scales + b * M * row_scales;
-  const uint8_t* bc = B_codes + (b * N + n0) * row_codes;
-  const uint8_t* bs = B_scales + (b * N + n0) * row_scales;
+  const __amdgpu_buffer_rsrc_t ac = buffer(A_codes + (b * M + m0) * row_codes, rows_a * row_codes);
+  const __amdgpu_buffer_rsrc_t as = buffer(A_scales + (b * M + m0) * row_scales, rows_a * row_scales);
+  const __amdgpu_buffer_rsrc_t bc = buffer(B_codes + (b * N + n0) * row_codes, rows_b * row_codes);
+  const __amdgpu_buffer_rsrc_t bs = buffer(B_scales + (b * N + n0) * row_scales, rows_b * row_scales);
+  constexpr int kNowhere = INT32_MIN;  // an offset past the end of any of these buffers
 
-  constexpr int kNowhere = INT32_MIN;                // an offset past the end of any of these buffers
-  int oc[MT > NT ? MT : NT], os[MT > NT ? MT : NT];  // byte offsets of the lane's piece of block 0 in row t R + r
+  // A direct-to-LDS load brings 8 rows x 128 bytes, whole cache lines: lane l fetches for row l / 8 the 16-byte chunk
+  // whose slot in LDS is l % 8. Chunk c of row q lies in slot c ^ ((q >> 1) & 7), so that the 64 lanes of a fragment read
+  // (16 bytes from each of R rows) spread over all banks.
+  const int chunk_even = (lane & 7) ^ (lane >> 4);  // of rows 16 i .. 16 i + 7; rows 16 i + 8 ..: ^ 4
+  const int gather = (lane >> 3) * row_codes;
+  uint8_t* const mine = lds + wave * kWaveBytes;
+  int read_off[Piece::kWords / 4];
 #pragma unroll
-  for (int t = 0; t < (MT > NT ? MT : NT); ++t) {
-    oc[t] = (t * R + r) * row_codes + piece * (Piece::kWords * 4);
-    os[t] = (t * R + r) * row_scales + piece * Piece::kScaleBytes;
-  }
+  for (int c = 0; c < Piece::kWords / 4; ++c)
+    read_off[c] = r * kRowBytes + (((piece * (Piece::kWords / 4) + c) ^ ((r >> 1) & 7)) << 4);
+  const int scale_off = r * row_scales + piece * Piece::kScaleBytes;
 
   acc_t acc[MT][NT];
 #pragma unroll
@@ -118,66 +133,81 @@ __global__ __launch_bounds__(64 * WAVES) void gemm_stream_kernel(
 #pragma unroll
       for (int v = 0; v < kAcc; ++v) acc[i][j][v] = 0.f;
 
-  // the scale entries of the lane's piece, byte by byte; entries of elements from `left` on read as zero
-  auto load_scale_bytes = [&](Piece& p, __amdgpu_buffer_rsrc_t rs, int t, int so, int left) {
-    const int k0 = piece * (Piece::kWords * 8);
+  uint32_t s_next[kTiles][Piece::kScaleWords];  // scale bytes of the block whose codes are on their way
+  // Requests block `blk` of all tiles: codes to LDS, scale bytes to s_next. left: elements of the block that exist (256
+  // but for a last, shorter block, whose chunks of 32 elements past K read as zero).
+  auto request = [&](int blk, [[maybe_unused]] int left) {
 #pragma unroll
-    for (int i = 0; i < (Piece::kScaleBytes < 4 ? 1 : Piece::kScaleBytes / 4); ++i) p.s[i] = 0;
+    for (int t = 0; t < kTiles; ++t) {
+      const bool is_a = t < MT;
+      const int row0 = (is_a ? t : t - MT) * R;
 #pragma unroll
-    for (int i = 0; i < Piece::kScaleBytes; ++i) {
-      const int e = ASYM ? i >> 1 : i;
-      const uint32_t v = (uint8_t)__builtin_amdgcn_raw_buffer_load_b8(rs, k0 + (e << GS_LOG2) < left ? os[t] : kNowhere, so + i, 0);
-      p.s[i >> 2] |= v << (8 * (i & 3));
+      for (int l = 0; l < R / 8; ++l) {
+        const int chunk = (l & 1) ? chunk_even ^ 4 : chunk_even;
+        int off = gather + chunk * 16;
+        if constexpr (!WHOLE) off = chunk * 32 < left ? off : kNowhere;
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(is_a ? ac : bc, (lds_ptr_t)(mine + (t * R + 8 * l) * kRowBytes), 16, off,
+                                                 (row0 + 8 * l) * row_codes + blk * kRowBytes, 0, 0);
+      }
+      const int so = row0 * row_scales + blk * ((kStreamBlockK >> GS_LOG2) * (ASYM ? 2 : 1));
+      if constexpr (!WHOLE) {
+#pragma unroll
+        for (int i = 0; i < Piece::kScaleWords; ++i) s_next[t][i] = 0;
+#pragma unroll
+        for (int i = 0; i < Piece::kScaleBytes; ++i) {
+          const int k = piece * (Piece::kWords * 8) + ((ASYM ? i >> 1 : i) << GS_LOG2);
+          const uint32_t v = (uint8_t)__builtin_amdgcn_raw_buffer_load_b8(is_a ? as : bs, k < left ? scale_off : kNowhere, so + i, 0);
+          s_next[t][i >> 2] |= v << (8 * (i & 3));
+        }
+      } else if constexpr (Piece::kScaleBytes == 16) {
+        const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(is_a ? as : bs, scale_off, so, 0);
+        s_next[t][0] = v[0], s_next[t][1] = v[1], s_next[t][2] = v[2], s_next[t][3] = v[3];
+      } else if constexpr (Piece::kScaleBytes == 8) {
+        const u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(is_a ? as : bs, scale_off, so, 0);
+        s_next[t][0] = v[0], s_next[t][1] = v[1];
+      } else if constexpr (Piece::kScaleBytes == 4) {
+        s_next[t][0] = __builtin_amdgcn_raw_buffer_load_b32(is_a ? as : bs, scale_off, so, 0);
+      } else {
+        s_next[t][0] = __builtin_amdgcn_raw_buffer_load_b16(is_a ? as : bs, scale_off, so, 0);
+      }
     }
-  };
-  // block `blk` of row tile t; `on` false (uniform): the buffer is empty, every load returns zero without a request
-  auto load_tile = [&](Piece& p, const uint8_t* codes, const uint8_t* scales, int rows, int t, int blk, bool on) {
-    const __amdgpu_buffer_rsrc_t rc = buffer(codes, on ? rows * row_codes : 0), rs = buffer(scales, on ? rows * row_scales : 0);
-#pragma unroll
-    for (int c = 0; c < Piece::kWords / 4; ++c)
-      p.w[c] = __builtin_amdgcn_raw_buffer_load_b128(rc, oc[t], blk * (kStreamBlockK / 2) + c * 16, 0);
-    const int so = blk * ((kStreamBlockK >> GS_LOG2) * (ASYM ? 2 : 1));
-    if constexpr (!WHOLE) {
-      load_scale_bytes(p, rs, t, so, kStreamBlockK);
-    } else if constexpr (Piece::kScaleBytes == 16) {
-      const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(rs, os[t], so, 0);
-      p.s[0] = v[0], p.s[1] = v[1], p.s[2] = v[2], p.s[3] = v[3];
-    } else if constexpr (Piece::kScaleBytes == 8) {
-      const u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(rs, os[t], so, 0);
-      p.s[0] = v[0], p.s[1] = v[1];
-    } else if constexpr (Piece::kScaleBytes == 4) {
-      p.s[0] = __builtin_amdgcn_raw_buffer_load_b32(rs, os[t], so, 0);
-    } else {
-      p.s[0] = __builtin_amdgcn_raw_buffer_load_b16(rs, os[t], so, 0);
-    }
-  };
-  // the last, shorter block: chunks of 32 elements past K read as zero
-  auto load_tail = [&](Piece& p, const uint8_t* codes, const uint8_t* scales, int rows, int t, int blk, int left) {
-    const __amdgpu_buffer_rsrc_t rc = buffer(codes, rows * row_codes), rs = buffer(scales, rows * row_scales);
-#pragma unroll
-    for (int c = 0; c < Piece::kWords / 4; ++c)
-      p.w[c] = __builtin_amdgcn_raw_buffer_load_b128(rc, piece * (Piece::kWords * 8) + 32 * c < left ? oc[t] : kNowhere,
-                                                     blk * (kStreamBlockK / 2) + c * 16, 0);
-    load_scale_bytes(p, rs, t, blk * ((kStreamBlockK >> GS_LOG2) * (ASYM ? 2 : 1)), left);
   };
 
-  auto multiply = [&](const Piece (&pa)[MT], const Piece (&pb)[NT]) {
+  // This wave's blocks are wave, wave + WAVES, .. A block's codes pass through the wave's own LDS into registers as soon as
+  // they have arrived; the next block's are then requested into the same LDS and travel while this one is multiplied. No
+  // other wave touches that LDS, so waiting for the wave's own loads is all the synchronisation there is.
+  const int blocks = (int)((K + kStreamBlockK - 1) / kStreamBlockK);
+  if (wave < blocks) request(wave, (int)K - wave * kStreamBlockK);
+  for (int blk = wave; blk < blocks; blk += WAVES) {
+    AMX_WAIT_VMCNT(0);
+    asm volatile("" ::: "memory");
+    u32x4 w[kTiles][Piece::kWords / 4];
+    uint32_t sc[kTiles][Piece::kScaleWords];
+#pragma unroll
+    for (int t = 0; t < kTiles; ++t) {
+#pragma unroll
+      for (int c = 0; c < Piece::kWords / 4; ++c)
+        w[t][c] = *reinterpret_cast<const u32x4*>(mine + t * R * kRowBytes + read_off[c]);
+#pragma unroll
+      for (int i = 0; i < Piece::kScaleWords; ++i) sc[t][i] = s_next[t][i];
+    }
+    __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): the codes are in registers, their LDS may be refilled
+    asm volatile("" ::: "memory");
+    if (blk + WAVES < blocks) request(blk + WAVES, (int)K - (blk + WAVES) * kStreamBlockK);
 #pragma unroll
     for (int e = 0; e < Piece::kEntries; ++e) {
-      uint32_t ap[MT], an[MT], bp[NT], bn[NT];
+      uint32_t s_pos[kTiles], s_neg[kTiles];
 #pragma unroll
-      for (int i = 0; i < MT; ++i) stream_scales<SCALE_KIND, ASYM>(pa[i].s, e, ap[i], an[i]);
-#pragma unroll
-      for (int j = 0; j < NT; ++j) stream_scales<SCALE_KIND, ASYM>(pb[j].s, e, bp[j], bn[j]);
+      for (int t = 0; t < kTiles; ++t) stream_scales<SCALE_KIND, ASYM>(sc[t], e, s_pos[t], s_neg[t]);
 #pragma unroll
       for (int x = 0; x < Piece::kWordsPerEntry; ++x) {
         const int s = e * Piece::kWordsPerEntry + x;
         u32x4 av[MT];
 #pragma unroll
-        for (int i = 0; i < MT; ++i) av[i] = stream_dequant<SCALE_KIND, ASYM>(pa[i].w[s >> 2][s & 3], ap[i], an[i]);
+        for (int i = 0; i < MT; ++i) av[i] = stream_dequant<SCALE_KIND, ASYM>(w[i][s >> 2][s & 3], s_pos[i], s_neg[i]);
 #pragma unroll
         for (int j = 0; j < NT; ++j) {
-          const u32x4 bv = stream_dequant<SCALE_KIND, ASYM>(pb[j].w[s >> 2][s & 3], bp[j], bn[j]);
+          const u32x4 bv = stream_dequant<SCALE_KIND, ASYM>(w[MT + j][s >> 2][s & 3], s_pos[MT + j], s_neg[MT + j]);
 #pragma unroll
           for (int i = 0; i < MT; ++i) {
             if constexpr (R == 32 && kF16)
@@ -196,48 +226,12 @@ __global__ __launch_bounds__(64 * WAVES) void gemm_stream_kernel(
         }
       }
     }
-  };
-
-  // This wave's full blocks are wave, wave + WAVES, ..: nb of them. Two register sets; a set is refilled as soon as it
-  // has been multiplied, two blocks ahead, so a block's loads travel while another one is multiplied. Loads past the
-  // last block go to an empty buffer instead of being skipped: the number of loads in flight is then the same on every
-  // path, and waiting for one set never means waiting for the other.
-  const int full = (int)(K / kStreamBlockK);
-  [[maybe_unused]] const int left = (int)(K % kStreamBlockK);
-  const int nb = full > wave ? (full - wave + WAVES - 1) / WAVES : 0;
-  auto load = [&](Piece (&pa)[MT], Piece (&pb)[NT], int i) {
-    const bool on = i < nb;
-    const int blk = wave + i * WAVES;
-#pragma unroll
-    for (int j = 0; j < NT; ++j) load_tile(pb[j], bc, bs, rows_b, j, blk, on);
-#pragma unroll
-    for (int t = 0; t < MT; ++t) load_tile(pa[t], ac, as, M, t, blk, on);
-  };
-  if (nb > 0) {
-    Piece a0[MT], b0[NT], a1[MT], b1[NT];
-    load(a0, b0, 0);
-    load(a1, b1, 1);
-    for (int i = 0;; i += 2) {
-      multiply(a0, b0);
-      if (i + 1 >= nb) break;
-      load(a0, b0, i + 2);
-      multiply(a1, b1);
-      if (i + 2 >= nb) break;
-      load(a1, b1, i + 3);
-    }
-  }
-  if constexpr (!WHOLE) {
-    if (left != 0 && wave == full % WAVES) {
-      Piece a0[MT], b0[NT];
-#pragma unroll
-      for (int j = 0; j < NT; ++j) load_tail(b0[j], bc, bs, rows_b, j, full, left);
-#pragma unroll
-      for (int t = 0; t < MT; ++t) load_tail(a0[t], ac, as, M, t, full, left);
-      multiply(a0, b0);
-    }
   }
 
-  // the waves' sums, added in ascending wave order
+  // the waves' sums, added in ascending wave order (other waves' codes may still be on their way into the LDS that the
+  // sums take)
+  float* sums = reinterpret_cast<float*>(lds);
+  __syncthreads();
 #pragma unroll
   for (int i = 0; i < MT; ++i)
 #pragma unroll
@@ -247,7 +241,7 @@ __global__ __launch_bounds__(64 * WAVES) void gemm_stream_kernel(
   __syncthreads();
   const float alpha = alpha_a ? alpha_a[0] * alpha_b[0] : 1.0f;
   constexpr int kTile = MT * NT * kAcc * 64;
-  float* Cb = C + b * M * ldc + n0;
+  float* Cb = C + (b * M + m0) * ldc + n0;
 #pragma unroll
   for (int e = 0; e < (kTile + 64 * WAVES - 1) / (64 * WAVES); ++e) {
     const int idx = e * 64 * WAVES + (int)threadIdx.x;
@@ -261,69 +255,89 @@ __global__ __launch_bounds__(64 * WAVES) void gemm_stream_kernel(
       const int col = j * R + l % R;
       if constexpr (SCALE_KIND == kScaleE5M2) s *= 64.0f;  // undo the two biases
       if (alpha_a) s *= alpha;
-      if (row < M && col < rows_b) Cb[row * ldc + col] = s;
+      if (row < rows_a && col < rows_b) Cb[row * ldc + col] = s;
     }
   }
 }
 
-bool stream_path_supported(int64_t group_size, int64_t M, int64_t K) {
-  return (group_size == 32 || group_size == 16) && M >= 1 && M <= kStreamMaxM && K % 32 == 0;
+static bool pot_scales(int scale_kind) { return scale_kind == kScaleE8M0Floor || scale_kind == kScaleE8M0Round; }
+
+// Time of this kernel for more than 64 rows, us, in the shape <2, 2, 4> below: workgroups of 64 x 64 outputs, 256 at a
+// time. Fitted to K 1024 .. 13824, N 1024 .. 28672, 80 .. 2048 rows, where it is within 10 %.
+static double stream_us(int scale_kind, bool asym, int64_t M, int64_t N, int64_t K) {
+  const double rounds = (double)(((M + 63) / 64 * ((N + 63) / 64) + 255) / 256), k = (double)K / 4096.0;
+  return asym ? 4.0 + k * (2.0 + 11.5 * rounds) : pot_scales(scale_kind) ? 3.0 + k * (1.5 + 7.3 * rounds) : 4.0 + k * (1.5 + 9.3 * rounds);
 }
 
-// Where the few-rows kernel of gemm_skinny.hip, which shares A through LDS and can cut K over workgroups, takes the same
-// operands (groups of 32, K a multiple of 256), it stays the faster one in two corners; us for the whole call, here / there:
-//   more than 16 rows, a long K and few columns, where K over the waves of one workgroup leaves each of them a long chain:
-//     32 x 4096 x 14336: 20.6 / 18.9;  32 x 8192 x 28672: 50 / 47;  64 x 4096 x 14336: 35 / 25;  (16 rows: 12.8 / 18.5)
-//   more than 32 rows against large weights, where dequantizing A in every wave is what counts:
-//     64 x 10240 x 8192: 34 / 30;  48 x 28672 x 8192: 69 / 57;  (64 x 8192 x 8192: 20.9 / 24.6;  40 x 14336 x 4096: 20 / 23)
-// Elsewhere this kernel: 1 x 4096 x 4096: 4.8 / 12.7;  64 x 1024 x 1024: 5.8 / 11.2;  32 x 11008 x 4096: 12.8 / 16.9;
-// 16 x 28672 x 8192: 39 / 46. The other formats would expand B to BF16 first (24 x 11008 x 4096 in groups of 16: 84 us).
-bool stream_path_preferred(int64_t group_size, int64_t M, int64_t N, int64_t K) {
-  if (!stream_path_supported(group_size, M, K)) return false;
-  if (group_size != 32 || K % kStreamBlockK != 0 || M <= 16) return true;
-  if (K >= 12288 && N <= 8192) return false;
-  return M <= 32 ? N * K < (int64_t(1) << 27) : N * K <= (int64_t(1) << 26);
+// The FP4 kernel (symmetric power-of-two scales, groups of 32) while its 256 x 256 tiles fit the compute units once: 31 us
+// at K 4096, 48 at 8192, 70 at 13824, whatever M and N are.
+static double fp4_us(int64_t K) { return 14.0 + 0.0041 * (double)K; }
+
+// More than 64 rows of that format: whether the FP4 kernel is the fastest of the three that could take them. The few-rows
+// kernel never is there (28672 x 8192: 80 rows 69 us, 256 rows 137, the FP4 kernel 48).
+bool fp4_beats_stream(int64_t M, int64_t N, int64_t K) {
+  return M > 64 && fp4_us(K) <= stream_us(kScaleE8M0Floor, false, M, N, K);
+}
+
+// Whether this kernel takes a product, single problems and batches alike unless said otherwise. us for the whole call,
+// AMXFP4-E5M2, here / the kernel that took it otherwise:
+//   up to 64 rows: always (1 x 4096 x 4096: 4.8 / 12.7;  64 x 1024 x 1024: 4.0 / 11.2;  32 x 11008 x 4096: 12.5 / 16.9;
+//     32 x 28672 x 8192: 41 / 47;  64 x 28672 x 8192: 56 / 60;  groups of 16, whose weights were expanded to BF16 first,
+//     24 x 11008 x 4096: 10 / 84)
+//   single problems from there on, symmetric power-of-two scales: where the estimates above say so
+//   the other formats: up to 256 rows, against weights below 2^27 elements (256 x 4096 x 4096: 17 / 50;  256 x 11008 x
+//     4096: 40 / 79;  but 256 x 28672 x 8192: 177 / 151 on the few-rows kernel, which shares the dequantized A);
+//     asymmetric power-of-two scales end here (prepared weights beyond 256 rows are their FP6 panel alone);
+//   up to 512 rows likewise (512 x 4096 x 4096: 28 / 46;  512 x 4096 x 11008: 67 / 128;  512 x 14336 x 4096: 91 / 143);
+//   up to 768 rows where the BF16 panels' tiles leave compute units idle: a long K or few columns (768 x 4096 x 11008:
+//     97 / 134;  768 x 1024 x 1024: 7.7 / 17;  but 768 x 14336 x 4096: 135 / 129).
+bool stream_path_preferred(int scale_kind, bool asym, int64_t group_size, int64_t M, int64_t N, int64_t K, int64_t batch) {
+  if ((group_size != 32 && group_size != 16) || K % 32 != 0) return false;
+  if (M <= 64) return true;
+  if (batch != 1) return false;
+  if (group_size == 32 && pot_scales(scale_kind)) {
+    if (!asym) return !fp4_path_supported(M, N, K) ? M <= 256 : !fp4_beats_stream(M, N, K);
+    return M <= 256 && N * K < (int64_t(1) << 27);
+  }
+  if (M > 768 || (N * K >= (int64_t(1) << 27) && (group_size == 32 || M > 256))) return false;
+  return M <= 512 || K >= 8192 || (M + 63) / 64 * ((N + 63) / 64) <= 512;
 }
 
 hipError_t launch_gemm_stream(int scale_kind, bool asym, int64_t group_size, int64_t M, int64_t N, int64_t K,
                               const uint8_t* A_codes, const uint8_t* A_scales, const uint8_t* B_codes,
                               const uint8_t* B_scales, const float* A_tensor_pair, const float* B_tensor_pair, float* C,
                               int64_t ldc, int64_t batch, hipStream_t s, const KernelTimer& timer) {
-  if (!stream_path_supported(group_size, M, K)) return hipErrorInvalidValue;
+  if ((group_size != 32 && group_size != 16) || K % 32 != 0) return hipErrorInvalidValue;
   hipError_t e = hipSuccess;
   if (timer.start && (e = hipEventRecord(timer.start, s)) != hipSuccess) return e;
   auto run = [&]<int SK, bool ASYM, int GSL, int R, int MT, int NT, int WAVES, bool WHOLE>() {
     hipLaunchKernelGGL((gemm_stream_kernel<SK, ASYM, GSL, R, MT, NT, WAVES, WHOLE>),
-                       dim3((unsigned)((N + NT * R - 1) / (NT * R)), 1, (unsigned)batch), dim3(64 * WAVES), 0, s, A_codes,
-                       A_scales, B_codes, B_scales, C, (int)M, N, K, ldc, A_tensor_pair, B_tensor_pair);
+                       dim3((unsigned)((N + NT * R - 1) / (NT * R)), (unsigned)((M + MT * R - 1) / (MT * R)), (unsigned)batch),
+                       dim3(64 * WAVES), 0, s, A_codes, A_scales, B_codes, B_scales, C, M, N, K, ldc, A_tensor_pair, B_tensor_pair);
     return hipGetLastError();
   };
-  // Columns per workgroup: as few as still give the 256 compute units one workgroup of eight waves each; beyond 1024
-  // tiles wider ones of four waves, several to a compute unit. (us by columns, AMXFP4-E5M2 16 rows: N 8192, K 8192:
-  // 16 columns 14.9, 32: 12.1, 64: 17.9;  N 6144, K 4096: 8.4, 7.5, 11.5;  N 4096: 5.4, 7.3, 11.4;  N 28672, K 8192: 64
-  // columns in eight waves 42.7, in four 39.0. 32 rows: N 14336, K 4096: 32 columns 14.8, 64: 13.4;  N 6144: 9.5, 12.8;
-  // N 4096: two tiles of 16 rows and 16 columns 7.4, one of 32 rows and columns 9.3.)
-  const int64_t t16 = (N + 15) / 16 * batch, t32 = (N + 31) / 32 * batch;
+  // The smallest tiles that still give the 256 compute units one workgroup of eight waves each; beyond that tiles of 64 x
+  // 64 in workgroups of four waves, two to a compute unit. (AMXFP4-E5M2, us by tile: 16 rows, N 4096, K 4096: 16 x 16 4.8,
+  // 16 x 32 6.1;  N 6144: 7.6, 6.8;  N 28672, K 8192: 39, 36, 16 x 64 35. 32 rows, N 4096: two 16-row tiles x 16 columns
+  // 6.8, 32 x 32 8.0;  N 11008: 32 x 32 13.0, 32 x 64 12.5;  N 28672, K 8192: 44.8, 45.7, the latter in four waves 40.6.
+  // 128 rows, N 4096: 32 x 32 13.2, 32 x 64 11.8;  256 rows: 22, 22, 64 x 64 in eight waves 16.7, in four 17.7;  512 rows:
+  // 43, 41, 31.6, 27.7, 64 x 128 27.9.)
+  const int64_t t16 = (N + 15) / 16 * batch, t32 = (N + 31) / 32 * batch, rows32 = (M + 31) / 32;
   auto shape = [&]<int SK, bool ASYM, int GSL>() {
-    if (K % kStreamBlockK != 0) {
-      if (M <= 16) return run.template operator()<SK, ASYM, GSL, 16, 1, 2, 8, false>();
-      if (M <= 32) return run.template operator()<SK, ASYM, GSL, 32, 1, 1, 8, false>();
-      return run.template operator()<SK, ASYM, GSL, 32, 2, 1, 8, false>();
-    }
-    if (M <= 16) {
-      if (t16 <= 256) return run.template operator()<SK, ASYM, GSL, 16, 1, 1, 8, true>();
-      if (t16 <= 512) return run.template operator()<SK, ASYM, GSL, 16, 1, 2, 8, true>();
-      if (t16 <= 1024) return run.template operator()<SK, ASYM, GSL, 16, 1, 4, 8, true>();
-      return run.template operator()<SK, ASYM, GSL, 16, 1, 4, 4, true>();
-    }
-    if (M <= 32) {
-      if (t32 <= 128) return run.template operator()<SK, ASYM, GSL, 16, 2, 1, 8, true>();
-      if (t32 <= 256) return run.template operator()<SK, ASYM, GSL, 32, 1, 1, 8, true>();
-      if (t32 <= 512) return run.template operator()<SK, ASYM, GSL, 32, 1, 2, 8, true>();
-      return run.template operator()<SK, ASYM, GSL, 32, 1, 2, 4, true>();
-    }
-    if (t32 <= 256) return run.template operator()<SK, ASYM, GSL, 32, 2, 1, 8, true>();
-    return run.template operator()<SK, ASYM, GSL, 32, 2, 2, 4, true>();
+    auto pick = [&]<bool WHOLE>() {
+      if (M <= 16) {
+        if (t16 <= 256) return run.template operator()<SK, ASYM, GSL, 16, 1, 1, 8, WHOLE>();
+        if (t16 <= 512) return run.template operator()<SK, ASYM, GSL, 16, 1, 2, 8, WHOLE>();
+        return run.template operator()<SK, ASYM, GSL, 16, 1, 4, 8, WHOLE>();
+      }
+      if (M <= 32 && t32 <= 128) return run.template operator()<SK, ASYM, GSL, 16, 2, 1, 8, WHOLE>();
+      if (rows32 * t32 <= 256) return run.template operator()<SK, ASYM, GSL, 32, 1, 1, 8, WHOLE>();
+      if (rows32 * ((t32 + 1) / 2) <= 256) return run.template operator()<SK, ASYM, GSL, 32, 1, 2, 8, WHOLE>();
+      if (M <= 32) return run.template operator()<SK, ASYM, GSL, 32, 1, 2, 4, WHOLE>();
+      if ((rows32 + 1) / 2 * ((t32 + 1) / 2) <= 256) return run.template operator()<SK, ASYM, GSL, 32, 2, 2, 8, WHOLE>();
+      return run.template operator()<SK, ASYM, GSL, 32, 2, 2, 4, WHOLE>();
+    };
+    return K % kStreamBlockK == 0 ? pick.template operator()<true>() : pick.template operator()<false>();
   };
   auto group = [&]<int SK, bool ASYM>() {
     return group_size == 16 ? shape.template operator()<SK, ASYM, 4>() : shape.template operator()<SK, ASYM, 5>();

@@ -1,6 +1,6 @@
-"""The GEMM for at most 64 rows that reads both operands as packed codes in one launch (gemm_stream.hip), against the
-oracle: every workgroup shape of its rule, partial row and column tiles, K tails, groups of 16, batches, tensor-wise
-scales, and nothing written outside the product."""
+"""The GEMM for few rows and small problems that reads both operands as packed codes in one launch (gemm_stream.hip),
+against the oracle: every workgroup shape of its rule, partial row and column tiles, K tails, groups of 16, batches,
+tensor-wise scales, and nothing written outside the product."""
 import numpy as np
 import pytest
 import torch
@@ -15,11 +15,13 @@ FORMATS = [(ref.FP8_E5M2, 1, 32), (ref.FP8_E5M2, 0, 32), (ref.E8M0_FLOOR, 1, 32)
            (ref.FP8_E4M3, 1, 32), (ref.FP8_E4M3, 0, 16), (ref.FP8_E4M3, 1, 16), (ref.FP8_E5M2, 1, 16),
            (ref.E8M0_FLOOR, 0, 16)]
 
-# M: both sides of 16, 32 and 64 rows. N: one column, partial tiles, each tile count at which the rule changes shape (256
-# tiles of 16 / 32 columns and one more). K: one block, one block per wave and one more, tails of one to seven groups.
+# M: both sides of 16, 32, 64, 256, 512 and 768 rows. N: one column, partial tiles, each tile count at which the rule
+# changes shape (256 tiles and one more). K: one block, one block per wave and one more, tails of one to seven groups.
 SHAPES = [(1, 1, 32), (16, 17, 256), (5, 100, 2304), (13, 33, 2272), (16, 4097, 256), (3, 8193, 288), (2, 16400, 256),
           (17, 31, 512), (32, 65, 2048), (20, 4097, 512), (32, 8193, 256), (25, 16385, 256), (31, 50, 4544),
-          (33, 64, 256), (64, 45, 2560), (40, 8193, 256), (64, 33, 96), (50, 70, 4448)]
+          (33, 64, 256), (64, 45, 2560), (40, 8193, 256), (64, 33, 96), (50, 70, 4448), (64, 4097, 256),
+          (65, 100, 512), (96, 8200, 256), (128, 4129, 288), (250, 4097, 256), (257, 65, 2304), (300, 4100, 256),
+          (512, 4160, 288), (513, 130, 2080), (768, 2050, 512)]
 
 
 def bound(a, b, K):
@@ -75,7 +77,21 @@ def test_every_scale_byte(M, scale, gs):
         assert (np.abs(C[i] - ad @ bd.T) <= bound(ad, bd, K)).all()
 
 
-@pytest.mark.parametrize("M,N,K,asym", [(1, 300, 1024, 0), (24, 4100, 512, 1), (64, 130, 4512, 0)])
+def test_fp4_kernel_for_few_rows_against_large_weights():
+    """Symmetric power-of-two scales, 80 rows against weights so large that the FP4 kernel is the fastest of those that
+    could take them: the workspace asked for is good for it, and the product is right with exactly that much."""
+    M, N, K = 80, 20000, 8192
+    fmt = binding.make_format(ref.E8M0_FLOOR, 0, 32)
+    ac, as_ = ref.quantize(synth.activations(M, K, seed=1), 32, ref.E8M0_FLOOR, 0)
+    bc, bs = ref.quantize(synth.weights(N, K, seed=2), 32, ref.E8M0_FLOOR, 0)
+    C = G.gpu_gemm(ac, as_, bc, bs, ref.E8M0_FLOOR, 0)
+    ad, bd = (ref.dequantize(c, s, 32, ref.E8M0_FLOOR, 0).astype(np.float64) for c, s in ((ac, as_), (bc, bs)))
+    assert (np.abs(C - ad @ bd.T) <= bound(ad, bd, K)).all()
+    few = binding.gemm_options(few_rows=1)
+    assert binding.gemm_workspace_bytes(fmt, M, N, K) >= binding.gemm_workspace_bytes(fmt, M, N, K, options=few)
+
+
+@pytest.mark.parametrize("M,N,K,asym", [(1, 300, 1024, 0), (24, 4100, 512, 1), (64, 130, 4512, 0), (200, 300, 1056, 1)])
 def test_tensor_scaled(M, N, K, asym):
     """Double scaling on the few-rows shapes: the product of the dequantized operands times the two tensor-wise scales."""
     fmt = binding.make_format(ref.FP8_E4M3, asym, 16)
