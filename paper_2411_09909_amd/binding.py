@@ -127,7 +127,9 @@ def _check(rc):
 
 
 def _stream():
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    # the handle of torch.cuda.current_stream(), without building the Stream object around it: 0.2 instead of 2.9 us, of a
+    # small cast's 7.4 and a small product's 9.4 us per call
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 def _need_cuda(*ts):
@@ -348,10 +350,11 @@ def gemm(fmt, a_codes, a_scales, b_codes, b_scales, out=None, workspace=None, ba
         raise AmxError("the scaled GEMM needs both tensor-scale pairs and has no mxfp4_* twin")
     if options is not None and (scaled or baseline):
         raise AmxError("kernel options go with the plain amxfp4_gemm only (clear fmt.asymmetric for the baseline)")
-    need = (load().amxfp4_gemm_scaled_workspace_bytes(ctypes.byref(fmt), M, N, K, batch) if scaled
-            else gemm_workspace_bytes(fmt, M, N, K, batch, options))
-    if workspace is None and need:
-        workspace = torch.empty(need, dtype=torch.uint8, device=a_codes.device)
+    if workspace is None:  # (one that is given is checked by the library)
+        need = (load().amxfp4_gemm_scaled_workspace_bytes(ctypes.byref(fmt), M, N, K, batch) if scaled
+                else gemm_workspace_bytes(fmt, M, N, K, batch, options))
+        if need:
+            workspace = torch.empty(need, dtype=torch.uint8, device=a_codes.device)
     ws_ptr = workspace.data_ptr() if workspace is not None else None
     ws_len = workspace.numel() * workspace.element_size() if workspace is not None else 0
     if scaled:
@@ -398,8 +401,8 @@ def attention_decode(fmt, q_codes, q_scales, k_codes, k_scales, v_codes, v_scale
         assert t.is_contiguous()
     if out is None:
         out = torch.empty((Hq, Sq, D), dtype=torch.float32, device=q_codes.device)
-    need = int(load().amxfp4_attention_decode_workspace_bytes(ctypes.byref(fmt), Hq, Hkv, Sq, Sk, D, key_splits))
     if workspace is None:
+        need = int(load().amxfp4_attention_decode_workspace_bytes(ctypes.byref(fmt), Hq, Hkv, Sq, Sk, D, key_splits))
         workspace = torch.empty(max(need, 256), dtype=torch.uint8, device=q_codes.device)
     _check(load().amxfp4_attention_decode(ctypes.byref(fmt), Hq, Hkv, Sq, Sk, D, q_codes.data_ptr(), q_scales.data_ptr(),
                                           k_codes.data_ptr(), k_scales.data_ptr(), v_codes.data_ptr(),
@@ -428,9 +431,10 @@ def gemm_prepared(fmt, a_codes, a_scales, b_codes, b_scales, prepared, out=None,
     N = b_codes.shape[0]
     if out is None:
         out = torch.empty((M, N), dtype=torch.float32, device=a_codes.device)
-    need = int(load().amxfp4_gemm_prepared_workspace_bytes(ctypes.byref(fmt), M, N, K))
-    if workspace is None and need:
-        workspace = torch.empty(need, dtype=torch.uint8, device=a_codes.device)
+    if workspace is None:
+        need = int(load().amxfp4_gemm_prepared_workspace_bytes(ctypes.byref(fmt), M, N, K))
+        if need:
+            workspace = torch.empty(need, dtype=torch.uint8, device=a_codes.device)
     ws_ptr = workspace.data_ptr() if workspace is not None else None
     ws_len = workspace.numel() * workspace.element_size() if workspace is not None else 0
     n_prep = prepared.numel() * prepared.element_size()
@@ -460,9 +464,10 @@ def attention(fmt, q_codes, q_scales, k_codes, k_scales, v_codes, v_scales, scal
         out = (_bf16_out((Sq, Hq * D), q_codes.device) if merged
                else torch.empty((Hq, Sq, D), dtype=torch.float32, device=q_codes.device))
     assert out.is_contiguous() and out.dtype == (torch.bfloat16 if merged else torch.float32)
-    need = attention_workspace_bytes(fmt, Hq, Hkv, Sq, Sk, D)
-    if workspace is None and need:
-        workspace = torch.empty(need, dtype=torch.uint8, device=q_codes.device)
+    if workspace is None:
+        need = attention_workspace_bytes(fmt, Hq, Hkv, Sq, Sk, D)
+        if need:
+            workspace = torch.empty(need, dtype=torch.uint8, device=q_codes.device)
     ws_ptr = workspace.data_ptr() if workspace is not None else None
     ws_len = workspace.numel() * workspace.element_size() if workspace is not None else 0
     call = load().amxfp4_attention_merged if merged else load().amxfp4_attention
