@@ -84,7 +84,8 @@ int amxfp4_silu_mul(const float* gate_up, int64_t rows, int64_t width, void* out
  *   out_bf16           device out, [M][ld_out] BF16 bit patterns, ld_out >= width.
  *   workspace          at least amxfp4_gemm_silu_mul_workspace_bytes() bytes, 256-byte aligned; may be NULL when
  *                      that is 0. The product runs on the tiled kernel of the format (block-scaled matrix
- *                      instructions for power-of-two scales of 32-groups, exact BF16 operands otherwise), whatever M.
+ *                      instructions for power-of-two scales of 32-groups, exact BF16 operands otherwise) or, with few
+ *                      rows and for small problems, on the one that reads both operands as packed codes.
  * Status codes as amxfp4_gemm.
  */
 size_t amxfp4_gemm_silu_mul_workspace_bytes(const amx_format_t* fmt, int64_t M, int64_t width, int64_t K);
@@ -94,7 +95,8 @@ int amxfp4_gemm_silu_mul(const amx_format_t* fmt, int64_t M, int64_t width, int6
 
 /*
  * amxfp4_gemm_silu_mul on prepared weights: `prepared` is what amxfp4_prepare_weights (include/amxfp4.h) wrote for the
- * INTERLEAVED weight matrix B [2 * width][K]; the call then expands only A. Same result, bit for bit. For formats with
+ * INTERLEAVED weight matrix B [2 * width][K]; the call then expands only A (few rows and small problems, M <= 768, read
+ * B_codes and B_scales and ignore it). Same result, bit for bit. For formats with
  * nothing to prepare (amxfp4_weights_prepared_bytes() == 0) `prepared` is ignored and the call is amxfp4_gemm_silu_mul.
  * workspace: at least amxfp4_gemm_silu_mul_prepared_workspace_bytes() bytes.
  */

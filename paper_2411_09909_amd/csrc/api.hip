@@ -444,6 +444,11 @@ static int glu_impl(const amx_format_t* fmt, int64_t M, int64_t width, int64_t K
   g_timer = amx::KernelTimer();
   hipStream_t hs = reinterpret_cast<hipStream_t>(stream);
   float* out = reinterpret_cast<float*>(out_bf16);
+  if (amx::stream_glu_preferred(f.scale, f.asymmetric != 0, f.group_size, M, 2 * width, K)) {  // (reads B's codes; no workspace)
+    hipError_t e = amx::launch_gemm_stream_glu(f.scale, f.asymmetric != 0, f.group_size, M, 2 * width, K, A_codes, A_scales,
+                                               B_codes, B_scales, out_bf16, ld_out, hs, timer);
+    return e == hipSuccess ? AMX_OK : hip_fail(e, "gemm_silu_mul launch");
+  }
   if (glu_kernel == kGemmFp8Merged) {
     hipError_t e = amx::launch_gemm_fp8m_path(M, 2 * width, K, A_codes, A_scales, B_codes, B_scales, out, ld_out, 1,
                                               workspace, hs, timer, true);

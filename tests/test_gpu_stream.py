@@ -108,3 +108,32 @@ def test_tensor_scaled(M, N, K, asym):
     # the sum's bound, and two more roundings: the product of the two scales and the product with it
     limit = (2.0 * (K + 4) * 2.0 ** -24) * (xd.abs() @ wd.abs().T) * alpha
     assert bool((err <= limit + 1e-30).all())
+
+
+@pytest.mark.parametrize("scale,asym,gs", [(ref.FP8_E5M2, 1, 32), (ref.E8M0_FLOOR, 1, 32), (ref.E8M0_FLOOR, 0, 32),
+                                           (ref.FP8_E4M3, 0, 16)])
+@pytest.mark.parametrize("M,width,K", [(1, 32, 256), (16, 2080, 288), (20, 96, 2304), (32, 8320, 256), (64, 64, 544),
+                                       (100, 4128, 256), (256, 160, 2048), (257, 96, 512), (500, 2080, 288)])
+def test_gated_product(M, width, K, scale, asym, gs):
+    """The gate / up projection with the activation in the epilogue: every workgroup shape, K tails, rows around 16, 32, 64
+    and 256, into a window of a larger buffer."""
+    fmt = binding.make_format(scale, asym, gs)
+    x = synth.activations(M, K, seed=M, n_outlier=1, outlier_gain=30.0)
+    wg, wu = (G.to_dev_bf16(synth.weights(width, K, seed=i)) for i in (1, 2))
+    xc, xs = binding.quantize(fmt, G.to_dev_bf16(x))
+    wc, ws = binding.quantize(fmt, binding.interleave_gate_up(wg, wu).contiguous())
+    pad = torch.full((M + 2, width + 8), -7.0, dtype=torch.bfloat16, device="cuda")
+    out = pad[1:M + 1, :width]
+    binding.gemm_silu_mul(fmt, xc, xs, wc, ws, out=out)
+    torch.cuda.synchronize()
+    xd = binding.dequantize(fmt, xc, xs, torch.float32).double()
+    gd, ud = (binding.dequantize(fmt, *binding.quantize(fmt, w), torch.float32).double() for w in (wg, wu))
+    g, u = xd @ gd.T, xd @ ud.T
+    # one BF16 rounding, a few FP32 ones, and what the sums' own errors do to silu(g) * u (|silu'| <= 1.1, |silu| <= |g|)
+    sums = 2.0 * (K + 2) * 2.0 ** -24
+    eg, eu = sums * (xd.abs() @ gd.abs().T), sums * (xd.abs() @ ud.abs().T)
+    want = torch.nn.functional.silu(g) * u
+    limit = (2.0 ** -8 + 2.0 ** -20) * want.abs() + 1.1 * eg * (u.abs() + eu) + g.abs() * eu + 1e-30
+    assert bool(((out.double() - want).abs() <= limit).all())
+    full = pad.float()
+    assert bool((full[0] == -7).all() and (full[M + 1] == -7).all() and (full[:, width:] == -7).all())
