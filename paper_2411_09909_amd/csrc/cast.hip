@@ -255,43 +255,36 @@ __global__ __launch_bounds__(256) void quantize_strided_kernel(const uint16_t* _
 
 // Tensor-wise scale (Sec. 5.3, double scaling): the largest magnitude of a BF16 tensor, then
 // S_t = amax / 2688 (2688 = 448 * 6 = largest E4M3 group scale times largest element), not below 2^-96, and
-// R_t = 1 / S_t, both correctly rounded FP32 divisions; an all-zero tensor gives 1, 1. pair[0] serves as the
-// accumulator of the maximum (bit pattern of a non-negative float) between the three launches.
-__global__ void tensor_amax_init_kernel(uint32_t* pair) {
-  pair[0] = 0u;
-  pair[1] = 0u;
+// R_t = 1 / S_t, both correctly rounded FP32 divisions; an all-zero tensor gives 1, 1.
+// What bounds it on activations is launches and atomics on the one accumulator, so a tensor of up to kAmaxOneGroup elements
+// is one workgroup's work and one launch. A larger one takes two: the pair serves as the accumulator of the maximum (bit
+// pattern of a non-negative float) and as the count of workgroups that have added theirs, both cleared by the first launch,
+// and the workgroup that is last to add writes the result; at most one workgroup per compute unit, since every one adds to
+// the count (with 512 of them 4096 x 8192 took 28 us). us, three launches of up to 2048 workgroups / now: 24 x 4096 5.9 /
+// 3.4, 32 x 8192 6.6 / 5.3, 512 x 4096 14.6 / 6.6, 2048 x 4096 24 / 8.2, 4096 x 8192 19 / 20.
+__device__ __forceinline__ uint32_t amax_of(uint4 v) {  // two 15-bit magnitudes
+  return pk_max_i16(pk_max_i16(v.x & 0x7FFF7FFFu, v.y & 0x7FFF7FFFu), pk_max_i16(v.z & 0x7FFF7FFFu, v.w & 0x7FFF7FFFu));
 }
 
-__global__ __launch_bounds__(256) void tensor_amax_kernel(const uint16_t* __restrict__ x, int64_t rows, int64_t K,
-                                                          int64_t row_stride, uint32_t* __restrict__ pair) {
-  const int64_t chunks_per_row = K >> 3, total = rows * chunks_per_row;
-  uint32_t m = 0;  // two running 15-bit magnitudes
-  for (int64_t c = (int64_t)blockIdx.x * 256 + threadIdx.x; c < total; c += (int64_t)gridDim.x * 256) {
-    const int64_t r = c / chunks_per_row, cc = c - r * chunks_per_row;
-    const uint4 v = *reinterpret_cast<const uint4*>(x + r * row_stride + cc * 8);
-    m = pk_max_i16(m, pk_max_i16(pk_max_i16(v.x & 0x7FFF7FFFu, v.y & 0x7FFF7FFFu),
-                                 pk_max_i16(v.z & 0x7FFF7FFFu, v.w & 0x7FFF7FFFu)));
-  }
+// the largest of all threads' pairs of magnitudes, as the bit pattern of a float, in thread 0
+template <int WAVES>
+__device__ __forceinline__ uint32_t workgroup_amax(uint32_t m) {
   uint32_t a = (m & 0xFFFFu) > (m >> 16) ? (m & 0xFFFFu) : (m >> 16);
 #pragma unroll
   for (int off = 32; off >= 1; off >>= 1) {
     const uint32_t o = (uint32_t)__shfl_xor((int)a, off, 64);
     a = a > o ? a : o;
   }
-  // one atomic per workgroup, and none when the running maximum already covers it (the maximum only grows, so a
-  // stale read can only cause a superfluous atomic)
-  __shared__ uint32_t wave_max[4];
+  __shared__ uint32_t wave_max[WAVES];
   if ((threadIdx.x & 63) == 0) wave_max[threadIdx.x >> 6] = a;
   __syncthreads();
-  if (threadIdx.x == 0) {
-    for (int w = 1; w < 4; ++w) a = a > wave_max[w] ? a : wave_max[w];
-    a <<= 16;
-    if (a > __builtin_nontemporal_load(pair)) atomicMax(pair, a);
-  }
+  if (threadIdx.x == 0)
+    for (int w = 1; w < WAVES; ++w) a = a > wave_max[w] ? a : wave_max[w];
+  return a << 16;
 }
 
-__global__ void tensor_scale_finalize_kernel(float* pair) {
-  const float amax = pair[0];  // the accumulated bit pattern is the float itself
+__device__ __forceinline__ void write_scale_pair(uint32_t amax_bits, float* pair) {
+  const float amax = u2f(amax_bits);
   float st = 1.0f, rt = 1.0f;
   if (amax > 0.f) {
     st = fmaxf(__fdiv_rn(amax, 2688.0f), 0x1p-96f);
@@ -299,6 +292,50 @@ __global__ void tensor_scale_finalize_kernel(float* pair) {
   }
   pair[0] = st;
   pair[1] = rt;
+}
+
+constexpr int64_t kAmaxOneGroup = int64_t(1) << 17;
+constexpr int64_t kAmaxGroups = 256;
+
+// grid of workgroups of 1024 threads; total <= 2^61 chunks of 8. ONE: the only workgroup, pair need not be cleared.
+template <bool ONE>
+__global__ __launch_bounds__(1024) void tensor_scale_kernel(const uint16_t* __restrict__ x, int64_t total,
+                                                            int64_t chunks_per_row, int64_t row_stride, uint32_t* pair) {
+  uint32_t m = 0;  // two running 15-bit magnitudes
+  auto chunk = [&](int64_t c) {
+    if (row_stride == chunks_per_row * 8) return *reinterpret_cast<const uint4*>(x + c * 8);  // (uniform)
+    const int64_t r = c / chunks_per_row, cc = c - r * chunks_per_row;
+    return *reinterpret_cast<const uint4*>(x + r * row_stride + cc * 8);
+  };
+  const int64_t step = ONE ? 1024 : (int64_t)gridDim.x * 1024;
+  int64_t c = (int64_t)blockIdx.x * 1024 + threadIdx.x;
+  for (; c + 7 * step < total; c += 8 * step) {  // eight loads in flight per thread
+    uint4 v[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) v[i] = chunk(c + i * step);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) m = pk_max_i16(m, amax_of(v[i]));
+  }
+  for (; c < total; c += step) m = pk_max_i16(m, amax_of(chunk(c)));
+  const uint32_t a = workgroup_amax<16>(m);
+  if (threadIdx.x != 0) return;
+  if constexpr (ONE) {
+    write_scale_pair(a, reinterpret_cast<float*>(pair));
+  } else {
+    // no atomic maximum when the running one already covers this workgroup's (it only grows, so a stale read can only
+    // cause a superfluous one); the count goes up after it, and whoever completes the count reads the final maximum
+    if (a > __builtin_nontemporal_load(pair)) atomicMax(pair, a);
+    __threadfence();
+    if (atomicAdd(pair + 1, 1u) == gridDim.x - 1) {
+      __threadfence();
+      write_scale_pair(atomicMax(pair, 0u), reinterpret_cast<float*>(pair));
+    }
+  }
+}
+
+__global__ void tensor_amax_init_kernel(uint32_t* pair) {
+  pair[0] = 0u;
+  pair[1] = 0u;
 }
 
 // x_hat = (-1)^s * elem * S_class (Eq. 1), times the tensor-wise scale tensor_pair[0] when that pointer is not null
@@ -470,11 +507,15 @@ hipError_t launch_dequantize(int scale_kind, bool asym, int64_t group_size, cons
 hipError_t launch_tensor_scale(const uint16_t* x, int64_t rows, int64_t K, int64_t row_stride, float* pair,
                                hipStream_t s) {
   uint32_t* acc = reinterpret_cast<uint32_t*>(pair);
+  const int64_t chunks_per_row = K / 8, total = rows * chunks_per_row;
+  if (rows * K <= kAmaxOneGroup) {
+    hipLaunchKernelGGL(tensor_scale_kernel<true>, dim3(1), dim3(1024), 0, s, x, total, chunks_per_row, row_stride, acc);
+    return hipGetLastError();
+  }
   hipLaunchKernelGGL(tensor_amax_init_kernel, dim3(1), dim3(1), 0, s, acc);
-  // 8 workgroups per CU, grid-stride: few atomics on the one accumulator
-  const int amax_blocks = grid_for(rows * (K / 8)) < 2048 ? grid_for(rows * (K / 8)) : 2048;
-  hipLaunchKernelGGL(tensor_amax_kernel, dim3(amax_blocks), dim3(256), 0, s, x, rows, K, row_stride, acc);
-  hipLaunchKernelGGL(tensor_scale_finalize_kernel, dim3(1), dim3(1), 0, s, pair);
+  const int64_t groups = (total + 8 * 1024 - 1) / (8 * 1024);
+  hipLaunchKernelGGL(tensor_scale_kernel<false>, dim3((unsigned)(groups < kAmaxGroups ? groups : kAmaxGroups)), dim3(1024), 0, s, x, total,
+                     chunks_per_row, row_stride, acc);
   return hipGetLastError();
 }
 

@@ -52,6 +52,21 @@ def test_tensor_scale_pair(gain):
     assert got[0] == want[0] and got[1] == want[1]
 
 
+@pytest.mark.parametrize("rows,K", [(1, 8), (3, 8200), (64, 4096), (65, 4096), (1, 8 * 40000), (2100, 4096)])
+def test_tensor_scale_on_both_sides_of_one_workgroup(rows, K):
+    """Up to 2^18 elements are one workgroup's, more are many: the maximum at the first element, the last, and in between,
+    the pair left over from a larger maximum before; several times, since nothing may depend on what the pair held."""
+    x = synth.activations(rows, K, seed=rows, n_outlier=1, outlier_gain=2.0)
+    pair = torch.full((2,), 3.0e38, device="cuda")
+    for at in (0, rows * K - 1, rows * K // 2, 0):
+        y = x.copy()
+        y.reshape(-1)[at] = 0xC3FA  # -500: larger than anything drawn
+        binding.tensor_scale(G.to_dev_bf16(y), out=pair)
+        want = ref.tensor_scale(y)
+        got = pair.cpu().numpy()
+        assert got[0] == want[0] and got[1] == want[1]
+
+
 def test_tensor_scale_of_extreme_tensors():
     z = np.zeros((4, 64), np.uint16)
     z[2, 9] = 0x8001   # one negative subnormal: the scale clamps at 2^-96
