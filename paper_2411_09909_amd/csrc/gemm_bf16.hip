@@ -43,18 +43,25 @@ size_t bf16_panel_bytes(int64_t rows, int64_t K) { return (size_t)(round_up(rows
 // s % 4 of group 4 h + s / 4 instead of the 8 elements h of the 16 that follow 16 s: a lane half then draws all its
 // 16 k-steps from one contiguous half (64 bytes of codes) of the block. The few-rows kernel reads its B operand in
 // that order straight from the packed codes and needs A to match (a product sums over k in any order).
-template <int SCALE_KIND, bool ASYM, bool F16, bool PERMUTE = false, bool HALF_LINE = false>
-__global__ __launch_bounds__(256) void expand_kernel(const uint8_t* __restrict__ codes,
-                                                     const uint8_t* __restrict__ scales, int64_t R, int64_t K,
-                                                     int64_t Rp, int64_t Kp, int gs_log2,
-                                                     uint16_t* __restrict__ panel) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int64_t rb = blockIdx.y;
-  const int64_t slice = (int64_t)blockIdx.x * 4 + wave;  // 64-wide K slice
+// One operand of an expansion: codes and scales of [batch][R][K] -> panel [batch][Rp / 32][Kp / 16] fragments.
+struct ExpandJob {
+  const uint8_t* codes;
+  const uint8_t* scales;
+  uint16_t* panel;
+  int64_t R, K, Rp, Kp;
+};
+
+// One wave's share: 64-wide slice `slice` of row block rb of batch entry b.
+template <int SCALE_KIND, bool ASYM, bool F16, bool PERMUTE, bool HALF_LINE>
+__device__ __forceinline__ void expand_slice(const ExpandJob& job, int gs_log2, int64_t slice, int64_t rb, int64_t b) {
+  const uint8_t* codes = job.codes;
+  const uint8_t* scales = job.scales;
+  uint16_t* panel = job.panel;
+  const int64_t R = job.R, K = job.K, Rp = job.Rp, Kp = job.Kp;
+  const int lane = threadIdx.x & 63;
   if (slice * 64 >= Kp) return;
   const int64_t r = rb * 32 + (lane & 31);
   const int64_t g = slice * 2 + (lane >> 5);  // the lane's block of 32 elements
-  const int64_t b = blockIdx.z;
   uint32_t w[4] = {0, 0, 0, 0};
   // scales of the first and of the second 16 elements of the block (they differ only for groups of 16)
   float s_pos[2] = {0.f, 0.f}, s_neg[2] = {0.f, 0.f};
@@ -117,6 +124,22 @@ __global__ __launch_bounds__(256) void expand_kernel(const uint8_t* __restrict__
       out = make_uint4(o[t][0], o[t][1], o[t][2], o[t][3]);
     *reinterpret_cast<uint4*>(dst + (t >> 1) * 512 + ((t & 1) * 32 + (lane & 31)) * 8) = out;
   }
+}
+
+template <int SCALE_KIND, bool ASYM, bool F16, bool PERMUTE = false, bool HALF_LINE = false>
+__global__ __launch_bounds__(256) void expand_kernel(ExpandJob job, int gs_log2) {
+  expand_slice<SCALE_KIND, ASYM, F16, PERMUTE, HALF_LINE>(job, gs_log2, (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6),
+                                                          blockIdx.y, blockIdx.z);
+}
+
+// Both operands of a product in one launch: row blocks of A, then of B (same K). A launch of its own for A's expansion cost
+// the call 4 to 5 us, whatever A's size.
+template <int SCALE_KIND, bool ASYM>
+__global__ __launch_bounds__(256) void expand_pair_kernel(ExpandJob ja, ExpandJob jb, int gs_log2) {
+  const int64_t blocks_a = ja.Rp >> 5, rb = blockIdx.y;
+  const bool second = rb >= blocks_a;
+  expand_slice<SCALE_KIND, ASYM, false, false, false>(second ? jb : ja, gs_log2, (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6),
+                                                      second ? rb - blocks_a : rb, blockIdx.z);
 }
 
 // ------------------------------------------------------------------------------------------------ GEMM ------------
@@ -277,7 +300,7 @@ template <int SK, bool ASYM, bool F16 = false>
 static hipError_t launch_expand(const uint8_t* codes, const uint8_t* scales, int64_t R, int64_t K, int64_t Rp,
                                 int64_t Kp, int gs_log2, int64_t batch, uint16_t* panel, hipStream_t s) {
   hipLaunchKernelGGL((expand_kernel<SK, ASYM, F16>), dim3((unsigned)((Kp + 255) / 256), (unsigned)(Rp / 32), (unsigned)batch),
-                     dim3(256), 0, s, codes, scales, R, K, Rp, Kp, gs_log2, panel);
+                     dim3(256), 0, s, (ExpandJob{codes, scales, panel, R, K, Rp, Kp}), gs_log2);
   return hipGetLastError();
 }
 
@@ -301,17 +324,16 @@ hipError_t launch_expand_bf16(int scale_kind, bool asym, int64_t group_size, con
   if (gs_log2 < 0 || !group_divides(K, group_size) || K % 32 != 0 || Rp % 32 != 0 || Kp % 64 != 0) return hipErrorInvalidValue;
   if (!permute) return expand_dispatch(scale_kind, asym, gs_log2, codes, scales, R, K, Rp, Kp, batch, panel, s);
   const dim3 grid((unsigned)((Kp + 255) / 256), (unsigned)(Rp / 32), (unsigned)batch);
+  const ExpandJob job = {codes, scales, panel, R, K, Rp, Kp};
   auto go = [&]<int SK, bool ASYM>() {
-    hipLaunchKernelGGL((expand_kernel<SK, ASYM, false, true>), grid, dim3(256), 0, s, codes, scales, R, K, Rp, Kp,
-                       gs_log2, panel);
+    hipLaunchKernelGGL((expand_kernel<SK, ASYM, false, true>), grid, dim3(256), 0, s, job, gs_log2);
     return hipGetLastError();
   };
   if (scale_kind == kScaleE5M2) {
     // FP16 with a bias of 2^-3 (every element * scale / 8 is an FP16 number): the probabilities it is multiplied with
     // come out of the attention kernel's cast as FP16 for this scale format
     auto go16 = [&]<bool ASYM>() {
-      hipLaunchKernelGGL((expand_kernel<kScaleE5M2, ASYM, true, true>), grid, dim3(256), 0, s, codes, scales, R, K, Rp,
-                         Kp, gs_log2, panel);
+      hipLaunchKernelGGL((expand_kernel<kScaleE5M2, ASYM, true, true>), grid, dim3(256), 0, s, job, gs_log2);
       return hipGetLastError();
     };
     return asym ? go16.template operator()<true>() : go16.template operator()<false>();
@@ -325,8 +347,8 @@ hipError_t launch_expand_half_line(int scale_kind, bool asym, const uint8_t* cod
   if (K % 256 != 0 || Rp % 32 != 0) return hipErrorInvalidValue;
   const dim3 grid((unsigned)(K / 256), (unsigned)(Rp / 32), (unsigned)batch);
   auto go = [&]<int SK, bool ASYM, bool F16>() {
-    hipLaunchKernelGGL((expand_kernel<SK, ASYM, F16, false, true>), grid, dim3(256), 0, s, codes, scales, R, K, Rp, K,
-                       5, panel);
+    hipLaunchKernelGGL((expand_kernel<SK, ASYM, F16, false, true>), grid, dim3(256), 0, s,
+                       (ExpandJob{codes, scales, panel, R, K, Rp, K}), 5);
     return hipGetLastError();
   };
   if (scale_kind == kScaleE5M2)
@@ -374,12 +396,25 @@ hipError_t launch_gemm_bf16_path(int scale_kind, bool asym, int64_t group_size, 
   const int64_t Mp = round_up(M, kPanelRows), Np = round_up(N, kPanelRows), Kp = round_up(K, kPanelK);
   uint16_t* Ap = reinterpret_cast<uint16_t*>(workspace);
   const uint16_t* Bp = B_panel ? reinterpret_cast<const uint16_t*>(B_panel) : Ap + batch * Mp * Kp;
-  hipError_t e = expand_dispatch(scale_kind, asym, gs_log2, A_codes, A_scales, M, K, Mp, Kp, batch, Ap, s);
-  if (e != hipSuccess) return e;
-  if (!B_panel) {  // (a panel the caller expanded once: launch_expand_b_panel)
-    e = expand_dispatch(scale_kind, asym, gs_log2, B_codes, B_scales, N, K, Np, Kp, batch, Ap + batch * Mp * Kp, s);
-    if (e != hipSuccess) return e;
+  hipError_t e;
+  if (B_panel || (Mp + Np) / 32 > 65535) {  // (a panel the caller expanded once: launch_expand_b_panel; or a grid too tall)
+    e = expand_dispatch(scale_kind, asym, gs_log2, A_codes, A_scales, M, K, Mp, Kp, batch, Ap, s);
+    if (e == hipSuccess && !B_panel)
+      e = expand_dispatch(scale_kind, asym, gs_log2, B_codes, B_scales, N, K, Np, Kp, batch, Ap + batch * Mp * Kp, s);
+  } else {
+    const ExpandJob ja = {A_codes, A_scales, Ap, M, K, Mp, Kp}, jb = {B_codes, B_scales, Ap + batch * Mp * Kp, N, K, Np, Kp};
+    const dim3 grid((unsigned)((Kp + 255) / 256), (unsigned)((Mp + Np) / 32), (unsigned)batch);
+    auto go = [&]<int SK>() {
+      if (asym)
+        hipLaunchKernelGGL((expand_pair_kernel<SK, true>), grid, dim3(256), 0, s, ja, jb, gs_log2);
+      else
+        hipLaunchKernelGGL((expand_pair_kernel<SK, false>), grid, dim3(256), 0, s, ja, jb, gs_log2);
+      return hipGetLastError();
+    };
+    e = scale_kind == kScaleE5M2 ? go.template operator()<kScaleE5M2>()
+        : scale_kind == kScaleE4M3 ? go.template operator()<kScaleE4M3>() : go.template operator()<kScaleE8M0Floor>();
   }
+  if (e != hipSuccess) return e;
   if (timer.start && (e = hipEventRecord(timer.start, s)) != hipSuccess) return e;
   // Tile shape. 256 x 256 (4 waves of 128 x 128) has the least operand traffic and LDS reads per MFMA and is what
   // large problems use; a problem with fewer such tiles than the chip has CUs, or with one side much smaller than a
