@@ -16,14 +16,12 @@
 #include "../../include/amxfp4.h"
 #include "attention_tile.h"
 #include "cast_math.h"
+#include "dequant_regs.h"
 #include "gemm_common.h"
 
 namespace amx {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
-
 // Waves per workgroup, 32 queries each. A wave's work on a tile is one long dependent chain (fragment reads -> eight
 // chained MFMAs -> maximum, exponentials, sum, cast -> MFMAs), and the barrier of a workgroup keeps its waves in the
 // same phase of it, so what hides the chain's latencies is waves of OTHER workgroups on the same SIMD: four waves per
@@ -38,9 +36,9 @@ constexpr int kAttnQ = 32 * kAttnWaves;     // queries per workgroup
 // ... (with more waves than fragments the first ones would bring K, the others V).
 template <int SCALE_KIND, int kAttnD>
 __global__ __launch_bounds__(64 * kAttnWaves) __attribute__((amdgpu_waves_per_eu(3, 3))) void attention_fused_kernel(
-    const uint16_t* __restrict__ Qp, const uint16_t* __restrict__ Kp, const uint16_t* __restrict__ Vp,
-    float* __restrict__ out, int Sq, int Sk, int Sqp, int Skv, int kv_group, float scale_log2, int causal,
-    int merged_bf16) {
+    const uint8_t* __restrict__ Q_codes, const uint8_t* __restrict__ Q_scales, int asym, const uint16_t* __restrict__ Kp,
+    const uint16_t* __restrict__ Vp, float* __restrict__ out, int Sq, int Sk, int Sqp, int Skv, int kv_group,
+    float scale_log2, int causal, int merged_bf16) {
   static_assert(kAttnD == 128 || kAttnD == 64, "head dimension");
   // FP8-E5M2 scales: the second product runs on FP16 operands. The cast leaves the probabilities as FP16 times 2^8
   // (the scale byte is the upper byte of an FP16: a conversion and a packed multiply per pair instead of a conversion,
@@ -110,16 +108,28 @@ __global__ __launch_bounds__(64 * kAttnWaves) __attribute__((amdgpu_waves_per_eu
     }                                                                                                              \
   } while (0)
 
-  // this wave's 32 queries as the B operand of the first product: 8 k-steps over D, resident in registers
+  // this wave's 32 queries as the B operand of the first product: 8 k-steps over D, resident in registers. They are
+  // dequantized here, once, from their codes (BF16: element * scale has at most 6 significant bits); expanding Q to a
+  // panel first was a pass over memory and a launch (32 heads x 4064: 9 us of the call). Rows past Sq repeat the last one.
   bf16x8 qf[kAttnKFrags];
-  if (wave_active) {
-    const uint8_t* qsrc = reinterpret_cast<const uint8_t*>(Qp) +
-                          (((int64_t)h * (Sqp / 32) + qw / 32) * kAttnKFrags) * kFragBytes + lane_off;
+  {
+    const int q = qw + (lane & 31) < Sq ? qw + (lane & 31) : Sq - 1;
+    const int64_t row = (int64_t)h * Sq + q;
+    const u32x4* codes = reinterpret_cast<const u32x4*>(Q_codes + row * (kAttnD / 2));
+    const uint8_t* sb = Q_scales + row * (kAttnD / 32) * (asym ? 2 : 1);
 #pragma unroll
-    for (int kb = 0; kb < kAttnKFrags; ++kb) qf[kb] = *reinterpret_cast<const bf16x8*>(qsrc + kb * kFragBytes);
-  } else {
+    for (int g = 0; g < kAttnD / 32; ++g) {  // a group of 32: k-steps 2 g and 2 g + 1; lane half h takes words h, 2 + h
+      const u32x4 w = codes[g];
+      const uint32_t bp = sb[asym ? 2 * g : g], bn = asym ? sb[2 * g + 1] : bp;
+      const uint32_t s_pos = f2u(scale_value<SCALE_KIND>(bp)), s_neg = f2u(scale_value<SCALE_KIND>(bn));
 #pragma unroll
-    for (int kb = 0; kb < kAttnKFrags; ++kb) qf[kb] = __builtin_bit_cast(bf16x8, u32x4{0, 0, 0, 0});
+      for (int k = 0; k < 2; ++k) {
+        const uint32_t word = (lane >> 5) ? w[2 * k + 1] : w[2 * k];
+        qf[2 * g + k] = __builtin_bit_cast(
+            bf16x8, u32x4{dequant2_f32<true, 0>(word, s_pos, s_neg), dequant2_f32<true, 1>(word, s_pos, s_neg),
+                          dequant2_f32<true, 2>(word, s_pos, s_neg), dequant2_f32<true, 3>(word, s_pos, s_neg)});
+      }
+    }
   }
 
   f32x16 o[kAttnD / 32];
@@ -212,13 +222,13 @@ size_t attention_workspace_bytes(int64_t Hq, int64_t Hkv, int64_t Sq, int64_t Sk
 }
 
 template <int SK, int kAttnD>
-static hipError_t launch_attn(const uint16_t* Qp, const uint16_t* Kp, const uint16_t* Vp, float* out, int64_t Hq,
-                              int64_t Hkv, int64_t Sq, int64_t Sk, float scale, int causal, int merged_bf16,
+static hipError_t launch_attn(const uint8_t* Qc, const uint8_t* Qs, bool asym, const uint16_t* Kp, const uint16_t* Vp,
+                              float* out, int64_t Hq, int64_t Hkv, int64_t Sq, int64_t Sk, float scale, int causal, int merged_bf16,
                               hipStream_t s) {
   const int64_t Sqp = round_up(Sq, 32);
   const dim3 grid((unsigned)Hq, (unsigned)((Sqp + kAttnQ - 1) / kAttnQ));
-  hipLaunchKernelGGL((attention_fused_kernel<SK, kAttnD>), grid, dim3(64 * kAttnWaves), 0, s, Qp, Kp, Vp, out, (int)Sq,
-                     (int)Sk, (int)Sqp, (int)round_up(Sk, 64), (int)(Hq / Hkv), scale * 1.4426950408889634f, causal,
+  hipLaunchKernelGGL((attention_fused_kernel<SK, kAttnD>), grid, dim3(64 * kAttnWaves), 0, s, Qc, Qs, asym ? 1 : 0, Kp,
+                     Vp, out, (int)Sq, (int)Sk, (int)Sqp, (int)round_up(Sk, 64), (int)(Hq / Hkv), scale * 1.4426950408889634f, causal,
                      merged_bf16);
   return hipGetLastError();
 }
@@ -229,23 +239,17 @@ static hipError_t launch_attention_fused_d(int scale_kind, bool asym, int64_t Hq
                                   const uint8_t* K_scales, const uint8_t* V_codes, const uint8_t* V_scales, float scale,
                                   int causal, float* out, bool merged_bf16, void* workspace, hipStream_t s,
                                   const KernelTimer& timer) {
-  const int64_t Sqp = round_up(Sq, 32);
-  uint16_t* Qp = reinterpret_cast<uint16_t*>(workspace);
-  uint16_t* Kp = Qp + Hq * Sqp * kAttnD;
+  uint16_t* Kp = reinterpret_cast<uint16_t*>(workspace);
   uint16_t* Vp = Kp + Hkv * Sk * kAttnD;
-  // Q, K: rows = tokens, K = head dimension; V^T: rows = head dimension, K = keys, in the accumulator's key order
-  hipError_t e = launch_expand_bf16(scale_kind, asym, 32, Q_codes, Q_scales, Sq, kAttnD, Sqp, kAttnD, Hq, false, Qp, s);
-  if (e != hipSuccess) return e;
-  e = launch_expand_bf16(scale_kind, asym, 32, K_codes, K_scales, Sk, kAttnD, Sk, kAttnD, Hkv, false, Kp, s);
-  if (e != hipSuccess) return e;
-  e = launch_expand_bf16(scale_kind, asym, 32, V_codes, V_scales, kAttnD, Sk, kAttnD, round_up(Sk, 64), Hkv, true, Vp, s);
+  // K: rows = tokens, K = head dimension; V^T: rows = head dimension, K = keys, in the accumulator's key order
+  hipError_t e = launch_expand_kv(scale_kind, asym, K_codes, K_scales, Kp, V_codes, V_scales, Vp, Sk, kAttnD, Hkv, s);
   if (e != hipSuccess) return e;
   if (timer.start && (e = hipEventRecord(timer.start, s)) != hipSuccess) return e;
   switch (scale_kind) {
-    case kScaleE5M2: e = launch_attn<kScaleE5M2, kAttnD>(Qp, Kp, Vp, out, Hq, Hkv, Sq, Sk, scale, causal, merged_bf16, s); break;
-    case kScaleE4M3: e = launch_attn<kScaleE4M3, kAttnD>(Qp, Kp, Vp, out, Hq, Hkv, Sq, Sk, scale, causal, merged_bf16, s); break;
-    case kScaleE8M0Floor: e = launch_attn<kScaleE8M0Floor, kAttnD>(Qp, Kp, Vp, out, Hq, Hkv, Sq, Sk, scale, causal, merged_bf16, s); break;
-    case kScaleE8M0Round: e = launch_attn<kScaleE8M0Round, kAttnD>(Qp, Kp, Vp, out, Hq, Hkv, Sq, Sk, scale, causal, merged_bf16, s); break;
+    case kScaleE5M2: e = launch_attn<kScaleE5M2, kAttnD>(Q_codes, Q_scales, asym, Kp, Vp, out, Hq, Hkv, Sq, Sk, scale, causal, merged_bf16, s); break;
+    case kScaleE4M3: e = launch_attn<kScaleE4M3, kAttnD>(Q_codes, Q_scales, asym, Kp, Vp, out, Hq, Hkv, Sq, Sk, scale, causal, merged_bf16, s); break;
+    case kScaleE8M0Floor: e = launch_attn<kScaleE8M0Floor, kAttnD>(Q_codes, Q_scales, asym, Kp, Vp, out, Hq, Hkv, Sq, Sk, scale, causal, merged_bf16, s); break;
+    case kScaleE8M0Round: e = launch_attn<kScaleE8M0Round, kAttnD>(Q_codes, Q_scales, asym, Kp, Vp, out, Hq, Hkv, Sq, Sk, scale, causal, merged_bf16, s); break;
     default: return hipErrorInvalidValue;
   }
   if (e != hipSuccess) return e;

@@ -317,29 +317,42 @@ static hipError_t expand_dispatch(int scale_kind, bool asym, int gs_log2, const 
               : launch_expand<kScaleE8M0Floor, false>(codes, scales, R, K, Rp, Kp, gs_log2, batch, panel, s);
 }
 
-hipError_t launch_expand_bf16(int scale_kind, bool asym, int64_t group_size, const uint8_t* codes,
-                              const uint8_t* scales, int64_t R, int64_t K, int64_t Rp, int64_t Kp, int64_t batch,
-                              bool permute, uint16_t* panel, hipStream_t s) {
-  const int gs_log2 = group_log2(group_size);
-  if (gs_log2 < 0 || !group_divides(K, group_size) || K % 32 != 0 || Rp % 32 != 0 || Kp % 64 != 0) return hipErrorInvalidValue;
-  if (!permute) return expand_dispatch(scale_kind, asym, gs_log2, codes, scales, R, K, Rp, Kp, batch, panel, s);
-  const dim3 grid((unsigned)((Kp + 255) / 256), (unsigned)(Rp / 32), (unsigned)batch);
-  const ExpandJob job = {codes, scales, panel, R, K, Rp, Kp};
-  auto go = [&]<int SK, bool ASYM>() {
-    hipLaunchKernelGGL((expand_kernel<SK, ASYM, false, true>), grid, dim3(256), 0, s, job, gs_log2);
+// The K and V panels of an attention in one launch: a wave takes one 64-wide slice of one 32-row block, the slices of K
+// (rows = keys, along the head dimension) in front of those of V (rows = head dimension, along the keys, permuted).
+// E5M2 scales: V as FP16 with a bias of 2^-3 (every element * scale / 8 is an FP16 number): the probabilities it is
+// multiplied with come out of the attention kernel's cast as FP16 for this scale format.
+template <int SCALE_KIND, bool ASYM>
+__global__ __launch_bounds__(256) void expand_kv_kernel(ExpandJob jk, ExpandJob jv, int slices_k, int slices_v, int blocks_k) {
+  const bool is_v = (int)blockIdx.x >= blocks_k;
+  const int unit = ((int)blockIdx.x - (is_v ? blocks_k : 0)) * 4 + (int)(threadIdx.x >> 6);
+  const int per_row_block = is_v ? slices_v : slices_k, rb = unit / per_row_block, slice = unit % per_row_block;
+  if (rb >= (int)((is_v ? jv.Rp : jk.Rp) >> 5)) return;
+  if (is_v)
+    expand_slice<SCALE_KIND, ASYM, SCALE_KIND == kScaleE5M2, true, false>(jv, 5, slice, rb, blockIdx.y);
+  else
+    expand_slice<SCALE_KIND, ASYM, false, false, false>(jk, 5, slice, rb, blockIdx.y);
+}
+
+hipError_t launch_expand_kv(int scale_kind, bool asym, const uint8_t* K_codes, const uint8_t* K_scales, uint16_t* K_panel,
+                            const uint8_t* V_codes, const uint8_t* V_scales, uint16_t* V_panel, int64_t Sk,
+                            int64_t head_dim, int64_t heads, hipStream_t s) {
+  if (Sk % 32 != 0 || head_dim % 64 != 0) return hipErrorInvalidValue;
+  const int64_t Skv = round_up(Sk, 64);
+  const ExpandJob jk = {K_codes, K_scales, K_panel, Sk, head_dim, Sk, head_dim};
+  const ExpandJob jv = {V_codes, V_scales, V_panel, head_dim, Sk, head_dim, Skv};
+  const int slices_k = (int)(head_dim / 64), slices_v = (int)(Skv / 64);
+  const int blocks_k = (int)((Sk / 32 * slices_k + 3) / 4), blocks_v = (int)((head_dim / 32 * slices_v + 3) / 4);
+  const dim3 grid((unsigned)(blocks_k + blocks_v), (unsigned)heads);
+  auto go = [&]<int SK>() {
+    if (asym)
+      hipLaunchKernelGGL((expand_kv_kernel<SK, true>), grid, dim3(256), 0, s, jk, jv, slices_k, slices_v, blocks_k);
+    else
+      hipLaunchKernelGGL((expand_kv_kernel<SK, false>), grid, dim3(256), 0, s, jk, jv, slices_k, slices_v, blocks_k);
     return hipGetLastError();
   };
-  if (scale_kind == kScaleE5M2) {
-    // FP16 with a bias of 2^-3 (every element * scale / 8 is an FP16 number): the probabilities it is multiplied with
-    // come out of the attention kernel's cast as FP16 for this scale format
-    auto go16 = [&]<bool ASYM>() {
-      hipLaunchKernelGGL((expand_kernel<kScaleE5M2, ASYM, true, true>), grid, dim3(256), 0, s, job, gs_log2);
-      return hipGetLastError();
-    };
-    return asym ? go16.template operator()<true>() : go16.template operator()<false>();
-  }
-  if (scale_kind == kScaleE4M3) return asym ? go.template operator()<kScaleE4M3, true>() : go.template operator()<kScaleE4M3, false>();
-  return asym ? go.template operator()<kScaleE8M0Floor, true>() : go.template operator()<kScaleE8M0Floor, false>();
+  if (scale_kind == kScaleE5M2) return go.template operator()<kScaleE5M2>();
+  if (scale_kind == kScaleE4M3) return go.template operator()<kScaleE4M3>();
+  return go.template operator()<kScaleE8M0Floor>();  // (floor and round share the byte encoding)
 }
 
 hipError_t launch_expand_half_line(int scale_kind, bool asym, const uint8_t* codes, const uint8_t* scales, int64_t R,

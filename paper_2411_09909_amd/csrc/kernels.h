@@ -67,13 +67,12 @@ size_t bf16_panel_bytes(int64_t rows, int64_t K);
 hipError_t launch_expand_b_panel(int scale_kind, bool asym, int64_t group_size, int64_t N, int64_t K,
                                  const uint8_t* B_codes, const uint8_t* B_scales, void* panel, hipStream_t s);
 
-// BF16 fragment-major panel [batch][Rp / 32][Kp / 16][64 lanes][8] of a quantized operand (rows >= R and columns >= K
-// zero; Rp % 32 == 0, Kp % 64 == 0). permute: the key order of the fused attention kernel's V operand (gemm_bf16.hip).
-hipError_t launch_expand_bf16(int scale_kind, bool asym, int64_t group_size, const uint8_t* codes,
-                              const uint8_t* scales, int64_t R, int64_t K, int64_t Rp, int64_t Kp, int64_t batch,
-                              bool permute, uint16_t* panel, hipStream_t s);
-// (a permuted panel of an FP8-E5M2 operand is FP16 biased by 2^-3 instead of BF16: what the attention kernel's second
-// product takes for that scale format)
+// The BF16 fragment-major panels [heads][rows / 32][.. / 16][64 lanes][8] of an attention's K (rows = keys) and V^T (rows =
+// head dimension, keys in the order the fused attention kernel multiplies them, keys padded to 64 with zeros; FP8-E5M2
+// scales: FP16 biased by 2^-3 instead of BF16).
+hipError_t launch_expand_kv(int scale_kind, bool asym, const uint8_t* K_codes, const uint8_t* K_scales, uint16_t* K_panel,
+                            const uint8_t* V_codes, const uint8_t* V_scales, uint16_t* V_panel, int64_t Sk,
+                            int64_t head_dim, int64_t heads, hipStream_t s);
 
 // gemm_skinny.hip: M <= 256, K a multiple of 256, groups of 32: B dequantized in registers straight from its codes
 // (workspace: the BF16 panel of A and, with several outer K slices, the partial tiles; forced_slices: 0 = the number
@@ -101,7 +100,8 @@ hipError_t launch_gemm_stream(int scale_kind, bool asym, int64_t group_size, int
                               const uint8_t* B_scales, const float* A_tensor_pair, const float* B_tensor_pair, float* C,
                               int64_t ldc, int64_t batch, hipStream_t s, const KernelTimer& timer);
 
-// attention.hip: fused quantized attention, head dimension 128 or 64, groups of 32 (workspace: the three BF16 panels).
+// attention.hip: fused quantized attention, head dimension 128 or 64, groups of 32 (workspace: the K and V
+// panels; what it asks for still has room for one of Q, which the kernel dequantizes itself).
 // merged_bf16: out is BF16 [Sq][Hq * head_dim] (token-major) instead of FP32 [Hq][Sq][head_dim]
 size_t attention_workspace_bytes(int64_t Hq, int64_t Hkv, int64_t Sq, int64_t Sk, int64_t head_dim);
 hipError_t launch_attention_fused(int scale_kind, bool asym, int64_t Hq, int64_t Hkv, int64_t Sq, int64_t Sk,
