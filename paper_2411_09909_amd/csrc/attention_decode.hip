@@ -69,11 +69,13 @@ __device__ __forceinline__ u32x4 decode_word(uint32_t word, uint32_t byte_pos, u
 }
 
 // One row's share of a lane for the first product: the D / 4 bytes of codes of dimensions (D / 2) h .. and the scale
-// bytes of their D / 64 groups (positive, negative; equal for symmetric formats).
+// bytes of their D / 64 groups, as they were loaded: taking the bytes apart is left to where they are used, since
+// anything done to them here would wait for the load (it did, once per key tile, for most of the tile's time).
+typedef uint32_t u32_a2 __attribute__((aligned(2)));  // scale arrays are 2-byte aligned by contract
 template <int D>
 struct RowPiece {
   uint32_t word[D / 16];
-  uint32_t sp[D / 64], sn[D / 64];
+  uint32_t scales;
 };
 
 template <int D, bool ASYM>
@@ -84,20 +86,29 @@ __device__ __forceinline__ void load_row_piece(const uint8_t* __restrict__ codes
   for (int i = 0; i < D / 64; ++i) {
     const uint4 c = src[i];
     p.word[4 * i] = c.x, p.word[4 * i + 1] = c.y, p.word[4 * i + 2] = c.z, p.word[4 * i + 3] = c.w;
-    const int64_t g = row * (D / 32) + h * (D / 64) + i;
-    if constexpr (ASYM) {
-      const uint32_t pair = *reinterpret_cast<const uint16_t*>(scales + g * 2);
-      p.sp[i] = pair & 255u, p.sn[i] = pair >> 8;
-    } else {
-      p.sp[i] = p.sn[i] = scales[g];
-    }
   }
+  constexpr int kBytes = (D / 64) * (ASYM ? 2 : 1);
+  const uint8_t* sb = scales + (row * (D / 32) + h * (D / 64)) * (ASYM ? 2 : 1);
+  if constexpr (kBytes == 4)
+    p.scales = *reinterpret_cast<const u32_a2*>(sb);
+  else if constexpr (kBytes == 2)
+    p.scales = *reinterpret_cast<const uint16_t*>(sb);
+  else
+    p.scales = *sb;
 }
 
-// A V^T row's share of a lane for one key tile: the 16 bytes of codes of the tile's 32 keys and the group's scales.
+// k-step s of a row piece as 16-bit floats (group s / 4 of the piece)
+template <int SCALE_KIND, bool ASYM, int D>
+__device__ __forceinline__ u32x4 decode_step(const RowPiece<D>& p, int s) {
+  const int i = s >> 2;
+  const uint32_t pos = (p.scales >> (ASYM ? 16 * i : 8 * i)) & 255u, neg = ASYM ? (p.scales >> (16 * i + 8)) & 255u : pos;
+  return decode_word<SCALE_KIND, ASYM>(p.word[s], pos, neg);
+}
+
+// A V^T row's share of a lane for one key tile: the 16 bytes of codes of the tile's 32 keys and the group's scale bytes.
 struct VPiece {
   uint4 codes;
-  uint32_t sp, sn;
+  uint32_t scales;
 };
 
 template <bool ASYM>
@@ -105,12 +116,10 @@ __device__ __forceinline__ void load_v_piece(const uint8_t* __restrict__ codes, 
                                              int64_t row, int64_t Sk, int t, VPiece& p) {
   p.codes = *reinterpret_cast<const uint4*>(codes + row * (Sk >> 1) + (int64_t)t * 16);
   const int64_t g = row * (Sk >> 5) + t;
-  if constexpr (ASYM) {
-    const uint32_t pair = *reinterpret_cast<const uint16_t*>(scales + g * 2);
-    p.sp = pair & 255u, p.sn = pair >> 8;
-  } else {
-    p.sp = p.sn = scales[g];
-  }
+  if constexpr (ASYM)
+    p.scales = *reinterpret_cast<const uint16_t*>(scales + g * 2);
+  else
+    p.scales = scales[g];
 }
 
 constexpr int kDecodeCols = 32;  // query columns of a wave
@@ -143,17 +152,6 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) void
   // a padding column multiplies zeros and sees every key: its numbers stay finite and are never read
   const int limit = col_valid && causal ? qi + off : Sk - 1;
 
-  // this column's query as the B operand of the first product, resident in registers
-  u32x4 qf[kSteps];
-  if (col_valid) {
-    RowPiece<D> q;
-    load_row_piece<D, ASYM>(Qc, Qs, ((int64_t)g * per + col / Sq) * Sq + qi, h, q);
-#pragma unroll
-    for (int s = 0; s < kSteps; ++s) qf[s] = decode_word<SCALE_KIND, ASYM>(q.word[s], q.sp[s >> 2], q.sn[s >> 2]);
-  } else {
-#pragma unroll
-    for (int s = 0; s < kSteps; ++s) qf[s] = u32x4{0, 0, 0, 0};
-  }
   // FP16 operands carry 2^-3 each: the scores come out divided by 2^6, the second product (probabilities times 2^8, so
   // that the smallest of them, 2^-17, is a normal FP16 number, times V / 8) multiplied by 2^5
   constexpr bool kF16 = kDecodeF16<SCALE_KIND>;
@@ -194,35 +192,68 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) void
   const int v_gather1 = (lane >> 3) * v_row_bytes + (((lane & 7) ^ (4 + (lane >> 4))) << 4);  // odd load units
   const int v_read_swz = (col >> 1) & 7;  // rows 32 db + col: (row >> 1) & 7 does not depend on db
 
-  RowPiece<D> kp;
+  // the chunk of key tile t (CHUNKED): lines and scale words of all D rows
+  auto fetch_chunk = [&](int t) {
+    const int chunk = t >> 3;
+#pragma unroll
+    for (int u = 0; u < D / 8; ++u)
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(v_rsrc, (lds_ptr_t)(v_lines + u * 1024), 16, (u & 1) ? v_gather1 : v_gather0,
+                                               u * 8 * v_row_bytes + chunk * 128, 0, 0);
+#pragma unroll
+    for (int q = 0; q < kScaleParts; ++q)
+#pragma unroll
+      for (int k = 0; k < D / 64; ++k)
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(vs_rsrc, (lds_ptr_t)(v_scale_words + (q * D + 64 * k) * 4), 4,
+                                                 lane * vs_row_bytes,
+                                                 64 * k * vs_row_bytes + chunk * (kScaleParts * 4) + q * 4, 0, 0);
+  };
+
+  // Everything the first tile needs is requested at once: the query, the K rows, V.
+  RowPiece<D> kp, query;
   VPiece vp[CHUNKED ? 1 : kRowBlocks];
+  load_row_piece<D, ASYM>(Qc, Qs, ((int64_t)g * per + (col_valid ? col / Sq : 0)) * Sq + qi, h, query);
   if (t0 < t1) {
     load_row_piece<D, ASYM>(Kc, Ks, krow0 + (int64_t)t0 * 32, h, kp);
-    if constexpr (!CHUNKED) {
+    if constexpr (CHUNKED) {
+      fetch_chunk(t0);
+    } else {
 #pragma unroll
       for (int db = 0; db < kRowBlocks; ++db) load_v_piece<ASYM>(Vc, Vs, vrow0 + db * 32, Sk, t0, vp[db]);
     }
   }
+  // this column's query as the B operand of the first product, resident in registers (zeros in a padding column)
+  u32x4 qf[kSteps];
+#pragma unroll
+  for (int s = 0; s < kSteps; ++s) {
+    qf[s] = decode_step<SCALE_KIND, ASYM, D>(query, s);
+    if (!col_valid) qf[s] = u32x4{0, 0, 0, 0};
+  }
   for (int t = t0; t < t1; ++t) {
     if constexpr (CHUNKED) {
-      if (t == t0 || (t & 7) == 0) {
+      if (t != t0 && (t & 7) == 0) {
         // the wave is done with the previous chunk (its reads have returned): fetch the chunk of tile t
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-        const int chunk = t >> 3;
-#pragma unroll
-        for (int u = 0; u < D / 8; ++u)
-          __builtin_amdgcn_raw_ptr_buffer_load_lds(v_rsrc, (lds_ptr_t)(v_lines + u * 1024), 16,
-                                                   (u & 1) ? v_gather1 : v_gather0,
-                                                   u * 8 * v_row_bytes + chunk * 128, 0, 0);
-#pragma unroll
-        for (int q = 0; q < kScaleParts; ++q)
-#pragma unroll
-          for (int k = 0; k < D / 64; ++k)
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(vs_rsrc, (lds_ptr_t)(v_scale_words + (q * D + 64 * k) * 4), 4,
-                                                     lane * vs_row_bytes,
-                                                     64 * k * vs_row_bytes + chunk * (kScaleParts * 4) + q * 4, 0, 0);
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        fetch_chunk(t);
       }
+      if (t == t0 || (t & 7) == 0) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    }
+    // CHUNKED: the tile's 16 bytes of V^T rows 32 db + col and the rows' scale bytes for it. They are taken out of LDS here,
+    // before the next K rows are requested: the compiler waits for everything in flight before it reads LDS that
+    // direct-to-LDS loads write, and further down that would be the K rows (4 sequences x 8192 keys: 24.1 -> 23.6 us).
+    uint4 v_codes[CHUNKED ? kRowBlocks : 1];
+    uint32_t v_scales[CHUNKED ? kRowBlocks : 1];
+    if constexpr (CHUNKED) {
+      const int tj = t & 7;
+#pragma unroll
+      for (int db = 0; db < kRowBlocks; ++db) {
+        const int row = db * 32 + col;
+        v_codes[db] = *reinterpret_cast<const uint4*>(v_lines + row * 128 + ((tj ^ v_read_swz) << 4));
+        if constexpr (ASYM)
+          v_scales[db] = *reinterpret_cast<const uint16_t*>(v_scale_words + ((tj >> 1) * D + row) * 4 + (tj & 1) * 2);
+        else
+          v_scales[db] = v_scale_words[((tj >> 2) * D + row) * 4 + (tj & 3)];
+      }
+      __builtin_amdgcn_sched_barrier(0);
     }
     // the next tile's bytes are requested before this tile's arithmetic
     RowPiece<D> kn = kp;
@@ -244,7 +275,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) void
     for (int v = 0; v < 16; ++v) s[v] = 0.f;
 #pragma unroll
     for (int ks = 0; ks < kSteps; ++ks) {
-      const u32x4 a = decode_word<SCALE_KIND, ASYM>(kp.word[ks], kp.sp[ks >> 2], kp.sn[ks >> 2]);
+      const u32x4 a = decode_step<SCALE_KIND, ASYM, D>(kp, ks);
       s = decode_mfma<SCALE_KIND>(a, qf[ks], s);
     }
     const bool masked = causal && t * 32 + 31 > off;  // some key of the tile is masked for the first query (uniform)
@@ -260,22 +291,9 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) void
       const u32x4 b = {pb[4 * j], pb[4 * j + 1], pb[4 * j + 2], pb[4 * j + 3]};
 #pragma unroll
       for (int db = 0; db < kRowBlocks; ++db) {
-        uint32_t w0, w1, vsp, vsn;
-        if constexpr (CHUNKED) {
-          // the tile's 16 bytes of V^T row 32 db + col, 8 of them per k-step, and the row's scale bytes for the tile
-          const int tj = t & 7, row = db * 32 + col;
-          const uint2 c = *reinterpret_cast<const uint2*>(v_lines + row * 128 + ((tj ^ v_read_swz) << 4) + 8 * j);
-          w0 = c.x, w1 = c.y;
-          if constexpr (ASYM) {
-            const uint32_t pair = *reinterpret_cast<const uint16_t*>(v_scale_words + ((tj >> 1) * D + row) * 4 + (tj & 1) * 2);
-            vsp = pair & 255u, vsn = pair >> 8;
-          } else {
-            vsp = vsn = v_scale_words[((tj >> 2) * D + row) * 4 + (tj & 3)];
-          }
-        } else {
-          w0 = j ? vp[db].codes.z : vp[db].codes.x, w1 = j ? vp[db].codes.w : vp[db].codes.y;
-          vsp = vp[db].sp, vsn = vp[db].sn;
-        }
+        const uint4 c = CHUNKED ? v_codes[CHUNKED ? db : 0] : vp[CHUNKED ? 0 : db].codes;
+        const uint32_t sc = CHUNKED ? v_scales[CHUNKED ? db : 0] : vp[CHUNKED ? 0 : db].scales;
+        const uint32_t w0 = j ? c.z : c.x, w1 = j ? c.w : c.y, vsp = sc & 255u, vsn = ASYM ? sc >> 8 : vsp;
         const u32x4 a = decode_word<SCALE_KIND, ASYM>(__builtin_amdgcn_perm(w1, w0, pick), vsp, vsn);
         o[db] = decode_mfma<SCALE_KIND>(a, b, o[db]);
       }
@@ -304,16 +322,27 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) void
 
 // One wave per (kv head, column that holds a query): the exact combination of the ranges, in FP32. The lanes first
 // share out the ranges (maximum, then every range's weight 2^(m_c - m*), 0 for a range in which the query saw no key,
-// and the weighted sum of the l_c), then the head dimensions (the ranges' rows are read whole lines at a time, eight
-// ranges in flight).
+// and the weighted sum of the l_c), then the head dimensions. It is a chain of memory latencies, so the first 32 ranges'
+// rows (D / 64 floats a lane of each) are requested before anything is known about their weights, and further ones 32 at
+// a time (one sequence x 8192 keys, 64 ranges, the whole call, together with the joined requests of the first tile:
+// 19.2 -> 16.4 us).
 constexpr int kDecodeMaxSplits = 1024;
 template <int D>
 __global__ __launch_bounds__(64) void attention_decode_combine_kernel(const float* __restrict__ part,
                                                                       float* __restrict__ out, int per, int Sq,
                                                                       int nsplits) {
+  typedef float row_t __attribute__((ext_vector_type(D / 64)));
+  constexpr int kInFlight = 32;
   __shared__ float weight[kDecodeMaxSplits];
   const int lane = threadIdx.x, col = (int)blockIdx.x, g = (int)blockIdx.y;
   const float* base = part + ((int64_t)g * kDecodeCols + col) * nsplits * (D + 2);
+  row_t rows[kInFlight];
+  auto request = [&](int c0) {  // (past the last range: the last one again, not used)
+#pragma unroll
+    for (int i = 0; i < kInFlight; ++i)
+      rows[i] = *reinterpret_cast<const row_t*>(base + (int64_t)min(c0 + i, nsplits - 1) * (D + 2) + lane * (D / 64));
+  };
+  request(0);
   float mx = -__builtin_inff();
   for (int c = lane; c < nsplits; c += 64)
     if (base[(int64_t)c * (D + 2) + D + 1] > 0.f) mx = fmaxf(mx, base[(int64_t)c * (D + 2) + D]);
@@ -330,14 +359,23 @@ __global__ __launch_bounds__(64) void attention_decode_combine_kernel(const floa
   for (int d = 32; d >= 1; d >>= 1) den += __shfl_xor(den, d, 64);
   __syncthreads();
   const float inv = 1.0f / den;
-  float* dst = out + (((int64_t)g * per + col / Sq) * Sq + col % Sq) * D;
+  row_t num;
 #pragma unroll
-  for (int d = lane; d < D; d += 64) {
-    float num = 0.f;
-#pragma unroll 8
-    for (int c = 0; c < nsplits; ++c) num += weight[c] * base[(int64_t)c * (D + 2) + d];
-    dst[d] = num * inv;
+  for (int e = 0; e < D / 64; ++e) num[e] = 0.f;
+  for (int c0 = 0; c0 < nsplits; c0 += kInFlight) {
+    if (c0 != 0) request(c0);
+#pragma unroll
+    for (int i = 0; i < kInFlight; ++i) {
+      if (c0 + i < nsplits) {
+#pragma unroll
+        for (int e = 0; e < D / 64; ++e) num[e] += weight[c0 + i] * rows[i][e];
+      }
+    }
   }
+  row_t* dst = reinterpret_cast<row_t*>(out + (((int64_t)g * per + col / Sq) * Sq + col % Sq) * D);
+#pragma unroll
+  for (int e = 0; e < D / 64; ++e) num[e] *= inv;
+  dst[lane] = num;
 }
 
 bool attention_decode_supported(int64_t Hq, int64_t Hkv, int64_t Sq, int64_t head_dim) {

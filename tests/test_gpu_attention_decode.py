@@ -98,6 +98,16 @@ def test_decoding_shape_at_full_size(scale_format, asym):
     compare(out, want)
 
 
+@pytest.mark.parametrize("splits,D", [(1, 128), (31, 128), (32, 64), (33, 128), (64, 64), (65, 128)])
+def test_ranges_around_what_the_combination_keeps_in_flight(splits, D):
+    """The combination reads 32 ranges' rows at a time: one range, the last of a batch missing, whole batches, one range
+    beyond. 66 tiles of keys (no whole V chunks): the last ranges hold fewer tiles, or none."""
+    Hq, Hkv, Sq, Sk = 4, 2, 2, 66 * 32
+    q, k, v = heads(Hq, Sq, 71, d=D), heads(Hkv, Sk, 72, d=D), heads(Hkv, Sk, 73, d=D)
+    want = attention_ref.fused_attention(q, k, v, D ** -0.5, True, ref.FP8_E5M2, 1, key_splits=splits)
+    compare(gpu_decode(q, k, v, D ** -0.5, True, ref.FP8_E5M2, 1, splits), want)
+
+
 def test_invalid_arguments():
     fmt = binding.make_format(ref.FP8_E5M2, 1, 32)
     z = lambda *s: torch.zeros(s, dtype=torch.uint8, device="cuda")  # noqa: E731
