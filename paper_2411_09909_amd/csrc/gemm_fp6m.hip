@@ -89,13 +89,16 @@ __device__ __forceinline__ bool fp6_out_of_window(uint32_t sp, uint32_t sn) {
 }
 
 // ---- pass 1: which group positions hold, in some row, scales too far apart -------------------------------------------
-// grid: (ceil(G / 64), chunks of kFp6FlagRows rows of A + the same of B, batch); block 256 = 64 group positions x 4
-// row lanes: a wave reads 64 consecutive scale pairs of one row; the four row lanes are ORed through LDS.
+// grid: (ceil(G / 64), chunks of kFp6FlagRows rows of A + the same of B, batch); block 1024 = 64 group positions x 16
+// row lanes: a wave reads 64 consecutive scale pairs of one row; the row lanes are ORed through LDS. There are few
+// workgroups (98 for 1777 x 28672), so the time is the chain of a lane's loads:
+// with 4 row lanes it took 7.6 us, with 16 and all of a lane's loads in flight 5.2.
 // flags: [batch][chunk][G] bytes, A's chunks then B's.
-__global__ __launch_bounds__(256) void fp6_flag_kernel(const uint8_t* __restrict__ As, const uint8_t* __restrict__ Bs,
+constexpr int kFp6FlagLanes = 16;
+__global__ __launch_bounds__(64 * kFp6FlagLanes) void fp6_flag_kernel(const uint8_t* __restrict__ As, const uint8_t* __restrict__ Bs,
                                                        int64_t M, int64_t N, int64_t G, int chunks_a, int chunks_b,
                                                        uint8_t* __restrict__ flags) {
-  __shared__ uint32_t any_lane[4][64];
+  __shared__ uint32_t any_lane[kFp6FlagLanes][64];
   const bool second = (int)blockIdx.y >= chunks_a;
   const int chunk = (int)blockIdx.y - (second ? chunks_a : 0);
   const int64_t b = blockIdx.z, R = second ? N : M;
@@ -105,21 +108,28 @@ __global__ __launch_bounds__(256) void fp6_flag_kernel(const uint8_t* __restrict
   const int64_t g = (int64_t)blockIdx.x * 64 + gx;
   uint32_t any = 0;
   if (g < G) {
-#pragma unroll 8
-    for (int64_t r = r0 + ry; r < r1; r += 4) {
-      const uint32_t s = src[r * G + g];
-      any |= fp6_out_of_window(s & 255u, s >> 8) ? 1u : 0u;
+    uint32_t s[kFp6FlagRows / kFp6FlagLanes];
+#pragma unroll
+    for (int i = 0; i < kFp6FlagRows / kFp6FlagLanes; ++i) {
+      const int64_t r = r0 + ry + i * kFp6FlagLanes;
+      s[i] = r < r1 ? src[r * G + g] : 0u;  // (0: a group of two dropped classes needs no split)
     }
+#pragma unroll
+    for (int i = 0; i < kFp6FlagRows / kFp6FlagLanes; ++i) any |= fp6_out_of_window(s[i] & 255u, s[i] >> 8) ? 1u : 0u;
   }
   any_lane[ry][gx] = any;
   __syncthreads();
-  if (ry == 0 && g < G)
-    flags[(b * (chunks_a + chunks_b) + blockIdx.y) * G + g] =
-        (uint8_t)(any_lane[0][gx] | any_lane[1][gx] | any_lane[2][gx] | any_lane[3][gx]);
+  if (ry == 0 && g < G) {
+#pragma unroll
+    for (int i = 1; i < kFp6FlagLanes; ++i) any |= any_lane[i][gx];
+    flags[(b * (chunks_a + chunks_b) + blockIdx.y) * G + g] = (uint8_t)any;
+  }
 }
 
 // ---- pass 2: where every group lands in the lengthened K ---------------------------------------------------------------
-// grid: (1, 1, batch); block 256. plan (per batch entry): pos[G + 1] words (first 32-block of group g; pos[G] = total
+// grid: (1, 1, batch); block 1024 (one group position per thread up to K = 32768: a single workgroup's chain of memory
+// latencies is all this pass is; 256 threads
+// took 7.8 us for 1777 x 28672 on prepared weights, this 4.8). plan (per batch entry): pos[G + 1] words (first 32-block of group g; pos[G] = total
 // blocks), then G bytes of split flags (bit 0: A's position is split, bit 1: B's), then - word aligned - the number
 // of K steps (total blocks / 2 rounded up to a multiple of kFp6StepPad).
 // With a prepared B (prepared_plan: the plan B's own passes left, pos and split of B alone): B's flags come from that
@@ -127,11 +137,12 @@ __global__ __launch_bounds__(256) void fp6_flag_kernel(const uint8_t* __restrict
 // lengthened K, the block i of B's prepared panel that stands there (zero-padding blocks: block 0, against A's zeros),
 // as the byte offset of its 16-byte part within a row block of the panel, (i / 2) * 1536 + (i % 2) * 512, with i % 2
 // in bit 0 (its 8-byte part lies at (i / 2) * 1536 + 1024 + (i % 2) * 256).
-__global__ __launch_bounds__(256) void fp6_plan_kernel(const uint8_t* __restrict__ flags, int64_t G, int chunks_a,
+constexpr int kFp6PlanThreads = 1024;
+__global__ __launch_bounds__(kFp6PlanThreads) void fp6_plan_kernel(const uint8_t* __restrict__ flags, int64_t G, int chunks_a,
                                                        int chunks_b, int64_t plan_stride, int64_t steps_offset,
                                                        uint8_t* __restrict__ plan_base,
                                                        const uint8_t* __restrict__ prepared_plan, int64_t table_offset) {
-  __shared__ uint32_t part[256];
+  __shared__ uint32_t part[kFp6PlanThreads / 64];  // the waves' totals
   __shared__ uint32_t totals[2];  // blocks in use, blocks after padding to whole K steps
   const int64_t b = blockIdx.z;
   const uint8_t* fl = flags + b * (chunks_a + chunks_b) * G;
@@ -142,39 +153,41 @@ __global__ __launch_bounds__(256) void fp6_plan_kernel(const uint8_t* __restrict
   // OR over the row chunks, all threads side by side, into LDS: one byte per group position (bit 0: A, bit 1: B)
   __shared__ uint32_t gathered[(1 << 15) / 4];  // K <= 2^20: at most 2^15 group positions
   const int64_t words = (G + 3) / 4;
-  for (int64_t w = threadIdx.x; w < words; w += 256) gathered[w] = 0;
+  const int64_t per = (G + kFp6PlanThreads - 1) / kFp6PlanThreads, g0 = threadIdx.x * per, g1 = g0 + per < G ? g0 + per : G;
+  // a prepared B's flag of this thread's first position and its place in the panel, requested before anything else
+  const uint8_t* split_b = prepared_plan + (G + 1) * 4;
+  const uint32_t* pos_b = reinterpret_cast<const uint32_t*>(prepared_plan);
+  const uint32_t first_split = prepared_plan && g0 < G ? split_b[g0] : 0u, first_pos = prepared_plan && g0 < G ? pos_b[g0] : 0u;
+  for (int64_t w = threadIdx.x; w < words; w += kFp6PlanThreads) gathered[w] = 0;
   __syncthreads();
   const int64_t total = (int64_t)(chunks_a + chunks_b) * G;
   if ((G & 3) == 0) {  // four flags per load
     const uint32_t* fl4 = reinterpret_cast<const uint32_t*>(fl);
-    for (int64_t idx0 = threadIdx.x; idx0 < total / 4; idx0 += 8 * 256) {  // eight loads in flight per thread
+    for (int64_t idx0 = threadIdx.x; idx0 < total / 4; idx0 += 8 * kFp6PlanThreads) {  // eight loads in flight per thread
       uint32_t v[8];
 #pragma unroll
-      for (int u = 0; u < 8; ++u) v[u] = idx0 + u * 256 < total / 4 ? fl4[idx0 + u * 256] : 0u;
+      for (int u = 0; u < 8; ++u) v[u] = idx0 + u * kFp6PlanThreads < total / 4 ? fl4[idx0 + u * kFp6PlanThreads] : 0u;
 #pragma unroll
       for (int u = 0; u < 8; ++u) {
-        const int64_t idx = idx0 + u * 256;
+        const int64_t idx = idx0 + u * kFp6PlanThreads;
         if (v[u]) atomicOr(&gathered[idx % words], idx / words < chunks_a ? v[u] : v[u] << 1);
       }
     }
   } else {
-    for (int64_t idx = threadIdx.x; idx < total; idx += 256)
+    for (int64_t idx = threadIdx.x; idx < total; idx += kFp6PlanThreads)
       if (fl[idx]) atomicOr(&gathered[(idx % G) >> 2], (idx / G < chunks_a ? 1u : 2u) << (8 * (idx % G & 3)));
   }
   __syncthreads();
   if (prepared_plan) {  // B's flags: bit 1 of its own plan's split bytes
-    const uint8_t* split_b = prepared_plan + (G + 1) * 4;
-    for (int64_t g = threadIdx.x; g < G; g += 256)
-      if (split_b[g] & 2u) atomicOr(&gathered[g >> 2], 2u << (8 * (g & 3)));
+    for (int64_t g = g0; g < g1; ++g)
+      if ((g == g0 ? first_split : split_b[g]) & 2u) atomicOr(&gathered[g >> 2], 2u << (8 * (g & 3)));
     __syncthreads();
   }
   auto flags_of = [&](int64_t g) { return (gathered[g >> 2] >> (8 * (g & 3))) & 3u; };
-  for (int64_t g = threadIdx.x; g < G; g += 256) split[g] = (uint8_t)flags_of(g);
-  const int64_t per = (G + 255) / 256, g0 = threadIdx.x * per, g1 = g0 + per < G ? g0 + per : G;
+  for (int64_t g = threadIdx.x; g < G; g += kFp6PlanThreads) split[g] = (uint8_t)flags_of(g);
   uint32_t sum = 0;
   for (int64_t g = g0; g < g1; ++g) sum += (1u + (flags_of(g) & 1u)) * (1u + (flags_of(g) >> 1));
-  // exclusive scan of the 256 partial sums: within each wave by lane shifts, then the four waves' totals (a serial
-  // scan by one thread is a chain of 256 dependent LDS accesses, 9 of this pass's 10 microseconds)
+  // exclusive scan of the threads' partial sums: within each wave by lane shifts, then the waves' totals
   uint32_t incl = sum;
 #pragma unroll
   for (int d = 1; d < 64; d <<= 1) {
@@ -185,7 +198,7 @@ __global__ __launch_bounds__(256) void fp6_plan_kernel(const uint8_t* __restrict
   __syncthreads();
   uint32_t before = 0, all = 0;
 #pragma unroll
-  for (int w = 0; w < 4; ++w) {
+  for (int w = 0; w < kFp6PlanThreads / 64; ++w) {
     if (w < (int)(threadIdx.x >> 6)) before += part[w];
     all += part[w];
   }
@@ -197,13 +210,12 @@ __global__ __launch_bounds__(256) void fp6_plan_kernel(const uint8_t* __restrict
   }
   __syncthreads();
   uint32_t run = before + incl - sum;
-  const uint32_t* pos_b = reinterpret_cast<const uint32_t*>(prepared_plan);
   uint32_t* table = reinterpret_cast<uint32_t*>(plan + table_offset);
   for (int64_t g = g0; g < g1; ++g) {
     pos[g] = run;
     const uint32_t fa = flags_of(g) & 1u, fb = flags_of(g) >> 1;
     if (prepared_plan) {  // A holds each sign class for as many blocks as B alternates: (b+, b-, b+, b-)
-      const uint32_t b0 = pos_b[g];
+      const uint32_t b0 = g == g0 ? first_pos : pos_b[g];
       for (uint32_t e = 0; e < (1u + fa) * (1u + fb); ++e) {
         const uint32_t i = b0 + (fb ? (e & 1u) : 0u);  // block i of B's panel: step i / 2, lanes 32 (i % 2) ..
         table[run + e] = (i >> 1) * (uint32_t)kFp6FragBytes + (i & 1u) * 512u + (i & 1u);
@@ -212,7 +224,7 @@ __global__ __launch_bounds__(256) void fp6_plan_kernel(const uint8_t* __restrict
     run += (1u + fa) * (1u + fb);
   }
   if (prepared_plan)  // the zero blocks that pad K, and the 17 stages the kernel's table reads may run past the end
-    for (uint32_t e = totals[0] + threadIdx.x; e < totals[1] + 34; e += 256) table[e] = 0;
+    for (uint32_t e = totals[0] + threadIdx.x; e < totals[1] + 34; e += kFp6PlanThreads) table[e] = 0;
 }
 
 // ---- pass 3: the merge ---------------------------------------------------------------------------------------------------
@@ -226,22 +238,30 @@ __device__ __forceinline__ void fp6_lut(int shift, uint32_t& lo, uint32_t& hi) {
 }
 
 // The 32 codes of a group (four words of eight nibbles) -> six words of 32 six-bit elements (element p in bits
-// 6 p .. 6 p + 5), through the two classes' pattern tables: a byte permute looks up four elements at a time.
+// 6 p .. 6 p + 5), through the two classes' pattern tables: a byte permute looks up four elements at a time, the even and
+// the odd ones of a word. The pass is bound by these instructions as much as by memory, hence no multiplication for the
+// sign masks (a permute turns selector bytes 0C / 0D into 00 / FF) and fields closed up with a shift and a bit select.
 __device__ __forceinline__ void fp6_convert(const uint32_t (&codes)[4], uint32_t pos_lo, uint32_t pos_hi, uint32_t neg_lo,
                                             uint32_t neg_hi, uint32_t (&w)[6]) {
+  auto select = [](uint32_t mask, uint32_t x, uint32_t y) { return (x & mask) | (y & ~mask); };
+  auto lookup = [&](uint32_t nibbles, uint32_t signs) {  // the low three bits / bit 0 of every byte count
+    const uint32_t sel = nibbles & 0x07070707u;
+    const uint32_t neg = __builtin_amdgcn_perm(0u, 0u, (signs & 0x01010101u) | 0x0C0C0C0Cu);
+    return select(neg, __builtin_amdgcn_perm(neg_hi, neg_lo, sel), __builtin_amdgcn_perm(pos_hi, pos_lo, sel));
+  };
+  auto close_up = [&](uint32_t y) {  // four bytes of 6 bits -> 24 bits
+    const uint32_t pairs = select(0x003F003Fu, y, y >> 2);  // two fields of 12 bits in 16 (bits 14, 15 of the lower: stray)
+    return select(0x00000FFFu, pairs, pairs >> 4);
+  };
 #pragma unroll
   for (int half = 0; half < 2; ++half) {
     uint32_t t[4];
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      uint32_t x = (codes[2 * half + (q >> 1)] >> (16 * (q & 1))) & 0xFFFFu;  // four nibbles ...
-      x = (x | (x << 8)) & 0x00FF00FFu;
-      x = (x | (x << 4)) & 0x0F0F0F0Fu;                                       // ... one per byte
-      const uint32_t sel = x & 0x07070707u;
-      const uint32_t pp = __builtin_amdgcn_perm(pos_hi, pos_lo, sel), pn = __builtin_amdgcn_perm(neg_hi, neg_lo, sel);
-      const uint32_t is_neg = ((x >> 3) & 0x01010101u) * 0xFFu;
-      const uint32_t y = (pn & is_neg) | (pp & ~is_neg);
-      t[q] = (y & 0x3Fu) | ((y >> 2) & 0xFC0u) | ((y >> 4) & 0x3F000u) | ((y >> 6) & 0xFC0000u);  // 4 x 6 bits
+    for (int q = 0; q < 2; ++q) {
+      const uint32_t c = codes[2 * half + q];
+      const uint32_t even = lookup(c, c >> 3), odd = lookup(c >> 4, c >> 7);
+      t[2 * q] = close_up(__builtin_amdgcn_perm(odd, even, 0x05010400u));
+      t[2 * q + 1] = close_up(__builtin_amdgcn_perm(odd, even, 0x07030602u));
     }
     w[3 * half] = t[0] | (t[1] << 24);
     w[3 * half + 1] = (t[1] >> 8) | (t[2] << 16);
@@ -259,10 +279,6 @@ __device__ __forceinline__ void fp6_store_block(const uint32_t (&w)[6], uint32_t
   anchor_base[((int64_t)(step >> 2) * 64 + lane) * 4 + (step & 3u)] = (uint8_t)anchor;
 }
 
-// grid: (Rp / 32 of A + Rp / 32 of B, ceil((G + 2 kFp6StepPad) / 8), batch); block 256 = 32 rows x 8 group positions:
-// wave w takes rows 8 w .. 8 w + 7, lane = 8 * (row % 8) + group, so that a wave reads eight whole 128-byte lines of
-// codes and writes 128 contiguous bytes per fragment half. Group slots >= G write the zero blocks that pad K' to whole
-// K steps.
 struct Fp6MergeJob {
   const uint8_t* codes;
   const uint8_t* scales;
@@ -270,36 +286,13 @@ struct Fp6MergeJob {
   uint8_t* anchors;
   int64_t R, Rp;
 };
-__global__ __launch_bounds__(256) void fp6_merge_kernel(Fp6MergeJob ja, Fp6MergeJob jb, int64_t K, int64_t max_steps,
-                                                        int64_t plan_stride, int64_t steps_offset,
-                                                        const uint8_t* __restrict__ plan_base) {
-  const int64_t G = K >> 5, b = blockIdx.z;
-  const bool second = (int64_t)blockIdx.x >= ja.Rp / 32;
-  const Fp6MergeJob& job = second ? jb : ja;
-  const int64_t rb = (int64_t)blockIdx.x - (second ? ja.Rp / 32 : 0);
-  const int row_in_block = 8 * (threadIdx.x >> 6) + ((threadIdx.x & 63) >> 3);
-  const int64_t r = rb * 32 + row_in_block, g = (int64_t)blockIdx.y * 8 + (threadIdx.x & 7);
-  const uint8_t* plan = plan_base + b * plan_stride;
-  const uint32_t* pos = reinterpret_cast<const uint32_t*>(plan);
-  const uint8_t* split = plan + (G + 1) * 4;
-  const uint32_t steps = *reinterpret_cast<const uint32_t*>(plan + steps_offset);
-  uint8_t* frag_base = job.panel + (b * (job.Rp / 32) + rb) * max_steps * kFp6FragBytes;
-  uint8_t* anchor_base = job.anchors + (b * (job.Rp / 32) + rb) * (max_steps / 4) * 256;
-  uint32_t w[6] = {0, 0, 0, 0, 0, 0};
-  if (g >= G) {  // padding blocks behind the last group
-    const uint32_t p = pos[G] + (uint32_t)(g - G);
-    if (p < 2 * steps) fp6_store_block(w, 0, frag_base, anchor_base, p, row_in_block);
-    return;
-  }
-  uint32_t codes[4] = {0, 0, 0, 0};
-  uint32_t sp = 0, sn = 0;
-  if (r < job.R) {
-    const uint4 c = *reinterpret_cast<const uint4*>(job.codes + (b * job.R + r) * (K >> 1) + g * 16);
-    codes[0] = c.x, codes[1] = c.y, codes[2] = c.z, codes[3] = c.w;
-    const uint32_t sb = *reinterpret_cast<const uint16_t*>(job.scales + ((b * job.R + r) * G + g) * 2);
-    sp = sb & 255u, sn = sb >> 8;
-  }
-  const uint32_t p = pos[g], sf = split[g];
+
+// One group (codes, its scale pair in sb) of row row_in_block at position p of the lengthened K; sf: the position's split
+// flags; second: the operand is B.
+__device__ __forceinline__ void fp6_merge_group(const uint32_t (&codes)[4], uint32_t sb, uint32_t p, uint32_t sf, bool second,
+                                                uint8_t* frag_base, uint8_t* anchor_base, int row_in_block) {
+  uint32_t w[6];
+  const uint32_t sp = sb & 255u, sn = sb >> 8;
   const bool mine = second ? (sf & 2u) != 0 : (sf & 1u) != 0, other = second ? (sf & 1u) != 0 : (sf & 2u) != 0;
   uint32_t pos_lo, pos_hi, neg_lo, neg_hi;
   if (!mine) {
@@ -338,30 +331,115 @@ __global__ __launch_bounds__(256) void fp6_merge_kernel(Fp6MergeJob ja, Fp6Merge
   }
 }
 
-// Prepared B: its anchors in the order of this call's lengthened K. grid: (Np / 32, ceil(words / 4)); block 256 = four
-// anchor words x 64 lanes. Word w of lane 32 h + r holds, in byte q, the block scale of (row r, 32-block h) of K step
-// 4 w + q, i.e. of block e = 2 (4 w + q) + h, which is block table[e] of the prepared panel; steps beyond the call's
-// count get byte 0 (they multiply A's zero blocks).
-__global__ __launch_bounds__(256) void fp6_gather_anchors_kernel(const uint8_t* __restrict__ prepared_anchors,
-                                                                 int64_t prepared_words, const uint8_t* __restrict__ plan,
-                                                                 int64_t steps_offset, int64_t table_offset,
-                                                                 int64_t max_words, uint8_t* __restrict__ out) {
-  const uint32_t steps = *reinterpret_cast<const uint32_t*>(plan + steps_offset);
-  const uint32_t* table = reinterpret_cast<const uint32_t*>(plan + table_offset);
-  const int64_t rb = blockIdx.x, w = (int64_t)blockIdx.y * 4 + (threadIdx.x >> 6);
+
+// Prepared B: its anchors in the order of this call's lengthened K, in the launch of the merge (both need the plan and
+// nothing of each other). words: anchor words per row block of the output array; word w of lane 32 h + r holds, in byte
+// q, the block scale of (row r, 32-block h) of K step 4 w + q, i.e. of block e = 2 (4 w + q) + h, which is block table[e]
+// of the prepared panel. Only the words of the call's K steps are written: the product reads no others.
+struct Fp6GatherJob {
+  const uint8_t* anchors;  // of the prepared panel
+  uint8_t* out;
+  int64_t row_blocks, prepared_words, words, table_offset;
+  int chunks;  // workgroups per row block, 16 words each and as often as needed
+};
+
+// One workgroup's words: wave w takes four neighbouring ones. The table entries are the same for the whole wave.
+__device__ __forceinline__ void fp6_gather_anchors(const Fp6GatherJob& job, int64_t blk, const uint8_t* plan, uint32_t steps) {
+  const uint32_t* table = reinterpret_cast<const uint32_t*>(plan + job.table_offset);
+  const int64_t rb = blk / job.chunks;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const uint32_t slot = threadIdx.x & 63, h = slot >> 5, r = slot & 31;
-  if (w >= max_words) return;
-  const uint8_t* src = prepared_anchors + rb * prepared_words * 256;
-  uint32_t word = 0;
+  const uint8_t* src = job.anchors + rb * job.prepared_words * 256 + r * 4;
+  uint32_t* out = reinterpret_cast<uint32_t*>(job.out) + rb * job.words * 64 + slot;
+  const int nwords = (int)(steps >> 2) < (int)job.words ? (int)(steps >> 2) : (int)job.words;
+  for (int w0 = (int)(blk % job.chunks) * 16 + wave * 4; w0 < nwords; w0 += job.chunks * 16) {
+    // the entries of the K steps 4 w0 .. 4 w0 + 15, in one go (the 34 zeros behind the last one cover what lies beyond)
+    uint32_t t[32], byte[16];
 #pragma unroll
-  for (uint32_t q = 0; q < 4; ++q) {
-    const uint32_t step = (uint32_t)w * 4 + q;
-    if (step < steps) {
-      const uint32_t t = table[2 * step + h], odd = t & 1u, istep = t / (uint32_t)kFp6FragBytes;
-      word |= (uint32_t)src[((int64_t)(istep >> 2) * 64 + odd * 32 + r) * 4 + (istep & 3u)] << (8 * q);
+    for (int e = 0; e < 32; ++e) t[e] = table[8 * w0 + e];
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      uint32_t off[2];
+#pragma unroll
+      for (int hh = 0; hh < 2; ++hh) {
+        const uint32_t istep = t[2 * i + hh] / (uint32_t)kFp6FragBytes;
+        off[hh] = (istep >> 2) * 256u + (t[2 * i + hh] & 1u) * 128u + (istep & 3u);
+      }
+      byte[i] = src[h ? off[1] : off[0]];
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      if (w0 + i < nwords)
+        out[(int64_t)(w0 + i) * 64] = byte[4 * i] | byte[4 * i + 1] << 8 | byte[4 * i + 2] << 16 | byte[4 * i + 3] << 24;
+  }
+}
+
+// grid: (merge_blocks + gather row blocks x chunks, 1, batch); block 256. Merge workgroup x: row block x % (row blocks of
+// A and B) and the kFp6MergeGroups = 16 group positions from 16 * (x / row blocks) on: 32 rows x 8 positions, twice. Wave
+// w takes rows 8 w .. 8 w + 7, lane = 8 * (row % 8) + position, so that a wave reads eight whole 128-byte lines of codes
+// and writes 128 contiguous bytes per fragment half. Positions >= G write the zero blocks that pad K' to whole K steps.
+// Bound by memory: 1777 x 28672 moves 67 MB (13 us at the copy rate), the anchors of 8192 prepared rows 14 MB more; the two
+// took 21 and 21 us as launches of their own (the gather with one workgroup per four words of the longest possible K',
+// 28672 of them, most without work), together 28. With the gather's workgroups first 32; 8 positions a workgroup: 31, and
+// 8192 x 28672 alone 72 instead of 69; row-block-major order: the same.
+constexpr int kFp6MergeGroups = 16;
+__global__ __launch_bounds__(256) void fp6_merge_kernel(Fp6MergeJob ja, Fp6MergeJob jb, Fp6GatherJob gather, int64_t K,
+                                                        int64_t max_steps, int64_t plan_stride, int64_t steps_offset,
+                                                        const uint8_t* __restrict__ plan_base, unsigned merge_blocks) {
+  const int64_t G = K >> 5, b = blockIdx.z;
+  const uint8_t* plan = plan_base + b * plan_stride;
+  const uint32_t* pos = reinterpret_cast<const uint32_t*>(plan);
+  const uint8_t* split = plan + (G + 1) * 4;
+  const uint32_t steps = *reinterpret_cast<const uint32_t*>(plan + steps_offset);
+  if (blockIdx.x >= merge_blocks) {
+    fp6_gather_anchors(gather, (int64_t)(blockIdx.x - merge_blocks), plan, steps);
+    return;
+  }
+  const unsigned row_blocks = (unsigned)((ja.Rp + jb.Rp) / 32);
+  const int64_t x = blockIdx.x % row_blocks, y = blockIdx.x / row_blocks;
+  const bool second = x >= ja.Rp / 32;
+  const Fp6MergeJob& job = second ? jb : ja;
+  const int64_t rb = x - (second ? ja.Rp / 32 : 0);
+  constexpr int kPer = kFp6MergeGroups / 8;
+  const int row_in_block = 8 * (threadIdx.x >> 6) + ((threadIdx.x & 63) >> 3);
+  const int64_t r = rb * 32 + row_in_block, g0 = y * kFp6MergeGroups + (threadIdx.x & 7);
+  uint8_t* frag_base = job.panel + (b * (job.Rp / 32) + rb) * max_steps * kFp6FragBytes;
+  uint8_t* anchor_base = job.anchors + (b * (job.Rp / 32) + rb) * (max_steps / 4) * 256;
+  // everything is requested at clamped places first, so that no load waits for another
+  uint4 codes[kPer];
+  uint32_t sb[kPer], p[kPer], sf[kPer];
+  const int64_t row = b * job.R + (r < job.R ? r : job.R - 1);
+#pragma unroll
+  for (int u = 0; u < kPer; ++u) {
+    const int64_t g = g0 + 8 * u, gc = g < G ? g : G - 1;
+    codes[u] = *reinterpret_cast<const uint4*>(job.codes + row * (K >> 1) + gc * 16);
+    sb[u] = *reinterpret_cast<const uint16_t*>(job.scales + (row * G + gc) * 2);
+    p[u] = pos[g < G ? g : G], sf[u] = split[gc];
+  }
+#pragma unroll
+  for (int u = 0; u < kPer; ++u) {
+    const int64_t g = g0 + 8 * u;
+    if (g >= G) {  // padding blocks behind the last group
+      const uint32_t zero[6] = {0, 0, 0, 0, 0, 0}, q = p[u] + (uint32_t)(g - G);
+      if (q < 2 * steps) fp6_store_block(zero, 0, frag_base, anchor_base, q, row_in_block);
+    } else {
+      const bool valid = r < job.R;
+      const uint32_t c[4] = {valid ? codes[u].x : 0u, valid ? codes[u].y : 0u, valid ? codes[u].z : 0u, valid ? codes[u].w : 0u};
+      fp6_merge_group(c, valid ? sb[u] : 0u, p[u], sf[u], second, frag_base, anchor_base, row_in_block);
     }
   }
-  reinterpret_cast<uint32_t*>(out)[(rb * max_words + w) * 64 + slot] = word;
+}
+
+// Merges either operand (a job without rows: none) and, where gather has row blocks, puts a prepared operand's anchors in order.
+static hipError_t launch_fp6_merge(const Fp6MergeJob& ja, const Fp6MergeJob& jb, const Fp6GatherJob& gather, int64_t K,
+                                   int64_t max_steps, int64_t plan_stride, int64_t steps_offset, const uint8_t* plan,
+                                   int64_t batch, hipStream_t s) {
+  const int64_t row_blocks = (ja.Rp + jb.Rp) / 32;
+  const int64_t merge_blocks = row_blocks * (((K >> 5) + 2 * kFp6StepPad + kFp6MergeGroups - 1) / kFp6MergeGroups);
+  const int64_t gather_blocks = gather.row_blocks * gather.chunks;
+  hipLaunchKernelGGL(fp6_merge_kernel, dim3((unsigned)(gather_blocks + merge_blocks), 1, (unsigned)batch), dim3(256), 0, s, ja, jb, gather, K,
+                     max_steps, plan_stride, steps_offset, plan, (unsigned)merge_blocks);
+  return hipGetLastError();
 }
 
 // ---- the GEMM ------------------------------------------------------------------------------------------------------------
@@ -642,15 +720,11 @@ hipError_t launch_gemm_fp6m_path(int64_t M, int64_t N, int64_t K, const uint8_t*
   const int64_t plan_stride = fp6_plan_bytes(K), steps_offset = round_up((G + 1) * 4 + G, 4);
   // (the flag array of one batch entry is (chunks_a + chunks_b) * G bytes; entries lie back to back)
   hipLaunchKernelGGL(fp6_flag_kernel, dim3((unsigned)((G + 63) / 64), (unsigned)(chunks_a + chunks_b), (unsigned)batch),
-                     dim3(256), 0, s,
-                     A_scales, B_scales, M, N, G, chunks_a, chunks_b, flags);
-  hipLaunchKernelGGL(fp6_plan_kernel, dim3(1, 1, (unsigned)batch), dim3(256), 0, s, flags, G, chunks_a, chunks_b,
+                     dim3(64 * kFp6FlagLanes), 0, s, A_scales, B_scales, M, N, G, chunks_a, chunks_b, flags);
+  hipLaunchKernelGGL(fp6_plan_kernel, dim3(1, 1, (unsigned)batch), dim3(kFp6PlanThreads), 0, s, flags, G, chunks_a, chunks_b,
                      plan_stride, steps_offset, plan, static_cast<const uint8_t*>(nullptr), (int64_t)0);
   const Fp6MergeJob ja = {A_codes, A_scales, Ap, Asc, M, Mp}, jb = {B_codes, B_scales, Bp, Bsc, N, Np};
-  hipLaunchKernelGGL(fp6_merge_kernel,
-                     dim3((unsigned)((Mp + Np) / 32), (unsigned)((G + 2 * kFp6StepPad + 7) / 8), (unsigned)batch),
-                     dim3(256), 0, s, ja, jb, K, max_steps, plan_stride, steps_offset, plan);
-  hipError_t e = hipGetLastError();
+  hipError_t e = launch_fp6_merge(ja, jb, Fp6GatherJob{}, K, max_steps, plan_stride, steps_offset, plan, batch, s);
   if (e != hipSuccess) return e;
   using Cfg = TileCfg<2, 2, 4, 4>;
   const int tiles_m = (int)((M + Cfg::kTileM - 1) / Cfg::kTileM), tiles_n = (int)((N + Cfg::kTileN - 1) / Cfg::kTileN);
@@ -683,14 +757,12 @@ hipError_t launch_fp6m_prepare_b(int64_t N, int64_t K, const uint8_t* B_codes, c
   uint8_t* flags = plan + fp6_plan_bytes(K);
   const int chunks_b = (int)((N + kFp6FlagRows - 1) / kFp6FlagRows);
   const int64_t steps_offset = round_up((G + 1) * 4 + G, 4);
-  hipLaunchKernelGGL(fp6_flag_kernel, dim3((unsigned)((G + 63) / 64), (unsigned)chunks_b, 1), dim3(256), 0, s,
+  hipLaunchKernelGGL(fp6_flag_kernel, dim3((unsigned)((G + 63) / 64), (unsigned)chunks_b, 1), dim3(64 * kFp6FlagLanes), 0, s,
                      static_cast<const uint8_t*>(nullptr), B_scales, (int64_t)0, N, G, 0, chunks_b, flags);
-  hipLaunchKernelGGL(fp6_plan_kernel, dim3(1, 1, 1), dim3(256), 0, s, flags, G, 0, chunks_b, fp6_plan_bytes(K),
+  hipLaunchKernelGGL(fp6_plan_kernel, dim3(1, 1, 1), dim3(kFp6PlanThreads), 0, s, flags, G, 0, chunks_b, fp6_plan_bytes(K),
                      steps_offset, plan, static_cast<const uint8_t*>(nullptr), (int64_t)0);
   const Fp6MergeJob none = {nullptr, nullptr, nullptr, nullptr, 0, 0}, jb = {B_codes, B_scales, Bp, Bsc, N, Np};
-  hipLaunchKernelGGL(fp6_merge_kernel, dim3((unsigned)(Np / 32), (unsigned)((G + 2 * kFp6StepPad + 7) / 8), 1), dim3(256), 0,
-                     s, none, jb, K, b_steps, fp6_plan_bytes(K), steps_offset, plan);
-  return hipGetLastError();
+  return launch_fp6_merge(none, jb, Fp6GatherJob{}, K, b_steps, fp6_plan_bytes(K), steps_offset, plan, 1, s);
 }
 
 hipError_t launch_gemm_fp6m_prepared(int64_t M, int64_t N, int64_t K, const uint8_t* A_codes, const uint8_t* A_scales,
@@ -709,17 +781,14 @@ hipError_t launch_gemm_fp6m_prepared(int64_t M, int64_t N, int64_t K, const uint
   const int chunks_a = (int)((M + kFp6FlagRows - 1) / kFp6FlagRows);
   const int64_t plan_stride = fp6_plan_bytes(K) + fp6_table_bytes(K), steps_offset = round_up((G + 1) * 4 + G, 4);
   const int64_t table_offset = fp6_table_offset(K);
-  hipLaunchKernelGGL(fp6_flag_kernel, dim3((unsigned)((G + 63) / 64), (unsigned)chunks_a, 1), dim3(256), 0, s, A_scales,
+  hipLaunchKernelGGL(fp6_flag_kernel, dim3((unsigned)((G + 63) / 64), (unsigned)chunks_a, 1), dim3(64 * kFp6FlagLanes), 0, s, A_scales,
                      static_cast<const uint8_t*>(nullptr), M, (int64_t)0, G, chunks_a, 0, flags);
-  hipLaunchKernelGGL(fp6_plan_kernel, dim3(1, 1, 1), dim3(256), 0, s, flags, G, chunks_a, 0, plan_stride, steps_offset, plan,
+  hipLaunchKernelGGL(fp6_plan_kernel, dim3(1, 1, 1), dim3(kFp6PlanThreads), 0, s, flags, G, chunks_a, 0, plan_stride, steps_offset, plan,
                      plan_b, table_offset);
   const Fp6MergeJob ja = {A_codes, A_scales, Ap, Asc, M, Mp}, none = {nullptr, nullptr, nullptr, nullptr, 0, 0};
-  hipLaunchKernelGGL(fp6_merge_kernel, dim3((unsigned)(Mp / 32), (unsigned)((G + 2 * kFp6StepPad + 7) / 8), 1), dim3(256), 0,
-                     s, ja, none, K, max_steps, plan_stride, steps_offset, plan);
-  const int64_t max_words = max_steps / 4;
-  hipLaunchKernelGGL(fp6_gather_anchors_kernel, dim3((unsigned)(Np / 32), (unsigned)((max_words + 3) / 4)), dim3(256), 0, s,
-                     Bsc_prepared, b_steps / 4, plan, steps_offset, table_offset, max_words, Bsc);
-  hipError_t e = hipGetLastError();
+  // (chunks: the words of a K of which a few positions are split; more are done in further turns)
+  const Fp6GatherJob gather = {Bsc_prepared, Bsc, Np / 32, b_steps / 4, max_steps / 4, table_offset, (int)(G / 128 + 1)};
+  hipError_t e = launch_fp6_merge(ja, none, gather, K, max_steps, plan_stride, steps_offset, plan, 1, s);
   if (e != hipSuccess) return e;
   using Cfg = TileCfg<2, 2, 4, 4>;
   const int tiles_m = (int)((M + Cfg::kTileM - 1) / Cfg::kTileM), tiles_n = (int)((N + Cfg::kTileN - 1) / Cfg::kTileN);

@@ -118,6 +118,32 @@ def test_prepared_fp6_weights_with_split_positions(gaps_a, gaps_b):
     assert G.rel_fro(got.cpu().numpy(), ref.gemm(ac, as_, bc, bs, 32, ref.E8M0_FLOOR, 1)) <= 2e-6
 
 
+@pytest.mark.parametrize("M,N,K,gaps_a,gaps_b", [
+    (300, 70, 32 * 256, (6, 7), (9, 8)),             # every position split in both: the anchors' gather takes several turns
+    (600, 33, 32 * 1030, (0, 6, 3), (5, 7, 0, 1)),   # more positions than the plan pass has threads, a ragged row chunk
+    (257, 290, 32 * 17, (0, 3, 8), (2, 6)),          # the merge's second half of positions partly beyond K
+])
+def test_prepared_fp6_weights_at_the_edges_of_the_small_passes(M, N, K, gaps_a, gaps_b):
+    """The passes that prepare the merged FP6 product: flags per 256 rows, the plan, the merge and the gather of B's
+    anchors. The same bits as the unprepared product, and the oracle to FP32 accumulation accuracy: K' products of exact
+    operands, each rounding at most 2^-24 of a partial sum, random in sign: 2^-24 sqrt(4 K) = 2.2e-5 at the longest K'
+    relative to the largest partial sums, which the norm of C is no smaller than by much; 1e-5 (measured below 1e-6)."""
+    from tests.test_gpu_fp6_merged import hand_made
+    rng = np.random.default_rng(13)
+    ac, as_ = hand_made(M, K, rng, gaps_a)
+    bc, bs = hand_made(N, K, rng, gaps_b)
+    fmt = binding.make_format(ref.E8M0_FLOOR, 1, 32)
+    dac, das, dbc, dbs = (G.to_dev_u8(t) for t in (ac, as_, bc, bs))
+    prepared = binding.prepare_weights(fmt, dbc, dbs)
+    plain = binding.gemm(fmt, dac, das, dbc, dbs, options=binding.gemm_options(few_rows=-1))
+    got = binding.gemm_prepared(fmt, dac, das, torch.zeros_like(dbc), dbs, prepared)
+    torch.cuda.synchronize()
+    assert torch.equal(got.view(torch.int32), plain.view(torch.int32))
+    err = G.rel_fro(got.cpu().numpy(), ref.gemm(ac, as_, bc, bs, 32, ref.E8M0_FLOOR, 1))
+    print("relative error %.3g" % err)
+    assert err <= 1e-5
+
+
 @pytest.mark.parametrize("scale,asym", [(ref.FP8_E5M2, 1), (ref.E8M0_FLOOR, 1), (ref.E8M0_FLOOR, 0)])
 def test_prepared_gated_gemm(scale, asym):
     """amxfp4_gemm_silu_mul_prepared against the plain gated GEMM: the same bits."""
