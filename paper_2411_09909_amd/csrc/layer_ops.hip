@@ -176,60 +176,83 @@ __global__ __launch_bounds__(256) void split_heads_rope_kernel(const float* __re
 }
 
 // split_heads_rope_kernel (rotate) followed by the cast of its result along the head dimension, in one pass: the
-// rotated BF16 heads are never written. One thread per (token, run of 8 dimensions d0 .. d0 + 7 below head_dim / 2)
-// and chunk of kRopeHeads heads: it forms the 8 outputs at d0 .. and the 8 at d0 + head_dim / 2 .. (they share their
-// angles), each run is one lane's share of a group of 32, and the four neighbouring threads of a group exchange their
-// extrema as the cast kernel's lanes do (cast_core.h). head_dim % 64 == 0, so a group never straddles the two halves
-// and the threads of a token are a whole number of quads. Same arithmetic as the two separate kernels: same bits.
+// rotated BF16 heads are never written. A workgroup takes kRopeTokens tokens and kRopeQuantizeHeads heads (blockIdx.y).
+// The angles of a token do not depend on the head: the workgroup's threads first work out one FP64 sine and cosine
+// each (two for head_dim > 128) and leave them in LDS, while the loads of their first items are under way. Then they
+// share out the items (token, head, run of 8 dimensions d0 .. d0 + 7 below head_dim / 2): an item is the 8 outputs at
+// d0 .. and the 8 at d0 + head_dim / 2 .., each run one lane's share of a group of 32, and the four neighbouring threads
+// of a group exchange their extrema as the cast kernel's lanes do (cast_core.h). head_dim % 64 == 0, so a group never
+// straddles the two halves and the items of a token and head are a whole number of quads. Same arithmetic as the two
+// separate kernels: same bits.
+// What bounds it is the FP64 trigonometry's chain, then memory: with every thread working out all 8 angles of its run
+// and walking 8 heads, 1504 tokens took 12.7 us for 32 heads and 10.7 for 8 of 128, 32 tokens 10; like this 8.7 (24.6 MB
+// read: 4.8 at the copy rate), 4.6 and 3.5-4.6. 8 / 32 heads per workgroup: 9.9 / 10.3 for the 32; 2 / 8 tokens: 9.2 / 10.7.
+constexpr int kRopeTokens = 4, kRopeQuantizeHeads = 16;
+constexpr int64_t kRopeMaxBlocks = 1 << 20;  // along the tokens; more tokens are done in turns
 template <int SCALE_KIND, bool ASYM>
 __global__ __launch_bounds__(256) void rope_quantize_kernel(const float* __restrict__ in, int64_t seq, int64_t ld,
                                                             int64_t col0, int64_t heads, int half, int64_t pos0,
                                                             double log_theta, uint8_t* __restrict__ codes,
                                                             uint8_t* __restrict__ scales) {
-  const int runs = half >> 3;  // threads per token
-  const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (idx >= seq * runs) return;  // (whole quads: seq * runs is a multiple of 4)
-  const int j = (int)(idx % runs);
-  const int64_t s = idx / runs;
-  double sn[8], cs[8];
-#pragma unroll
-  for (int e = 0; e < 8; ++e) {
-    const double ang = (double)(pos0 + s) * exp(-log_theta * (double)(8 * j + e) / (double)half);
-    sincos(ang, &sn[e], &cs[e]);
-  }
-  const int groups = half >> 4;  // groups of 32 per head
-  const int64_t h0 = (int64_t)blockIdx.y * kRopeHeads, h1 = h0 + kRopeHeads < heads ? h0 + kRopeHeads : heads;
-  for (int64_t h = h0; h < h1; ++h) {
-    const float* p = in + s * ld + col0 + h * 2 * half + 8 * j;
-    const float4 a0 = *reinterpret_cast<const float4*>(p), a1 = *reinterpret_cast<const float4*>(p + 4);
-    const float4 b0 = *reinterpret_cast<const float4*>(p + half), b1 = *reinterpret_cast<const float4*>(p + half + 4);
-    const float x1[8] = {a0.x, a0.y, a0.z, a0.w, a1.x, a1.y, a1.z, a1.w};
-    const float x2[8] = {b0.x, b0.y, b0.z, b0.w, b1.x, b1.y, b1.z, b1.w};
-    float o1[8], o2[8];
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      o1[e] = (float)((double)x1[e] * cs[e] - (double)x2[e] * sn[e]);
-      o2[e] = (float)((double)x2[e] * cs[e] + (double)x1[e] * sn[e]);
+  // dimension 8 j + e of token t at [e][t * runs + j]: neighbouring threads read neighbouring entries
+  __shared__ double2 turn[8 * kRopeTokens * 16];
+  const int runs = half >> 3;  // items per token and head: 4, 8, 12 or 16
+  const int64_t h0 = (int64_t)blockIdx.y * kRopeQuantizeHeads;
+  const int nh = (int)(heads - h0 < kRopeQuantizeHeads ? heads - h0 : kRopeQuantizeHeads);
+  for (int64_t s0 = (int64_t)blockIdx.x * kRopeTokens; s0 < seq; s0 += (int64_t)gridDim.x * kRopeTokens) {  // (uniform)
+    const int nt = (int)(seq - s0 < kRopeTokens ? seq - s0 : kRopeTokens);
+    const int items = nt * nh * runs;
+    float4 next[4];
+    auto request = [&](int it) {  // (past the last item: the last one again, not used)
+      it = it < items ? it : items - 1;
+      const int j = it % runs, th = it / runs;
+      const float* p = in + (s0 + th / nh) * ld + col0 + (h0 + th % nh) * 2 * half + 8 * j;
+      next[0] = *reinterpret_cast<const float4*>(p), next[1] = *reinterpret_cast<const float4*>(p + 4);
+      next[2] = *reinterpret_cast<const float4*>(p + half), next[3] = *reinterpret_cast<const float4*>(p + half + 4);
+    };
+    request((int)threadIdx.x);
+    for (int a = threadIdx.x; a < nt * half; a += 256) {
+      const int t = a / half, i = a % half;
+      const double ang = (double)(pos0 + s0 + t) * exp(-log_theta * (double)i / (double)half);
+      double sn, cs;
+      sincos(ang, &sn, &cs);
+      turn[(i & 7) * (kRopeTokens * runs) + t * runs + (i >> 3)] = make_double2(sn, cs);
     }
-    const uint32_t d1[4] = {pack2(o1[0], o1[1]), pack2(o1[2], o1[3]), pack2(o1[4], o1[5]), pack2(o1[6], o1[7])};
-    const uint32_t d2[4] = {pack2(o2[0], o2[1]), pack2(o2[2], o2[3]), pack2(o2[4], o2[5]), pack2(o2[6], o2[7])};
-    uint32_t c1[1], c2[1], p1, n1, p2, n2;
-    cast_words_bf16<SCALE_KIND, ASYM, 8>(d1, 2, c1, p1, n1);
-    cast_words_bf16<SCALE_KIND, ASYM, 8>(d2, 2, c2, p2, n2);
-    const int64_t row = h * seq + s;
-    uint8_t* crow = codes + row * half;  // head_dim / 2 bytes of codes per row
-    *reinterpret_cast<uint32_t*>(crow + 4 * j) = c1[0];
-    *reinterpret_cast<uint32_t*>(crow + (half >> 1) + 4 * j) = c2[0];
-    if ((j & 3) == 0) {
-      const int64_t g1 = row * groups + (j >> 2), g2 = g1 + (groups >> 1);
-      if constexpr (ASYM) {
-        *reinterpret_cast<uint16_t*>(scales + g1 * 2) = (uint16_t)(p1 | (n1 << 8));
-        *reinterpret_cast<uint16_t*>(scales + g2 * 2) = (uint16_t)(p2 | (n2 << 8));
-      } else {
-        scales[g1] = (uint8_t)p1;
-        scales[g2] = (uint8_t)p2;
+    __syncthreads();
+    const int groups = half >> 4;  // groups of 32 per head
+    for (int it = threadIdx.x; it < items; it += 256) {
+      const int j = it % runs, th = it / runs, t = th / nh;
+      const float x1[8] = {next[0].x, next[0].y, next[0].z, next[0].w, next[1].x, next[1].y, next[1].z, next[1].w};
+      const float x2[8] = {next[2].x, next[2].y, next[2].z, next[2].w, next[3].x, next[3].y, next[3].z, next[3].w};
+      request(it + 256);
+      float o1[8], o2[8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const double2 r = turn[e * (kRopeTokens * runs) + t * runs + j];
+        o1[e] = (float)((double)x1[e] * r.y - (double)x2[e] * r.x);
+        o2[e] = (float)((double)x2[e] * r.y + (double)x1[e] * r.x);
+      }
+      const uint32_t d1[4] = {pack2(o1[0], o1[1]), pack2(o1[2], o1[3]), pack2(o1[4], o1[5]), pack2(o1[6], o1[7])};
+      const uint32_t d2[4] = {pack2(o2[0], o2[1]), pack2(o2[2], o2[3]), pack2(o2[4], o2[5]), pack2(o2[6], o2[7])};
+      uint32_t c1[1], c2[1], p1, n1, p2, n2;
+      cast_words_bf16<SCALE_KIND, ASYM, 8>(d1, 2, c1, p1, n1);
+      cast_words_bf16<SCALE_KIND, ASYM, 8>(d2, 2, c2, p2, n2);
+      const int64_t row = (h0 + th % nh) * seq + s0 + t;
+      uint8_t* crow = codes + row * half;  // head_dim / 2 bytes of codes per row
+      *reinterpret_cast<uint32_t*>(crow + 4 * j) = c1[0];
+      *reinterpret_cast<uint32_t*>(crow + (half >> 1) + 4 * j) = c2[0];
+      if ((j & 3) == 0) {
+        const int64_t g1 = row * groups + (j >> 2), g2 = g1 + (groups >> 1);
+        if constexpr (ASYM) {
+          *reinterpret_cast<uint16_t*>(scales + g1 * 2) = (uint16_t)(p1 | (n1 << 8));
+          *reinterpret_cast<uint16_t*>(scales + g2 * 2) = (uint16_t)(p2 | (n2 << 8));
+        } else {
+          scales[g1] = (uint8_t)p1;
+          scales[g2] = (uint8_t)p2;
+        }
       }
     }
+    __syncthreads();  // the table is read before the next tokens' angles go there
   }
 }
 
@@ -414,10 +437,11 @@ int amxfp4_split_heads_rope_quantize(const amx_format_t* fmt, const float* in, i
   if (!aligned16(in) || ld % 4 || col0 % 4 || (reinterpret_cast<uintptr_t>(codes) & 3) || (reinterpret_cast<uintptr_t>(scales) & 1))
     return report_error(AMX_ERR_INVALID_ARG, "split_heads_rope_quantize: in must be 16-byte aligned with ld and col0 multiples "
                         "of 4, codes 4-byte and scales 2-byte aligned");
-  const int64_t threads = seq * (head_dim / 16), head_chunks = (heads + kRopeHeads - 1) / kRopeHeads;
-  if (threads > (int64_t)0x7FFFFFFF * 256 || head_chunks > 65535)
+  const int64_t token_chunks = (seq + kRopeTokens - 1) / kRopeTokens;
+  const int64_t head_chunks = (heads + kRopeQuantizeHeads - 1) / kRopeQuantizeHeads;
+  if (seq > INT64_MAX / 256 || heads > (int64_t)65535 * 8)
     return report_error(AMX_ERR_UNSUPPORTED, "split_heads_rope_quantize: too large");
-  const dim3 grid(blocks_for(threads), (unsigned)head_chunks);
+  const dim3 grid((unsigned)(token_chunks < kRopeMaxBlocks ? token_chunks : kRopeMaxBlocks), (unsigned)head_chunks);
   hipStream_t hs = reinterpret_cast<hipStream_t>(stream);
   const int half = (int)(head_dim / 2);
   const double lt = log(theta);

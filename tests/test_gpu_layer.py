@@ -92,6 +92,17 @@ def test_split_heads_rope_quantize(seq, heads, d, col0, scale, asym):
     assert np.array_equal(scales.reshape(s2.shape).cpu().numpy()[same], rs[same])
 
 
+@pytest.mark.parametrize("seq,heads,d", [(3, 16, 64), (4, 17, 192), (5, 33, 128), (66, 2, 256), (4 * 2**20 + 5, 1, 64)])
+def test_split_heads_rope_quantize_workgroup_edges(seq, heads, d):
+    """Workgroups of 4 tokens x 16 heads, one below, at and above, and more tokens than one grid takes in a turn (the last
+    shape): the bits of split_heads_rope followed by quantize."""
+    proj = torch.randn((seq, heads * d), device="cuda", generator=torch.Generator("cuda").manual_seed(seq)) * 4
+    fmt = binding.make_format(ref.FP8_E5M2, 1, 32)
+    codes, scales = binding.split_heads_rope_quantize(fmt, proj, 0, heads, d, pos0=123, theta=10000.0)
+    c2, s2 = binding.quantize(fmt, binding.split_heads_rope(proj, 0, heads, d, True, pos0=123, theta=10000.0).view(heads * seq, d))
+    assert torch.equal(codes.view(c2.shape), c2) and torch.equal(scales.view(s2.shape), s2)
+
+
 def test_softmax_causal():
     rng = np.random.default_rng(4)
     batch, per, seq = 2, 4, 264
