@@ -399,6 +399,25 @@ static hipError_t launch_tiles(const uint16_t* Ap, const uint16_t* Bp, float* C,
   return hipGetLastError();
 }
 
+// Tile shape (1: 256 x 256, 2: 256 x 128, 3: 64 x 256). 256 x 256 (4 waves of 128 x 128) has the least operand traffic and
+// LDS reads per MFMA and is what large problems use; a problem with fewer such tiles than the chip has CUs, or with one
+// side much smaller than a tile, finishes sooner with 256 x 128 or 64 x 256 tiles that fill the CUs. The choice minimises
+// (rounds of 256 workgroups) x (measured cost of one tile relative to a 256 x 256 one: 0.6 and 0.4), and leaves
+// 256 x 256 only for a predicted gain: of more than 15 % for 64 x 256, of more than 8 % for 256 x 128, which takes in the
+// problems of 257 to 384 large tiles: two rounds of those, three of the halves. Us per call, 256 x 256 / 256 x 128:
+// 2048 x 11008 x 4096 213-219 / 183, 1700 x 11008 x 4096 196-198 / 170, 1900 x 10240 x 8192 403 / 339, 2600 x 8192 x 8192
+// 355 / 337, 3800 x 4544 x 4544 201 / 186, 1300 x 13824 x 5120 221 / 220.
+int bf16_tile_choice(int64_t M, int64_t N, int64_t batch) {
+  auto rounds = [&](int64_t tile_m, int64_t tile_n) {
+    const int64_t tiles = ((M + tile_m - 1) / tile_m) * ((N + tile_n - 1) / tile_n) * batch;
+    return (double)((tiles + 255) / 256);
+  };
+  const double est1 = rounds(256, 256), est2 = 0.6 * rounds(256, 128), est3 = 0.4 * rounds(64, 256);
+  const bool ok3 = est3 < 0.85 * est1;
+  const bool ok2 = est2 < 0.92 * est1 && M > 256;  // (with a single row of 256-row tiles the 64-row tile was never worse)
+  return ok3 && (!ok2 || est3 <= est2) ? 3 : ok2 ? 2 : 1;
+}
+
 hipError_t launch_gemm_bf16_path(int scale_kind, bool asym, int64_t group_size, int64_t M, int64_t N, int64_t K,
                                  const uint8_t* A_codes, const uint8_t* A_scales, const uint8_t* B_codes,
                                  const uint8_t* B_scales, const float* A_tensor_pair, const float* B_tensor_pair,
@@ -429,21 +448,7 @@ hipError_t launch_gemm_bf16_path(int scale_kind, bool asym, int64_t group_size, 
   }
   if (e != hipSuccess) return e;
   if (timer.start && (e = hipEventRecord(timer.start, s)) != hipSuccess) return e;
-  // Tile shape. 256 x 256 (4 waves of 128 x 128) has the least operand traffic and LDS reads per MFMA and is what
-  // large problems use; a problem with fewer such tiles than the chip has CUs, or with one side much smaller than a
-  // tile, finishes sooner with 256 x 128 or 64 x 256 tiles that fill the CUs. The choice minimises
-  // (rounds of 256 workgroups) x (measured cost of one tile relative to a 256 x 256 one: 0.6 and 0.4), and leaves
-  // 256 x 256 only for a predicted gain of more than 15 %. A caller's option (tile != 0) overrides it.
-  auto rounds = [&](int64_t tile_m, int64_t tile_n) {
-    const int64_t tiles = ((M + tile_m - 1) / tile_m) * ((N + tile_n - 1) / tile_n) * batch;
-    return (double)((tiles + 255) / 256);
-  };
-  if (tile == 0) {
-    const double est1 = rounds(256, 256), est2 = 0.6 * rounds(256, 128), est3 = 0.4 * rounds(64, 256);
-    const bool ok3 = est3 < 0.85 * est1;
-    const bool ok2 = est2 < 0.85 * est1 && M > 256;  // (with a single row of 256-row tiles the 64-row tile was never worse)
-    tile = ok3 && (!ok2 || est3 <= est2) ? 3 : ok2 ? 2 : 1;
-  }
+  if (tile == 0) tile = bf16_tile_choice(M, N, batch);  // (a caller's option overrides the choice)
   if (tile == 2)
     e = launch_tiles<4, 1, 2, 4>(Ap, Bp, C, M, N, Mp, Np, Kp, ldc, batch, A_tensor_pair, B_tensor_pair, glu, s);  // 256 x 128
   else if (tile == 3)

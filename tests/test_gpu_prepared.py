@@ -144,6 +144,47 @@ def test_prepared_fp6_weights_at_the_edges_of_the_small_passes(M, N, K, gaps_a, 
     assert err <= 1e-5
 
 
+@pytest.mark.parametrize("asym", [1, 0])
+@pytest.mark.parametrize("M,width,K,pad", [(800, 5504, 256, 0), (897, 5536, 128, 0), (1100, 5504, 384, 8), (800, 5504, 128, 3)])
+def test_wide_products_expand_b_in_the_kernel_with_the_same_bits(M, width, K, pad, asym):
+    """FP8-E5M2 scales, few rounds of tiles and many columns: the plain call expands B's codes inside the kernel, the call
+    on prepared weights reads the panel. Exact operands, the same order of the sums: the same bits, for the product (an
+    odd number of columns) and for the gated product (ragged rows, a partial last tile, out rows that are not 16-byte aligned)."""
+    gen = torch.Generator("cuda").manual_seed(M + K)
+    fmt = binding.make_format(ref.FP8_E5M2, asym, 32)
+    a = (torch.randn((M, K), generator=gen, device="cuda") * 3).bfloat16()
+    b = (torch.randn((2 * width, K), generator=gen, device="cuda") * 0.05).bfloat16()
+    (ac, as_), (bc, bs) = binding.quantize(fmt, a), binding.quantize(fmt, b)
+    n = 2 * width - 1
+    plain = binding.gemm(fmt, ac, as_, bc[:n], bs[:n])
+    panel = binding.gemm(fmt, ac, as_, bc[:n], bs[:n], options=binding.gemm_options(tile="256x256"))
+    assert torch.equal(plain.view(torch.int32), panel.view(torch.int32))
+    prepared = binding.prepare_weights(fmt, bc, bs)
+    outs = []
+    for p in (None, prepared):
+        out = torch.zeros((M, width + pad), dtype=torch.bfloat16, device="cuda")
+        outs.append(gated(fmt, ac, as_, bc, bs, p, out, width))
+    assert torch.equal(outs[0].view(torch.int16), outs[1].view(torch.int16))
+    assert outs[0][:, :width].abs().sum() > 0 and (outs[0][:, width:] == 0).all()
+
+
+def gated(fmt, ac, as_, bc, bs, prepared, out, width):
+    """The gated product into the first `width` columns of out, whose rows may be longer."""
+    L, M, K, ld = binding.load(), ac.shape[0], ac.shape[1] * 2, out.shape[1]
+    f = ctypes.byref(fmt)
+    need = int(L.amxfp4_gemm_silu_mul_workspace_bytes(f, M, width, K))
+    ws = torch.empty(need, dtype=torch.uint8, device="cuda")
+    if prepared is None:
+        rc = L.amxfp4_gemm_silu_mul(f, M, width, K, ac.data_ptr(), as_.data_ptr(), bc.data_ptr(), bs.data_ptr(), out.data_ptr(),
+                                    ld, ws.data_ptr(), need, None)
+    else:
+        rc = L.amxfp4_gemm_silu_mul_prepared(f, M, width, K, ac.data_ptr(), as_.data_ptr(), bc.data_ptr(), bs.data_ptr(),
+                                             prepared.data_ptr(), prepared.numel(), out.data_ptr(), ld, ws.data_ptr(), need, None)
+    assert rc == 0
+    torch.cuda.synchronize()
+    return out
+
+
 @pytest.mark.parametrize("scale,asym", [(ref.FP8_E5M2, 1), (ref.E8M0_FLOOR, 1), (ref.E8M0_FLOOR, 0)])
 def test_prepared_gated_gemm(scale, asym):
     """amxfp4_gemm_silu_mul_prepared against the plain gated GEMM: the same bits."""

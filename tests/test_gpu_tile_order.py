@@ -25,7 +25,8 @@ def operand(rows, K, unit, asym, seed):
 @pytest.mark.parametrize("M,N", [(20, 33 * 256 - 7),    # one row of tiles, 33 columns
                                  (2300, 5100),          # 9 x 20 tiles: bands of 5 and 4 rows
                                  (1290, 28 * 256 + 1),  # 6 x 29
-                                 (300, 250)])           # supertiles
+                                 (300, 250),            # fewer tiles than XCDs
+                                 (2040, 8190)])         # 8 x 32: whole supertiles
 @pytest.mark.parametrize("scale,asym,options", [
     (ref.FP8_E5M2, 1, dict(tile="256x256")), (ref.FP8_E5M2, 1, dict(tile="256x128")), (ref.FP8_E5M2, 1, dict(tile="64x256")),
     (ref.FP8_E5M2, 1, dict(e5m2_kernel="hybrid")), (ref.FP8_E5M2, 0, dict(e5m2_kernel="fused")),
