@@ -3,6 +3,8 @@
 // of the BF16 bytes, so this kernel reads the packed codes and scales of B straight from memory, dequantizes them in
 // registers to exact 16-bit floats (element * scale has at most 6 significant bits) and feeds the 16-bit MFMA; only
 // the small A operand goes through a panel (expand_kernel). No operand of B is ever written back.
+// (Without options most of these shapes take gemm_stream.hip; this kernel is what the few_rows option asks for, and what
+// runs where the rule there prefers it.)
 // The dequantization is the kernel's bound (vector instructions per MFMA), so it uses packed 16-bit arithmetic where
 // the scale format allows it:
 //   FP8-E5M2 scales: FP16 operands biased by 2^-3 (every element * scale * 2^-3 lies in [2^-20, 43008] and has at most
