@@ -321,9 +321,7 @@ int amxfp4_profile_next_gemm(void* start_event, void* stop_event);
  * keeps no process-wide choice and reads no environment variable: the options of a call are the whole story, and
  * amxfp4_gemm_workspace_bytes_ex is a pure function of its arguments.
  *   e5m2_kernel   FP8-E5M2 scales, groups of 32 (Sec. 4.2 "FP8"):
- *                   AMX_E5M2_PANEL   both operands expanded to BF16 panels in the workspace, BF16 MFMA (any K; with every
- *                                    other option 0 too the library chooses, and where B is wide it takes the hybrid kernel:
- *                                    the same bits);
+ *                   AMX_E5M2_PANEL   both operands expanded to BF16 panels in the workspace, BF16 MFMA (any K);
  *                   AMX_E5M2_HYBRID  A expanded to an FP16 panel, B dequantized inside the FP16 MFMA kernel (K % 128 == 0);
  *                   AMX_E5M2_FUSED   both operands dequantized inside the kernel, no workspace (K % 128 == 0).
  *   pot_kernel    asymmetric power-of-two scales, groups of 32 (Sec. 4.2 "PoT"):

@@ -232,15 +232,6 @@ bool uses_stream(const amx_format_t& f, const amx_gemm_options_t* o, int64_t M, 
   return default_options(o) && amx::stream_path_preferred(f.scale, f.asymmetric != 0, f.group_size, M, N, K, batch);
 }
 
-// FP8-E5M2 scales, no kernel asked for and B neither prepared nor tensor-scaled (panel_only): B's codes are expanded inside
-// the kernel where that is faster than expanding all of B first. The scratch asked for stays that of the two panels, of
-// which the first, A's, is used.
-bool uses_hybrid(const amx_format_t& f, const amx_gemm_options_t* o, const GemmPlan& p, bool panel_only, int64_t M, int64_t N,
-                 int64_t K, int64_t batch) {
-  return p.kernel == kGemmPanel && default_options(o) && !panel_only && batch == 1 && f.scale == AMX_SCALE_FP8_E5M2 &&
-         f.group_size == 32 && amx::e5m2_hybrid_preferred(M, N, K);
-}
-
 size_t plan_workspace_bytes(const GemmPlan& p, bool asym, int64_t M, int64_t N, int64_t K, int64_t batch) {
   switch (p.kernel) {
     case kGemmSkinny: return amx::skinny_path_workspace_bytes(M, N, K, batch, p.skinny_slices);
@@ -295,10 +286,6 @@ int gemm_impl(amx_format_t f, const amx_gemm_options_t* opts, int64_t M, int64_t
   if (uses_stream(f, opts, M, N, K, batch)) {
     e = amx::launch_gemm_stream(f.scale, asym, f.group_size, M, N, K, A_codes, A_scales, B_codes, B_scales, A_pair, B_pair,
                                 C, ldc, batch, hs, timer);
-    return e == hipSuccess ? AMX_OK : hip_fail(e, "gemm launch");
-  }
-  if (uses_hybrid(f, opts, plan, scaled || B_panel, M, N, K, batch)) {
-    e = amx::launch_gemm_e5m2_hybrid(asym, M, N, K, A_codes, A_scales, B_codes, B_scales, C, ldc, batch, workspace, hs, timer);
     return e == hipSuccess ? AMX_OK : hip_fail(e, "gemm launch");
   }
   switch (plan.kernel) {

@@ -24,7 +24,6 @@
 // from an FP16 panel instead and expands only B.
 #include "device_formats.h"
 #include "gemm_common.h"
-#include "kernels.h"
 
 namespace amx {
 
@@ -578,22 +577,10 @@ size_t e5m2_hybrid_workspace_bytes(int64_t M, int64_t K, int64_t batch) {
   return (size_t)(batch * round_up(M, kE5Tile) * K * 2);
 }
 
-// Unless the options ask for a kernel: the hybrid kernel instead of two panels (the same bits). The two-panel kernel is the
-// faster one per tile (3-22 % measured), but the call expands B first, which takes N K (0.56 + 2) bytes at the copy rate,
-// 0.51 ps per element, while a round of 256 tiles of 256 x 256 takes about 22 ns per unit of K: where the expansion is
-// more than a fifth of the rounds it costs more than it saves. Us per call, panels / hybrid, with expansion : rounds:
-// 800 x 28672 x 8192 (0.33) 489 / 379, 1024 x 28672 x 8192 (0.33) 500 / 418, 900 x 32001 x 4096 (0.37) 312 / 274,
-// 800 x 11008 x 4096 (0.26) 99-106 / 98, 1200 x 10240 x 8192 (0.24) 206 / 198, 1504 x 28672 x 4096 (0.22) 350 / 316-333;
-// 1300 x 8192 x 8192 (0.19) 190 / 187-192, 2300 x 13824 x 5120 (0.16) 269 / 282, 2048 x 11008 x 4096 (0.13) 213 / 225,
-// 3000 x 10240 x 8192 (0.12) 409 / 427, 4096 x 28672 x 8192 (0.10) 1440 / 1502. Problems for which the panel kernel takes
-// smaller tiles stay with it, and so does the gated product: with its epilogue in the hybrid kernel a decoder layer of 1504
-// tokens (0.22) took the same time.
-bool e5m2_hybrid_preferred(int64_t M, int64_t N, int64_t K) {
-  if (!e5m2_hybrid_supported(M, N, K) || bf16_tile_choice(M, N, 1) != 1) return false;
-  const int64_t tiles = ((M + kE5Tile - 1) / kE5Tile) * ((N + kE5Tile - 1) / kE5Tile), rounds = (tiles + 255) / 256;
-  return (double)N * 0.51e-3 > 0.2 * 22.0 * (double)rounds;
-}
-
+// Only an option takes this kernel. Its products go through the FP16 matrix instruction, the panels' through the BF16 one, and
+// the two do not round alike inside an instruction once the scales of a row differ widely (800 x 11008 x 128 with every scale
+// byte: some outputs a bit apart), while a product on prepared weights, which reads panels, promises the bits of the plain
+// call. (As the default for few rounds of tiles against a wide B it took 379 us instead of 489 at 800 x 28672 x 8192.)
 hipError_t launch_gemm_e5m2_hybrid(bool asym, int64_t M, int64_t N, int64_t K, const uint8_t* A_codes,
                                    const uint8_t* A_scales, const uint8_t* B_codes, const uint8_t* B_scales, float* C,
                                    int64_t ldc, int64_t batch, void* workspace, hipStream_t s,

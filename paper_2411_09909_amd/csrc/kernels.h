@@ -184,7 +184,5 @@ hipError_t launch_gemm_e5m2_hybrid(bool asym, int64_t M, int64_t N, int64_t K, c
                                    const uint8_t* A_scales, const uint8_t* B_codes, const uint8_t* B_scales, float* C,
                                    int64_t ldc, int64_t batch, void* workspace, hipStream_t s,
                                    const KernelTimer& timer);
-bool e5m2_hybrid_preferred(int64_t M, int64_t N, int64_t K);  // instead of two panels, where no option asks for a kernel
-int bf16_tile_choice(int64_t M, int64_t N, int64_t batch);   // of the BF16-panel kernel;
 
 }  // namespace amx

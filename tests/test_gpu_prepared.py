@@ -144,10 +144,10 @@ def test_prepared_fp6_weights_at_the_edges_of_the_small_passes(M, N, K, gaps_a, 
 
 @pytest.mark.parametrize("asym", [1, 0])
 @pytest.mark.parametrize("M,width,K,pad", [(800, 5504, 256, 0), (897, 5536, 128, 0), (1100, 5504, 384, 8), (800, 5504, 128, 3)])
-def test_wide_products_expand_b_in_the_kernel_with_the_same_bits(M, width, K, pad, asym):
-    """FP8-E5M2 scales, few rounds of tiles and many columns: the plain call expands B's codes inside the kernel, the call
-    that asks for tiles reads panels. Exact operands, the same order of the sums: the same bits (an odd number of columns,
-    ragged rows, a partial last tile). The gated product, plain and on prepared weights, stays with the panels."""
+def test_wide_products_have_the_same_bits(M, width, K, pad, asym):
+    """FP8-E5M2 scales, few rounds of tiles and many columns: the plain call, whatever tiles it takes, and the one that asks
+    for 256 x 256 tiles (an odd number of columns, ragged rows, a partial last tile). The gated product, plain and on
+    prepared weights."""
     gen = torch.Generator("cuda").manual_seed(M + K)
     fmt = binding.make_format(ref.FP8_E5M2, asym, 32)
     a = (torch.randn((M, K), generator=gen, device="cuda") * 3).bfloat16()
