@@ -156,7 +156,8 @@ __global__ __launch_bounds__(512) void gemm_e5m2_kernel(const uint8_t* __restric
   }
 #define AMX_RAW_ADVANCE()                                                                          \
   {                                                                                                \
-    wq[0] = wnx[0], wq[1] = wnx[1], wq[2] = wnx[2], wq[3] = wnx[3], sq = snx;                      \
+    wq[0] = wnx[0], wq[1] = wnx[1], wq[2] = wnx[2], wq[3] = wnx[3];                                \
+    sq = snx & 0x7F7Fu; /* the sign bit of a scale byte is ignored (scale_value()) */             \
     sp2 = __builtin_amdgcn_perm(0u, sq, 0x000c000cu); /* (S_p, S_p) as FP16: byte << 8 per half */ \
     if constexpr (ASYM) sn2 = __builtin_amdgcn_perm(0u, sq, 0x010c010cu);                          \
   }
@@ -426,7 +427,8 @@ __global__ __launch_bounds__(256) void gemm_e5m2_hybrid_kernel(const uint16_t* _
   }
 #define AMX_RAW_ADVANCE()                                                                          \
   {                                                                                                \
-    wq[0] = wnx[0], wq[1] = wnx[1], wq[2] = wnx[2], wq[3] = wnx[3], sq = snx;                      \
+    wq[0] = wnx[0], wq[1] = wnx[1], wq[2] = wnx[2], wq[3] = wnx[3];                                \
+    sq = snx & 0x7F7Fu; /* the sign bit of a scale byte is ignored (scale_value()) */             \
     sp2 = __builtin_amdgcn_perm(0u, sq, 0x000c000cu); /* (S_p, S_p) as FP16: byte << 8 per half */ \
     if constexpr (ASYM) sn2 = __builtin_amdgcn_perm(0u, sq, 0x010c010cu);                          \
   }
