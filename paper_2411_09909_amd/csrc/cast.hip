@@ -260,8 +260,10 @@ __global__ __launch_bounds__(256) void quantize_strided_kernel(const uint16_t* _
 // is one workgroup's work and one launch. A larger one takes two: the pair serves as the accumulator of the maximum (bit
 // pattern of a non-negative float) and as the count of workgroups that have added theirs, both cleared by the first launch,
 // and the workgroup that is last to add writes the result; at most one workgroup per compute unit, since every one adds to
-// the count (with 512 of them 4096 x 8192 took 28 us). us, three launches of up to 2048 workgroups / now: 24 x 4096 5.9 /
-// 3.4, 32 x 8192 6.6 / 5.3, 512 x 4096 14.6 / 6.6, 2048 x 4096 24 / 8.2, 4096 x 8192 19 / 20.
+// the count (with 512 of them 4096 x 8192 took 28 us). From kAmaxManyGroups elements on reading the tensor is the bound, which
+// takes more workgroups, too many for the count: three launches, the last of which writes the result. us, three launches / one
+// or two: 24 x 4096 6.1 / 3.6, 32 x 8192 7.0 / 5.5, 512 x 4096 17 / 6.5, 4096 x 4096 28 / 11 (rows apart 14-18 / 13), 4096 x
+// 8192 19.6-22 / 19.8 (rows apart 17-19 / 20), 8192 x 8192 25 / 29, 4096 x 28672 38 / 42, 28672 x 8192 79 / 88.
 __device__ __forceinline__ uint32_t amax_of(uint4 v) {  // two 15-bit magnitudes
   return pk_max_i16(pk_max_i16(v.x & 0x7FFF7FFFu, v.y & 0x7FFF7FFFu), pk_max_i16(v.z & 0x7FFF7FFFu, v.w & 0x7FFF7FFFu));
 }
@@ -294,21 +296,22 @@ __device__ __forceinline__ void write_scale_pair(uint32_t amax_bits, float* pair
   pair[1] = rt;
 }
 
-constexpr int64_t kAmaxOneGroup = int64_t(1) << 17;
-constexpr int64_t kAmaxGroups = 256;
+constexpr int64_t kAmaxOneGroup = int64_t(1) << 17, kAmaxManyGroups = int64_t(1) << 25;
+constexpr int kAmaxGroups = 256;
 
-// grid of workgroups of 1024 threads; total <= 2^61 chunks of 8. ONE: the only workgroup, pair need not be cleared.
+// grid of workgroups of 1024 threads; total <= kAmaxManyGroups / 8 chunks of 8 (32-bit divisions: 64-bit ones were most of the
+// time of a small tensor whose rows lie apart, 31 x 4096 7.0 us). ONE: the only workgroup, pair need not be cleared.
 template <bool ONE>
-__global__ __launch_bounds__(1024) void tensor_scale_kernel(const uint16_t* __restrict__ x, int64_t total,
-                                                            int64_t chunks_per_row, int64_t row_stride, uint32_t* pair) {
+__global__ __launch_bounds__(1024) void tensor_scale_kernel(const uint16_t* __restrict__ x, uint32_t total,
+                                                            uint32_t chunks_per_row, int64_t row_stride, uint32_t* pair) {
   uint32_t m = 0;  // two running 15-bit magnitudes
-  auto chunk = [&](int64_t c) {
-    if (row_stride == chunks_per_row * 8) return *reinterpret_cast<const uint4*>(x + c * 8);  // (uniform)
-    const int64_t r = c / chunks_per_row, cc = c - r * chunks_per_row;
-    return *reinterpret_cast<const uint4*>(x + r * row_stride + cc * 8);
+  auto chunk = [&](uint32_t c) {
+    if (row_stride == (int64_t)chunks_per_row * 8) return *reinterpret_cast<const uint4*>(x + (int64_t)c * 8);  // (uniform)
+    const uint32_t r = c / chunks_per_row, cc = c - r * chunks_per_row;
+    return *reinterpret_cast<const uint4*>(x + r * row_stride + (int64_t)cc * 8);
   };
-  const int64_t step = ONE ? 1024 : (int64_t)gridDim.x * 1024;
-  int64_t c = (int64_t)blockIdx.x * 1024 + threadIdx.x;
+  const uint32_t step = ONE ? 1024u : gridDim.x * 1024u;
+  uint32_t c = blockIdx.x * 1024u + threadIdx.x;
   for (; c + 7 * step < total; c += 8 * step) {  // eight loads in flight per thread
     uint4 v[8];
 #pragma unroll
@@ -337,6 +340,21 @@ __global__ void tensor_amax_init_kernel(uint32_t* pair) {
   pair[0] = 0u;
   pair[1] = 0u;
 }
+
+// The maximum of a large tensor into pair[0], and what the pair becomes then. total: chunks of 8.
+__global__ __launch_bounds__(256) void tensor_amax_kernel(const uint16_t* __restrict__ x, int64_t total,
+                                                          int64_t chunks_per_row, int64_t row_stride,
+                                                          uint32_t* __restrict__ pair) {
+  uint32_t m = 0;
+  for (int64_t c = (int64_t)blockIdx.x * 256 + threadIdx.x; c < total; c += (int64_t)gridDim.x * 256) {
+    const int64_t r = c / chunks_per_row, cc = c - r * chunks_per_row;
+    m = pk_max_i16(m, amax_of(*reinterpret_cast<const uint4*>(x + r * row_stride + cc * 8)));
+  }
+  const uint32_t a = workgroup_amax<4>(m);
+  if (threadIdx.x == 0 && a > __builtin_nontemporal_load(pair)) atomicMax(pair, a);
+}
+
+__global__ void tensor_scale_finalize_kernel(float* pair) { write_scale_pair(f2u(pair[0]), pair); }
 
 // x_hat = (-1)^s * elem * S_class (Eq. 1), times the tensor-wise scale tensor_pair[0] when that pointer is not null
 // (Sec. 5.3; FP32 output only: one rounding of the exact product). One lane expands 8 codes.
@@ -509,13 +527,20 @@ hipError_t launch_tensor_scale(const uint16_t* x, int64_t rows, int64_t K, int64
   uint32_t* acc = reinterpret_cast<uint32_t*>(pair);
   const int64_t chunks_per_row = K / 8, total = rows * chunks_per_row;
   if (rows * K <= kAmaxOneGroup) {
-    hipLaunchKernelGGL(tensor_scale_kernel<true>, dim3(1), dim3(1024), 0, s, x, total, chunks_per_row, row_stride, acc);
+    hipLaunchKernelGGL(tensor_scale_kernel<true>, dim3(1), dim3(1024), 0, s, x, (uint32_t)total, (uint32_t)chunks_per_row,
+                       row_stride, acc);
     return hipGetLastError();
   }
   hipLaunchKernelGGL(tensor_amax_init_kernel, dim3(1), dim3(1), 0, s, acc);
-  const int64_t groups = (total + 8 * 1024 - 1) / (8 * 1024);
-  hipLaunchKernelGGL(tensor_scale_kernel<false>, dim3((unsigned)(groups < kAmaxGroups ? groups : kAmaxGroups)), dim3(1024), 0, s, x, total,
-                     chunks_per_row, row_stride, acc);
+  if (rows * K < kAmaxManyGroups || (rows * K == kAmaxManyGroups && row_stride == K)) {
+    const int groups = (int)((total + 8 * 1024 - 1) / (8 * 1024));
+    hipLaunchKernelGGL(tensor_scale_kernel<false>, dim3(groups < kAmaxGroups ? groups : kAmaxGroups), dim3(1024), 0, s, x,
+                       (uint32_t)total, (uint32_t)chunks_per_row, row_stride, acc);
+  } else {  // 8 workgroups per CU: few atomics on the one accumulator
+    hipLaunchKernelGGL(tensor_amax_kernel, dim3(grid_for(total) < 2048 ? grid_for(total) : 2048), dim3(256), 0, s, x, total,
+                       chunks_per_row, row_stride, acc);
+    hipLaunchKernelGGL(tensor_scale_finalize_kernel, dim3(1), dim3(1), 0, s, pair);
+  }
   return hipGetLastError();
 }
 

@@ -52,10 +52,12 @@ def test_tensor_scale_pair(gain):
     assert got[0] == want[0] and got[1] == want[1]
 
 
-@pytest.mark.parametrize("rows,K", [(1, 8), (3, 8200), (64, 4096), (65, 4096), (1, 8 * 40000), (2100, 4096)])
+@pytest.mark.parametrize("rows,K", [(1, 8), (3, 8200), (31, 4096), (32, 4096), (33, 4096), (64, 4096), (65, 4096), (1, 8 * 40000),
+                                    (2100, 4096)])
 def test_tensor_scale_on_both_sides_of_one_workgroup(rows, K):
-    """Up to 2^18 elements are one workgroup's, more are many: the maximum at the first element, the last, and in between,
-    the pair left over from a larger maximum before; several times, since nothing may depend on what the pair held."""
+    """Up to 2^17 elements are one workgroup's (31 x 4096: eight loads per thread, then a remainder), more are many: the
+    maximum at the first element, the last, and in between, the pair left over from a larger maximum before; several
+    times, since nothing may depend on what the pair held."""
     x = synth.activations(rows, K, seed=rows, n_outlier=1, outlier_gain=2.0)
     pair = torch.full((2,), 3.0e38, device="cuda")
     for at in (0, rows * K - 1, rows * K // 2, 0):
@@ -65,6 +67,25 @@ def test_tensor_scale_on_both_sides_of_one_workgroup(rows, K):
         want = ref.tensor_scale(y)
         got = pair.cpu().numpy()
         assert got[0] == want[0] and got[1] == want[1]
+
+
+@pytest.mark.parametrize("rows,K,gap", [(31, 4096, 8), (32, 4096, 64), (33, 4096, 64), (4095, 8192, 0), (4096, 8192, 0),
+                                        (4095, 8192, 16), (4096, 8192, 8)])
+def test_tensor_scale_of_rows_apart_and_of_many_workgroups(rows, K, gap):
+    """Rows that lie apart, larger values between them, on both sides of the sizes at which one workgroup's work becomes
+    many workgroups' and two launches become three (2^25 elements): the maximum first, last and in between."""
+    x = torch.full((rows, K + gap), 7.0e30, dtype=torch.bfloat16, device="cuda")
+    view = x[:, :K]
+    view.fill_(-0.5)
+    pair = torch.full((2,), 3.0e38, device="cuda")
+    for i, at in enumerate((0, rows * K - 1, rows * K // 2 + 5)):
+        value = 2.0 ** (i + 3)
+        view[at // K, at % K] = -value
+        binding.tensor_scale(view, out=pair)
+        view[at // K, at % K] = 0.25
+        st = np.float32(value) / np.float32(2688)
+        got = pair.cpu().numpy()
+        assert got[0] == st and got[1] == np.float32(1) / st
 
 
 def test_tensor_scale_of_extreme_tensors():
