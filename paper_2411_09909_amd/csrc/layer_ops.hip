@@ -176,22 +176,65 @@ __global__ __launch_bounds__(256) void split_heads_rope_kernel(const float* __re
 }
 
 // split_heads_rope_kernel (rotate) followed by the cast of its result along the head dimension, in one pass: the
-// rotated BF16 heads are never written. A workgroup takes kRopeTokens tokens and kRopeQuantizeHeads heads (blockIdx.y).
-// The angles of a token do not depend on the head: the workgroup's threads first work out one FP64 sine and cosine
-// each (two for head_dim > 128) and leave them in LDS, while the loads of their first items are under way. Then they
-// share out the items (token, head, run of 8 dimensions d0 .. d0 + 7 below head_dim / 2): an item is the 8 outputs at
-// d0 .. and the 8 at d0 + head_dim / 2 .., each run one lane's share of a group of 32, and the four neighbouring threads
-// of a group exchange their extrema as the cast kernel's lanes do (cast_core.h). head_dim % 64 == 0, so a group never
-// straddles the two halves and the items of a token and head are a whole number of quads. Same arithmetic as the two
-// separate kernels: same bits.
+// rotated BF16 heads are never written. The work is cut into items (token, head, run of 8 dimensions d0 .. d0 + 7 below
+// head_dim / 2): the 8 outputs at d0 .. and the 8 at d0 + head_dim / 2 .., each run one lane's share of a group of 32, and
+// the four neighbouring threads of a group exchange their extrema as the cast kernel's lanes do (cast_core.h). head_dim %
+// 64 == 0, so a group never straddles the two halves and the items of a token and head are a whole number of quads. Same
+// arithmetic as the two separate kernels: same bits, in both kernels below.
+//
+// One item: its 16 inputs x (8 of the first half, 8 of the second), the sines and cosines of its 8 dimensions, to run j of `row`.
+template <int SCALE_KIND, bool ASYM, class Angle>
+__device__ __forceinline__ void rope_quantize_item(const float4 (&x)[4], Angle angle, int64_t row, int j, int half,
+                                                   uint8_t* __restrict__ codes, uint8_t* __restrict__ scales) {
+  const float x1[8] = {x[0].x, x[0].y, x[0].z, x[0].w, x[1].x, x[1].y, x[1].z, x[1].w};
+  const float x2[8] = {x[2].x, x[2].y, x[2].z, x[2].w, x[3].x, x[3].y, x[3].z, x[3].w};
+  float o1[8], o2[8];
+#pragma unroll
+  for (int e = 0; e < 8; ++e) {
+    const double2 r = angle(e);  // sine, cosine
+    o1[e] = (float)((double)x1[e] * r.y - (double)x2[e] * r.x);
+    o2[e] = (float)((double)x2[e] * r.y + (double)x1[e] * r.x);
+  }
+  const uint32_t d1[4] = {pack2(o1[0], o1[1]), pack2(o1[2], o1[3]), pack2(o1[4], o1[5]), pack2(o1[6], o1[7])};
+  const uint32_t d2[4] = {pack2(o2[0], o2[1]), pack2(o2[2], o2[3]), pack2(o2[4], o2[5]), pack2(o2[6], o2[7])};
+  uint32_t c1[1], c2[1], p1, n1, p2, n2;
+  cast_words_bf16<SCALE_KIND, ASYM, 8>(d1, 2, c1, p1, n1);
+  cast_words_bf16<SCALE_KIND, ASYM, 8>(d2, 2, c2, p2, n2);
+  uint8_t* crow = codes + row * half;  // head_dim / 2 bytes of codes per row
+  *reinterpret_cast<uint32_t*>(crow + 4 * j) = c1[0];
+  *reinterpret_cast<uint32_t*>(crow + (half >> 1) + 4 * j) = c2[0];
+  if ((j & 3) == 0) {
+    const int groups = half >> 4;  // groups of 32 per head
+    const int64_t g1 = row * groups + (j >> 2), g2 = g1 + (groups >> 1);
+    if constexpr (ASYM) {
+      *reinterpret_cast<uint16_t*>(scales + g1 * 2) = (uint16_t)(p1 | (n1 << 8));
+      *reinterpret_cast<uint16_t*>(scales + g2 * 2) = (uint16_t)(p2 | (n2 << 8));
+    } else {
+      scales[g1] = (uint8_t)p1;
+      scales[g2] = (uint8_t)p2;
+    }
+  }
+}
+
+__device__ __forceinline__ void rope_request(float4 (&x)[4], const float* p, int half) {
+  x[0] = *reinterpret_cast<const float4*>(p), x[1] = *reinterpret_cast<const float4*>(p + 4);
+  x[2] = *reinterpret_cast<const float4*>(p + half), x[3] = *reinterpret_cast<const float4*>(p + half + 4);
+}
+
+// Both kernels: `tokens` of a sequence of `seq`, in, pos0, codes and scales those of the first of them.
+//
+// A workgroup takes kRopeTokens tokens and kRopeQuantizeHeads heads (blockIdx.y). The angles of a token do not depend on
+// the head: the workgroup's threads first work out one FP64 sine and cosine each (two for head_dim > 128) and leave them
+// in LDS, while the loads of their first items are under way; then they share out the items.
 // What bounds it is the FP64 trigonometry's chain, then memory: with every thread working out all 8 angles of its run
-// and walking 8 heads, 1504 tokens took 12.7 us for 32 heads and 10.7 for 8 of 128, 32 tokens 10; like this 8.7 (24.6 MB
-// read: 4.8 at the copy rate), 4.6 and 3.5-4.6. 8 / 32 heads per workgroup: 9.9 / 10.3 for the 32; 2 / 8 tokens: 9.2 / 10.7.
+// and walking 8 heads, 1504 tokens took 12.7 us for 32 heads and 10.7 for 8 of 128, 32 tokens 10; like this, on inputs in
+// the last-level cache, 8.7 (24.6 MB read: 4.8 at the copy rate), 4.6 and 3.5-4.6, within a layer 12.1 and 5.8 for the
+// 1504. 8 / 32 heads per workgroup: 9.9 / 10.3 for the 32; 2 / 8 tokens: 9.2 / 10.7.
 constexpr int kRopeTokens = 4, kRopeQuantizeHeads = 16;
-constexpr int64_t kRopeMaxBlocks = 1 << 20;  // along the tokens; more tokens are done in turns
+constexpr int64_t kRopeMaxTokens = 1 << 22;  // of one launch; more take several
 template <int SCALE_KIND, bool ASYM>
-__global__ __launch_bounds__(256) void rope_quantize_kernel(const float* __restrict__ in, int64_t seq, int64_t ld,
-                                                            int64_t col0, int64_t heads, int half, int64_t pos0,
+__global__ __launch_bounds__(256) void rope_quantize_kernel(const float* __restrict__ in, int64_t tokens, int64_t seq,
+                                                            int64_t ld, int64_t col0, int64_t heads, int half, int64_t pos0,
                                                             double log_theta, uint8_t* __restrict__ codes,
                                                             uint8_t* __restrict__ scales) {
   // dimension 8 j + e of token t at [e][t * runs + j]: neighbouring threads read neighbouring entries
@@ -199,60 +242,66 @@ __global__ __launch_bounds__(256) void rope_quantize_kernel(const float* __restr
   const int runs = half >> 3;  // items per token and head: 4, 8, 12 or 16
   const int64_t h0 = (int64_t)blockIdx.y * kRopeQuantizeHeads;
   const int nh = (int)(heads - h0 < kRopeQuantizeHeads ? heads - h0 : kRopeQuantizeHeads);
-  for (int64_t s0 = (int64_t)blockIdx.x * kRopeTokens; s0 < seq; s0 += (int64_t)gridDim.x * kRopeTokens) {  // (uniform)
-    const int nt = (int)(seq - s0 < kRopeTokens ? seq - s0 : kRopeTokens);
-    const int items = nt * nh * runs;
-    float4 next[4];
-    auto request = [&](int it) {  // (past the last item: the last one again, not used)
-      it = it < items ? it : items - 1;
-      const int j = it % runs, th = it / runs;
-      const float* p = in + (s0 + th / nh) * ld + col0 + (h0 + th % nh) * 2 * half + 8 * j;
-      next[0] = *reinterpret_cast<const float4*>(p), next[1] = *reinterpret_cast<const float4*>(p + 4);
-      next[2] = *reinterpret_cast<const float4*>(p + half), next[3] = *reinterpret_cast<const float4*>(p + half + 4);
-    };
-    request((int)threadIdx.x);
-    for (int a = threadIdx.x; a < nt * half; a += 256) {
-      const int t = a / half, i = a % half;
-      const double ang = (double)(pos0 + s0 + t) * exp(-log_theta * (double)i / (double)half);
-      double sn, cs;
-      sincos(ang, &sn, &cs);
-      turn[(i & 7) * (kRopeTokens * runs) + t * runs + (i >> 3)] = make_double2(sn, cs);
-    }
-    __syncthreads();
-    const int groups = half >> 4;  // groups of 32 per head
-    for (int it = threadIdx.x; it < items; it += 256) {
-      const int j = it % runs, th = it / runs, t = th / nh;
-      const float x1[8] = {next[0].x, next[0].y, next[0].z, next[0].w, next[1].x, next[1].y, next[1].z, next[1].w};
-      const float x2[8] = {next[2].x, next[2].y, next[2].z, next[2].w, next[3].x, next[3].y, next[3].z, next[3].w};
-      request(it + 256);
-      float o1[8], o2[8];
+  const int64_t s0 = (int64_t)blockIdx.x * kRopeTokens;
+  const int nt = (int)(tokens - s0 < kRopeTokens ? tokens - s0 : kRopeTokens);
+  const int items = nt * nh * runs;
+  float4 next[4];
+  auto request = [&](int it) {  // (past the last item: the last one again, not used)
+    it = it < items ? it : items - 1;
+    const int j = it % runs, th = it / runs;
+    rope_request(next, in + (s0 + th / nh) * ld + col0 + (h0 + th % nh) * 2 * half + 8 * j, half);
+  };
+  request((int)threadIdx.x);
+  for (int a = threadIdx.x; a < nt * half; a += 256) {
+    const int t = a / half, i = a % half;
+    const double ang = (double)(pos0 + s0 + t) * exp(-log_theta * (double)i / (double)half);
+    double sn, cs;
+    sincos(ang, &sn, &cs);
+    turn[(i & 7) * (kRopeTokens * runs) + t * runs + (i >> 3)] = make_double2(sn, cs);
+  }
+  __syncthreads();
+  for (int it = threadIdx.x; it < items; it += 256) {
+    const int j = it % runs, th = it / runs, t = th / nh;
+    const float4 x[4] = {next[0], next[1], next[2], next[3]};
+    request(it + 256);
+    rope_quantize_item<SCALE_KIND, ASYM>(x, [&](int e) { return turn[e * (kRopeTokens * runs) + t * runs + j]; },
+                                         (h0 + th % nh) * seq + s0 + t, j, half, codes, scales);
+  }
+}
+
+// The same for long inputs: a thread takes one run of one token, works out its 8 angles and walks a chunk of kRopeHeads heads
+// (blockIdx.y). Its chain is longer, but neighbouring threads write neighbouring rows and nobody waits for a table, which
+// pays once the tables would take more than some 2500 workgroups. us, table / this: 8192 tokens of 64 heads of 128 67 / 57,
+// 4096 of 200 of 64 56 / 43, 16384 of 12 of 64 17.8 / 14.2, 8192 of 32 of 128 32.3 / 31.6; but 4096 of 32 of 128 16 / 18.8,
+// 1504 of 64 of 128 14.6 / 18, 8192 of 12 of 64 10.5 / 12.6, and 16 of 256 at any length (8192 31.8 / 35, 16384 64 / 65).
+// Few heads leave most of a table's workgroup idle: 2000 of them, with 256 dimensions 1000 (8192 of 1 of 64 7.9 / 5.5, of 2
+// of 128 8.8 / 6.1, 4096 of 3 of 256 8.2 / 6.9; but 4096 of 2 of 128 5.8 / 6.2, 2900 of 3 of 256 7.0 / 7.2).
+inline bool rope_by_thread(int64_t seq, int64_t heads, int half) {
+  const int64_t tables = seq / kRopeTokens * ((heads + kRopeQuantizeHeads - 1) / kRopeQuantizeHeads);
+  return heads > 4 ? half < 128 && tables > 2500 : tables > (half == 128 ? 1000 : 2000);
+}
+
+template <int SCALE_KIND, bool ASYM>
+__global__ __launch_bounds__(256) void rope_quantize_long_kernel(const float* __restrict__ in, int64_t tokens, int64_t seq,
+                                                                 int64_t ld, int64_t col0, int64_t heads, int half,
+                                                                 int64_t pos0, double log_theta, uint8_t* __restrict__ codes,
+                                                                 uint8_t* __restrict__ scales) {
+  const int runs = half >> 3;
+  const uint32_t idx = blockIdx.x * 256u + threadIdx.x;  // tokens * runs <= 2^26
+  if (idx >= (uint32_t)tokens * (uint32_t)runs) return;   // (whole quads: tokens * runs is a multiple of 4)
+  const int j = (int)(idx % (uint32_t)runs);
+  const int64_t s = idx / (uint32_t)runs;
+  double2 turn[8];
 #pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        const double2 r = turn[e * (kRopeTokens * runs) + t * runs + j];
-        o1[e] = (float)((double)x1[e] * r.y - (double)x2[e] * r.x);
-        o2[e] = (float)((double)x2[e] * r.y + (double)x1[e] * r.x);
-      }
-      const uint32_t d1[4] = {pack2(o1[0], o1[1]), pack2(o1[2], o1[3]), pack2(o1[4], o1[5]), pack2(o1[6], o1[7])};
-      const uint32_t d2[4] = {pack2(o2[0], o2[1]), pack2(o2[2], o2[3]), pack2(o2[4], o2[5]), pack2(o2[6], o2[7])};
-      uint32_t c1[1], c2[1], p1, n1, p2, n2;
-      cast_words_bf16<SCALE_KIND, ASYM, 8>(d1, 2, c1, p1, n1);
-      cast_words_bf16<SCALE_KIND, ASYM, 8>(d2, 2, c2, p2, n2);
-      const int64_t row = (h0 + th % nh) * seq + s0 + t;
-      uint8_t* crow = codes + row * half;  // head_dim / 2 bytes of codes per row
-      *reinterpret_cast<uint32_t*>(crow + 4 * j) = c1[0];
-      *reinterpret_cast<uint32_t*>(crow + (half >> 1) + 4 * j) = c2[0];
-      if ((j & 3) == 0) {
-        const int64_t g1 = row * groups + (j >> 2), g2 = g1 + (groups >> 1);
-        if constexpr (ASYM) {
-          *reinterpret_cast<uint16_t*>(scales + g1 * 2) = (uint16_t)(p1 | (n1 << 8));
-          *reinterpret_cast<uint16_t*>(scales + g2 * 2) = (uint16_t)(p2 | (n2 << 8));
-        } else {
-          scales[g1] = (uint8_t)p1;
-          scales[g2] = (uint8_t)p2;
-        }
-      }
-    }
-    __syncthreads();  // the table is read before the next tokens' angles go there
+  for (int e = 0; e < 8; ++e) {
+    const double ang = (double)(pos0 + s) * exp(-log_theta * (double)(8 * j + e) / (double)half);
+    sincos(ang, &turn[e].x, &turn[e].y);
+  }
+  const int64_t h0 = (int64_t)blockIdx.y * kRopeHeads, h1 = h0 + kRopeHeads < heads ? h0 + kRopeHeads : heads;
+  for (int64_t h = h0; h < h1; ++h) {
+    float4 x[4];
+    rope_request(x, in + s * ld + col0 + h * 2 * half + 8 * j, half);
+    rope_quantize_item<SCALE_KIND, ASYM>(x, [&](int e) { return turn[e]; }, h * seq + s, j, half, codes, scales);
   }
 }
 
@@ -437,17 +486,28 @@ int amxfp4_split_heads_rope_quantize(const amx_format_t* fmt, const float* in, i
   if (!aligned16(in) || ld % 4 || col0 % 4 || (reinterpret_cast<uintptr_t>(codes) & 3) || (reinterpret_cast<uintptr_t>(scales) & 1))
     return report_error(AMX_ERR_INVALID_ARG, "split_heads_rope_quantize: in must be 16-byte aligned with ld and col0 multiples "
                         "of 4, codes 4-byte and scales 2-byte aligned");
-  const int64_t token_chunks = (seq + kRopeTokens - 1) / kRopeTokens;
-  const int64_t head_chunks = (heads + kRopeQuantizeHeads - 1) / kRopeQuantizeHeads;
   if (seq > INT64_MAX / 256 || heads > (int64_t)65535 * 8)
     return report_error(AMX_ERR_UNSUPPORTED, "split_heads_rope_quantize: too large");
-  const dim3 grid((unsigned)(token_chunks < kRopeMaxBlocks ? token_chunks : kRopeMaxBlocks), (unsigned)head_chunks);
   hipStream_t hs = reinterpret_cast<hipStream_t>(stream);
   const int half = (int)(head_dim / 2);
   const double lt = log(theta);
+  const bool by_thread = rope_by_thread(seq, heads, half);
   auto go = [&]<int SK, bool ASYM>() {
-    hipLaunchKernelGGL((rope_quantize_kernel<SK, ASYM>), grid, dim3(256), 0, hs, in, seq, ld, col0, heads, half, pos0, lt,
-                       codes, scales);
+    for (int64_t first = 0; first < seq; first += kRopeMaxTokens) {
+      const int64_t tokens = seq - first < kRopeMaxTokens ? seq - first : kRopeMaxTokens;
+      const float* in1 = in + first * ld;
+      uint8_t* codes1 = codes + first * half;
+      uint8_t* scales1 = scales + first * (half >> 4) * (ASYM ? 2 : 1);
+      if (by_thread) {
+        const dim3 grid(blocks_for(tokens * (half >> 3)), (unsigned)((heads + kRopeHeads - 1) / kRopeHeads));
+        hipLaunchKernelGGL((rope_quantize_long_kernel<SK, ASYM>), grid, dim3(256), 0, hs, in1, tokens, seq, ld, col0, heads,
+                           half, pos0 + first, lt, codes1, scales1);
+      } else {
+        const dim3 grid(blocks_for(tokens * (256 / kRopeTokens)), (unsigned)((heads + kRopeQuantizeHeads - 1) / kRopeQuantizeHeads));
+        hipLaunchKernelGGL((rope_quantize_kernel<SK, ASYM>), grid, dim3(256), 0, hs, in1, tokens, seq, ld, col0, heads, half,
+                           pos0 + first, lt, codes1, scales1);
+      }
+    }
   };
   const bool asym = fmt->asymmetric != 0;
   switch (fmt->scale) {

@@ -92,10 +92,13 @@ def test_split_heads_rope_quantize(seq, heads, d, col0, scale, asym):
     assert np.array_equal(scales.reshape(s2.shape).cpu().numpy()[same], rs[same])
 
 
-@pytest.mark.parametrize("seq,heads,d", [(3, 16, 64), (4, 17, 192), (5, 33, 128), (66, 2, 256), (4 * 2**20 + 5, 1, 64)])
+@pytest.mark.parametrize("seq,heads,d", [(3, 16, 64), (4, 17, 192), (5, 33, 128), (66, 2, 256), (4 * 2**20 + 5, 1, 64),
+                                         (4003, 3, 256), (4005, 3, 256), (8003, 1, 64), (8004, 4, 128), (5003, 17, 128),
+                                         (5005, 17, 128), (5007, 24, 192)])
 def test_split_heads_rope_quantize_workgroup_edges(seq, heads, d):
-    """Workgroups of 4 tokens x 16 heads, one below, at and above, and more tokens than one grid takes in a turn (the last
-    shape): the bits of split_heads_rope followed by quantize."""
+    """Workgroups of 4 tokens x 16 heads, one below, at and above; both sides of the sizes from which a thread works out its
+    own angles, few heads and many, and more tokens than such threads take in a turn (4194309): the bits of
+    split_heads_rope followed by quantize."""
     proj = torch.randn((seq, heads * d), device="cuda", generator=torch.Generator("cuda").manual_seed(seq)) * 4
     fmt = binding.make_format(ref.FP8_E5M2, 1, 32)
     codes, scales = binding.split_heads_rope_quantize(fmt, proj, 0, heads, d, pos0=123, theta=10000.0)
