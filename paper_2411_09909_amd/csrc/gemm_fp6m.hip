@@ -127,9 +127,11 @@ __global__ __launch_bounds__(64 * kFp6FlagLanes) void fp6_flag_kernel(const uint
 }
 
 // ---- pass 2: where every group lands in the lengthened K ---------------------------------------------------------------
-// grid: (1, 1, batch); block 1024 (one group position per thread up to K = 32768: a single workgroup's chain of memory
-// latencies is all this pass is; 256 threads
-// took 7.8 us for 1777 x 28672 on prepared weights, this 4.8). plan (per batch entry): pos[G + 1] words (first 32-block of group g; pos[G] = total
+// grid: (1, 1, batch); block kThreads. A single workgroup's chain of memory latencies and barriers is all that this pass
+// costs: 1024 threads give each one group position up to K = 32768 (1777 x 28672 on prepared weights: 4.8 us, with 256
+// threads 7.8); where 256 threads too have one position and at most eight flag words each, their barriers are cheaper
+// (preparing 1024 x 1024: the call 10.2 -> 9.8 us).
+// plan (per batch entry): pos[G + 1] words (first 32-block of group g; pos[G] = total
 // blocks), then G bytes of split flags (bit 0: A's position is split, bit 1: B's), then - word aligned - the number
 // of K steps (total blocks / 2 rounded up to a multiple of kFp6StepPad).
 // With a prepared B (prepared_plan: the plan B's own passes left, pos and split of B alone): B's flags come from that
@@ -137,12 +139,13 @@ __global__ __launch_bounds__(64 * kFp6FlagLanes) void fp6_flag_kernel(const uint
 // lengthened K, the block i of B's prepared panel that stands there (zero-padding blocks: block 0, against A's zeros),
 // as the byte offset of its 16-byte part within a row block of the panel, (i / 2) * 1536 + (i % 2) * 512, with i % 2
 // in bit 0 (its 8-byte part lies at (i / 2) * 1536 + 1024 + (i % 2) * 256).
-constexpr int kFp6PlanThreads = 1024;
-__global__ __launch_bounds__(kFp6PlanThreads) void fp6_plan_kernel(const uint8_t* __restrict__ flags, int64_t G, int chunks_a,
-                                                       int chunks_b, int64_t plan_stride, int64_t steps_offset,
-                                                       uint8_t* __restrict__ plan_base,
-                                                       const uint8_t* __restrict__ prepared_plan, int64_t table_offset) {
-  __shared__ uint32_t part[kFp6PlanThreads / 64];  // the waves' totals
+template <int kThreads>
+__global__ __launch_bounds__(kThreads) void fp6_plan_kernel(const uint8_t* __restrict__ flags, int64_t G, int chunks_a,
+                                                            int chunks_b, int64_t plan_stride, int64_t steps_offset,
+                                                            uint8_t* __restrict__ plan_base,
+                                                            const uint8_t* __restrict__ prepared_plan,
+                                                            int64_t table_offset) {
+  __shared__ uint32_t part[kThreads / 64];  // the waves' totals
   __shared__ uint32_t totals[2];  // blocks in use, blocks after padding to whole K steps
   const int64_t b = blockIdx.z;
   const uint8_t* fl = flags + b * (chunks_a + chunks_b) * G;
@@ -153,28 +156,28 @@ __global__ __launch_bounds__(kFp6PlanThreads) void fp6_plan_kernel(const uint8_t
   // OR over the row chunks, all threads side by side, into LDS: one byte per group position (bit 0: A, bit 1: B)
   __shared__ uint32_t gathered[(1 << 15) / 4];  // K <= 2^20: at most 2^15 group positions
   const int64_t words = (G + 3) / 4;
-  const int64_t per = (G + kFp6PlanThreads - 1) / kFp6PlanThreads, g0 = threadIdx.x * per, g1 = g0 + per < G ? g0 + per : G;
+  const int64_t per = (G + kThreads - 1) / kThreads, g0 = threadIdx.x * per, g1 = g0 + per < G ? g0 + per : G;
   // a prepared B's flag of this thread's first position and its place in the panel, requested before anything else
   const uint8_t* split_b = prepared_plan + (G + 1) * 4;
   const uint32_t* pos_b = reinterpret_cast<const uint32_t*>(prepared_plan);
   const uint32_t first_split = prepared_plan && g0 < G ? split_b[g0] : 0u, first_pos = prepared_plan && g0 < G ? pos_b[g0] : 0u;
-  for (int64_t w = threadIdx.x; w < words; w += kFp6PlanThreads) gathered[w] = 0;
+  for (int64_t w = threadIdx.x; w < words; w += kThreads) gathered[w] = 0;
   __syncthreads();
   const int64_t total = (int64_t)(chunks_a + chunks_b) * G;
   if ((G & 3) == 0) {  // four flags per load
     const uint32_t* fl4 = reinterpret_cast<const uint32_t*>(fl);
-    for (int64_t idx0 = threadIdx.x; idx0 < total / 4; idx0 += 8 * kFp6PlanThreads) {  // eight loads in flight per thread
+    for (int64_t idx0 = threadIdx.x; idx0 < total / 4; idx0 += 8 * kThreads) {  // eight loads in flight per thread
       uint32_t v[8];
 #pragma unroll
-      for (int u = 0; u < 8; ++u) v[u] = idx0 + u * kFp6PlanThreads < total / 4 ? fl4[idx0 + u * kFp6PlanThreads] : 0u;
+      for (int u = 0; u < 8; ++u) v[u] = idx0 + u * kThreads < total / 4 ? fl4[idx0 + u * kThreads] : 0u;
 #pragma unroll
       for (int u = 0; u < 8; ++u) {
-        const int64_t idx = idx0 + u * kFp6PlanThreads;
+        const int64_t idx = idx0 + u * kThreads;
         if (v[u]) atomicOr(&gathered[idx % words], idx / words < chunks_a ? v[u] : v[u] << 1);
       }
     }
   } else {
-    for (int64_t idx = threadIdx.x; idx < total; idx += kFp6PlanThreads)
+    for (int64_t idx = threadIdx.x; idx < total; idx += kThreads)
       if (fl[idx]) atomicOr(&gathered[(idx % G) >> 2], (idx / G < chunks_a ? 1u : 2u) << (8 * (idx % G & 3)));
   }
   __syncthreads();
@@ -184,7 +187,7 @@ __global__ __launch_bounds__(kFp6PlanThreads) void fp6_plan_kernel(const uint8_t
     __syncthreads();
   }
   auto flags_of = [&](int64_t g) { return (gathered[g >> 2] >> (8 * (g & 3))) & 3u; };
-  for (int64_t g = threadIdx.x; g < G; g += kFp6PlanThreads) split[g] = (uint8_t)flags_of(g);
+  for (int64_t g = threadIdx.x; g < G; g += kThreads) split[g] = (uint8_t)flags_of(g);
   uint32_t sum = 0;
   for (int64_t g = g0; g < g1; ++g) sum += (1u + (flags_of(g) & 1u)) * (1u + (flags_of(g) >> 1));
   // exclusive scan of the threads' partial sums: within each wave by lane shifts, then the waves' totals
@@ -198,7 +201,7 @@ __global__ __launch_bounds__(kFp6PlanThreads) void fp6_plan_kernel(const uint8_t
   __syncthreads();
   uint32_t before = 0, all = 0;
 #pragma unroll
-  for (int w = 0; w < kFp6PlanThreads / 64; ++w) {
+  for (int w = 0; w < kThreads / 64; ++w) {
     if (w < (int)(threadIdx.x >> 6)) before += part[w];
     all += part[w];
   }
@@ -224,7 +227,19 @@ __global__ __launch_bounds__(kFp6PlanThreads) void fp6_plan_kernel(const uint8_t
     run += (1u + fa) * (1u + fb);
   }
   if (prepared_plan)  // the zero blocks that pad K, and the 17 stages the kernel's table reads may run past the end
-    for (uint32_t e = totals[0] + threadIdx.x; e < totals[1] + 34; e += kFp6PlanThreads) table[e] = 0;
+    for (uint32_t e = totals[0] + threadIdx.x; e < totals[1] + 34; e += kThreads) table[e] = 0;
+}
+
+static void launch_fp6_plan(const uint8_t* flags, int64_t G, int chunks_a, int chunks_b, int64_t plan_stride,
+                            int64_t steps_offset, uint8_t* plan, const uint8_t* prepared_plan, int64_t table_offset,
+                            int64_t batch, hipStream_t s) {
+  const dim3 grid(1, 1, (unsigned)batch);
+  if (G <= 256 && (chunks_a + chunks_b) * G <= 8 * 4 * 256)
+    hipLaunchKernelGGL(fp6_plan_kernel<256>, grid, dim3(256), 0, s, flags, G, chunks_a, chunks_b, plan_stride, steps_offset,
+                       plan, prepared_plan, table_offset);
+  else
+    hipLaunchKernelGGL(fp6_plan_kernel<1024>, grid, dim3(1024), 0, s, flags, G, chunks_a, chunks_b, plan_stride, steps_offset,
+                       plan, prepared_plan, table_offset);
 }
 
 // ---- pass 3: the merge ---------------------------------------------------------------------------------------------------
@@ -721,8 +736,7 @@ hipError_t launch_gemm_fp6m_path(int64_t M, int64_t N, int64_t K, const uint8_t*
   // (the flag array of one batch entry is (chunks_a + chunks_b) * G bytes; entries lie back to back)
   hipLaunchKernelGGL(fp6_flag_kernel, dim3((unsigned)((G + 63) / 64), (unsigned)(chunks_a + chunks_b), (unsigned)batch),
                      dim3(64 * kFp6FlagLanes), 0, s, A_scales, B_scales, M, N, G, chunks_a, chunks_b, flags);
-  hipLaunchKernelGGL(fp6_plan_kernel, dim3(1, 1, (unsigned)batch), dim3(kFp6PlanThreads), 0, s, flags, G, chunks_a, chunks_b,
-                     plan_stride, steps_offset, plan, static_cast<const uint8_t*>(nullptr), (int64_t)0);
+  launch_fp6_plan(flags, G, chunks_a, chunks_b, plan_stride, steps_offset, plan, nullptr, 0, batch, s);
   const Fp6MergeJob ja = {A_codes, A_scales, Ap, Asc, M, Mp}, jb = {B_codes, B_scales, Bp, Bsc, N, Np};
   hipError_t e = launch_fp6_merge(ja, jb, Fp6GatherJob{}, K, max_steps, plan_stride, steps_offset, plan, batch, s);
   if (e != hipSuccess) return e;
@@ -759,8 +773,7 @@ hipError_t launch_fp6m_prepare_b(int64_t N, int64_t K, const uint8_t* B_codes, c
   const int64_t steps_offset = round_up((G + 1) * 4 + G, 4);
   hipLaunchKernelGGL(fp6_flag_kernel, dim3((unsigned)((G + 63) / 64), (unsigned)chunks_b, 1), dim3(64 * kFp6FlagLanes), 0, s,
                      static_cast<const uint8_t*>(nullptr), B_scales, (int64_t)0, N, G, 0, chunks_b, flags);
-  hipLaunchKernelGGL(fp6_plan_kernel, dim3(1, 1, 1), dim3(kFp6PlanThreads), 0, s, flags, G, 0, chunks_b, fp6_plan_bytes(K),
-                     steps_offset, plan, static_cast<const uint8_t*>(nullptr), (int64_t)0);
+  launch_fp6_plan(flags, G, 0, chunks_b, fp6_plan_bytes(K), steps_offset, plan, nullptr, 0, 1, s);
   const Fp6MergeJob none = {nullptr, nullptr, nullptr, nullptr, 0, 0}, jb = {B_codes, B_scales, Bp, Bsc, N, Np};
   return launch_fp6_merge(none, jb, Fp6GatherJob{}, K, b_steps, fp6_plan_bytes(K), steps_offset, plan, 1, s);
 }
@@ -783,8 +796,7 @@ hipError_t launch_gemm_fp6m_prepared(int64_t M, int64_t N, int64_t K, const uint
   const int64_t table_offset = fp6_table_offset(K);
   hipLaunchKernelGGL(fp6_flag_kernel, dim3((unsigned)((G + 63) / 64), (unsigned)chunks_a, 1), dim3(64 * kFp6FlagLanes), 0, s, A_scales,
                      static_cast<const uint8_t*>(nullptr), M, (int64_t)0, G, chunks_a, 0, flags);
-  hipLaunchKernelGGL(fp6_plan_kernel, dim3(1, 1, 1), dim3(kFp6PlanThreads), 0, s, flags, G, chunks_a, 0, plan_stride, steps_offset, plan,
-                     plan_b, table_offset);
+  launch_fp6_plan(flags, G, chunks_a, 0, plan_stride, steps_offset, plan, plan_b, table_offset, 1, s);
   const Fp6MergeJob ja = {A_codes, A_scales, Ap, Asc, M, Mp}, none = {nullptr, nullptr, nullptr, nullptr, 0, 0};
   // (chunks: the words of a K of which a few positions are split; more are done in further turns)
   const Fp6GatherJob gather = {Bsc_prepared, Bsc, Np / 32, b_steps / 4, max_steps / 4, table_offset, (int)(G / 128 + 1)};

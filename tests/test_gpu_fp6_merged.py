@@ -20,10 +20,11 @@ def fp6():
 
 @pytest.mark.parametrize("scale", [ref.E8M0_FLOOR, ref.E8M0_ROUND])
 @pytest.mark.parametrize("M,N,K", [(1, 1, 32), (33, 65, 96), (100, 200, 160), (257, 255, 544), (300, 520, 1024),
-                                   (31, 257, 384), (260, 300, 768), (64, 1024, 1024), (513, 129, 4096)])
+                                   (31, 257, 384), (260, 300, 768), (64, 1024, 1024), (513, 129, 4096),
+                                   (70, 65, 8192), (70, 65, 8224)])
 def test_ragged_shapes(M, N, K, scale):
     """Partial tiles in M and N; K from one group (padded to twelve K steps of zero blocks) to many ring turns, with
-    and without a K tail. The activations carry an outlier channel, so some group positions of A are split."""
+    and without a K tail; 256 group positions, the most of the plan's small workgroup, and 257. The activations carry an outlier channel, so some group positions of A are split."""
     a = synth.activations(M, K, seed=M + K, n_outlier=1, outlier_gain=60.0)
     b = synth.weights(N, K, seed=N)
     ac, as_ = ref.quantize(a, 32, scale, 1)
