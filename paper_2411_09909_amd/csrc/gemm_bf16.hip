@@ -378,6 +378,65 @@ hipError_t launch_expand_f16_e5m2(bool asym, const uint8_t* codes, const uint8_t
               : launch_expand<kScaleE5M2, false, true>(codes, scales, R, K, Rp, Kp, 5, batch, panel, s);
 }
 
+// Whether equal runs of tiles of 256 x tile_cols, per_xcd to an XCD, end sooner than supertiles where those leave a fifth of their slots
+// empty. What counts is the tiles that an XCD really has (its share; 32 CUs: one round of 32 at a time), measured in both orders
+// over 1 .. 16 rows and 2 .. 251 columns of tiles, us of the kernel, supertiles / runs:
+//   fewer rounds: runs (12 x 20 tiles, K 13824, a share of 64 tiles or 30: 520 / 292;  9 x 112, K 4096, 224 or 126: 556 / 392)
+//   one round either way: runs, which spread the tiles over all XCDs (8 x 16, K 4096, 32 or 16: 98 / 76;  1 x 126: 193 / 123),
+//     but with a partial row of supertiles, whose XCDs alternate between full and nearly empty, only for much smaller shares
+//     (9 x 16, K 4096, 32 or 18: 87 / 77;  12 x 16 tiles of 256 x 128, K 2048, 32 or 24: 28 / 29)
+//   several rounds, as many either way: runs
+//     up to two rows of tiles (2 x 112, K 4096: 174 / 117), and three of 256 x 128 (3 x 172, the call: 177 / 150)
+//     where no more than two XCDs carry the largest share or 8 tiles less (8 x 40, K 8192, 64 or 40: 358 / 311;  14 x 20 of FP6,
+//       the call: 238 / 214)
+//     without a partial row of supertiles where the last round of that share is nearly full (6 x 112, K 4096, 96 or 84: 340 / 292)
+//   otherwise they only make every XCD take a last round that few took (6 x 86 of 256 x 128, 72 or 65: 132 / 143;  4 x 224 of
+//     them, 112 either way: 222 / 244;  10 x 32, K 8192, 64 or 40: 289 / 309;  12 x 43, K 4096, 96 or 65: 248 / 261, FP4 100 /
+//     106;  14 x 43 of FP4, the call: 107 / 113;  3 x 86 of it, gated, 59 / 64)
+//   one or two columns and many rows: a run shares fewer rows of A (32 x 2 FP4 tiles, K 28672, the call: 175 / 189)
+static bool equal_runs_pay(int tiles_m, int tiles_n, int tile_cols, int64_t per_xcd) {
+  if (tiles_n <= 2 && tiles_m > 2 * kSuperM) return false;
+  const int super_m = (tiles_m + kSuperM - 1) / kSuperM, super_n = (tiles_n + kSuperN - 1) / kSuperN;
+  int64_t tiles[8] = {}, share = 0;
+  for (int st = 0; st < super_m * super_n; ++st) {
+    const int m = tiles_m - st % super_m * kSuperM, n = tiles_n - st / super_m * kSuperN;
+    int64_t& t = tiles[st & 7];
+    t += (m < kSuperM ? m : kSuperM) * (n < kSuperN ? n : kSuperN);
+    share = t > share ? t : share;
+  }
+  constexpr int kRound = kSuperM * kSuperN;
+  const bool partial_row = tiles_m > kSuperM && tiles_m % kSuperM != 0;
+  if ((per_xcd + kRound - 1) / kRound < (share + kRound - 1) / kRound || tiles_m <= (tile_cols < 256 ? 3 : 2))
+    return true;
+  if (share <= kRound) return !partial_row || 8 * per_xcd <= 5 * share;
+  int fullest = 0;
+  for (int64_t t : tiles) fullest += t >= share - 8;
+  return fullest <= 2 || (!partial_row && (share - 1) % kRound >= 19);
+}
+
+// Grid size (x) for a tiles_m x tiles_n problem, and the order of its tiles (super_m, for tile_of_workgroup()).
+// Supertiles are dealt 8 at a time, one per XCD. Where tiles_m is no multiple of 8, or the last 8 supertiles are not all
+// there, an XCD has whole supertiles of work while others have none or leave CUs empty: then equal runs of tiles are dealt
+// where they pay (bands of fewer than 8 rows share the staged panels a little less). The rule above is for one problem of tiles
+// that fill a CU; with tiles of fewer rows, and in a batch, whose entries all start at the same XCD, the runs are dealt
+// wherever a fifth of the slots is empty (8 x 1024 x 1024 x 128 on FP4: 41 / 12.5; 1504 x 1024 x 1024 on 64-row tiles: 20 / 18).
+// Per call, E5M2 asymmetric on the panel kernel: 3000 x 5120 x 13824, 12 x 20 tiles, 543 -> 345 us; 2300 x 13824 x 5120, 9 x
+// 54, 387 -> 269; 1504 x 28672 x 4096, 6 x 112, 400 -> 347; 1504 x 6144 x 4096, 6 x 24, 92 -> 87; 4067 x 4544 x 4544, 16 x 36
+// of the 256 x 128 tiles, 183 -> 173. Merged FP6, 3000 x 10240 x 8192: 228 -> 179. Where few slots are empty, supertiles: 4096
+// x 28672 x 8192 stays at 1430-1440.
+unsigned supertile_grid(int tiles_m, int tiles_n, int tile_rows, int tile_cols, int64_t batch, int& super_m) {
+  super_m = (tiles_m + kSuperM - 1) / kSuperM;
+  const int super_n = (tiles_n + kSuperN - 1) / kSuperN;
+  const int rounds = (super_m * super_n + 7) / 8;
+  const int64_t tiles = (int64_t)tiles_m * tiles_n, per_xcd = (tiles + 7) / 8;
+  if (tiles < (int64_t(1) << 30) && 5 * per_xcd <= 4 * (int64_t)rounds * kSuperM * kSuperN &&
+      (batch > 1 || tile_rows < 256 || equal_runs_pay(tiles_m, tiles_n, tile_cols, per_xcd))) {
+    super_m = 0;
+    return (unsigned)(per_xcd * 8);
+  }
+  return (unsigned)(rounds * 8 * kSuperM * kSuperN);
+}
+
 template <int WM, int WN, int FM, int FN>
 static hipError_t launch_tiles(const uint16_t* Ap, const uint16_t* Bp, float* C, int64_t M, int64_t N, int64_t Mp,
                                int64_t Np, int64_t Kp, int64_t ldc, int64_t batch, const float* alpha_a,
@@ -385,7 +444,7 @@ static hipError_t launch_tiles(const uint16_t* Ap, const uint16_t* Bp, float* C,
   using Cfg = TileCfg<WM, WN, FM, FN>;
   const int tiles_m = (int)((M + Cfg::kTileM - 1) / Cfg::kTileM), tiles_n = (int)((N + Cfg::kTileN - 1) / Cfg::kTileN);
   int super_m;
-  const unsigned grid = supertile_grid(tiles_m, tiles_n, super_m);
+  const unsigned grid = supertile_grid(tiles_m, tiles_n, Cfg::kTileM, Cfg::kTileN, batch, super_m);
   if (glu)
     hipLaunchKernelGGL((gemm_bf16_kernel<WM, WN, FM, FN, false, true>), dim3(grid, 1, (unsigned)batch),
                        dim3(Cfg::kThreads), 0, s, Ap, Bp, C, M, N, Mp, Np, Kp, ldc, tiles_m, tiles_n, super_m, alpha_a,

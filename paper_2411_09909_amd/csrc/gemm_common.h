@@ -55,25 +55,9 @@ __device__ __forceinline__ bool tile_of_workgroup(int p, int tiles_m, int tiles_
   return tm < tiles_m && tn < tiles_n;
 }
 
-// Grid size (x) for a tiles_m x tiles_n problem, and the order of its tiles (super_m, for tile_of_workgroup()).
-// Supertiles are dealt 8 at a time, one per XCD. Where tiles_m is no multiple of 8, or the last 8 supertiles are not all
-// there, an XCD has whole supertiles of work while others have none or leave CUs empty: if the largest share of an XCD is
-// at least a fifth smaller with equal runs of tiles, those are dealt (bands of fewer than 8 rows share the staged panels a
-// little less). Per call, E5M2 asymmetric on the panel kernel: 3000 x 5120 x 13824, 12 x 20 tiles, 543 -> 345 us;
-// 2300 x 13824 x 5120, 9 x 54, 387 -> 269; 1504 x 28672 x 4096, 6 x 112, 400 -> 347; 1504 x 6144 x 4096, 6 x 24, 92 -> 87;
-// 4067 x 4544 x 4544, 16 x 36 of the 256 x 128 tiles, 183 -> 173. Merged FP6, 3000 x 10240 x 8192: 228 -> 179. Where the
-// shares are alike, supertiles: 4096 x 28672 x 8192 stays at 1430-1440.
-inline unsigned supertile_grid(int tiles_m, int tiles_n, int& super_m) {
-  super_m = (tiles_m + kSuperM - 1) / kSuperM;
-  const int super_n = (tiles_n + kSuperN - 1) / kSuperN;
-  const int rounds = (super_m * super_n + 7) / 8;
-  const int64_t tiles = (int64_t)tiles_m * tiles_n, per_xcd = (tiles + 7) / 8;
-  if (tiles < (int64_t(1) << 30) && 5 * per_xcd <= 4 * (int64_t)rounds * kSuperM * kSuperN) {
-    super_m = 0;
-    return (unsigned)(per_xcd * 8);
-  }
-  return (unsigned)(rounds * 8 * kSuperM * kSuperN);
-}
+// Grid size (x) for a tiles_m x tiles_n problem of a batch, and the order of its tiles (super_m, for tile_of_workgroup()).
+// Defined with its rule in gemm_bf16.hip.
+unsigned supertile_grid(int tiles_m, int tiles_n, int tile_rows, int tile_cols, int64_t batch, int& super_m);
 
 // s_waitcnt immediate that waits until at most n (< 64) vector-memory operations are outstanding and nothing else
 // (gfx9 encoding: vmcnt = bits 3:0 and 15:14, expcnt = bits 6:4, lgkmcnt = bits 11:8)

@@ -306,7 +306,7 @@ hipError_t launch_gemm_e5m2_fused(bool asym, int64_t M, int64_t N, int64_t K, co
                                   int64_t ldc, int64_t batch, hipStream_t s, const KernelTimer& timer) {
   const int tiles_m = (int)((M + kE5Tile - 1) / kE5Tile), tiles_n = (int)((N + kE5Tile - 1) / kE5Tile);
   int super_m;
-  const dim3 grid(supertile_grid(tiles_m, tiles_n, super_m), 1, (unsigned)batch);
+  const dim3 grid(supertile_grid(tiles_m, tiles_n, kE5Tile, kE5Tile, batch, super_m), 1, (unsigned)batch);
   hipError_t e;
   if (timer.start && (e = hipEventRecord(timer.start, s)) != hipSuccess) return e;
   if (asym)
@@ -593,7 +593,7 @@ hipError_t launch_gemm_e5m2_hybrid(bool asym, int64_t M, int64_t N, int64_t K, c
   if (e != hipSuccess) return e;
   const int tiles_m = (int)((M + kE5Tile - 1) / kE5Tile), tiles_n = (int)((N + kE5Tile - 1) / kE5Tile);
   int super_m;
-  const dim3 grid(supertile_grid(tiles_m, tiles_n, super_m), 1, (unsigned)batch);
+  const dim3 grid(supertile_grid(tiles_m, tiles_n, kE5Tile, kE5Tile, batch, super_m), 1, (unsigned)batch);
   if (timer.start && (e = hipEventRecord(timer.start, s)) != hipSuccess) return e;
   if (asym)
     hipLaunchKernelGGL((gemm_e5m2_hybrid_kernel<true>), grid, dim3(256), 0, s, Ap, B_codes, B_scales, C, M, N, Mp, K,

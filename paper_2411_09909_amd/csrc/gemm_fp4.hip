@@ -442,7 +442,7 @@ static hipError_t launch_fp4(int64_t M, int64_t N, int64_t K, const uint8_t* Ac,
   using Cfg = TileCfg<2, 2, 4, 4>;
   const int tiles_m = (int)((M + Cfg::kTileM - 1) / Cfg::kTileM), tiles_n = (int)((N + Cfg::kTileN - 1) / Cfg::kTileN);
   int super_m;
-  const unsigned grid = supertile_grid(tiles_m, tiles_n, super_m);
+  const unsigned grid = supertile_grid(tiles_m, tiles_n, Cfg::kTileM, Cfg::kTileN, batch, super_m);
   // the scale bytes of both operands, re-laid in the order the waves fetch them
   constexpr int SB = ASYM ? 2 : 1;
   const int64_t Mp = round_up(M, kPanelRows), Np = round_up(N, kPanelRows), G = K >> 5;

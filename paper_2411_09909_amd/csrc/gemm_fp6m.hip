@@ -743,7 +743,7 @@ hipError_t launch_gemm_fp6m_path(int64_t M, int64_t N, int64_t K, const uint8_t*
   using Cfg = TileCfg<2, 2, 4, 4>;
   const int tiles_m = (int)((M + Cfg::kTileM - 1) / Cfg::kTileM), tiles_n = (int)((N + Cfg::kTileN - 1) / Cfg::kTileN);
   int super_m;
-  const unsigned grid = supertile_grid(tiles_m, tiles_n, super_m);
+  const unsigned grid = supertile_grid(tiles_m, tiles_n, Cfg::kTileM, Cfg::kTileN, batch, super_m);
   if (timer.start && (e = hipEventRecord(timer.start, s)) != hipSuccess) return e;
   const int steps_cap = (int)max_steps;
   if (glu)
@@ -805,7 +805,7 @@ hipError_t launch_gemm_fp6m_prepared(int64_t M, int64_t N, int64_t K, const uint
   using Cfg = TileCfg<2, 2, 4, 4>;
   const int tiles_m = (int)((M + Cfg::kTileM - 1) / Cfg::kTileM), tiles_n = (int)((N + Cfg::kTileN - 1) / Cfg::kTileN);
   int super_m;
-  const unsigned grid = supertile_grid(tiles_m, tiles_n, super_m);
+  const unsigned grid = supertile_grid(tiles_m, tiles_n, Cfg::kTileM, Cfg::kTileN, 1, super_m);
   if (timer.start && (e = hipEventRecord(timer.start, s)) != hipSuccess) return e;
   const int steps_cap = (int)max_steps, b_cap = (int)b_steps;
   if (glu)

@@ -1,0 +1,58 @@
+"""Which kernel, tile or order of tiles a size takes: the sizes at which the alternatives were measured, on the host alone
+(the rules are functions of the library; no GPU is touched). A line that moves shows up here with the case that it moves."""
+import ctypes
+import os
+
+import pytest
+
+from paper_2411_09909_amd import binding
+
+
+def rule(symbol, result, *arguments):
+    """A function of the library's C++ side by its mangled name."""
+    if not os.path.exists(binding.LIB_PATH):
+        from paper_2411_09909_amd import build
+        build.build(verbose=False)
+    f = getattr(ctypes.CDLL(binding.LIB_PATH), symbol)
+    f.restype, f.argtypes = result, arguments
+    return f
+
+
+i64, i32 = ctypes.c_int64, ctypes.c_int
+
+
+def tile_order(tiles_m, tiles_n, tile_rows=256, tile_cols=256, batch=1):
+    """(workgroups along x, rows of supertiles or 0 for equal runs)"""
+    super_m = i32(-1)
+    grid = rule("_ZN3amx14supertile_gridEiiiilRi", ctypes.c_uint, i32, i32, i32, i32, i64, ctypes.POINTER(i32))
+    return grid(tiles_m, tiles_n, tile_rows, tile_cols, batch, ctypes.byref(super_m)), super_m.value
+
+
+@pytest.mark.parametrize("tiles_m,tiles_n,tile_cols,runs", [
+    (12, 20, 256, 1), (9, 112, 256, 1),   # fewer rounds (520 / 292 us, 556 / 392)
+    (8, 16, 256, 1), (1, 126, 256, 1), (9, 16, 256, 1), (12, 16, 128, 0),  # one round: 98 / 76, 193 / 123, 87 / 77, 28 / 29
+    (2, 112, 256, 1), (3, 172, 128, 1), (8, 40, 256, 1), (14, 20, 256, 1), (6, 112, 256, 1),
+    (6, 86, 128, 0), (4, 224, 128, 0), (10, 32, 256, 0), (12, 43, 256, 0), (14, 43, 256, 0), (3, 86, 256, 0),
+    (32, 2, 256, 0), (16, 112, 256, 0), (8, 32, 256, 0)])
+def test_order_of_tiles_that_fill_a_compute_unit(tiles_m, tiles_n, tile_cols, runs):
+    grid, super_m = tile_order(tiles_m, tiles_n, 256, tile_cols)
+    assert (super_m == 0) == bool(runs)
+
+
+@pytest.mark.parametrize("tiles_m,tiles_n,rows,batch,runs", [(4, 4, 256, 8, 1), (24, 4, 64, 1, 1), (10, 32, 256, 4, 1),
+                                                             (8, 32, 256, 4, 0)])
+def test_order_in_a_batch_and_of_small_tiles(tiles_m, tiles_n, rows, batch, runs):
+    """Runs wherever a fifth of the slots is empty."""
+    assert (tile_order(tiles_m, tiles_n, rows, 256, batch)[1] == 0) == bool(runs)
+
+
+def test_grid_has_a_workgroup_for_every_tile():
+    for tiles_m in range(1, 40):
+        for tiles_n in range(1, 70):
+            for batch in (1, 2):
+                grid, super_m = tile_order(tiles_m, tiles_n, batch=batch)
+                assert grid % 8 == 0 and grid >= tiles_m * tiles_n
+                if super_m:
+                    assert super_m == -(-tiles_m // 8) and grid == 8 * 32 * -(-(super_m * -(-tiles_n // 4)) // 8)
+                else:
+                    assert grid < tiles_m * tiles_n + 8
