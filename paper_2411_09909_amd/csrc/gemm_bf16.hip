@@ -465,7 +465,9 @@ static hipError_t launch_tiles(const uint16_t* Ap, const uint16_t* Bp, float* C,
 // 256 x 256 only for a predicted gain: of more than 15 % for 64 x 256, of more than 8 % for 256 x 128, which takes in the
 // problems of 257 to 384 large tiles: two rounds of those, three of the halves. Us per call, 256 x 256 / 256 x 128:
 // 2048 x 11008 x 4096 213-219 / 183, 1700 x 11008 x 4096 196-198 / 170, 1900 x 10240 x 8192 403 / 339, 2600 x 8192 x 8192
-// 355 / 337, 3800 x 4544 x 4544 201 / 186, 1300 x 13824 x 5120 221 / 220.
+// 355 / 337, 3800 x 4544 x 4544 201 / 186, 1300 x 13824 x 5120 221 / 220. With no more than three rows of tiles that needs a
+// second round of hardly any large tiles (768 x 22016 x 4096, 258 tiles, gated, prepared, 167 / 150; but 768 x 28672 x 8192,
+// 336 tiles, 490 / 522, gated x 4096, prepared, 170 / 182; 640 x 32001 x 4096, 378 tiles, prepared, 214 / 221).
 int bf16_tile_choice(int64_t M, int64_t N, int64_t batch) {
   auto rounds = [&](int64_t tile_m, int64_t tile_n) {
     const int64_t tiles = ((M + tile_m - 1) / tile_m) * ((N + tile_n - 1) / tile_n) * batch;
@@ -473,7 +475,8 @@ int bf16_tile_choice(int64_t M, int64_t N, int64_t batch) {
   };
   const double est1 = rounds(256, 256), est2 = 0.6 * rounds(256, 128), est3 = 0.4 * rounds(64, 256);
   const bool ok3 = est3 < 0.85 * est1;
-  const bool ok2 = est2 < 0.92 * est1 && M > 256;  // (with a single row of 256-row tiles the 64-row tile was never worse)
+  const bool two_rounds = M > 768 || (M + 255) / 256 * ((N + 255) / 256) * batch <= 288;
+  const bool ok2 = est2 < (two_rounds ? 0.92 : 0.85) * est1 && M > 256;  // (with a single row of 256-row tiles the 64-row tile was never worse)
   return ok3 && (!ok2 || est3 <= est2) ? 3 : ok2 ? 2 : 1;
 }
 

@@ -56,3 +56,12 @@ def test_grid_has_a_workgroup_for_every_tile():
                     assert super_m == -(-tiles_m // 8) and grid == 8 * 32 * -(-(super_m * -(-tiles_n // 4)) // 8)
                 else:
                     assert grid < tiles_m * tiles_n + 8
+
+
+@pytest.mark.parametrize("M,N,tile", [
+    (2048, 11008, 2), (1900, 10240, 2), (2600, 8192, 2), (3800, 4544, 2),  # 257 .. 384 large tiles (213 / 183, 403 / 339, ...)
+    (768, 22016, 2), (768, 28672, 1), (640, 32001, 1),                     # three rows of them: 258, 336, 378 large tiles
+    (256, 11008, 3), (500, 4096, 3), (4096, 28672, 1), (4096, 4096, 1)])
+def test_tile_of_the_bf16_panel_kernel(M, N, tile):
+    """1: 256 x 256, 2: 256 x 128, 3: 64 x 256"""
+    assert rule("_ZN3amx16bf16_tile_choiceElll", i32, i64, i64, i64)(M, N, 1) == tile
