@@ -6,6 +6,11 @@ namespace amx {
 
 static bool pot_scales(int scale_kind) { return scale_kind == kScaleE8M0Floor || scale_kind == kScaleE8M0Round; }
 
+// The rounded power-of-two scale of a BF16 maximum above 1.41 * 2^127 is 2^126, and its largest element 4: a value of 2^128,
+// which no 16-bit float holds. The block-scaled kernels, which never form it, keep what they took of that format; this one
+// takes it only where the few-rows kernel, with the same limit, did.
+static bool rounded_pot(int scale_kind, int64_t group_size) { return scale_kind == kScaleE8M0Round && group_size == 32; }
+
 // Time of this kernel for more than 64 rows, us, in the shape <2, 2, 4> below: workgroups of 64 x 64 outputs, 256 at a
 // time. Fitted to K 1024 .. 13824, N 1024 .. 28672, 80 .. 2048 rows, where it is within 10 %.
 static double stream_us(int scale_kind, bool asym, int64_t M, int64_t N, int64_t K) {
@@ -37,6 +42,7 @@ bool fp4_beats_stream(int64_t M, int64_t N, int64_t K) {
 //     97 / 134;  768 x 1024 x 1024: 7.7 / 17;  but 768 x 14336 x 4096: 135 / 129).
 bool stream_path_preferred(int scale_kind, bool asym, int64_t group_size, int64_t M, int64_t N, int64_t K, int64_t batch) {
   if ((group_size != 32 && group_size != 16) || K % 32 != 0) return false;
+  if (rounded_pot(scale_kind, group_size) && !skinny_path_supported(M, N, K, batch)) return false;
   if (M <= 64) return true;
   if (batch != 1) return false;
   if (group_size == 32 && pot_scales(scale_kind)) {
@@ -52,6 +58,7 @@ bool stream_path_preferred(int scale_kind, bool asym, int64_t group_size, int64_
 // here too (AMXFP4-E5M2, 28672 x 8192, 256 rows: 177 us against 350), and asymmetric power-of-two scales while the FP6
 // kernel's merge of the weights and its one round of tiles, 20 us + 4.7 ns K + 0.37 ps N K, takes longer.
 bool stream_glu_preferred(int scale_kind, bool asym, int64_t group_size, int64_t M, int64_t N, int64_t K) {
+  if (rounded_pot(scale_kind, group_size)) return false;
   if (M > 256 || M <= 64) return stream_path_preferred(scale_kind, asym, group_size, M, N, K, 1);
   if ((group_size != 32 && group_size != 16) || K % 32 != 0) return false;
   if (group_size == 32 && pot_scales(scale_kind)) {
