@@ -15,17 +15,22 @@ static bool rounded_pot(int scale_kind, int64_t group_size) { return scale_kind 
 // time. Fitted to K 1024 .. 13824, N 1024 .. 28672, 80 .. 2048 rows, where it is within 10 %.
 static double stream_us(int scale_kind, bool asym, int64_t M, int64_t N, int64_t K) {
   const double rounds = (double)(((M + 63) / 64 * ((N + 63) / 64) + 255) / 256), k = (double)K / 4096.0;
-  return asym ? 4.0 + k * (2.0 + 11.5 * rounds) : pot_scales(scale_kind) ? 3.0 + k * (1.5 + 7.3 * rounds) : 4.0 + k * (1.5 + 9.3 * rounds);
+  return asym ? 4.0 + k * (2.0 + 11.5 * rounds) : 4.0 + k * (1.5 + 9.3 * rounds);
 }
 
-// The FP4 kernel (symmetric power-of-two scales, groups of 32) while its 256 x 256 tiles fit the compute units once: 31 us
-// at K 4096, 48 at 8192, 70 at 13824, whatever M and N are.
-static double fp4_us(int64_t K) { return 14.0 + 0.0041 * (double)K; }
-
-// More than 64 rows of that format: whether the FP4 kernel is the fastest of the three that could take them. The few-rows
-// kernel never is there (28672 x 8192: 80 rows 69 us, 256 rows 137, the FP4 kernel 48).
-bool fp4_beats_stream(int64_t M, int64_t N, int64_t K) {
-  return M > 64 && fp4_us(K) <= stream_us(kScaleE8M0Floor, false, M, N, K);
+// Symmetric power-of-two scales of 32-groups, more than 64 rows: whether the FP4 kernel is the fastest of the three that
+// could take them. Besides the output it takes 11 us + 5 ns K, from K 2048 on 12.8 + 4.2 ns K, while its 256 x 256 tiles fit the
+// compute units once (512 x 11008 x 1024 20 us, 1024 x 4096 x 2048 23, x 4096 31.6, output included); this kernel 3 us and per round of 256
+// workgroups 1.25 us + 1.1 ns K, or 1.7 ns K if that is more (512 x 4096 x 4096, two rounds, 19; 1024 x 4096 x 2048, four, 20; 2048
+// x 4096 x 128, eight, 20, the FP4 kernel 12.6). Up to 16384 rows; beyond, the FP4 kernel (32768 x 128 x 128 10.3 against 12.2,
+// 100000 x 512 x 128 47 against 104). The few-rows kernel never is the fastest there (28672 x 8192: 80 rows 69 us, 256 rows 137,
+// the FP4 kernel 66-69).
+bool fp4_beats_stream(int64_t M, int64_t N, int64_t K, double c_bytes) {
+  if (M <= 64) return false;
+  const double k = (double)K, c = c_bytes * (double)M * (double)N, rounds = (double)(((M + 63) / 64 * ((N + 63) / 64) + 255) / 256);
+  const double fp4 = (K < 2048 ? 11.0 + 0.005 * k : 12.8 + 0.0042 * k) + c / 6.5e6;
+  const double short_k = 1.25 + 0.00107 * k, long_k = 0.00171 * k;
+  return M > 16384 || fp4 <= 3.0 + rounds * (short_k > long_k ? short_k : long_k) + c / 5.1e6;
 }
 
 // Whether this kernel takes a product, single problems and batches alike unless said otherwise. us for the whole call,
@@ -46,7 +51,7 @@ bool stream_path_preferred(int scale_kind, bool asym, int64_t group_size, int64_
   if (M <= 64) return true;
   if (batch != 1) return false;
   if (group_size == 32 && pot_scales(scale_kind)) {
-    if (!asym) return !fp4_path_supported(M, N, K) ? M <= 256 : !fp4_beats_stream(M, N, K);
+    if (!asym) return !fp4_path_supported(M, N, K) ? M <= 256 : !fp4_beats_stream(M, N, K, 4.0);
     return M <= 256 && N * K < (int64_t(1) << 27);
   }
   if (M > 768 || (N * K >= (int64_t(1) << 27) && (group_size == 32 || M > 256))) return false;
@@ -59,10 +64,11 @@ bool stream_path_preferred(int scale_kind, bool asym, int64_t group_size, int64_
 // kernel's merge of the weights and its one round of tiles, 20 us + 4.7 ns K + 0.37 ps N K, takes longer.
 bool stream_glu_preferred(int scale_kind, bool asym, int64_t group_size, int64_t M, int64_t N, int64_t K) {
   if (rounded_pot(scale_kind, group_size)) return false;
+  if (M > 64 && group_size == 32 && scale_kind == kScaleE8M0Floor && !asym)
+    return !fp4_path_supported(M, N, K) ? M <= 256 : !fp4_beats_stream(M, N, K, 1.0);
   if (M > 256 || M <= 64) return stream_path_preferred(scale_kind, asym, group_size, M, N, K, 1);
   if ((group_size != 32 && group_size != 16) || K % 32 != 0) return false;
   if (group_size == 32 && pot_scales(scale_kind)) {
-    if (!asym) return stream_path_preferred(scale_kind, asym, group_size, M, N, K, 1);
     return stream_us(scale_kind, asym, M, N, K) < 20.0 + 0.0047 * (double)K + 3.7e-7 * (double)N * (double)K;
   }
   return true;

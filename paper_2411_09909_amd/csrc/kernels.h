@@ -93,8 +93,9 @@ hipError_t launch_gemm_stream_glu(int scale_kind, bool asym, int64_t group_size,
                                   const uint8_t* A_codes, const uint8_t* A_scales, const uint8_t* B_codes,
                                   const uint8_t* B_scales, void* out_bf16, int64_t ld_out, hipStream_t s,
                                   const KernelTimer& timer);
-// more than 64 rows, symmetric power-of-two scales of 32-groups: the FP4 kernel is faster than that one
-bool fp4_beats_stream(int64_t M, int64_t N, int64_t K);
+// more than 64 rows, symmetric power-of-two scales of 32-groups: the FP4 kernel is faster than that one (c_bytes: of the output
+// per element of M x N)
+bool fp4_beats_stream(int64_t M, int64_t N, int64_t K, double c_bytes = 4.0);
 hipError_t launch_gemm_stream(int scale_kind, bool asym, int64_t group_size, int64_t M, int64_t N, int64_t K,
                               const uint8_t* A_codes, const uint8_t* A_scales, const uint8_t* B_codes,
                               const uint8_t* B_scales, const float* A_tensor_pair, const float* B_tensor_pair, float* C,

@@ -18,7 +18,7 @@ def rule(symbol, result, *arguments):
     return f
 
 
-i64, i32 = ctypes.c_int64, ctypes.c_int
+i64, i32, f64, flag = ctypes.c_int64, ctypes.c_int, ctypes.c_double, ctypes.c_bool
 
 
 def tile_order(tiles_m, tiles_n, tile_rows=256, tile_cols=256, batch=1):
@@ -65,3 +65,12 @@ def test_grid_has_a_workgroup_for_every_tile():
 def test_tile_of_the_bf16_panel_kernel(M, N, tile):
     """1: 256 x 256, 2: 256 x 128, 3: 64 x 256"""
     assert rule("_ZN3amx16bf16_tile_choiceElll", i32, i64, i64, i64)(M, N, 1) == tile
+
+
+@pytest.mark.parametrize("M,N,K,fp4", [
+    (2048, 4096, 128, 1), (512, 4096, 4096, 0), (1024, 4096, 2048, 0),         # 20 / 12.6 us, 19 / 31.6, 20 / 23
+    (32768, 128, 128, 1), (100000, 512, 128, 1),                               # 12.2 / 10.3, 104 / 47
+    (80, 28672, 8192, 1), (256, 28672, 8192, 1), (64, 28672, 8192, 0), (96, 4096, 4096, 0), (4096, 4096, 4096, 1)])
+def test_symmetric_power_of_two_scales_of_many_rows(M, N, K, fp4):
+    """The FP4 kernel or the one that reads both operands as packed codes, in one launch."""
+    assert rule("_ZN3amx16fp4_beats_streamEllld", flag, i64, i64, i64, f64)(M, N, K, 4.0) == bool(fp4)
