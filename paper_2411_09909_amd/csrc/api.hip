@@ -228,8 +228,9 @@ GemmPlan plan_gemm(const amx_format_t& f, const amx_gemm_options_t* o, bool scal
 // No kernel asked for by the options, and few rows or a small problem: the kernel that reads both operands as packed codes,
 // in one launch. It needs no workspace, but the call still asks for the one of the kernel that plan_gemm() names (what a
 // caller sized for these shapes keeps its meaning, and so does what is refused).
-bool uses_stream(const amx_format_t& f, const amx_gemm_options_t* o, int64_t M, int64_t N, int64_t K, int64_t batch) {
-  return default_options(o) && amx::stream_path_preferred(f.scale, f.asymmetric != 0, f.group_size, M, N, K, batch);
+bool uses_stream(const amx_format_t& f, const amx_gemm_options_t* o, bool scaled, int64_t M, int64_t N, int64_t K,
+                 int64_t batch) {
+  return default_options(o) && amx::stream_path_preferred(f.scale, f.asymmetric != 0, f.group_size, scaled, M, N, K, batch);
 }
 
 size_t plan_workspace_bytes(const GemmPlan& p, bool asym, int64_t M, int64_t N, int64_t K, int64_t batch) {
@@ -283,7 +284,7 @@ int gemm_impl(amx_format_t f, const amx_gemm_options_t* opts, int64_t M, int64_t
   hipStream_t hs = reinterpret_cast<hipStream_t>(stream);
   const bool asym = f.asymmetric != 0;
   hipError_t e;
-  if (uses_stream(f, opts, M, N, K, batch)) {
+  if (uses_stream(f, opts, scaled, M, N, K, batch)) {
     e = amx::launch_gemm_stream(f.scale, asym, f.group_size, M, N, K, A_codes, A_scales, B_codes, B_scales, A_pair, B_pair,
                                 C, ldc, batch, hs, timer);
     return e == hipSuccess ? AMX_OK : hip_fail(e, "gemm launch");

@@ -33,11 +33,37 @@ bool fp4_beats_stream(int64_t M, int64_t N, int64_t K, double c_bytes) {
   return M > 16384 || fp4 <= 3.0 + rounds * (short_k > long_k ? short_k : long_k) + c / 5.1e6;
 }
 
-// Whether this kernel takes a product, single problems and batches alike unless said otherwise. us for the whole call,
-// AMXFP4-E5M2, here / the kernel that took it otherwise:
-//   up to 64 rows: always (1 x 4096 x 4096: 4.8 / 12.7;  64 x 1024 x 1024: 4.0 / 11.2;  32 x 11008 x 4096: 12.5 / 16.9;
-//     32 x 28672 x 8192: 41 / 47;  64 x 28672 x 8192: 56 / 60;  groups of 16, whose weights were expanded to BF16 first,
-//     24 x 11008 x 4096: 10 / 84)
+// Up to 64 rows against K so long that the few-rows kernel, which cuts K into slices for workgroups of their own, is the
+// faster one: here a workgroup's eight waves share all of K, a block of 256 each in turn (the more rows, the longer), and few
+// columns are few workgroups. AMXFP4-E5M2, us here / there: 32 x 1024 x 28672 27 / 22, x 16384 16.6 / 17.5; 32 x 4096 x 28672
+// 27.4 / 25.2; 64 x 128 x 24576 29.5 / 26.2, 64 x 8192 x 28672 59.6 / 53.9, x 20480 the same; 1 x 512 x 40960 25 / 23, x 28672
+// 19 / 21; 32 x 32 x 16384 16.4 / 14.1. Symmetric scales, whose dequantization is half the work: 32 x 512 x 65536 1.25 times,
+// x 40960 1.08 and 17 rows of it 0.85.
+static bool long_k_few_rows(int scale_kind, bool asym, int64_t M, int64_t N, int64_t K) {
+  if (N <= 64) K += K * 3 / 10;  // one or two workgroups: the lines lie lower
+  if (!asym) return M > 16 && (M <= 32 ? K > 49152 && N <= 2048 : K > 57344 && N <= 64);
+  const bool e4m3 = scale_kind == kScaleE4M3;  // (its few-rows kernel dequantizes through FP32: slower)
+  if (M <= 16) return K > (e4m3 ? 49152 : 32768) && N <= 2048;
+  if (M <= 32) return K > 24576 && !e4m3 ? N <= 4096 : K > (e4m3 ? 20480 : 16384) && N <= 2048;
+  if (e4m3) return K > 32768 && N <= 8192;
+  return K > 20480 ? N <= 8192 : K > 16384 && N <= 512;
+}
+
+// A batch of more than 32 rows each and more than two rounds of workgroups: the few-rows kernel, which dequantizes A once, where
+// its 256 columns per workgroup are filled, and where K is a single block, which one wave here takes alone (us here / there: 32 x
+// 64 x 4096 x 1024 38.4 / 34.5;  512 x 64 x 512 x 256 51 / 33;  but 32 x 64 x 2048 x 1024 21 / 23, 512 x 64 x 128 x 4096 66 / 170), or
+// with asymmetric scales or very many workgroups two (64 x 48 x 2048 x 512 30 / 25, symmetric 24.5 / 23.2; but symmetric 24 x 48 x
+// 2048 x 512 12.1 / 13.9).
+static bool batch_few_rows(bool asym, int64_t M, int64_t N, int64_t K, int64_t batch) {
+  const int64_t groups = batch * ((N + 63) / 64);
+  return M > 32 && groups > 512 && (N >= 4096 || (N >= 512 && K <= (asym || groups >= 2048 ? 2 : 1) * kStreamBlockK));
+}
+
+// Whether this kernel takes a product. scaled: with tensor-wise scales (then the panels are the only other kernel). us for
+// the whole call, AMXFP4-E5M2, here / the kernel that took it otherwise:
+//   up to 64 rows, except for a long K and for some batches (above): 1 x 4096 x 4096 4.8 / 12.7;  64 x 1024 x 1024 4.0 / 11.2;
+//     32 x 11008 x 4096 12.5 / 16.9;  32 x 28672 x 8192 41 / 47;  64 x 28672 x 8192 56 / 60;  groups of 16, whose weights were
+//     expanded to BF16 first, 24 x 11008 x 4096 10 / 84;
 //   single problems from there on, symmetric power-of-two scales: where the estimates above say so
 //   the other formats: up to 256 rows, against weights below 2^27 elements (256 x 4096 x 4096: 17 / 50;  256 x 11008 x
 //     4096: 40 / 79;  but 256 x 28672 x 8192: 177 / 151 on the few-rows kernel, which shares the dequantized A);
@@ -45,10 +71,13 @@ bool fp4_beats_stream(int64_t M, int64_t N, int64_t K, double c_bytes) {
 //   up to 512 rows likewise (512 x 4096 x 4096: 28 / 46;  512 x 4096 x 11008: 67 / 128;  512 x 14336 x 4096: 91 / 143);
 //   up to 768 rows where the BF16 panels' tiles leave compute units idle: a long K or few columns (768 x 4096 x 11008:
 //     97 / 134;  768 x 1024 x 1024: 7.7 / 17;  but 768 x 14336 x 4096: 135 / 129).
-bool stream_path_preferred(int scale_kind, bool asym, int64_t group_size, int64_t M, int64_t N, int64_t K, int64_t batch) {
+bool stream_path_preferred(int scale_kind, bool asym, int64_t group_size, bool scaled, int64_t M, int64_t N, int64_t K,
+                           int64_t batch) {
   if ((group_size != 32 && group_size != 16) || K % 32 != 0) return false;
-  if (rounded_pot(scale_kind, group_size) && !skinny_path_supported(M, N, K, batch)) return false;
-  if (M <= 64) return true;
+  const bool few_rows = group_size == 32 && !scaled && skinny_path_supported(M, N, K, batch);  // the kernel of that name
+  if (!scaled && rounded_pot(scale_kind, group_size) && !few_rows) return false;
+  if (M <= 64)
+    return !few_rows || (batch > 1 ? !batch_few_rows(asym, M, N, K, batch) : !long_k_few_rows(scale_kind, asym, M, N, K));
   if (batch != 1) return false;
   if (group_size == 32 && pot_scales(scale_kind)) {
     if (!asym) return !fp4_path_supported(M, N, K) ? M <= 256 : !fp4_beats_stream(M, N, K, 4.0);
@@ -63,11 +92,11 @@ bool stream_path_preferred(int scale_kind, bool asym, int64_t group_size, int64_
 // here too (AMXFP4-E5M2, 28672 x 8192, 256 rows: 177 us against 350), and asymmetric power-of-two scales while the FP6
 // kernel's merge of the weights and its one round of tiles, 20 us + 4.7 ns K + 0.37 ps N K, takes longer.
 bool stream_glu_preferred(int scale_kind, bool asym, int64_t group_size, int64_t M, int64_t N, int64_t K) {
-  if (rounded_pot(scale_kind, group_size)) return false;
+  if ((group_size != 32 && group_size != 16) || K % 32 != 0 || rounded_pot(scale_kind, group_size)) return false;
+  if (M <= 64) return true;
   if (M > 64 && group_size == 32 && scale_kind == kScaleE8M0Floor && !asym)
     return !fp4_path_supported(M, N, K) ? M <= 256 : !fp4_beats_stream(M, N, K, 1.0);
-  if (M > 256 || M <= 64) return stream_path_preferred(scale_kind, asym, group_size, M, N, K, 1);
-  if ((group_size != 32 && group_size != 16) || K % 32 != 0) return false;
+  if (M > 256) return stream_path_preferred(scale_kind, asym, group_size, false, M, N, K, 1);
   if (group_size == 32 && pot_scales(scale_kind)) {
     return stream_us(scale_kind, asym, M, N, K) < 20.0 + 0.0047 * (double)K + 3.7e-7 * (double)N * (double)K;
   }

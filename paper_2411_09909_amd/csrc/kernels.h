@@ -86,7 +86,8 @@ hipError_t launch_gemm_skinny_path(int scale_kind, bool asym, int64_t M, int64_t
 
 // gemm_stream.hip: few rows and small problems, groups of 32 or 16, any K the format takes: one launch that reads both
 // operands as packed codes (no workspace; tensor pairs: both or neither)
-bool stream_path_preferred(int scale_kind, bool asym, int64_t group_size, int64_t M, int64_t N, int64_t K, int64_t batch);
+bool stream_path_preferred(int scale_kind, bool asym, int64_t group_size, bool scaled, int64_t M, int64_t N, int64_t K,
+                           int64_t batch);
 // the gated product (rows of B interleaved; N = 2 * width, a multiple of 64; out: BF16 [M][ld_out])
 bool stream_glu_preferred(int scale_kind, bool asym, int64_t group_size, int64_t M, int64_t N, int64_t K);
 hipError_t launch_gemm_stream_glu(int scale_kind, bool asym, int64_t group_size, int64_t M, int64_t N, int64_t K,

@@ -5,6 +5,7 @@ import os
 
 import pytest
 
+from oracle import ref
 from paper_2411_09909_amd import binding
 
 
@@ -18,6 +19,7 @@ def rule(symbol, result, *arguments):
     return f
 
 
+E5, E4, FLOOR, ROUND = ref.FP8_E5M2, ref.FP8_E4M3, ref.E8M0_FLOOR, ref.E8M0_ROUND
 i64, i32, f64, flag = ctypes.c_int64, ctypes.c_int, ctypes.c_double, ctypes.c_bool
 
 
@@ -74,3 +76,42 @@ def test_tile_of_the_bf16_panel_kernel(M, N, tile):
 def test_symmetric_power_of_two_scales_of_many_rows(M, N, K, fp4):
     """The FP4 kernel or the one that reads both operands as packed codes, in one launch."""
     assert rule("_ZN3amx16fp4_beats_streamEllld", flag, i64, i64, i64, f64)(M, N, K, 4.0) == bool(fp4)
+
+
+def one_launch(scale, asym, M, N, K, batch=1, group=32, scaled=False):
+    """Whether the product goes to the kernel that reads both operands as packed codes."""
+    f = rule("_ZN3amx21stream_path_preferredEiblbllll", flag, i32, flag, i64, flag, i64, i64, i64, i64)
+    return f(scale, bool(asym), group, scaled, M, N, K, batch)
+
+
+def one_launch_gated(scale, asym, M, N, K, group=32):
+    return rule("_ZN3amx20stream_glu_preferredEibllll", flag, i32, flag, i64, i64, i64, i64)(scale, bool(asym), group, M, N, K)
+
+
+@pytest.mark.parametrize("scale,asym,M,N,K,here", [
+    (E5, 1, 1, 4096, 4096, 1), (E5, 1, 64, 28672, 8192, 1), (E5, 0, 64, 11008, 4096, 1),
+    (E5, 1, 32, 1024, 28672, 0), (E5, 1, 32, 1024, 16384, 1), (E5, 1, 32, 4096, 28672, 0),  # 27 / 22 us, 16.6 / 17.5, 27.4 / 25.2
+    (E5, 1, 64, 128, 24576, 0), (E5, 1, 64, 8192, 28672, 0), (E5, 1, 1, 512, 40960, 0), (E5, 1, 1, 512, 28672, 1),
+    (E5, 1, 32, 32, 16384, 0), (E5, 0, 32, 512, 65536, 0), (E5, 0, 17, 512, 40960, 1), (E5, 0, 1, 512, 65536, 1),
+    (E4, 1, 32, 1024, 16384, 1), (E4, 1, 32, 1024, 28672, 0)])
+def test_few_rows_and_a_long_k(scale, asym, M, N, K, here):
+    """Up to 64 rows: one launch, unless K is so long that the few-rows kernel's slices of it are faster."""
+    assert one_launch(scale, asym, M, N, K) == bool(here)
+    assert one_launch(scale, asym, M, N, K, scaled=True) and one_launch(scale, asym, M, N, K, group=16)
+    assert one_launch_gated(scale, asym, M, N, K)
+
+
+@pytest.mark.parametrize("asym,batch,M,N,K,here", [
+    (1, 32, 64, 4096, 1024, 0), (1, 512, 64, 512, 256, 0), (1, 64, 48, 2048, 512, 0), (0, 64, 48, 2048, 512, 0),
+    (1, 32, 64, 2048, 1024, 1), (1, 512, 64, 128, 4096, 1), (0, 24, 48, 2048, 512, 1), (1, 32, 32, 4096, 1024, 1),
+    (1, 512, 16, 512, 256, 1), (1, 2, 64, 4096, 1024, 1)])
+def test_batches_of_few_rows(asym, batch, M, N, K, here):
+    """Two rounds of workgroups and 33 to 64 rows each: the few-rows kernel, which dequantizes A once, for a short K or many
+    columns (38.4 / 34.5 us, 51 / 33, 30 / 25, 24.5 / 23.2; but 21 / 23, 66 / 170, 12.1 / 13.9)."""
+    assert one_launch(E5, asym, M, N, K, batch) == bool(here)
+
+
+@pytest.mark.parametrize("asym", [0, 1])
+@pytest.mark.parametrize("M,N,K", [(40, 4096, 288), (300, 4096, 4096), (800, 4096, 512)])
+def test_rounded_power_of_two_scales_stay_where_their_largest_values_are_finite(M, N, K, asym):
+    assert not one_launch(ROUND, asym, M, N, K) and not one_launch_gated(ROUND, asym, M, N, K)
