@@ -480,6 +480,20 @@ int bf16_tile_choice(int64_t M, int64_t N, int64_t batch) {
   return ok3 && (!ok2 || est3 <= est2) ? 3 : ok2 ? 2 : 1;
 }
 
+// Estimate of a call that expands both operands, us, up to some 800 rows: B's expansion at the copy rate, and the rounds of
+// tiles at the rate of a lone tile (256 x 256 14 ns per unit of K, 256 x 128 9.3, 64 x 256 6.6 to 8 as they fill the chip) or
+// the chip's, and half of the store of C, c_bytes per element of M x N. Measured / estimated: 512 x 4096 x 4096 44 / 44, 512 x 11008 x 4096 66 / 68, 768 x 8192 x
+// 8192 121 / 124, 512 x 13824 x 5120 95 / 102, 512 x 4096 x 11008 106 / 109, 448 x 4544 x 4544 50 / 50.
+double bf16_path_us(int64_t M, int64_t N, int64_t K, double c_bytes) {
+  const int tile = bf16_tile_choice(M, N, 1);
+  const int64_t tile_m = tile == 3 ? 64 : 256, tile_n = tile == 2 ? 128 : 256;
+  const int64_t tiles = ((M + tile_m - 1) / tile_m) * ((N + tile_n - 1) / tile_n);
+  const double fill = tiles < 256 ? (double)tiles / 256.0 : 1.0;
+  const double lone = (tile == 1 ? 14.0 : tile == 2 ? 9.3 : 6.6 + 1.4 * fill) * 1e-3 * (double)((tiles + 255) / 256);
+  const double full = (double)(tiles * tile_m * tile_n) * 2.0 / 1.25e9;
+  return 5.0 + 0.51e-6 * (double)(N * K) + (lone > full ? lone : full) * (double)K + 0.5 * c_bytes * (double)(M * N) / 5.1e6;
+}
+
 hipError_t launch_gemm_bf16_path(int scale_kind, bool asym, int64_t group_size, int64_t M, int64_t N, int64_t K,
                                  const uint8_t* A_codes, const uint8_t* A_scales, const uint8_t* B_codes,
                                  const uint8_t* B_scales, const float* A_tensor_pair, const float* B_tensor_pair,

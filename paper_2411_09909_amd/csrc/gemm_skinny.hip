@@ -120,6 +120,18 @@ static int64_t skinny_panel_rows(int64_t M) {
   return full * kSkinnyMaxM + 32 * skinny_row_tiles(M - full * kSkinnyMaxM);
 }
 
+// Estimate of one call of at most kSkinnyMaxM rows, asymmetric formats, us: 10, the K blocks of a workgroup one after the
+// other, and the partial tiles written and read once. Within 20 % (the low side for few K blocks): 96 x 10240 x 8192, 6
+// slices of 6 blocks, 35 (37); 256 x 32001 x 4096, 16 blocks, 83 (80); 256 x 5120 x 13824, 5 slices of 11, 70 (70).
+double skinny_path_us(int64_t M, int64_t N, int64_t K) {
+  const int tiles = skinny_row_tiles(M);
+  const int64_t Mp = 32 * tiles, cols = skinny_cols(tiles), groups = (N + cols - 1) / cols;
+  int bps;
+  const int slices = skinny_outer_slices(groups, K / kSkinnyBlockK, Mp, 0, bps);
+  const double block = tiles == 1 ? 0.95 : tiles == 2 ? 2.2 : tiles == 3 ? 2.8 : tiles == 4 ? 3.7 : tiles == 6 ? 3.4 : 4.4;
+  return 10.0 + (double)((groups * slices + 255) / 256 * bps) * block + (slices > 1 ? (double)(slices * Mp * N) * 8.0 / 4.7e6 : 0.0);
+}
+
 // bytes of partial tiles one chunk of `rows` rows needs (0 with a single slice)
 static size_t skinny_partial_bytes(int64_t rows, int64_t N, int64_t K, int64_t batch, int forced_slices) {
   const int64_t Mp = 32 * skinny_row_tiles(rows), cols = skinny_cols(skinny_row_tiles(rows));

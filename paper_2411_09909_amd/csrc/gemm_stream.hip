@@ -11,11 +11,18 @@ static bool pot_scales(int scale_kind) { return scale_kind == kScaleE8M0Floor ||
 // takes it only where the few-rows kernel, with the same limit, did.
 static bool rounded_pot(int scale_kind, int64_t group_size) { return scale_kind == kScaleE8M0Round && group_size == 32; }
 
-// Time of this kernel for more than 64 rows, us, in the shape <2, 2, 4> below: workgroups of 64 x 64 outputs, 256 at a
-// time. Fitted to K 1024 .. 13824, N 1024 .. 28672, 80 .. 2048 rows, where it is within 10 %.
-static double stream_us(int scale_kind, bool asym, int64_t M, int64_t N, int64_t K) {
-  const double rounds = (double)(((M + 63) / 64 * ((N + 63) / 64) + 255) / 256), k = (double)K / 4096.0;
-  return asym ? 4.0 + k * (2.0 + 11.5 * rounds) : 4.0 + k * (1.5 + 9.3 * rounds);
+// Time of this kernel for more than 64 rows, us: 64 x 64 outputs per workgroup, 256 workgroups at a time, or the smaller
+// shapes that still give each compute unit one; writing C counts (c_bytes per element of M x N), and so does loading scale bytes
+// one by one where K is no multiple of 256. Within some 10 % at 96 .. 768 rows, N 1024 .. 32001, K 1024 .. 14336.
+static double stream_us(bool asym, int64_t group_size, int64_t M, int64_t N, int64_t K, double c_bytes) {
+  const int64_t rows32 = (M + 31) / 32, t32 = (N + 31) / 32, t64 = (N + 63) / 64;
+  const double rounds = (double)(((M + 63) / 64 * t64 + 255) / 256);
+  const double per_4096 = rows32 * t32 <= 256   ? (asym ? 4.4 : 3.0)
+                          : rows32 * t64 <= 256 ? (asym ? 7.5 : 5.0)
+                          : rounds == 1.0       ? (asym ? 11.0 : 9.0)
+                                                : (asym ? 10.4 : 7.8) * rounds;
+  const double tail = K % kStreamBlockK == 0 ? 1.0 : group_size == 16 ? (asym ? 2.0 : 1.65) : asym ? 1.5 : 1.25;
+  return tail * (3.5 + per_4096 * (double)K / 4096.0) + c_bytes * (double)M * (double)N / 5.1e6;
 }
 
 // Symmetric power-of-two scales of 32-groups, more than 64 rows: whether the FP4 kernel is the fastest of the three that
@@ -65,42 +72,51 @@ static bool batch_few_rows(bool asym, int64_t M, int64_t N, int64_t K, int64_t b
 //     32 x 11008 x 4096 12.5 / 16.9;  32 x 28672 x 8192 41 / 47;  64 x 28672 x 8192 56 / 60;  groups of 16, whose weights were
 //     expanded to BF16 first, 24 x 11008 x 4096 10 / 84;
 //   single problems from there on, symmetric power-of-two scales: where the estimates above say so
-//   the other formats: up to 256 rows, against weights below 2^27 elements (256 x 4096 x 4096: 17 / 50;  256 x 11008 x
-//     4096: 40 / 79;  but 256 x 28672 x 8192: 177 / 151 on the few-rows kernel, which shares the dequantized A);
-//     asymmetric power-of-two scales end here (prepared weights beyond 256 rows are their FP6 panel alone);
-//   up to 512 rows likewise (512 x 4096 x 4096: 28 / 46;  512 x 4096 x 11008: 67 / 128;  512 x 14336 x 4096: 91 / 143);
-//   up to 768 rows where the BF16 panels' tiles leave compute units idle: a long K or few columns (768 x 4096 x 11008:
-//     97 / 134;  768 x 1024 x 1024: 7.7 / 17;  but 768 x 14336 x 4096: 135 / 129).
-bool stream_path_preferred(int scale_kind, bool asym, int64_t group_size, bool scaled, int64_t M, int64_t N, int64_t K,
-                           int64_t batch) {
+//   the other formats up to 256 rows, against weights below 2^27 elements: where the estimates of this and of the few-rows
+//     kernel, which shares the dequantized A, say so (256 x 4096 x 4096 17 / 50;  256 x 11008 x 4096 40 / 79;  but 96 x 10240
+//     x 8192 45 / 35;  256 x 5120 x 13824 74 / 70;  256 x 32001 x 4096 99 / 83), always with symmetric scales (256 x 32001 x
+//     4096 73 / 78). Asymmetric power-of-two scales end here (prepared weights beyond 256 rows are their FP6 panel alone);
+//   up to 512 rows, and to 768 rows with a long K or few columns: where the estimate is below that of the panels, B's
+//     expansion included (512 x 4096 x 4096 27 / 44;  512 x 4096 x 11008 63 / 106;  448 x 11008 x 4096 62 / 65, but 512 rows
+//     73 / 66;  640 x 8192 x 8192 110 / 116, but 768 rows 133 / 121;  448 x 4544 x 4544 43 / 50, but 512 rows 58 / 51).
+//     A product on prepared weights comes here with the plain one, whose bits it promises, although it would save the
+//     expansion: that costs it 1 us at 384-512 x 6144 x 4096 and 320-448 x 4544 x 4544 (37 / 36 and 42 / 41, the plain calls
+//     37 / 47 and 42 / 50), and where several rounds are taken (384 x 11008 x 4096: 60 / 45, plain 60 / 64) more.
+// c_bytes: of the output per element of M x N.
+static bool stream_preferred(int scale_kind, bool asym, int64_t group_size, bool scaled, int64_t M, int64_t N, int64_t K,
+                             int64_t batch, double c_bytes) {
   if ((group_size != 32 && group_size != 16) || K % 32 != 0) return false;
   const bool few_rows = group_size == 32 && !scaled && skinny_path_supported(M, N, K, batch);  // the kernel of that name
   if (!scaled && rounded_pot(scale_kind, group_size) && !few_rows) return false;
   if (M <= 64)
     return !few_rows || (batch > 1 ? !batch_few_rows(asym, M, N, K, batch) : !long_k_few_rows(scale_kind, asym, M, N, K));
   if (batch != 1) return false;
-  if (group_size == 32 && pot_scales(scale_kind)) {
-    if (!asym) return !fp4_path_supported(M, N, K) ? M <= 256 : !fp4_beats_stream(M, N, K, 4.0);
-    return M <= 256 && N * K < (int64_t(1) << 27);
-  }
-  if (M > 768 || (N * K >= (int64_t(1) << 27) && (group_size == 32 || M > 256))) return false;
-  return M <= 512 || K >= 8192 || (M + 63) / 64 * ((N + 63) / 64) <= 512;
+  const bool pot = group_size == 32 && pot_scales(scale_kind);
+  if (pot && !asym) return !fp4_path_supported(M, N, K) ? M <= 256 : !fp4_beats_stream(M, N, K, c_bytes);
+  if (N * K >= (int64_t(1) << 27) && (group_size == 32 || M > 256)) return false;
+  if (M <= 256 && few_rows) return !asym || stream_us(asym, group_size, M, N, K, c_bytes) <= skinny_path_us(M, N, K);
+  if (pot) return M <= 256;
+  if (M > 768 || (M > 512 && K < 8192 && (M + 63) / 64 * ((N + 63) / 64) > 512)) return false;
+  return stream_us(asym, group_size, M, N, K, c_bytes) <= bf16_path_us(M, N, K, c_bytes);
 }
 
-// The same for the gated product, B [2 width][K] = [N][K]. Beyond 256 rows exactly where the plain product comes here (the
-// two give the same bits); up to 256 rows the alternative is a tiled kernel, never the few-rows one, so large weights come
-// here too (AMXFP4-E5M2, 28672 x 8192, 256 rows: 177 us against 350), and asymmetric power-of-two scales while the FP6
-// kernel's merge of the weights and its one round of tiles, 20 us + 4.7 ns K + 0.37 ps N K, takes longer.
+bool stream_path_preferred(int scale_kind, bool asym, int64_t group_size, bool scaled, int64_t M, int64_t N, int64_t K,
+                           int64_t batch) {
+  return stream_preferred(scale_kind, asym, group_size, scaled, M, N, K, batch, 4.0);
+}
+
+// The same for the gated product, B [2 width][K] = [N][K], whose output is BF16 and half as wide. Beyond 256 rows by the same
+// estimates; up to 256 rows the alternative is a tiled kernel, never the few-rows one, so large weights come here too
+// (AMXFP4-E5M2, 28672 x 8192, 256 rows: 177 us against 350), and asymmetric power-of-two scales while this kernel's 4 us + (0.5
+// + 2.8 per round) ns K is less than the FP6 kernel's merge of the weights and its one round of tiles, 20 us + 4.7 ns K + 0.37
+// ps N K (256 x 22016 x 4096: 70 against 63, on prepared weights 48).
 bool stream_glu_preferred(int scale_kind, bool asym, int64_t group_size, int64_t M, int64_t N, int64_t K) {
   if ((group_size != 32 && group_size != 16) || K % 32 != 0 || rounded_pot(scale_kind, group_size)) return false;
   if (M <= 64) return true;
-  if (M > 64 && group_size == 32 && scale_kind == kScaleE8M0Floor && !asym)
-    return !fp4_path_supported(M, N, K) ? M <= 256 : !fp4_beats_stream(M, N, K, 1.0);
-  if (M > 256) return stream_path_preferred(scale_kind, asym, group_size, false, M, N, K, 1);
-  if (group_size == 32 && pot_scales(scale_kind)) {
-    return stream_us(scale_kind, asym, M, N, K) < 20.0 + 0.0047 * (double)K + 3.7e-7 * (double)N * (double)K;
-  }
-  return true;
+  const bool pot = group_size == 32 && pot_scales(scale_kind);
+  if (M > 256 || (pot && !asym)) return stream_preferred(scale_kind, asym, group_size, false, M, N, K, 1, 1.0);
+  const double k = (double)K, rounds = (double)(((M + 63) / 64 * ((N + 63) / 64) + 255) / 256);
+  return !pot || 4.0 + k / 4096.0 * (2.0 + 11.5 * rounds) < 20.0 + 0.0047 * k + 3.7e-7 * (double)N * k;
 }
 
 hipError_t launch_gemm_stream(int scale_kind, bool asym, int64_t group_size, int64_t M, int64_t N, int64_t K,

@@ -64,6 +64,7 @@ hipError_t launch_gemm_bf16_path(int scale_kind, bool asym, int64_t group_size, 
 // B's panel alone, expanded once for weights that stay (bf16_panel_bytes(N, K) bytes); passed as B_panel above, the
 // call then expands only A and its workspace is bf16_panel_bytes(M, K) per batch entry.
 size_t bf16_panel_bytes(int64_t rows, int64_t K);
+double bf16_path_us(int64_t M, int64_t N, int64_t K, double c_bytes);  // estimate of the call, both operands expanded
 hipError_t launch_expand_b_panel(int scale_kind, bool asym, int64_t group_size, int64_t N, int64_t K,
                                  const uint8_t* B_codes, const uint8_t* B_scales, void* panel, hipStream_t s);
 
@@ -78,6 +79,7 @@ hipError_t launch_expand_kv(int scale_kind, bool asym, const uint8_t* K_codes, c
 // (workspace: the BF16 panel of A and, with several outer K slices, the partial tiles; forced_slices: 0 = the number
 // of outer K slices comes from a cost model, n > 0 = n of them, at most K / 256)
 bool skinny_path_supported(int64_t M, int64_t N, int64_t K, int64_t batch);
+double skinny_path_us(int64_t M, int64_t N, int64_t K);  // estimate of the call, asymmetric formats, M <= 256
 size_t skinny_path_workspace_bytes(int64_t M, int64_t N, int64_t K, int64_t batch, int forced_slices);
 hipError_t launch_gemm_skinny_path(int scale_kind, bool asym, int64_t M, int64_t N, int64_t K, const uint8_t* A_codes,
                                    const uint8_t* A_scales, const uint8_t* B_codes, const uint8_t* B_scales, float* C,

@@ -115,3 +115,23 @@ def test_batches_of_few_rows(asym, batch, M, N, K, here):
 @pytest.mark.parametrize("M,N,K", [(40, 4096, 288), (300, 4096, 4096), (800, 4096, 512)])
 def test_rounded_power_of_two_scales_stay_where_their_largest_values_are_finite(M, N, K, asym):
     assert not one_launch(ROUND, asym, M, N, K) and not one_launch_gated(ROUND, asym, M, N, K)
+
+
+@pytest.mark.parametrize("scale,asym,M,N,K,here", [
+    (E5, 1, 256, 4096, 4096, 1), (E5, 1, 256, 11008, 4096, 1), (E5, 1, 96, 10240, 8192, 0), (E5, 1, 256, 5120, 13824, 0),
+    (E5, 1, 256, 32001, 4096, 0), (E5, 0, 256, 32001, 4096, 1), (E5, 1, 256, 28672, 8192, 0),
+    (E5, 1, 512, 4096, 4096, 1), (E5, 1, 512, 4096, 11008, 1), (E5, 1, 448, 11008, 4096, 1), (E5, 1, 512, 11008, 4096, 0),
+    (E5, 1, 640, 8192, 8192, 1), (E5, 1, 768, 8192, 8192, 0), (E5, 1, 448, 4544, 4544, 1), (E5, 1, 512, 4544, 4544, 0),
+    (E5, 1, 768, 1024, 1024, 1), (E5, 1, 769, 1024, 1024, 0), (FLOOR, 1, 256, 4096, 4096, 1), (FLOOR, 1, 257, 4096, 4096, 0)])
+def test_routes_of_65_to_768_rows(scale, asym, M, N, K, here):
+    """us, this kernel / the other: 17 / 50, 40 / 79, 45 / 35, 74 / 70, 99 / 83, 73 / 78, 177 / 151; 27 / 44, 63 / 106, 62 / 65,
+    73 / 66, 110 / 116, 133 / 121, 43 / 50, 58 / 51; the ends of the range"""
+    assert one_launch(scale, asym, M, N, K) == bool(here)
+
+
+@pytest.mark.parametrize("scale,asym,M,N,K,here", [(E5, 1, 256, 28672, 8192, 1), (E5, 1, 257, 28672, 8192, 0),
+                                                   (FLOOR, 1, 256, 22016, 4096, 0), (FLOOR, 1, 128, 22016, 4096, 1),
+                                                   (FLOOR, 0, 800, 11008, 1024, 0)])
+def test_routes_of_the_gated_product(scale, asym, M, N, K, here):
+    """Up to 256 rows its other kernel is a tiled one: large weights stay (177 / 350)."""
+    assert one_launch_gated(scale, asym, M, N, K) == bool(here)
