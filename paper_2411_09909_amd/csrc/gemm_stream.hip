@@ -105,16 +105,18 @@ bool stream_path_preferred(int scale_kind, bool asym, int64_t group_size, bool s
   return stream_preferred(scale_kind, asym, group_size, scaled, M, N, K, batch, 4.0);
 }
 
-// The same for the gated product, B [2 width][K] = [N][K], whose output is BF16 and half as wide. Beyond 256 rows by the same
-// estimates; up to 256 rows the alternative is a tiled kernel, never the few-rows one, so large weights come here too
+// The same for the gated product, B [2 width][K] = [N][K], whose output is BF16 and half as wide. Beyond 256 rows exactly where
+// the plain product comes here: the two give the same bits. Up to 256 rows symmetric power-of-two scales by the same
+// estimates, and otherwise the alternative is a tiled kernel, never the few-rows one, so large weights come here too
 // (AMXFP4-E5M2, 28672 x 8192, 256 rows: 177 us against 350), and asymmetric power-of-two scales while this kernel's 4 us + (0.5
 // + 2.8 per round) ns K is less than the FP6 kernel's merge of the weights and its one round of tiles, 20 us + 4.7 ns K + 0.37
 // ps N K (256 x 22016 x 4096: 70 against 63, on prepared weights 48).
 bool stream_glu_preferred(int scale_kind, bool asym, int64_t group_size, int64_t M, int64_t N, int64_t K) {
   if ((group_size != 32 && group_size != 16) || K % 32 != 0 || rounded_pot(scale_kind, group_size)) return false;
+  if (M > 256) return stream_path_preferred(scale_kind, asym, group_size, false, M, N, K, 1);
   if (M <= 64) return true;
   const bool pot = group_size == 32 && pot_scales(scale_kind);
-  if (M > 256 || (pot && !asym)) return stream_preferred(scale_kind, asym, group_size, false, M, N, K, 1, 1.0);
+  if (pot && !asym) return stream_preferred(scale_kind, asym, group_size, false, M, N, K, 1, 1.0);
   const double k = (double)K, rounds = (double)(((M + 63) / 64 * ((N + 63) / 64) + 255) / 256);
   return !pot || 4.0 + k / 4096.0 * (2.0 + 11.5 * rounds) < 20.0 + 0.0047 * k + 3.7e-7 * (double)N * k;
 }

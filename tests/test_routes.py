@@ -135,3 +135,13 @@ def test_routes_of_65_to_768_rows(scale, asym, M, N, K, here):
 def test_routes_of_the_gated_product(scale, asym, M, N, K, here):
     """Up to 256 rows its other kernel is a tiled one: large weights stay (177 / 350)."""
     assert one_launch_gated(scale, asym, M, N, K) == bool(here)
+
+
+@pytest.mark.parametrize("scale,group", [(E5, 32), (E4, 32), (E4, 16), (FLOOR, 32), (FLOOR, 16), (ROUND, 32)])
+def test_beyond_256_rows_the_gated_product_goes_where_the_plain_one_does(scale, group):
+    """Their sums are promised to be the same bits there (but for products that the few-rows kernel takes against large weights)."""
+    for asym in (0, 1):
+        for M in (257, 300, 384, 448, 512, 513, 640, 768, 769, 1504, 4096, 20000):
+            for N in (64, 1024, 2048, 5632, 11008, 22016, 28672):
+                for K in (96, 256, 1024, 2048, 4096, 8192, 11008):
+                    assert one_launch_gated(scale, asym, M, N, K, group) == one_launch(scale, asym, M, N, K, 1, group)
