@@ -4,7 +4,7 @@ import numpy as np
 import pytest
 
 from oracle import ref
-from paper_2411_09909_amd import synth
+from paper_2411_09909_amd import binding, synth
 from tests import gpu_util as G
 
 pytestmark = pytest.mark.gpu
@@ -258,30 +258,47 @@ SKINNY_FORMATS = [(ref.FP8_E5M2, 1), (ref.FP8_E5M2, 0), (ref.E8M0_FLOOR, 1), (re
                                    (128, 257, 1024), (129, 300, 512), (192, 257, 1024), (200, 129, 256),
                                    (256, 4101, 768)])
 def test_few_rows_against_many_columns(M, N, K, scale, asym):
-    """M <= 256 with K a multiple of 256: the kernel that dequantizes B in registers straight from its codes. One to
-    eight row tiles, partial column tiles, one K block per workgroup up to many, with and without outer K slices; up to
-    32 rows, where two waves share a column tile and take alternate K blocks: one block, even and odd counts."""
+    """M <= 256 with K a multiple of 256: the kernel that dequantizes B in registers straight from its codes, asked for by
+    a number of outer K slices, one and three (or as many as K has blocks). One to eight row tiles, partial column tiles,
+    one K block per workgroup up to many; up to 32 rows, where two waves share a column tile and take alternate K blocks:
+    one block, even and odd counts. And the library's own choice, mostly the kernel that reads both operands as packed codes."""
     a = synth.activations(M, K, seed=M + K, n_outlier=1, outlier_gain=60.0)
     b = synth.weights(N, K, seed=N)
     ac, as_ = ref.quantize(a, 32, scale, asym)
     bc, bs = ref.quantize(b, 32, scale, asym)
+    Cr = ref.gemm(ac, as_, bc, bs, 32, scale, asym)
+    for slices in (0, 1, min(3, K // 256)):
+        C = G.gpu_gemm(ac, as_, bc, bs, scale, asym, options=binding.gemm_options(few_rows=slices))
+        assert C.shape == (M, N)
+        assert G.rel_fro(C, Cr) <= TOL
+        assert np.allclose(C, Cr, rtol=1e-4, atol=1e-4 * np.abs(Cr).max())
+
+
+@pytest.mark.parametrize("scale,asym", SKINNY_FORMATS)
+@pytest.mark.parametrize("M,N,K", [(65, 70, 512), (100, 300, 2304), (192, 129, 1024), (256, 1025, 768)])
+def test_few_rows_in_a_batch(M, N, K, scale, asym):
+    """65 to 256 rows in a batch: the few-rows kernel by default, in the number of K slices of its own cost model."""
+    a, b = synth.activations(2 * M, K, seed=M, n_outlier=1, outlier_gain=60.0), synth.weights(2 * N, K, seed=N)
+    (ac, as_), (bc, bs) = ([t.reshape((2, rows) + t.shape[1:]) for t in ref.quantize(x, 32, scale, asym)]
+                           for x, rows in ((a, M), (b, N)))
     C = G.gpu_gemm(ac, as_, bc, bs, scale, asym)
     Cr = ref.gemm(ac, as_, bc, bs, 32, scale, asym)
-    assert C.shape == (M, N)
+    assert C.shape == (2, M, N)
     assert G.rel_fro(C, Cr) <= TOL
     assert np.allclose(C, Cr, rtol=1e-4, atol=1e-4 * np.abs(Cr).max())
 
 
 @pytest.mark.parametrize("scale,asym,M", [(ref.FP8_E5M2, 1, 300), (ref.FP8_E5M2, 1, 600), (ref.E8M0_FLOOR, 0, 768)])
 def test_row_chunks_against_a_large_b(scale, asym, M):
-    """257 .. 768 rows against at least 2^27 weight elements run as row chunks of 256 through the few-rows kernel.
-    The oracle multiplies a sample of rows (first, last and both sides of every chunk boundary among them)."""
+    """257 .. 768 rows against at least 2^27 weight elements run as row chunks of 256 through the few-rows kernel, with
+    symmetric power-of-two scales, which the FP4 kernel takes by default, where the options ask for it. The oracle multiplies a sample of rows (first, last and both sides of every chunk boundary among them)."""
     N, K = 16389, 8192
     a = synth.activations(M, K, seed=M, n_outlier=2, outlier_gain=40.0)
     b = synth.weights(N, K, seed=3)
     ac, as_ = ref.quantize(a, 32, scale, asym)
     bc, bs = ref.quantize(b, 32, scale, asym)
-    C = G.gpu_gemm(ac, as_, bc, bs, scale, asym)
+    options = binding.gemm_options(few_rows=2 if scale == ref.E8M0_FLOOR and not asym else 0)
+    C = G.gpu_gemm(ac, as_, bc, bs, scale, asym, options=options)
     assert C.shape == (M, N)
     rows = sorted(set([0, 1, 255, 256, 257, 299, M - 1] + [r for r in (511, 512, 513) if r < M] +
                       list(np.random.default_rng(M).integers(0, M, 12))))
@@ -297,7 +314,8 @@ def test_row_chunks_against_a_large_b(scale, asym, M):
 def test_few_rows_integer_exact_batched_and_repeatable(asym, M):
     """Scales 1 and integer codes: exact integers below 2^24 in any summation order, so the result must equal the
     oracle bit for bit; batch > 1; and two calls give identical bits (the K slices, and with one row tile the two
-    waves' halves of a slice, are added in a fixed order)."""
+    waves' halves of a slice, are added in a fixed order). By default these go to the kernel that reads both operands as
+    packed codes, with a number of slices to the few-rows kernel."""
     rng = np.random.default_rng(11)
     batch, N, K = 3, 70, 1024
     mags = np.array([0, 2, 4, 5, 6, 7])
@@ -311,12 +329,15 @@ def test_few_rows_integer_exact_batched_and_repeatable(asym, M):
 
     ac, as_ = operand(M)
     bc, bs = operand(N)
-    C1 = G.gpu_gemm(ac, as_, bc, bs, ref.E8M0_FLOOR, asym)
-    C2 = G.gpu_gemm(ac, as_, bc, bs, ref.E8M0_FLOOR, asym)
-    assert np.array_equal(C1, ref.gemm(ac, as_, bc, bs, 32, ref.E8M0_FLOOR, asym))
-    assert np.array_equal(C1, C2)
+    Cr = ref.gemm(ac, as_, bc, bs, 32, ref.E8M0_FLOOR, asym)
+    for slices in (0, 1, 3):
+        C1, C2 = (G.gpu_gemm(ac, as_, bc, bs, ref.E8M0_FLOOR, asym, options=binding.gemm_options(few_rows=slices)) for _ in range(2))
+        assert np.array_equal(C1, Cr)
+        assert np.array_equal(C1, C2)
     # real-valued operands: repeatable too
     a = synth.activations(M, K, seed=1)
     b = synth.weights(4000, K, seed=2)
     qa, qb = ref.quantize(a, 32, ref.FP8_E5M2, asym), ref.quantize(b, 32, ref.FP8_E5M2, asym)
-    assert np.array_equal(G.gpu_gemm(*qa, *qb, ref.FP8_E5M2, asym), G.gpu_gemm(*qa, *qb, ref.FP8_E5M2, asym))
+    for slices in (0, 3):
+        C1, C2 = (G.gpu_gemm(*qa, *qb, ref.FP8_E5M2, asym, options=binding.gemm_options(few_rows=slices)) for _ in range(2))
+        assert np.array_equal(C1, C2)

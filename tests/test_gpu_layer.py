@@ -153,7 +153,7 @@ def test_gemm_with_gated_activation_epilogue(scale, asym, M, width, K):
     # the same product through the plain GEMM on the panel kernel, then the separate operator
     cc, cs = binding.quantize(fmt, torch.cat([G.to_dev_bf16(wg), G.to_dev_bf16(wu)], 0).contiguous())
     need = binding.gemm_silu_mul_workspace_bytes(fmt, M, width, K)
-    if M > 256:  # (with fewer rows the plain GEMM takes the few-rows kernel, whose sums run in another order)
+    if M > 256:  # (with fewer rows the two may take kernels, or shapes of one, whose sums run in another order)
         two = binding.silu_mul(binding.gemm(fmt, ac, as_, cc, cs))
         assert torch.equal(two.view(torch.int16), got.view(torch.int16))
     qa = ref.quantize(a, 32, scale, asym)
@@ -235,26 +235,28 @@ def test_decoder_layer_cut_down(scale, asym, fused):
 
 
 @pytest.mark.parametrize("fused", [False, True])
-@pytest.mark.parametrize("scale,asym", [(ref.FP8_E5M2, 1), (ref.E8M0_FLOOR, 0), (ref.E8M0_FLOOR, 1)])
-def test_decoder_layer_on_the_tiled_kernels(scale, asym, fused):
-    """The same comparison with 640 tokens and twice the widths: M = 640 (2.5 tiles of 256 rows) sends the four linear
-    layers, the gated GEMM and the attention products through the kernels a full-size layer uses: BF16 panels for the
-    FP8-E5M2 scales, the block-scaled FP4 kernel for OCP MXFP4, the merged FP8 kernel for asymmetric power-of-two
-    scales; d_ff = 2816 = 11 tiles of 256 columns."""
+@pytest.mark.parametrize("scale,asym,tokens", [(ref.FP8_E5M2, 1, 640), (ref.E8M0_FLOOR, 0, 640), (ref.E8M0_FLOOR, 1, 640),
+                                               (ref.FP8_E5M2, 1, 1024)])
+def test_decoder_layer_on_the_tiled_kernels(scale, asym, tokens, fused):
+    """The same comparison with twice the widths and 640 or 1024 tokens. 640 (2.5 tiles of 256 rows) are a small problem at
+    these widths, whose linear layers read both operands as packed codes, but for asymmetric power-of-two scales, which
+    take the merged FP6 kernel beyond 256 rows; 1024 send the FP8-E5M2 scales' through the BF16 panels."""
     cfg = layer.LayerConfig(d_model=1024, n_heads=8, n_kv_heads=2, head_dim=128, d_ff=2816)
-    err, exact = run_layer(cfg, 640, scale, asym, fused)
+    err, exact = run_layer(cfg, tokens, scale, asym, fused)
     assert err <= LAYER_ERR, "layer output differs from the oracle by %.4f of the layer's update" % err
     assert exact >= LAYER_EXACT, "only %.3f of the output elements are bit-identical" % exact
 
 
+@pytest.mark.parametrize("tokens", [640, 1024])
 @pytest.mark.parametrize("scale,asym", [(ref.FP8_E5M2, 1), (ref.FP8_E4M3, 1), (ref.E8M0_FLOOR, 1), (ref.E8M0_FLOOR, 0)])
-def test_decoder_layer_on_prepared_weights_gives_the_same_bits(scale, asym):
+def test_decoder_layer_on_prepared_weights_gives_the_same_bits(scale, asym, tokens):
     """The layer with its weights' kernel-private form written once (BF16 panels for the FP8 scales, the merged FP6 panel
     for asymmetric power-of-two scales, nothing for symmetric ones): all four linear layers, the gated GEMM included,
-    must give the bits of the plain calls."""
+    must give the bits of the plain calls (with FP8 scales those of 640 tokens mostly read the packed codes, prepared or
+    not; those of 1024 read the panels)."""
     cfg = layer.LayerConfig(d_model=1024, n_heads=8, n_kv_heads=2, head_dim=128, d_ff=2816)
     w = synth.layer_weights(cfg, seed=0)
-    x = G.to_dev_bf16(synth.layer_input(640, cfg.d_model, seed=0))
+    x = G.to_dev_bf16(synth.layer_input(tokens, cfg.d_model, seed=0))
     fmt = binding.make_format(scale, asym)
     wd = {k: (dev_f32(v) if v.dtype == np.float32 else G.to_dev_bf16(v)) for k, v in w.items()}
     plain = layer.DecoderLayer(cfg, wd, fmt, fused_attention=True).forward(x)

@@ -42,13 +42,19 @@ def both_ways(scale, asym, batch, M, N, K, seed):
 
 # (scale, asymmetric, first problem, second, smaller problem): one pair per kernel family that uses scratch
 PAIRS = [
-    # few-rows kernel: A panel + partial tiles of 4 outer K slices, then one slice
+    # both operands read as packed codes: no scratch
     (ref.FP8_E5M2, 1, (1, 64, 1024, 1024), (1, 5, 70, 512)),
+    # few-rows kernel: A panel + partial tiles of outer K slices, then fewer of them
+    (ref.FP8_E5M2, 1, (2, 100, 1024, 2304), (2, 65, 70, 512)),
+    (ref.E8M0_FLOOR, 0, (2, 256, 300, 2304), (2, 65, 70, 512)),
+    # few-rows kernel, K so long that its slices are faster for one problem too
+    (ref.FP8_E5M2, 1, (1, 32, 256, 28672), (1, 20, 200, 25600)),
     # BF16-panel kernel: both operands' panels (padded rows and K are rewritten as zeros by every call)
-    (ref.FP8_E5M2, 1, (1, 600, 700, 1056), (2, 257, 130, 160)),
+    (ref.FP8_E5M2, 1, (1, 800, 700, 1056), (2, 257, 130, 160)),
+    (ref.FP8_E5M2, 1, (1, 600, 700, 1056), (2, 257, 130, 160)),  # (the first without scratch)
     # merged FP6 kernel: merged panels, anchor words, split flags and plan
     (ref.E8M0_FLOOR, 1, (1, 600, 700, 1056), (1, 300, 31, 96)),
-    # few rows against a weight-matrix-sized B (32 tokens, 8 MB of weights): the decoding shape this call is for
+    # few rows against a weight-matrix-sized B (32 tokens, 8 MB of weights): the decoding shape this call is for (no scratch)
     (ref.FP8_E5M2, 1, (1, 32, 4096, 4096), (1, 1, 4096, 4096)),
 ]
 
