@@ -137,11 +137,14 @@ int amxfp4_dequantize(const amx_format_t* fmt, const uint8_t* codes, const uint8
  *   batch              number of independent back-to-back problems (attention heads), >= 1.
  *   Groups of 32 with power-of-two scales run on the block-scaled FP4 / FP8 matrix instructions; FP8 scales and the
  *   other group sizes are multiplied as exact BF16 operands (element * scale has at most 6 significant bits). With
- *   M <= 256 (M <= 768 for batch == 1 and N * K >= 2^27), groups of 32 and K a multiple of 256, B is read as packed
+ *   M <= 256 (M <= 768 for batch == 1 and N * K >= 2^27), groups of 32 and K a multiple of 256, B may be read as packed
  *   codes and dequantized in registers to exact 16-bit floats (the weights-bound case of a few tokens against a
- *   weight matrix); with few rows (M <= 64) and for small problems (M <= 768), groups of 32 or 16 and any K, mostly both
- *   operands are, in one launch that leaves the workspace alone; results do not depend on the kernel beyond the FP32
- *   summation order.
+ *   weight matrix); with few rows (M <= 64) and for small problems (M <= 768; symmetric power-of-two scales of 32-groups:
+ *   any M at which it is the faster way), groups of 32 or 16 and any K, mostly both operands are, in one launch that
+ *   leaves the workspace alone. Results do not depend on the kernel beyond the FP32 summation order, with one exception:
+ *   AMX_SCALE_E8M0_ROUND turns BF16 maxima above 1.41 * 2^127 into values of 2^128, which only the block-scaled matrix
+ *   instructions multiply; what reads packed codes gives infinities or NaN for those (it is not chosen for that format
+ *   except with K a multiple of 256 and M <= 256 or a large B).
  *   workspace          device scratch of at least amxfp4_gemm_workspace_bytes() bytes, 256-byte aligned;
  *                      contents are undefined afterwards. May be NULL when the required size is 0.
  */
@@ -161,7 +164,7 @@ int amxfp4_gemm(const amx_format_t* fmt, int64_t M, int64_t N, int64_t K, const 
  *   amxfp4_prepare_weights          writes it: `prepared` device out, 256-byte aligned, at least that many bytes
  *                                   (AMX_ERR_WORKSPACE otherwise). Depends on fmt, N, K and B only.
  *   amxfp4_gemm_prepared            C = A . B^T with B's prepared form. B_codes / B_scales are still passed: shapes
- *                                   with few rows and small problems (M <= 768, see amxfp4_gemm) read B as packed codes
+ *                                   with few rows and small problems (see amxfp4_gemm) read B as packed codes
  *                                   and ignore `prepared`. One problem per call (no batch). workspace: at least
  *                                   amxfp4_gemm_prepared_workspace_bytes(), 256-byte aligned (A's expansion only).
  * `prepared` is opaque, valid for this library build, fmt, N and K; the caller owns it and keeps it unchanged while
@@ -343,9 +346,11 @@ int amxfp4_profile_next_gemm(void* start_event, void* stop_event);
  *                                    product: far inside the 1e-3 tolerance in norm, not bit-exact.
  *   tile          workgroup tile of the BF16-panel kernel: AMX_TILE_AUTO (a cost model over the shape), or
  *                 AMX_TILE_256x256 / AMX_TILE_256x128 / AMX_TILE_64x256 on any shape.
- *   few_rows      the kernel that reads B as packed codes (M <= 256, or <= 768 against a large B; K % 256 == 0):
- *                 0 = use it where it applies, -1 = never, n > 0 = use it where it applies with n outer K slices
- *                 (at most 16 and at most K / 256).
+ *   few_rows      the kernel that reads B, but not A, as packed codes (M <= 256, or <= 768 against a large B; K % 256
+ *                 == 0): 0 = use it where it applies and the library finds it the fastest (with all options 0 the kernel
+ *                 that reads both operands as packed codes takes most of these shapes), in a number of outer K slices
+ *                 from its cost model; -1 = never, and not that other kernel either; n > 0 = use it where it applies,
+ *                 with n outer K slices (at most 16 and at most K / 256).
  * A kernel that does not take the shape or format falls back to the default one. Unknown values: AMX_ERR_INVALID_ARG.
  */
 enum { AMX_E5M2_PANEL = 0, AMX_E5M2_HYBRID = 1, AMX_E5M2_FUSED = 2 };

@@ -76,7 +76,8 @@ int amxfp4_silu_mul(const float* gate_up, int64_t rows, int64_t width, void* out
 /*
  * The fused gate / up projection with the gated activation applied before anything is written: out[r, c] =
  * bf16( silu(g) * u ) with (g | u) = the quantized product A . B^T of amxfp4_gemm (Sec. 4.3) and the arithmetic of
- * amxfp4_silu_mul, bit for bit; the FP32 product never goes to memory.
+ * amxfp4_silu_mul, bit for bit; the FP32 product never goes to memory. (Up to 256 rows, and up to 768 against 2 * width * K
+ * >= 2^27 weights, the product may be summed in another order than amxfp4_gemm's.)
  *   A                  [M][K] quantized activations (codes, scales as for amxfp4_gemm).
  *   B                  [2 * width][K] quantized weights with the rows of the gate and of the up projection INTERLEAVED
  *                      in blocks of 32: rows 64 t .. 64 t + 31 are gate rows 32 t .. 32 t + 31, rows 64 t + 32 ..
@@ -85,7 +86,8 @@ int amxfp4_silu_mul(const float* gate_up, int64_t rows, int64_t width, void* out
  *   workspace          at least amxfp4_gemm_silu_mul_workspace_bytes() bytes, 256-byte aligned; may be NULL when
  *                      that is 0. The product runs on the tiled kernel of the format (block-scaled matrix
  *                      instructions for power-of-two scales of 32-groups, exact BF16 operands otherwise) or, with few
- *                      rows and for small problems, on the one that reads both operands as packed codes.
+ *                      rows and for small problems (see amxfp4_gemm), on the one that reads both operands as packed
+ *                      codes.
  * Status codes as amxfp4_gemm.
  */
 size_t amxfp4_gemm_silu_mul_workspace_bytes(const amx_format_t* fmt, int64_t M, int64_t width, int64_t K);
@@ -95,7 +97,7 @@ int amxfp4_gemm_silu_mul(const amx_format_t* fmt, int64_t M, int64_t width, int6
 
 /*
  * amxfp4_gemm_silu_mul on prepared weights: `prepared` is what amxfp4_prepare_weights (include/amxfp4.h) wrote for the
- * INTERLEAVED weight matrix B [2 * width][K]; the call then expands only A (few rows and small problems, M <= 768, read
+ * INTERLEAVED weight matrix B [2 * width][K]; the call then expands only A (few rows and small problems read
  * B_codes and B_scales and ignore it). Same result, bit for bit. For formats with
  * nothing to prepare (amxfp4_weights_prepared_bytes() == 0) `prepared` is ignored and the call is amxfp4_gemm_silu_mul.
  * workspace: at least amxfp4_gemm_silu_mul_prepared_workspace_bytes() bytes.

@@ -194,7 +194,8 @@ bool default_options(const amx_gemm_options_t* o) {
   return !o || (o->e5m2_kernel == 0 && o->pot_kernel == 0 && o->tile == 0 && o->few_rows == 0);
 }
 
-// scaled: the tensor-wise double scaling (Sec. 5.3), which only the BF16-panel kernel's epilogue applies.
+// scaled: the tensor-wise double scaling (Sec. 5.3), which of the kernels named here only the BF16-panel kernel's epilogue
+// applies (uses_stream() below has few rows and small problems of it).
 GemmPlan plan_gemm(const amx_format_t& f, const amx_gemm_options_t* o, bool scaled, int64_t M, int64_t N, int64_t K,
                    int64_t batch) {
   static const amx_gemm_options_t kDefaults = {0, 0, 0, 0};
@@ -250,7 +251,7 @@ size_t plan_workspace_bytes(const GemmPlan& p, bool asym, int64_t M, int64_t N, 
 }
 
 // A_pair / B_pair: device {S_t, 1 / S_t} of the operands' tensor-wise scales (Sec. 5.3), both null for none. Scaled
-// products always take the BF16 expansion path, whose kernel has the scaling epilogue.
+// products take the BF16 expansion path or, with few rows and small problems, the one-launch kernel: both apply the factor.
 int gemm_impl(amx_format_t f, const amx_gemm_options_t* opts, int64_t M, int64_t N, int64_t K, const uint8_t* A_codes,
               const uint8_t* A_scales, const float* A_pair, const uint8_t* B_codes, const uint8_t* B_scales,
               const float* B_pair, float* C, int64_t ldc, int64_t batch, void* workspace, size_t workspace_bytes,
@@ -320,7 +321,8 @@ int gemm_impl(amx_format_t f, const amx_gemm_options_t* opts, int64_t M, int64_t
   return e == hipSuccess ? AMX_OK : hip_fail(e, "gemm launch");
 }
 
-// The gated GEMM runs on the tiled kernels only (the block-scaled ones for power-of-two scales, else the BF16 panels).
+// The gated GEMM runs on the tiled kernels (the block-scaled ones for power-of-two scales, else the BF16 panels), except where
+// stream_glu_preferred() takes it.
 GemmPlan plan_glu(const amx_format_t& f, int64_t M, int64_t N, int64_t K) {
   static const amx_gemm_options_t kTiledOnly = {0, AMX_POT_MERGED_FP6, 0, -1};
   GemmPlan p = plan_gemm(f, &kTiledOnly, false, M, N, K, 1);

@@ -11,7 +11,7 @@
 // 4c + r: all 32 keys of a query sit in the two lanes l and l ^ 32, so the row maximum, the row sum and the group
 // maximum of the cast are 16 in-lane steps and one exchange, and registers 8j .. 8j+7 of S^T, converted to BF16, are
 // already the B operand of k-step j of the second product, provided V^T was staged with its keys in that order
-// (expand_kernel<PERMUTE>). Workgroup = kAttnWaves waves x 32 queries; the K and V fragments of a key tile are brought into
+// (expand_kv_kernel). Workgroup = kAttnWaves waves x 32 queries; the K and V fragments of a key tile are brought into
 // LDS once per workgroup by direct-to-LDS loads, double buffered.
 #include "../../include/amxfp4.h"
 #include "attention_tile.h"

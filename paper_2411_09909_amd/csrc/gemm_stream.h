@@ -1,5 +1,5 @@
-// Kernel and launch rule of the fully quantized GEMM (Sec. 4.3) for few rows on the A side and for small problems: one launch, both operands read as
-// packed codes.
+// Kernel and launch rule of the fully quantized GEMM (Sec. 4.3) for few rows on the A side and for small problems: one
+// launch, both operands read as packed codes.
 //
 // What bounds a product with few rows is reading the weights (B) once, or, for small weights, the chain of launches and
 // memory latencies. So nothing is prepared in memory and nothing is shared between waves while they run: a wave owns MT x
@@ -83,7 +83,8 @@ __device__ __forceinline__ u32x4 stream_dequant(uint32_t word, uint32_t s_pos, u
 // grid: (ceil(N / (NT R)), ceil(M / (MT R)), batch); block: WAVES waves. WHOLE: K is a multiple of 256 (so every row's scale
 // bytes start on a multiple of four, as their vector loads need); otherwise scale entries are loaded byte by byte.
 // GLU: B's rows are the gate and up rows interleaved in blocks of 32; C is then the BF16 output [M][ldc] of N / 2 columns,
-// bf16(silu(gate) * up), by the same sums in the same order as the plain product.
+// bf16(silu(gate) * up). Its sums are the plain product's in the same order wherever both come here in the same shape, which
+// is everywhere but at 17 to 32 rows and N <= 4096 (there the plain form has R = 16, the gated one always R = 32).
 template <int SCALE_KIND, bool ASYM, int GS_LOG2, int R, int MT, int NT, int WAVES, bool WHOLE, bool GLU>
 __global__ __launch_bounds__(64 * WAVES) void gemm_stream_kernel(
     const uint8_t* A_codes, const uint8_t* A_scales, const uint8_t* B_codes, const uint8_t* B_scales, float* C,

@@ -11,8 +11,8 @@ static bool pot_scales(int scale_kind) { return scale_kind == kScaleE8M0Floor ||
 // takes it only where the few-rows kernel, with the same limit, did.
 static bool rounded_pot(int scale_kind, int64_t group_size) { return scale_kind == kScaleE8M0Round && group_size == 32; }
 
-// Time of this kernel for more than 64 rows, us: 64 x 64 outputs per workgroup, 256 workgroups at a time, or the smaller
-// shapes that still give each compute unit one; writing C counts (c_bytes per element of M x N), and so does loading scale bytes
+// Time of this kernel for more than 64 rows, us: 64 x 64 outputs per workgroup, counted in rounds of 256 (two share a compute
+// unit and its vector unit, which is the bound), or the smaller shapes that still give each compute unit one; writing C counts (c_bytes per element of M x N), and so does loading scale bytes
 // one by one where K is no multiple of 256. Within some 10 % at 96 .. 768 rows, N 1024 .. 32001, K 1024 .. 14336.
 static double stream_us(bool asym, int64_t group_size, int64_t M, int64_t N, int64_t K, double c_bytes) {
   const int64_t rows32 = (M + 31) / 32, t32 = (N + 31) / 32, t64 = (N + 63) / 64;
