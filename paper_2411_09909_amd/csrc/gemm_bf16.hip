@@ -378,9 +378,9 @@ hipError_t launch_expand_f16_e5m2(bool asym, const uint8_t* codes, const uint8_t
               : launch_expand<kScaleE5M2, false, true>(codes, scales, R, K, Rp, Kp, 5, batch, panel, s);
 }
 
-// Whether equal runs of tiles of 256 x tile_cols, per_xcd to an XCD, end sooner than supertiles where those leave a fifth of their slots
-// empty. What counts is the tiles that an XCD really has (its share; 32 CUs: one round of 32 at a time), measured in both orders
-// over 1 .. 16 rows and 2 .. 251 columns of tiles, us of the kernel, supertiles / runs:
+// Whether equal runs of tiles of 256 x tile_cols, per_xcd to an XCD, end sooner than supertiles where those leave a fifth
+// of their slots empty. What counts is the tiles that an XCD really has (its share; 32 CUs: one round of 32 at a time),
+// measured in both orders over 1 .. 16 rows and 2 .. 251 columns of tiles, us of the kernel, supertiles / runs:
 //   fewer rounds: runs (12 x 20 tiles, K 13824, a share of 64 tiles or 30: 520 / 292;  9 x 112, K 4096, 224 or 126: 556 / 392)
 //   one round either way: runs, which spread the tiles over all XCDs (8 x 16, K 4096, 32 or 16: 98 / 76;  1 x 126: 193 / 123),
 //     but with a partial row of supertiles, whose XCDs alternate between full and nearly empty, only for much smaller shares
@@ -476,14 +476,16 @@ int bf16_tile_choice(int64_t M, int64_t N, int64_t batch) {
   const double est1 = rounds(256, 256), est2 = 0.6 * rounds(256, 128), est3 = 0.4 * rounds(64, 256);
   const bool ok3 = est3 < 0.85 * est1;
   const bool two_rounds = M > 768 || (M + 255) / 256 * ((N + 255) / 256) * batch <= 288;
-  const bool ok2 = est2 < (two_rounds ? 0.92 : 0.85) * est1 && M > 256;  // (with a single row of 256-row tiles the 64-row tile was never worse)
+  // (with a single row of 256-row tiles the 64-row tile was never worse)
+  const bool ok2 = est2 < (two_rounds ? 0.92 : 0.85) * est1 && M > 256;
   return ok3 && (!ok2 || est3 <= est2) ? 3 : ok2 ? 2 : 1;
 }
 
-// Estimate of a call that expands both operands, us, up to some 800 rows: B's expansion at the copy rate, and the rounds of
-// tiles at the rate of a lone tile (256 x 256 14 ns per unit of K, 256 x 128 9.3, 64 x 256 6.6 to 8 as they fill the chip) or
-// the chip's, and half of the store of C, c_bytes per element of M x N. Measured / estimated: 512 x 4096 x 4096 44 / 44, 512 x 11008 x 4096 66 / 68, 768 x 8192 x
-// 8192 121 / 124, 512 x 13824 x 5120 95 / 102, 512 x 4096 x 11008 106 / 109, 448 x 4544 x 4544 50 / 50.
+// Estimate of a call that expands both operands, us, up to some 800 rows: B's expansion at the copy rate, and the rounds
+// of tiles at the rate of a lone tile (256 x 256 14 ns per unit of K, 256 x 128 9.3, 64 x 256 6.6 to 8 as they fill the
+// chip) or the chip's, and half of the store of C, c_bytes per element of M x N. Measured / estimated: 512 x 4096 x 4096
+// 44 / 44, 512 x 11008 x 4096 66 / 68, 768 x 8192 x 8192 121 / 124, 512 x 13824 x 5120 95 / 102, 512 x 4096 x 11008 106 /
+// 109, 448 x 4544 x 4544 50 / 50.
 double bf16_path_us(int64_t M, int64_t N, int64_t K, double c_bytes) {
   const int tile = bf16_tile_choice(M, N, 1);
   const int64_t tile_m = tile == 3 ? 64 : 256, tile_n = tile == 2 ? 128 : 256;

@@ -3,8 +3,8 @@
 // of the BF16 bytes, so this kernel reads the packed codes and scales of B straight from memory, dequantizes them in
 // registers to exact 16-bit floats (element * scale has at most 6 significant bits) and feeds the 16-bit MFMA; only
 // the small A operand goes through a panel (expand_kernel). No operand of B is ever written back.
-// (Without options most of these shapes take gemm_stream.hip; this kernel is what the few_rows option asks for, and what
-// runs where the rule there prefers it.)
+// (Without options most of these shapes take gemm_stream.hip; this kernel is what the few_rows option asks for, what batches
+// of more than 64 rows take, and what runs where the rule there prefers it.)
 // The dequantization is the kernel's bound (vector instructions per MFMA), so it uses packed 16-bit arithmetic where
 // the scale format allows it:
 //   FP8-E5M2 scales: FP16 operands biased by 2^-3 (every element * scale * 2^-3 lies in [2^-20, 43008] and has at most
@@ -129,7 +129,8 @@ double skinny_path_us(int64_t M, int64_t N, int64_t K) {
   int bps;
   const int slices = skinny_outer_slices(groups, K / kSkinnyBlockK, Mp, 0, bps);
   const double block = tiles == 1 ? 0.95 : tiles == 2 ? 2.2 : tiles == 3 ? 2.8 : tiles == 4 ? 3.7 : tiles == 6 ? 3.4 : 4.4;
-  return 10.0 + (double)((groups * slices + 255) / 256 * bps) * block + (slices > 1 ? (double)(slices * Mp * N) * 8.0 / 4.7e6 : 0.0);
+  const double partial = slices > 1 ? (double)(slices * Mp * N) * 8.0 / 4.7e6 : 0.0;
+  return 10.0 + (double)((groups * slices + 255) / 256 * bps) * block + partial;
 }
 
 // bytes of partial tiles one chunk of `rows` rows needs (0 with a single slice)

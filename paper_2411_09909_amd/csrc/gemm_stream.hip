@@ -11,9 +11,10 @@ static bool pot_scales(int scale_kind) { return scale_kind == kScaleE8M0Floor ||
 // takes it only where the few-rows kernel, with the same limit, did.
 static bool rounded_pot(int scale_kind, int64_t group_size) { return scale_kind == kScaleE8M0Round && group_size == 32; }
 
-// Time of this kernel for more than 64 rows, us: 64 x 64 outputs per workgroup, counted in rounds of 256 (two share a compute
-// unit and its vector unit, which is the bound), or the smaller shapes that still give each compute unit one; writing C counts (c_bytes per element of M x N), and so does loading scale bytes
-// one by one where K is no multiple of 256. Within some 10 % at 96 .. 768 rows, N 1024 .. 32001, K 1024 .. 14336.
+// Time of this kernel for more than 64 rows, us: 64 x 64 outputs per workgroup, counted in rounds of 256 (two share a
+// compute unit and its vector unit, which is the bound), or the smaller shapes that still give each compute unit one;
+// writing C counts (c_bytes per element of M x N), and so does loading scale bytes one by one where K is no multiple of
+// 256. Within some 10 % at 96 .. 768 rows, N 1024 .. 32001, K 1024 .. 14336.
 static double stream_us(bool asym, int64_t group_size, int64_t M, int64_t N, int64_t K, double c_bytes) {
   const int64_t rows32 = (M + 31) / 32, t32 = (N + 31) / 32, t64 = (N + 63) / 64;
   const double rounds = (double)(((M + 63) / 64 * t64 + 255) / 256);
@@ -26,12 +27,12 @@ static double stream_us(bool asym, int64_t group_size, int64_t M, int64_t N, int
 }
 
 // Symmetric power-of-two scales of 32-groups, more than 64 rows: whether the FP4 kernel is the fastest of the three that
-// could take them. Besides the output it takes 11 us + 5 ns K, from K 2048 on 12.8 + 4.2 ns K, while its 256 x 256 tiles fit the
-// compute units once (512 x 11008 x 1024 20 us, 1024 x 4096 x 2048 23, x 4096 31.6, output included); this kernel 3 us and per round of 256
-// workgroups 1.25 us + 1.1 ns K, or 1.7 ns K if that is more (512 x 4096 x 4096, two rounds, 19; 1024 x 4096 x 2048, four, 20; 2048
-// x 4096 x 128, eight, 20, the FP4 kernel 12.6). Up to 16384 rows; beyond, the FP4 kernel (32768 x 128 x 128 10.3 against 12.2,
-// 100000 x 512 x 128 47 against 104). The few-rows kernel never is the fastest there (28672 x 8192: 80 rows 69 us, 256 rows 137,
-// the FP4 kernel 66-69).
+// could take them. Besides the output it takes 11 us + 5 ns K, from K 2048 on 12.8 + 4.2 ns K, while its 256 x 256 tiles
+// fit the compute units once (512 x 11008 x 1024 20 us, 1024 x 4096 x 2048 23, x 4096 31.6, output included); this kernel
+// 3 us and per round of 256 workgroups 1.25 us + 1.1 ns K, or 1.7 ns K if that is more (512 x 4096 x 4096, two rounds,
+// 19; 1024 x 4096 x 2048, four, 20; 2048 x 4096 x 128, eight, 20, the FP4 kernel 12.6). Up to 16384 rows; beyond, the FP4
+// kernel (32768 x 128 x 128 10.3 against 12.2, 100000 x 512 x 128 47 against 104). The few-rows kernel never is the
+// fastest there (28672 x 8192: 80 rows 69 us, 256 rows 137, the FP4 kernel 66-69).
 bool fp4_beats_stream(int64_t M, int64_t N, int64_t K, double c_bytes) {
   if (M <= 64) return false;
   const double k = (double)K, c = c_bytes * (double)M * (double)N, rounds = (double)(((M + 63) / 64 * ((N + 63) / 64) + 255) / 256);
@@ -41,11 +42,11 @@ bool fp4_beats_stream(int64_t M, int64_t N, int64_t K, double c_bytes) {
 }
 
 // Up to 64 rows against K so long that the few-rows kernel, which cuts K into slices for workgroups of their own, is the
-// faster one: here a workgroup's eight waves share all of K, a block of 256 each in turn (the more rows, the longer), and few
-// columns are few workgroups. AMXFP4-E5M2, us here / there: 32 x 1024 x 28672 27 / 22, x 16384 16.6 / 17.5; 32 x 4096 x 28672
-// 27.4 / 25.2; 64 x 128 x 24576 29.5 / 26.2, 64 x 8192 x 28672 59.6 / 53.9, x 20480 the same; 1 x 512 x 40960 25 / 23, x 28672
-// 19 / 21; 32 x 32 x 16384 16.4 / 14.1. Symmetric scales, whose dequantization is half the work: 32 x 512 x 65536 1.25 times,
-// x 40960 1.08 and 17 rows of it 0.85.
+// faster one: here a workgroup's eight waves share all of K, a block of 256 each in turn (the more rows, the longer), and
+// few columns are few workgroups. AMXFP4-E5M2, us here / there: 32 x 1024 x 28672 27 / 22, x 16384 16.6 / 17.5; 32 x 4096
+// x 28672 27.4 / 25.2; 64 x 128 x 24576 29.5 / 26.2, 64 x 8192 x 28672 59.6 / 53.9, x 20480 the same; 1 x 512 x 40960 25
+// / 23, x 28672 19 / 21; 32 x 32 x 16384 16.4 / 14.1. Symmetric scales, whose dequantization is half the work: 32 x 512 x
+// 65536 1.25 times, x 40960 1.08 and 17 rows of it 0.85.
 static bool long_k_few_rows(int scale_kind, bool asym, int64_t M, int64_t N, int64_t K) {
   if (N <= 64) K += K * 3 / 10;  // one or two workgroups: the lines lie lower
   if (!asym) return M > 16 && (M <= 32 ? K > 49152 && N <= 2048 : K > 57344 && N <= 64);
@@ -56,11 +57,11 @@ static bool long_k_few_rows(int scale_kind, bool asym, int64_t M, int64_t N, int
   return K > 20480 ? N <= 8192 : K > 16384 && N <= 512;
 }
 
-// A batch of more than 32 rows each and more than two rounds of workgroups: the few-rows kernel, which dequantizes A once, where
-// its 256 columns per workgroup are filled, and where K is a single block, which one wave here takes alone (us here / there: 32 x
-// 64 x 4096 x 1024 38.4 / 34.5;  512 x 64 x 512 x 256 51 / 33;  but 32 x 64 x 2048 x 1024 21 / 23, 512 x 64 x 128 x 4096 66 / 170), or
-// with asymmetric scales or very many workgroups two (64 x 48 x 2048 x 512 30 / 25, symmetric 24.5 / 23.2; but symmetric 24 x 48 x
-// 2048 x 512 12.1 / 13.9).
+// A batch of more than 32 rows each and more than two rounds of workgroups: the few-rows kernel, which dequantizes A
+// once, where its 256 columns per workgroup are filled, and where K is a single block, which one wave here takes alone
+// (us here / there: 32 x 64 x 4096 x 1024 38.4 / 34.5; 512 x 64 x 512 x 256 51 / 33; but 32 x 64 x 2048 x 1024 21 / 23,
+// 512 x 64 x 128 x 4096 66 / 170), or with asymmetric scales or very many workgroups two (64 x 48 x 2048 x 512 30 / 25,
+// symmetric 24.5 / 23.2; but symmetric 24 x 48 x 2048 x 512 12.1 / 13.9).
 static bool batch_few_rows(bool asym, int64_t M, int64_t N, int64_t K, int64_t batch) {
   const int64_t groups = batch * ((N + 63) / 64);
   return M > 32 && groups > 512 && (N >= 4096 || (N >= 512 && K <= (asym || groups >= 2048 ? 2 : 1) * kStreamBlockK));

@@ -503,7 +503,8 @@ int amxfp4_split_heads_rope_quantize(const amx_format_t* fmt, const float* in, i
         hipLaunchKernelGGL((rope_quantize_long_kernel<SK, ASYM>), grid, dim3(256), 0, hs, in1, tokens, seq, ld, col0, heads,
                            half, pos0 + first, lt, codes1, scales1);
       } else {
-        const dim3 grid(blocks_for(tokens * (256 / kRopeTokens)), (unsigned)((heads + kRopeQuantizeHeads - 1) / kRopeQuantizeHeads));
+        const dim3 grid(blocks_for(tokens * (256 / kRopeTokens)),
+                        (unsigned)((heads + kRopeQuantizeHeads - 1) / kRopeQuantizeHeads));
         hipLaunchKernelGGL((rope_quantize_kernel<SK, ASYM>), grid, dim3(256), 0, hs, in1, tokens, seq, ld, col0, heads, half,
                            pos0 + first, lt, codes1, scales1);
       }
