@@ -59,12 +59,12 @@ static bool long_k_few_rows(int scale_kind, bool asym, int64_t M, int64_t N, int
 
 // A batch of more than 32 rows each and more than two rounds of workgroups: the few-rows kernel, which dequantizes A
 // once, where its 256 columns per workgroup are filled, and where K is a single block, which one wave here takes alone
-// (us here / there: 32 x 64 x 4096 x 1024 38.4 / 34.5; 512 x 64 x 512 x 256 51 / 33; but 32 x 64 x 2048 x 1024 21 / 23,
-// 512 x 64 x 128 x 4096 66 / 170), or with asymmetric scales or very many workgroups two (64 x 48 x 2048 x 512 30 / 25,
-// symmetric 24.5 / 23.2; but symmetric 24 x 48 x 2048 x 512 12.1 / 13.9).
-static bool batch_few_rows(bool asym, int64_t M, int64_t N, int64_t K, int64_t batch) {
+// (us here / there: 32 x 64 x 4096 x 1024 38.4 / 34.5;  512 x 64 x 512 x 256 51 / 33;  but 32 x 64 x 2048 x 1024 21 / 23,
+// 512 x 64 x 128 x 4096 66 / 170), or with very many workgroups two blocks (64 x 48 x 2048 x 512 29.6 / 24.3, symmetric 24.2
+// / 22.6;  but 24 x 48 x 2048 x 512 14.5 / 14.7, symmetric 11.9 / 13.8).
+static bool batch_few_rows(int64_t M, int64_t N, int64_t K, int64_t batch) {
   const int64_t groups = batch * ((N + 63) / 64);
-  return M > 32 && groups > 512 && (N >= 4096 || (N >= 512 && K <= (asym || groups >= 2048 ? 2 : 1) * kStreamBlockK));
+  return M > 32 && groups > 512 && (N >= 4096 || (N >= 512 && K <= (groups >= 2048 ? 2 : 1) * kStreamBlockK));
 }
 
 // Whether this kernel takes a product. scaled: with tensor-wise scales (then the panels are the only other kernel). us for
@@ -90,7 +90,7 @@ static bool stream_preferred(int scale_kind, bool asym, int64_t group_size, bool
   const bool few_rows = group_size == 32 && !scaled && skinny_path_supported(M, N, K, batch);  // the kernel of that name
   if (!scaled && rounded_pot(scale_kind, group_size) && !few_rows) return false;
   if (M <= 64)
-    return !few_rows || (batch > 1 ? !batch_few_rows(asym, M, N, K, batch) : !long_k_few_rows(scale_kind, asym, M, N, K));
+    return !few_rows || (batch > 1 ? !batch_few_rows(M, N, K, batch) : !long_k_few_rows(scale_kind, asym, M, N, K));
   if (batch != 1) return false;
   const bool pot = group_size == 32 && pot_scales(scale_kind);
   if (pot && !asym) return !fp4_path_supported(M, N, K) ? M <= 256 : !fp4_beats_stream(M, N, K, c_bytes);
