@@ -25,9 +25,6 @@ PEAK_FP8_TFLOPS = 5000.0    # MI355X dense block-scaled FP8 MFMA
 # HBM bytes per GEMM-kernel launch measured with rocprofv3 --pmc (FETCH_SIZE, WRITE_SIZE), see
 # profiles/gemm_bf16_c3_up_counters.md.
 MEASURED_TRAFFIC_BYTES = 3.31e9  # 2.84 GB fetched + 0.47 GB written
-# the few-rows kernel on c3_70b_up_32tokens_32x8192x28672 (profiles/gemm_skinny_c3_up_32tokens_kernel_trace.md):
-# FETCH_SIZE 139.8 MB + WRITE_SIZE 3.7 MB per launch
-MEASURED_TRAFFIC_FEW_ROWS = 143.5e6
 # the GEMM kernels of the block-scaled variants on the headline workload, same counters
 # (profiles/gemm_fp4_c3_up_counters.md, profiles/gemm_fp6m_c3_up_counters.md)
 MEASURED_TRAFFIC_VARIANTS = {"mxfp4_e8m0": 0.749e9 + 0.470e9, "amxfp4_e8m0": 1.138e9 + 0.470e9}
@@ -407,19 +404,20 @@ def main():
                   M * (K // (16 if scaled else args.group_size)) * (2 if r["asym"] else 1))
     kernel_name = "gemm_fp4_kernel" if r["mfma"] == "fp4" else "gemm_fp8m_kernel" if r["mfma"] == "fp8" else "gemm_fp6m_kernel" if r["mfma"] == "fp6" else {"panel": "gemm_bf16_kernel", "hybrid":
                   "gemm_e5m2_hybrid_kernel", "fused": "gemm_e5m2_kernel"}[args.e5m2_kernel if args.group_size == 32 else "panel"]
-    if M <= 256 and K % 256 == 0 and args.group_size == 32 and args.format not in DOUBLE_SCALED:
-        kernel_name = "gemm_skinny_kernel"  # few rows: B dequantized in registers straight from its codes
+    gs = 16 if scaled else args.group_size
+    # few rows: both operands, or with an option B alone, dequantized in registers straight from their codes
+    stream = M <= 64 and gs in (16, 32) and (scaled or (args.e5m2_kernel == "panel" and args.pot_kernel == "merged_fp6"))
+    few_rows = stream or (M <= 256 and K % 256 == 0 and gs == 32 and not scaled)
     dtype = r["mfma"]
-    if kernel_name == "gemm_skinny_kernel":
-        dtype = "f16" if FORMATS[args.format][0] == 2 else "bf16"  # the few-rows kernel's MFMA operand type
-    if kernel_name == "gemm_skinny_kernel":
-        # a few rows against a weight matrix: bound by reading B's codes and scales (plus A's panel and C) from HBM
-        kbytes = N * K // 2 + N * (K // 32) * (2 if r["asym"] else 1) + ((M + 31) // 32 * 32) * K * 2 + M * N * 4
+    if few_rows:
+        kernel_name = "gemm_stream_kernel" if stream else "gemm_skinny_kernel"
+        dtype = "f16" if FORMATS[args.format][0] in ((2, 3) if stream else (2,)) else "bf16"  # its MFMA operand type
+        # a few rows against a weight matrix: bound by reading B's codes and scales (plus A's and C) from HBM
+        kbytes = (M + N) * (K // 2 + (K // gs) * (2 if r["asym"] else 1)) + M * N * 4
         gbps = kbytes / (r["kern_ms"] * 1e-3) / 1e9
         roofline = {"bound": "hbm", "kernel": kernel_name, "achieved": round(gbps, 1), "peak": 8000.0, "unit": "GB/s",
                     "frac": round(gbps / 8000.0, 4),
-                    "traffic": MEASURED_TRAFFIC_FEW_ROWS if args.format == "amxfp4_e5m2" and args.group_size == 32
-                    and args.workload == "c3_70b_up_32tokens_32x8192x28672" else None,
+                    "traffic": None,
                     "kernel_ms": round(r["kern_ms"], 4),
                     "algorithmic_bytes": kbytes}
     else:
@@ -434,7 +432,7 @@ def main():
         "higher_is_better": True, "scaling": "weak", "vs_baseline": None, "dtype": dtype, "data": "synthetic",
         "config": {"workload": args.workload, "M": M, "N": N, "K": K, "format": args.format, "group_size": 16 if args.format in DOUBLE_SCALED else args.group_size,
                    "tensor_scale": args.format in DOUBLE_SCALED,
-                   "e5m2_kernel": ("packed_codes" if kernel_name == "gemm_skinny_kernel" else args.e5m2_kernel)
+                   "e5m2_kernel": ("packed_codes" if few_rows else args.e5m2_kernel)
                    if FORMATS[args.format][0] == 2 and args.group_size == 32 else None,
                    "step": "amxfp4_quantize(X) + amxfp4_gemm(Xq, Wq), W pre-cast"},
         "roofline": roofline,

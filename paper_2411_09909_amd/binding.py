@@ -161,8 +161,8 @@ TILES = {"auto": 0, "256x256": 1, "256x128": 2, "64x256": 3}
 
 
 def gemm_options(e5m2_kernel="panel", pot_kernel="merged_fp6", tile="auto", few_rows=0):
-    """The per-call kernel choice of amxfp4_gemm_ex (names or the header's integers); few_rows: 0 = where it applies,
-    -1 = never, n > 0 = with n outer K slices."""
+    """The per-call kernel choice of amxfp4_gemm_ex (names or the header's integers); few_rows: 0 = the
+    library's choice, -1 = never, n > 0 = that kernel where it applies, with n outer K slices."""
     return AmxGemmOptions(E5M2_KERNELS.get(e5m2_kernel, e5m2_kernel), POT_KERNELS.get(pot_kernel, pot_kernel),
                           TILES.get(tile, tile), int(few_rows))
 
