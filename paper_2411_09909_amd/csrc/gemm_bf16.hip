@@ -179,10 +179,12 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_bf16_kernel(const uint16_t*
                          ((b * (Mp >> 5) + (int64_t)tm * (Cfg::kTileM / 32)) * kblocks) * kFragBytes;
   const uint8_t* Bbase = reinterpret_cast<const uint8_t*>(Bp) +
                          ((b * (Np >> 5) + (int64_t)tn * (Cfg::kTileN / 32)) * kblocks) * kFragBytes;
+  // (tiles of 192 rows or columns do not divide the panels' 256: the last one may reach beyond its panel)
+  const int left_a = (int)(Mp >> 5) - tm * (Cfg::kTileM / 32), left_b = (int)(Np >> 5) - tn * (Cfg::kTileN / 32);
   const __amdgpu_buffer_rsrc_t Ar = __builtin_amdgcn_make_buffer_rsrc(
-      const_cast<uint8_t*>(Abase), 0, (Cfg::kTileM / 32) * kblocks * kFragBytes, 0x00020000);
+      const_cast<uint8_t*>(Abase), 0, (left_a < Cfg::kTileM / 32 ? left_a : Cfg::kTileM / 32) * kblocks * kFragBytes, 0x00020000);
   const __amdgpu_buffer_rsrc_t Br = __builtin_amdgcn_make_buffer_rsrc(
-      const_cast<uint8_t*>(Bbase), 0, (Cfg::kTileN / 32) * kblocks * kFragBytes, 0x00020000);
+      const_cast<uint8_t*>(Bbase), 0, (left_b < Cfg::kTileN / 32 ? left_b : Cfg::kTileN / 32) * kblocks * kFragBytes, 0x00020000);
   const int lane_off = lane * 16;
 
   f32x16 acc[FM][FN];
@@ -223,8 +225,9 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_bf16_kernel(const uint16_t*
   AMX_WAIT_VMCNT(kLoads);
   AMX_BARRIER();
 
-  // register rings: the A fragment for step t lives in aR[t & 3] (read two steps ahead), the B fragments of k-step ks
-  // in bR[ks & 1] (read during the previous k-step)
+  // register rings: the A fragment for step t lives in aR[t & 3] (read two steps ahead; t counts on through the four stages
+  // of the loop below, T0 being a stage's first step), the B fragments of k-step ks in bR[ks & 1] (read during the previous
+  // k-step)
   bf16x8 aR[4], bR[2][FN];
   const int offA = lane_off + (wm * FM) * 2 * kFragBytes;
   const int offB = lane_off + (Cfg::kFragsA + (wn * FN) * 2) * kFragBytes;
@@ -238,7 +241,7 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_bf16_kernel(const uint16_t*
   // S + 1, FETCH the one stage S + 3 lands in (last read during stage S - 1). Past the end of K the fetch is pointed
   // at the last real stage instead of being skipped: it lands in a slot nobody reads any more and the body stays free
   // of branches.
-#define AMX_STAGE(S, CUR, NXT, FETCH)                                                                                \
+#define AMX_STAGE(S, CUR, NXT, FETCH, T0)                                                                                \
   {                                                                                                                  \
     const int fetch_ = (S) + 3 < nstages ? (S) + 3 : nstages - 1;                                                    \
     _Pragma("unroll") for (int ks = 0; ks < 2; ++ks) {                                                               \
@@ -247,7 +250,7 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_bf16_kernel(const uint16_t*
         {                                                                                                            \
           const int t2 = t + 2, ks2 = t2 / FM, i2 = t2 % FM;                                                         \
           const uint8_t* src_ = ks2 < 2 ? (CUR) : (NXT);                                                             \
-          aR[t2 & 3] = *reinterpret_cast<const bf16x8*>(src_ + offA + (i2 * 2 + (ks2 & 1)) * kFragBytes);           \
+          aR[(T0 + t2) & 3] = *reinterpret_cast<const bf16x8*>(src_ + offA + (i2 * 2 + (ks2 & 1)) * kFragBytes);    \
         }                                                                                                            \
         _Pragma("unroll") for (int jj = 2 * i; jj < 2 * i + 2; ++jj) {                                               \
           if (jj < FN) {                                                                                             \
@@ -258,7 +261,7 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_bf16_kernel(const uint16_t*
         }                                                                                                            \
         _Pragma("unroll") for (int l = t; l < kLoads; l += 2 * FM) AMX_ISSUE_LOAD(l, fetch_, FETCH);            \
         _Pragma("unroll") for (int j = 0; j < FN; ++j) acc[i][j] =                                                   \
-            __builtin_amdgcn_mfma_f32_32x32x16_bf16(aR[t & 3], bR[ks & 1][j], acc[i][j], 0, 0, 0);                   \
+            __builtin_amdgcn_mfma_f32_32x32x16_bf16(aR[(T0 + t) & 3], bR[ks & 1][j], acc[i][j], 0, 0, 0);            \
         __builtin_amdgcn_sched_barrier(0);                                                                           \
       }                                                                                                              \
     }                                                                                                                \
@@ -269,10 +272,10 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_bf16_kernel(const uint16_t*
   }
 
   for (int s = 0; s < nstages; s += 4) {
-    AMX_STAGE(s, lds0, lds1, lds3);
-    AMX_STAGE(s + 1, lds1, lds2, lds0);
-    AMX_STAGE(s + 2, lds2, lds3, lds1);
-    AMX_STAGE(s + 3, lds3, lds0, lds2);
+    AMX_STAGE(s, lds0, lds1, lds3, 0);
+    AMX_STAGE(s + 1, lds1, lds2, lds0, 2 * FM);
+    AMX_STAGE(s + 2, lds2, lds3, lds1, 4 * FM);
+    AMX_STAGE(s + 3, lds3, lds0, lds2, 6 * FM);
   }
   AMX_WAIT_VMCNT(0);  // nothing may still be writing this workgroup's LDS when it retires
 #undef AMX_STAGE
@@ -378,6 +381,22 @@ hipError_t launch_expand_f16_e5m2(bool asym, const uint8_t* codes, const uint8_t
               : launch_expand<kScaleE5M2, false, true>(codes, scales, R, K, Rp, Kp, 5, batch, panel, s);
 }
 
+// Tiles of every XCD, and of the one with the most, where whole supertiles are dealt.
+struct SupertileShare {
+  int64_t tiles[8], most;
+};
+static SupertileShare supertile_share(int tiles_m, int tiles_n) {
+  const int super_m = (tiles_m + kSuperM - 1) / kSuperM, super_n = (tiles_n + kSuperN - 1) / kSuperN;
+  SupertileShare r = {};
+  for (int st = 0; st < super_m * super_n; ++st) {
+    const int m = tiles_m - st % super_m * kSuperM, n = tiles_n - st / super_m * kSuperN;
+    int64_t& t = r.tiles[st & 7];
+    t += (m < kSuperM ? m : kSuperM) * (n < kSuperN ? n : kSuperN);
+    r.most = t > r.most ? t : r.most;
+  }
+  return r;
+}
+
 // Whether equal runs of tiles of 256 x tile_cols, per_xcd to an XCD, end sooner than supertiles where those leave a fifth
 // of their slots empty. What counts is the tiles that an XCD really has (its share; 32 CUs: one round of 32 at a time),
 // measured in both orders over 1 .. 16 rows and 2 .. 251 columns of tiles, us of the kernel, supertiles / runs:
@@ -396,21 +415,15 @@ hipError_t launch_expand_f16_e5m2(bool asym, const uint8_t* codes, const uint8_t
 //   one or two columns and many rows: a run shares fewer rows of A (32 x 2 FP4 tiles, K 28672, the call: 175 / 189)
 static bool equal_runs_pay(int tiles_m, int tiles_n, int tile_cols, int64_t per_xcd) {
   if (tiles_n <= 2 && tiles_m > 2 * kSuperM) return false;
-  const int super_m = (tiles_m + kSuperM - 1) / kSuperM, super_n = (tiles_n + kSuperN - 1) / kSuperN;
-  int64_t tiles[8] = {}, share = 0;
-  for (int st = 0; st < super_m * super_n; ++st) {
-    const int m = tiles_m - st % super_m * kSuperM, n = tiles_n - st / super_m * kSuperN;
-    int64_t& t = tiles[st & 7];
-    t += (m < kSuperM ? m : kSuperM) * (n < kSuperN ? n : kSuperN);
-    share = t > share ? t : share;
-  }
+  const SupertileShare shares = supertile_share(tiles_m, tiles_n);
+  const int64_t share = shares.most;
   constexpr int kRound = kSuperM * kSuperN;
   const bool partial_row = tiles_m > kSuperM && tiles_m % kSuperM != 0;
   if ((per_xcd + kRound - 1) / kRound < (share + kRound - 1) / kRound || tiles_m <= (tile_cols < 256 ? 3 : 2))
     return true;
   if (share <= kRound) return !partial_row || 8 * per_xcd <= 5 * share;
   int fullest = 0;
-  for (int64_t t : tiles) fullest += t >= share - 8;
+  for (int64_t t : shares.tiles) fullest += t >= share - 8;
   return fullest <= 2 || (!partial_row && (share - 1) % kRound >= 19);
 }
 
@@ -437,6 +450,13 @@ unsigned supertile_grid(int tiles_m, int tiles_n, int tile_rows, int tile_cols, 
   return (unsigned)(rounds * 8 * kSuperM * kSuperN);
 }
 
+// The most tiles that one XCD has in the order that supertile_grid() gives.
+static int64_t largest_share(int tiles_m, int tiles_n, int tile_rows, int tile_cols) {
+  int super_m;
+  const unsigned grid = supertile_grid(tiles_m, tiles_n, tile_rows, tile_cols, 1, super_m);
+  return super_m == 0 ? grid / 8 : supertile_share(tiles_m, tiles_n).most;
+}
+
 template <int WM, int WN, int FM, int FN>
 static hipError_t launch_tiles(const uint16_t* Ap, const uint16_t* Bp, float* C, int64_t M, int64_t N, int64_t Mp,
                                int64_t Np, int64_t Kp, int64_t ldc, int64_t batch, const float* alpha_a,
@@ -445,11 +465,14 @@ static hipError_t launch_tiles(const uint16_t* Ap, const uint16_t* Bp, float* C,
   const int tiles_m = (int)((M + Cfg::kTileM - 1) / Cfg::kTileM), tiles_n = (int)((N + Cfg::kTileN - 1) / Cfg::kTileN);
   int super_m;
   const unsigned grid = supertile_grid(tiles_m, tiles_n, Cfg::kTileM, Cfg::kTileN, batch, super_m);
-  if (glu)
-    hipLaunchKernelGGL((gemm_bf16_kernel<WM, WN, FM, FN, false, true>), dim3(grid, 1, (unsigned)batch),
-                       dim3(Cfg::kThreads), 0, s, Ap, Bp, C, M, N, Mp, Np, Kp, ldc, tiles_m, tiles_n, super_m, alpha_a,
-                       alpha_b);
-  else if (alpha_a && alpha_b)
+  if (glu) {
+    if constexpr (FN % 2 == 0)  // (gate and up columns alternate in blocks of 32)
+      hipLaunchKernelGGL((gemm_bf16_kernel<WM, WN, FM, FN, false, true>), dim3(grid, 1, (unsigned)batch),
+                         dim3(Cfg::kThreads), 0, s, Ap, Bp, C, M, N, Mp, Np, Kp, ldc, tiles_m, tiles_n, super_m, alpha_a,
+                         alpha_b);
+    else
+      return hipErrorInvalidValue;
+  } else if (alpha_a && alpha_b)
     hipLaunchKernelGGL((gemm_bf16_kernel<WM, WN, FM, FN, true>), dim3(grid, 1, (unsigned)batch), dim3(Cfg::kThreads), 0,
                        s, Ap, Bp, C, M, N, Mp, Np, Kp, ldc, tiles_m, tiles_n, super_m, alpha_a, alpha_b);
   else
@@ -479,6 +502,48 @@ int bf16_tile_choice(int64_t M, int64_t N, int64_t batch) {
   // (with a single row of 256-row tiles the 64-row tile was never worse)
   const bool ok2 = est2 < (two_rounds ? 0.92 : 0.85) * est1 && M > 256;
   return ok3 && (!ok2 || est3 <= est2) ? 3 : ok2 ? 2 : 1;
+}
+
+// The same for a single problem with the shapes between those three: 4: 192 x 256, 5: 192 x 128, 6: 128 x 128, 7: 192 x 192
+// (not gated: gate and up columns alternate in blocks of 32, so a wave's column tiles come in pairs). `choice` stays unless
+// one of them is estimated to be 3 % faster. The estimate, us of the kernel: the rounds of the XCD with the most tiles (32 CUs;
+// the shapes with two workgroups on a CU take less for the second round) at the time of a lone tile per unit of K, which
+// grows with the share of the chip that is busy (the clock falls: a lone 256 x 256 tile takes 15 ns per unit of K, a full
+// chip of them 20), or all tiles at the rate the shape reaches on a full chip, and the store of C. Fitted to 280 sizes of
+// 40 to 4097 rows, mean error 5 %; the smaller shapes in the first rounds only, beyond which the larger tiles' lower traffic
+// decides (954 x 28672 x 4096: 256 x 256 195, 192 x 192 228), and 128 x 128 not for a K below 2048 (813 x 1024 x 1024, the call:
+// 64 x 256 13.9, 128 x 128 14.6). Us per call
+// on three sets of buffers in turn, E5M2 asymmetric, before / with the chosen one: 1504 x 6144 x 4096 86 / 73 (192 x 192: 256
+// tiles instead of 144), 1600 x 10240 x 8192 350 / 278 (the same), 1504 x 4096 x 14336 255 / 223 and 1024 x 5120 x 13824 228 /
+// 207 (192 x 128), 2048 x 11008 x 4096 180 / 165 and 3000 x 4096 x 4096 94 / 87 (192 x 256); 281 x 8192 x 8192 67 / 58 (the
+// kernel; 128 x 128). All shapes add the products of an output in
+// the same order: their bits are the same.
+int bf16_tile_refined(int choice, int64_t M, int64_t N, int64_t K, int64_t batch, bool gated) {
+  struct Shape {
+    int tile, rows, cols, rounds;    // at most so many rounds
+    double lone, pair, grows, rate;  // ns per unit of K: one round, two; slower by this share on a full chip; TFLOP/s
+  };
+  static constexpr Shape kShapes[] = {
+      {1, 256, 256, 0, 14.4, 28.8, 0.30, 1500}, {2, 256, 128, 0, 7.6, 15.2, 0.23, 1330}, {3, 64, 256, 0, 6.1, 11.0, 0.23, 1080},
+      {4, 192, 256, 3, 10.7, 21.4, 0.26, 1440}, {5, 192, 128, 1, 6.4, 12.5, 0.21, 1500}, {6, 128, 128, 1, 5.4, 9.0, 0.24, 1370},
+      {7, 192, 192, 1, 8.2, 16.4, 0.25, 1530}};
+  if (batch != 1 || ((M + 255) / 256) * ((N + 255) / 256) > 3 * 256) return choice;
+  double us[8];
+  bool ok[8] = {};
+  for (const Shape& s : kShapes) {
+    const int tiles_m = (int)((M + s.rows - 1) / s.rows), tiles_n = (int)((N + s.cols - 1) / s.cols);
+    const int64_t r = (largest_share(tiles_m, tiles_n, s.rows, s.cols) + 31) / 32, tiles = (int64_t)tiles_m * tiles_n;
+    const double per = (double)(r / 2) * s.pair + (double)(r % 2) * s.lone;
+    const double own = per * (1.0 + s.grows * (double)tiles / (256.0 * (double)r)) * 1e-3 * (double)K;
+    const double full = (double)(tiles * s.rows * s.cols) * 2e-6 * (double)K / s.rate;
+    us[s.tile] = 7.0 + (own > full ? own : full) + 0.6 * 4.0 * (double)(M * N) / 5.1e6;
+    ok[s.tile] = r <= s.rounds && !(gated && s.tile == 7) && !(s.tile == 6 && K < 2048);
+  }
+  int best = choice;
+  double limit = 0.97 * us[choice];
+  for (int t = 4; t <= 7; ++t)
+    if (ok[t] && us[t] < limit) best = t, limit = us[t];
+  return best;
 }
 
 // Estimate of a call that expands both operands, us, up to some 800 rows: B's expansion at the copy rate, and the rounds
@@ -526,13 +591,19 @@ hipError_t launch_gemm_bf16_path(int scale_kind, bool asym, int64_t group_size, 
   }
   if (e != hipSuccess) return e;
   if (timer.start && (e = hipEventRecord(timer.start, s)) != hipSuccess) return e;
-  if (tile == 0) tile = bf16_tile_choice(M, N, batch);  // (a caller's option overrides the choice)
-  if (tile == 2)
-    e = launch_tiles<4, 1, 2, 4>(Ap, Bp, C, M, N, Mp, Np, Kp, ldc, batch, A_tensor_pair, B_tensor_pair, glu, s);  // 256 x 128
-  else if (tile == 3)
-    e = launch_tiles<1, 4, 2, 2>(Ap, Bp, C, M, N, Mp, Np, Kp, ldc, batch, A_tensor_pair, B_tensor_pair, glu, s);  // 64 x 256
-  else
-    e = launch_tiles<2, 2, 4, 4>(Ap, Bp, C, M, N, Mp, Np, Kp, ldc, batch, A_tensor_pair, B_tensor_pair, glu, s);
+  if (tile == 0) tile = bf16_tile_refined(bf16_tile_choice(M, N, batch), M, N, K, batch, glu);  // (an option overrides it)
+  auto go = [&]<int WM, int WN, int FM, int FN>() {
+    return launch_tiles<WM, WN, FM, FN>(Ap, Bp, C, M, N, Mp, Np, Kp, ldc, batch, A_tensor_pair, B_tensor_pair, glu, s);
+  };
+  switch (tile) {
+    case 2: e = go.template operator()<4, 1, 2, 4>(); break;  // 256 x 128
+    case 3: e = go.template operator()<1, 4, 2, 2>(); break;  // 64 x 256
+    case 4: e = go.template operator()<2, 2, 3, 4>(); break;  // 192 x 256
+    case 5: e = go.template operator()<2, 2, 3, 2>(); break;  // 192 x 128
+    case 6: e = go.template operator()<2, 2, 2, 2>(); break;  // 128 x 128
+    case 7: e = go.template operator()<2, 2, 3, 3>(); break;  // 192 x 192
+    default: e = go.template operator()<2, 2, 4, 4>();        // 256 x 256
+  }
   if (e != hipSuccess) return e;
   if (timer.stop) e = hipEventRecord(timer.stop, s);
   return e;

@@ -26,7 +26,6 @@ struct TileCfg {
   static constexpr int kLoads = (kFragsA + kFragsB) / kWaves;  // direct-to-LDS loads per wave per stage
   static constexpr int kStageBytes = (kFragsA + kFragsB) * kFragBytes;
   static_assert(kFragsA % kWaves == 0 && kFragsB % kWaves == 0, "fragments must divide evenly over the waves");
-  static_assert(FM % 2 == 0, "the A register ring of 4 needs an even number of steps per k-step");
 };
 
 // Supertile: the tiles that run at the same time on one XCD (32 CUs, one L2): 8 along M x 4 along N, so that every

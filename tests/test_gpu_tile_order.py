@@ -41,3 +41,20 @@ def test_every_tile_once(M, N, scale, asym, options):
     got = binding.gemm(binding.make_format(scale, asym, 32), ac, as_, bc, bs, out=out,
                        options=binding.gemm_options(few_rows=-1, **options))
     assert torch.equal(got.double(), a @ b.T)
+
+
+@pytest.mark.parametrize("M,N,K,tile", [
+    (1290, 8001, 384, 4), (1500, 7000, 256, 4),     # 192 x 256; 700 and 1290 rows: no multiple of 256
+    (300, 16001, 128, 5), (700, 6130, 1024, 5),     # 192 x 128
+    (70, 130, 2048, 6), (257, 8191, 4096, 6),       # 128 x 128
+    (700, 11001, 128, 7), (1290, 6130, 1024, 7)])   # 192 x 192
+def test_tiles_between_the_three_large_ones(M, N, K, tile):
+    """The shapes that only the rule picks: remainders in M and N, tiles that reach beyond the 256 rows a panel ends on."""
+    from tests.test_routes import i32, i64, flag, rule
+    choice = rule("_ZN3amx16bf16_tile_choiceElll", i32, i64, i64, i64)(M, N, 1)
+    assert rule("_ZN3amx17bf16_tile_refinedEillllb", i32, i32, i64, i64, i64, i64, flag)(choice, M, N, K, 1, False) == tile
+    ac, as_, a = operand(M, K, 0x3C, 1, 3)
+    bc, bs, b = operand(N, K, 0x3C, 1, 4)
+    out = torch.full((M, N), float("nan"), device="cuda")
+    got = binding.gemm(binding.make_format(ref.FP8_E5M2, 1, 32), ac, as_, bc, bs, out=out, options=binding.gemm_options(few_rows=-1))
+    assert torch.equal(got.double(), a @ b.T)
