@@ -4,15 +4,17 @@
 // tile of probabilities is cast as ONE group per query along the keys (the same element and scale format as the
 // operands; FP32 values go into the cast), multiplied with the V tile, and the row sum divides at the end.
 //
-// Everything is computed transposed so that no data has to change lanes between the two products:
-//   S^T[key, query] = K_tile[32 keys x D] . Q^T[D x 32 queries]      (MFMA 32x32x16 BF16, A = K rows, B = Q rows)
-//   O^T[d, query]  += V^T[d x 32 keys]    . P^T[32 keys x 32 queries] (A = V^T, B = the probabilities)
-// In a 32x32 accumulator lane l holds column l % 32 (one query) and rows 8c + 4(l/32) + r (c, r = 0..3) in register
+// The scores are computed transposed so that no data has to change lanes between the two products:
+//   S^T[key, query] = K_tile[32 keys x D] . Q^T[D x 32 queries]   (MFMA 32x32x16 BF16, A = K rows, B = Q rows)
+//   O[query, d]    += P[32 queries x 32 keys] . V[32 keys x d]    (A = the probabilities, B = V^T rows)
+// In a 32x32 accumulator lane l holds column l % 32 (of S^T: one query) and rows 8c + 4(l/32) + r (c, r = 0..3) in register
 // 4c + r: all 32 keys of a query sit in the two lanes l and l ^ 32, so the row maximum, the row sum and the group
 // maximum of the cast are 16 in-lane steps and one exchange, and registers 8j .. 8j+7 of S^T, converted to BF16, are
-// already the B operand of k-step j of the second product, provided V^T was staged with its keys in that order
-// (expand_kv_kernel). Workgroup = kAttnWaves waves x 32 queries; the K and V fragments of a key tile are brought into
-// LDS once per workgroup by direct-to-LDS loads, double buffered.
+// already the A operand of k-step j of the second product, provided V^T was staged with its keys in that order
+// (expand_kv_kernel). The queries are the rows of O, its registers: where the running maximum of a query moves, only the
+// registers of its eight rows are multiplied (with the queries in the lanes it was all 64, in half of the tiles: 11 % of the
+// kernel), by a factor that comes from the query's lane through LDS, behind the exponentials. Workgroup = kAttnWaves waves x
+// 32 queries; the K and V fragments of a key tile are brought into LDS once per workgroup by direct-to-LDS loads.
 #include "../../include/amxfp4.h"
 #include "attention_tile.h"
 #include "cast_math.h"
@@ -23,19 +25,23 @@ namespace amx {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 // Waves per workgroup, 32 queries each. A wave's work on a tile is one long dependent chain (fragment reads -> eight
-// chained MFMAs -> maximum, exponentials, sum, cast -> MFMAs), and the barrier of a workgroup keeps its waves in the
-// same phase of it, so what hides the chain's latencies is waves of OTHER workgroups on the same SIMD: four waves per
-// workgroup and a register budget of a third of the file put three workgroups on a compute unit (8 waves with two
-// per SIMD: 0.243-0.248 ms for 32 heads x 4096; this: 0.229; a quarter of the file, four workgroups: 0.251, the heavy
-// and light query blocks of a causal problem then all start at once).
+// chained MFMAs -> maximum, exponentials, sum, cast -> MFMAs), about 1 us where it has a SIMD to itself, and the barrier of a
+// workgroup keeps its waves in the same phase of it, so what hides the chain's latencies is waves of OTHER workgroups on the
+// same SIMD (of one wave, vector instructions and MFMAs add up; of three, an MFMA of 32 cycles is free beside 16 vector
+// instructions): four waves per workgroup and a register budget of a third of the file put three workgroups on a compute
+// unit. A grid that does not fill these is bound by the chain: up to kPairsMost workgroups the kernel walks over pairs of key
+// tiles with half of the register file, so that the latencies are paid once for two tiles. Us per call, AMXFP4-E5M2, causal,
+// before / tile by tile / pairs, 32 / 8 heads: 512 tokens 23.8 / 23.0 / 22.3, 1504 57.4 / 56.3 / 54.9, 2688 (672 workgroups)
+// 99 / 96 / 90, 3008 (768) 117 / 114 / 119, 4064 190 / 180 / 197, 8192 616 / 600 / 628; 64 heads x 1504 (768) 64 / 60 / 64.
+constexpr int64_t kPairsMost = 704;
 constexpr int kAttnWaves = 4;
 constexpr int kAttnQ = 32 * kAttnWaves;     // queries per workgroup
 
 // kAttnD: the head dimension, 128 or 64. A key tile is kAttnD / 16 K fragments (one per 16 of D) and as many V^T
-// fragments (D / 32 row blocks x 2 k-steps), dealt over the waves: wave w brings K and V fragments w, w + kAttnWaves,
-// ... (with more waves than fragments the first ones would bring K, the others V).
-template <int SCALE_KIND, int kAttnD>
-__global__ __launch_bounds__(64 * kAttnWaves) __attribute__((amdgpu_waves_per_eu(3, 3))) void attention_fused_kernel(
+// fragments (D / 32 row blocks x 2 k-steps), dealt over the waves. All fragments of a product's operand are requested before
+// its first MFMA (two at a time, as the compiler had them, each pair waited out its trip to LDS).
+template <int SCALE_KIND, int kAttnD, bool PAIRS>
+__global__ __launch_bounds__(64 * kAttnWaves) __attribute__((amdgpu_waves_per_eu(PAIRS ? 2 : 3, PAIRS ? 2 : 3))) void attention_fused_kernel(
     const uint8_t* __restrict__ Q_codes, const uint8_t* __restrict__ Q_scales, int asym, const uint16_t* __restrict__ Kp,
     const uint16_t* __restrict__ Vp, float* __restrict__ out, int Sq, int Sk, int Sqp, int Skv, int kv_group,
     float scale_log2, int causal, int merged_bf16) {
@@ -46,14 +52,10 @@ __global__ __launch_bounds__(64 * kAttnWaves) __attribute__((amdgpu_waves_per_eu
   // sum at the end. Same values, same sums.
   constexpr bool kPF16 = SCALE_KIND == kScaleE5M2;
   constexpr int kAttnKFrags = kAttnD / 16, kAttnVFrags = (kAttnD / 32) * 2;
-  static_assert(kAttnKFrags == kAttnVFrags && (kAttnKFrags % kAttnWaves == 0 || 2 * kAttnKFrags == kAttnWaves),
-                "fragments must divide over the waves");
-  // two stages of (K tile, V tile), separate arrays so that loads into one stage are known not to alias reads of the
-  // other
-  __shared__ __attribute__((aligned(1024))) uint8_t ldsK0[kAttnKFrags * kFragBytes];
-  __shared__ __attribute__((aligned(1024))) uint8_t ldsV0[kAttnVFrags * kFragBytes];
-  __shared__ __attribute__((aligned(1024))) uint8_t ldsK1[kAttnKFrags * kFragBytes];
-  __shared__ __attribute__((aligned(1024))) uint8_t ldsV1[kAttnVFrags * kFragBytes];
+  static_assert(kAttnKFrags == kAttnVFrags && kAttnKFrags % kAttnWaves == 0, "fragments must divide over the waves");
+  constexpr int kStageBytes = (kAttnKFrags + kAttnVFrags) * kFragBytes;
+  __shared__ __attribute__((aligned(1024))) uint8_t lds[3 * kStageBytes];
+  __shared__ __attribute__((aligned(16))) float alphas[kAttnWaves][2][32];  // a wave's own: no barrier
 
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -80,33 +82,33 @@ __global__ __launch_bounds__(64 * kAttnWaves) __attribute__((amdgpu_waves_per_eu
   const int64_t kfrags_head = (int64_t)tiles_all * kAttnKFrags, vfrags_head = (int64_t)(kAttnD / 32) * (Skv / 16);
   const uint8_t* Kbase = reinterpret_cast<const uint8_t*>(Kp) + g * kfrags_head * kFragBytes;
   const uint8_t* Vbase = reinterpret_cast<const uint8_t*>(Vp) + g * vfrags_head * kFragBytes;
-  const __amdgpu_buffer_rsrc_t Kr =
-      __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t*>(Kbase), 0, (int)(kfrags_head * kFragBytes), 0x00020000);
-  const __amdgpu_buffer_rsrc_t Vr =
-      __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t*>(Vbase), 0, (int)(vfrags_head * kFragBytes), 0x00020000);
+  auto window = [](const uint8_t* base, int64_t bytes) {
+    const uint64_t p = reinterpret_cast<uint64_t>(base);
+    return u32x4{(uint32_t)p, (uint32_t)(p >> 32), (uint32_t)bytes, 0x00020000u};
+  };
+  const u32x4 Kr = window(Kbase, kfrags_head * kFragBytes), Vr = window(Vbase, vfrags_head * kFragBytes);
   const int lane_off = lane * 16;
 
-  // wave w brings K fragments w, w + kAttnWaves, .. and the V fragments of the same numbers (V fragment f = row block
-  // f / 2, k-step f % 2) of tile T into stage (DK, DV)
-#define AMX_ATTN_LOAD(T, DK, DV)                                                                                   \
-  do {                                                                                                             \
-    if constexpr (kAttnKFrags >= kAttnWaves) {                                                                     \
-      _Pragma("unroll") for (int i_ = 0; i_ < kAttnKFrags / kAttnWaves; ++i_) {                                    \
-        const int f_ = wave + kAttnWaves * i_;                                                                     \
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(Kr, (lds_ptr_t)((DK) + f_ * kFragBytes), 16, lane_off,            \
-                                                 ((T) * kAttnKFrags + f_) * kFragBytes, 0, 0);                     \
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(Vr, (lds_ptr_t)((DV) + f_ * kFragBytes), 16, lane_off,            \
-                                                 ((f_ >> 1) * (Skv / 16) + (f_ & 1) + 2 * (T)) * kFragBytes, 0, 0);\
-      }                                                                                                            \
-    } else if (wave < kAttnKFrags) { /* uniform over the wave */                                                   \
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(Kr, (lds_ptr_t)((DK) + wave * kFragBytes), 16, lane_off,            \
-                                               ((T) * kAttnKFrags + wave) * kFragBytes, 0, 0);                     \
-    } else {                                                                                                       \
-      const int f_ = wave - kAttnKFrags;                                                                           \
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(Vr, (lds_ptr_t)((DV) + f_ * kFragBytes), 16, lane_off,              \
-                                               ((f_ >> 1) * (Skv / 16) + (f_ & 1) + 2 * (T)) * kFragBytes, 0, 0);  \
-    }                                                                                                              \
-  } while (0)
+  // Loads of the key tiles' fragments, dealt over the waves: wave w brings fragments w, w + kAttnWaves, .. of a tile (or of a
+  // pair of tiles). They are written out so that the compiler, which cannot tell the stages of a ring apart, does not wait
+  // for the newest of them in front of every fragment read; they write no registers, and the loops below wait by count.
+  // `past`: 0, or an offset beyond any panel, which brings zeros without a trip to memory.
+  constexpr int kLoads = (kAttnKFrags + kAttnVFrags) / kAttnWaves;  // of a wave and key tile
+  constexpr uint32_t kPast = 0x80000000u;
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_ptr_t)lds;
+  auto load_fragment = [&](const u32x4& window, uint32_t to, uint32_t offset) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
+                 :: "s"(to), "v"(lane_off), "s"(window), "s"(offset) : "memory");
+  };
+  auto load_k = [&](int tile, uint32_t to, int i, uint32_t past) {  // number i of this wave's; a pair's two tiles are adjacent
+    const int f = wave + kAttnWaves * i;
+    load_fragment(Kr, to + f * kFragBytes, past | (uint32_t)((tile * kAttnKFrags + f) * kFragBytes));
+  };
+  auto load_v = [&](int tile, uint32_t to, int i, uint32_t past) {  // fragment f: row block f / 2, k-step f % 2
+    const int n = wave + kAttnWaves * i, f = n % kAttnVFrags;
+    load_fragment(Vr, to + n * kFragBytes,
+                  past | (uint32_t)(((f >> 1) * (Skv / 16) + (f & 1) + 2 * (tile + n / kAttnVFrags)) * kFragBytes));
+  };
 
   // this wave's 32 queries as the B operand of the first product: 8 k-steps over D, resident in registers. They are
   // dequantized here, once, from their codes (BF16: element * scale has at most 6 significant bits); expanding Q to a
@@ -139,81 +141,252 @@ __global__ __launch_bounds__(64 * kAttnWaves) __attribute__((amdgpu_waves_per_eu
     for (int v = 0; v < 16; ++v) o[db][v] = 0.f;
   float m = -__builtin_inff(), l = 0.f;  // running maximum (scaled score, in units of log2) and sum of this lane's query
   const int limit = causal ? qw + (lane & 31) + off : Sk - 1;  // last key this lane's query may attend to
+  const int first_limit = causal ? qw + off : Sk - 1;         // the smallest of the wave's
   const int row_in_tile = 4 * (lane >> 5);                    // key of register v: 8 (v / 4) + row_in_tile + v % 4
 
-  // One key tile from stage (CK, CV).
-#define AMX_ATTN_TILE(T, CK, CV)                                                                                   \
-  if ((T) < nt_wave) {                                                                                             \
-    f32x16 s;                                                                                                      \
-    _Pragma("unroll") for (int v = 0; v < 16; ++v) s[v] = 0.f;                                                     \
-    _Pragma("unroll") for (int kb = 0; kb < kAttnKFrags; ++kb) {                                                   \
-      const bf16x8 a = *reinterpret_cast<const bf16x8*>((CK) + kb * kFragBytes + lane_off);                        \
-      s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, qf[kb], s, 0, 0, 0);                                          \
-    }                                                                                                              \
-    const bool diagonal = causal && (T) * 32 + 31 > qw + off; /* some key of the tile is masked for some query */ \
-    AMX_ATTENTION_TILE_PROBS(false, s, scale_log2, diagonal, (T) * 32 + row_in_tile, limit, m, l, pb, alpha, kPF16)       \
-    if (__builtin_amdgcn_ballot_w64(alpha != 1.0f) != 0) { /* the maximum moved for some query: rescale */        \
-      _Pragma("unroll") for (int db = 0; db < kAttnD / 32; ++db)                                                   \
-        _Pragma("unroll") for (int v = 0; v < 16; ++v) o[db][v] *= alpha;                                          \
-    }                                                                                                              \
-    _Pragma("unroll") for (int j = 0; j < 2; ++j) {                                                                \
-      const u32x4 b = {pb[4 * j], pb[4 * j + 1], pb[4 * j + 2], pb[4 * j + 3]};                                    \
-      _Pragma("unroll") for (int db = 0; db < kAttnD / 32; ++db) {                                                 \
-        const u32x4 a = *reinterpret_cast<const u32x4*>((CV) + (db * 2 + j) * kFragBytes + lane_off);              \
-        if constexpr (kPF16)                                                                                       \
-          o[db] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, a), __builtin_bit_cast(f16x8, b), \
-                                                         o[db], 0, 0, 0);                                          \
-        else                                                                                                       \
-          o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a),                           \
-                                                          __builtin_bit_cast(bf16x8, b), o[db], 0, 0, 0);          \
+  // o *= alpha by accumulator row, where the maximum moved: MOVED has a bit per query, AL the factors of the lane's rows
+#define AMX_ATTN_RESCALE(MOVED, AL)                                                                                \
+  if ((MOVED) != 0) {                                                                                              \
+    _Pragma("unroll") for (int c = 0; c < 4; ++c) {                                                                \
+      if ((MOVED) & (0xFFu << (8 * c))) { /* uniform: rows 8 c .. 8 c + 7 */                                       \
+        asm volatile(""); /* (keeps the branch: without it all rows are multiplied and selected) */                \
+        _Pragma("unroll") for (int db = 0; db < kAttnD / 32; ++db) {                                               \
+          o[db][4 * c] *= (AL)[c].x, o[db][4 * c + 1] *= (AL)[c].y;                                                \
+          o[db][4 * c + 2] *= (AL)[c].z, o[db][4 * c + 3] *= (AL)[c].w;                                            \
+        }                                                                                                          \
       }                                                                                                            \
     }                                                                                                              \
   }
+  // the factors of the lane's accumulator rows from those of the queries, through LDS of the wave's own
+#define AMX_ATTN_BY_ROW(AL, ALPHA, SLOT)                                                                           \
+  float4 AL[4];                                                                                                    \
+  alphas[wave][SLOT][lane & 31] = (ALPHA);                                                                         \
+  _Pragma("unroll") for (int c = 0; c < 4; ++c) AL[c] = *reinterpret_cast<const float4*>(&alphas[wave][SLOT][8 * c + row_in_tile]);
+#define AMX_ATTN_PV(P, VF, J, STEP) /* k-step J: registers 4 J .. of the probabilities, V fragments J, STEP + J, .. */ \
+  {                                                                                                                \
+    const u32x4 p = {(P)[4 * (J)], (P)[4 * (J) + 1], (P)[4 * (J) + 2], (P)[4 * (J) + 3]};                          \
+    _Pragma("unroll") for (int db = 0; db < kAttnD / 32; ++db) {                                                   \
+      const u32x4 v = (VF)[(STEP) * db + (J)];                                                                     \
+      if constexpr (kPF16)                                                                                         \
+        o[db] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, p), __builtin_bit_cast(f16x8, v), \
+                                                       o[db], 0, 0, 0);                                            \
+      else                                                                                                         \
+        o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, p), __builtin_bit_cast(bf16x8, v), \
+                                                        o[db], 0, 0, 0);                                           \
+    }                                                                                                              \
+  }
 
-  // prologue: tile 0 into stage 0
-  AMX_ATTN_LOAD(0, ldsK0, ldsV0);
-  AMX_WAIT_VMCNT(0);
-  AMX_BARRIER();
-  for (int t = 0; t < nt; t += 2) {
-    // stage 1 was last read during tile t - 1; the barrier that ended it lets every wave refill it now
-    if (t + 1 < nt) AMX_ATTN_LOAD(t + 1, ldsK1, ldsV1);
-    AMX_ATTN_TILE(t, ldsK0, ldsV0);
-    AMX_WAIT_VMCNT(0);
-    AMX_BARRIER();
-    if (t + 1 < nt) {  // uniform over the workgroup
-      if (t + 2 < nt) AMX_ATTN_LOAD(t + 2, ldsK0, ldsV0);
-      AMX_ATTN_TILE(t + 1, ldsK1, ldsV1);
-      AMX_WAIT_VMCNT(0);
+  if constexpr (PAIRS) {
+    // K of a pair of tiles in one slot, V in two: V(t + 2) is requested when pair t starts, K(t + 2) when its scores are
+    // done; two barriers to a pair.
+    constexpr uint32_t kPairV = 2 * kAttnVFrags * kFragBytes;
+    uint32_t v_now = 2 * kAttnKFrags * kFragBytes, v_next = v_now + kPairV;
+#pragma unroll
+    for (int i = 0; i < kLoads; ++i) load_k(0, lds0, i, 0u);
+#pragma unroll
+    for (int i = 0; i < kLoads; ++i) load_v(0, lds0 + v_now, i, 0u);
+    for (int t = 0; t < nt; t += 2) {
+      __builtin_amdgcn_s_waitcnt(0x0070);  // vmcnt(0) lgkmcnt(0)
       AMX_BARRIER();
+      const uint32_t past = t + 2 < nt ? 0u : kPast;
+#pragma unroll
+      for (int i = 0; i < kLoads; ++i) load_v(t + 2, lds0 + v_next, i, past);
+      const bool active = t < nt_wave;  // uniform
+      f32x16 s[2];
+      if (active) {
+        bf16x8 kf[2][kAttnKFrags];  // all requested before the first is used
+#pragma unroll
+        for (int kb = 0; kb < kAttnKFrags; ++kb)
+#pragma unroll
+          for (int i = 0; i < 2; ++i)
+            kf[i][kb] = *reinterpret_cast<const bf16x8*>(lds + (i * kAttnKFrags + kb) * kFragBytes + lane_off);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+          for (int v = 0; v < 16; ++v) s[i][v] = 0.f;
+#pragma unroll
+        for (int kb = 0; kb < kAttnKFrags; ++kb)
+#pragma unroll
+          for (int i = 0; i < 2; ++i) s[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[i][kb], qf[kb], s[i], 0, 0, 0);
+      }
+      __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0)
+      AMX_BARRIER();                       // every wave is past its reads of K
+#pragma unroll
+      for (int i = 0; i < kLoads; ++i) load_k(t + 2, lds0, i, past);
+      if (active) {
+        // AMX_ATTENTION_TILE_MAX and _EXP for both tiles at a time: the second one's maximum follows the first one's
+        float x[2][16], mx[2];
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+          for (int v = 0; v < 16; ++v) x[i][v] = s[i][v] * scale_log2;
+        if (t * 32 + 63 > first_limit) {  // uniform: some key of the pair is masked for some query, or past the last one
+#pragma unroll
+          for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int v = 0; v < 16; ++v)
+              if ((t + i) * 32 + row_in_tile + 8 * (v >> 2) + (v & 3) > limit) x[i][v] = -__builtin_inff();
+        }
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+          mx[i] = -__builtin_inff();
+#pragma unroll
+          for (int v = 0; v < 16; ++v) mx[i] = fmaxf(mx[i], x[i][v]);
+        }
+#pragma unroll
+        for (int i = 0; i < 2; ++i) mx[i] = fmaxf(mx[i], __shfl_xor(mx[i], 32, 64));
+        const float m0 = fmaxf(m, mx[0]), m1 = fmaxf(m0, mx[1]);
+        const float alpha0 = __builtin_amdgcn_exp2f(m - m0), alpha1 = __builtin_amdgcn_exp2f(m0 - m1);
+        AMX_ATTN_BY_ROW(al0, alpha0, 0)
+        AMX_ATTN_BY_ROW(al1, alpha1, 1)
+        const uint32_t moved0 = (uint32_t)__builtin_amdgcn_ballot_w64(alpha0 != 1.0f);
+        const uint32_t moved1 = (uint32_t)__builtin_amdgcn_ballot_w64(alpha1 != 1.0f);
+        float psum[2] = {0.f, 0.f}, pmax[2];
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+          const float mi = i ? m1 : m0;
+          pmax[i] = __builtin_amdgcn_exp2f(mx[i] - mi);
+#pragma unroll
+          for (int v = 0; v < 16; ++v) {
+            x[i][v] = __builtin_amdgcn_exp2f(x[i][v] - mi);
+            psum[i] += x[i][v];
+          }
+        }
+#pragma unroll
+        for (int i = 0; i < 2; ++i) psum[i] += __shfl_xor(psum[i], 32, 64);
+        l = (l * alpha0 + psum[0]) * alpha1 + psum[1];
+        m = m1;
+        uint32_t pb0[8], pb1[8];
+        AMX_ATTENTION_TILE_CAST(x[0], pmax[0], pb0, kPF16)
+        AMX_ATTENTION_TILE_CAST(x[1], pmax[1], pb1, kPF16)
+        u32x4 vf[kAttnVFrags];
+#pragma unroll
+        for (int f = 0; f < kAttnVFrags; ++f) vf[f] = *reinterpret_cast<const u32x4*>(lds + v_now + f * kFragBytes + lane_off);
+        AMX_ATTN_RESCALE(moved0, al0)
+        AMX_ATTN_PV(pb0, vf, 0, 2)
+        AMX_ATTN_PV(pb0, vf, 1, 2)
+        if (t + 1 < nt_wave) {  // (otherwise all its probabilities are 0)
+#pragma unroll
+          for (int f = 0; f < kAttnVFrags; ++f)
+            vf[f] = *reinterpret_cast<const u32x4*>(lds + v_now + (kAttnVFrags + f) * kFragBytes + lane_off);
+          AMX_ATTN_RESCALE(moved1, al1)
+          AMX_ATTN_PV(pb1, vf, 0, 2)
+          AMX_ATTN_PV(pb1, vf, 1, 2)
+        }
+      }
+      const uint32_t other = v_now;
+      v_now = v_next;
+      v_next = other;
+    }
+  } else {
+    // Three stages of (K tile, V tile): tile t + 2 is requested during tile t, piece by piece, into the stage of t - 1. Past
+    // the last tile the loads bring zeros instead of being skipped: a branch around each of them cost 5 %.
+    static_assert(kLoads == 4 || kLoads == 2, "places of the loads in a tile");
+#pragma unroll
+    for (int st = 0; st < 2; ++st)
+#pragma unroll
+      for (int i = 0; i < kLoads / 2; ++i) {
+        load_k(st, lds0 + st * kStageBytes, i, st < nt ? 0u : kPast);
+        load_v(st, lds0 + st * kStageBytes + kAttnKFrags * kFragBytes, i, st < nt ? 0u : kPast);
+      }
+    uint32_t stage = 0, free_stage = 2 * kStageBytes;
+    for (int t = 0; t < nt; ++t) {
+      // tile t has landed (t + 1 stays in flight), and every wave is past tile t - 1
+      __builtin_amdgcn_s_waitcnt(0x0070 | kLoads);  // vmcnt(kLoads) lgkmcnt(0)
+      AMX_BARRIER();
+      const uint32_t past = t + 2 < nt ? 0u : kPast, to = lds0 + free_stage;
+      const uint8_t* cur = lds + stage;
+      if (t < nt_wave) {
+        f32x16 s;
+#pragma unroll
+        for (int v = 0; v < 16; ++v) s[v] = 0.f;
+        bf16x8 kf[kAttnKFrags];  // all requested before the first is used
+#pragma unroll
+        for (int kb = 0; kb < kAttnKFrags; ++kb) kf[kb] = *reinterpret_cast<const bf16x8*>(cur + kb * kFragBytes + lane_off);
+        __builtin_amdgcn_sched_barrier(0);
+        load_k(t + 2, to, 0, past);
+        if constexpr (kLoads > 2) load_k(t + 2, to, 1, past);
+#pragma unroll
+        for (int kb = 0; kb < kAttnKFrags; ++kb) s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[kb], qf[kb], s, 0, 0, 0);
+        const bool masked = t * 32 + 31 > first_limit;  // some key of the tile is masked for some query
+        AMX_ATTENTION_TILE_MAX(false, s, scale_log2, masked, t * 32 + row_in_tile, limit, m, alpha)
+        AMX_ATTN_BY_ROW(al, alpha, 0)  // travels behind the exponentials
+        const uint32_t moved = (uint32_t)__builtin_amdgcn_ballot_w64(alpha != 1.0f);
+        __builtin_amdgcn_sched_barrier(0);
+        load_v(t + 2, to + kAttnKFrags * kFragBytes, 0, past);
+        AMX_ATTENTION_TILE_EXP(false, m, l, alpha)
+        AMX_ATTN_RESCALE(moved, al)
+        u32x4 vf[kAttnVFrags];
+#pragma unroll
+        for (int f = 0; f < kAttnVFrags; f += 2)
+          vf[f] = *reinterpret_cast<const u32x4*>(cur + (kAttnKFrags + f) * kFragBytes + lane_off);
+        __builtin_amdgcn_sched_barrier(0);
+        uint32_t pb[8];
+        AMX_ATTENTION_TILE_CAST(x, pmax, pb, kPF16)
+        if constexpr (kLoads > 2) load_v(t + 2, to + kAttnKFrags * kFragBytes, 1, past);
+#pragma unroll
+        for (int f = 1; f < kAttnVFrags; f += 2)
+          vf[f] = *reinterpret_cast<const u32x4*>(cur + (kAttnKFrags + f) * kFragBytes + lane_off);
+        AMX_ATTN_PV(pb, vf, 0, 2)
+        AMX_ATTN_PV(pb, vf, 1, 2)
+      } else {
+#pragma unroll
+        for (int i = 0; i < kLoads / 2; ++i) {
+          load_k(t + 2, to, i, past);
+          load_v(t + 2, to + kAttnKFrags * kFragBytes, i, past);
+        }
+      }
+      free_stage = stage;
+      stage = stage == 2 * kStageBytes ? 0 : stage + kStageBytes;
     }
   }
-#undef AMX_ATTN_TILE
-#undef AMX_ATTN_LOAD
+  AMX_WAIT_VMCNT(0);  // nothing may still be writing this workgroup's LDS when it retires
+#undef AMX_ATTN_RESCALE
+#undef AMX_ATTN_BY_ROW
+#undef AMX_ATTN_PV
 
-  // out[h][query][d] = O^T[d][query] / l; register 4c + r of row block db is d = 32 db + 8 c + 4 (lane / 32) + r.
+  // out[h][query][d] = O[query][d] / l; register 4c + r of column block db is query 8 c + 4 (lane / 32) + r, d = 32 db +
+  // lane % 32.
   // merged_bf16: the same values rounded to BF16 and written token-major, out[query][h * D + d] (the layout the output
-  // projection's cast reads: no head-merge pass over an FP32 copy).
-  const int q = qw + (lane & 31);
-  if (wave_active && q < Sq && merged_bf16) {
-    const float inv = (kPF16 ? 0.03125f : 1.0f) / l;
-    uint16_t* dst = reinterpret_cast<uint16_t*>(out) + ((int64_t)q * nheads + h) * kAttnD + row_in_tile;
+  // projection's cast reads: no head-merge pass over an FP32 copy); two neighbouring lanes swap a value so that the even one
+  // stores two columns of register v's row and the odd one the same two of register v + 1's.
+  // The stores go through a window of the wave's valid rows: rows past Sq fall outside it and are dropped, without a branch
+  // around every store.
+  if (!wave_active) return;
+  const float inv = (kPF16 ? 0.03125f : 1.0f) / l;
+  const int rows = Sq - qw < 32 ? Sq - qw : 32;
+  if (merged_bf16) {
+    const int odd = lane & 1, pitch = nheads * kAttnD * 2;
+    const __amdgpu_buffer_rsrc_t window = __builtin_amdgcn_make_buffer_rsrc(
+        reinterpret_cast<uint16_t*>(out) + ((int64_t)qw * nheads + h) * kAttnD, 0, (rows - 1) * pitch + kAttnD * 2, 0x00020000);
+    const int lane_to = (row_in_tile + odd) * pitch + (lane & 30) * 2;
 #pragma unroll
-    for (int db = 0; db < kAttnD / 32; ++db)
+    for (int v = 0; v < 16; v += 2) {
+      const int qr = 8 * (v >> 2) + (v & 3);
+      const float inv0 = __shfl(inv, qr + row_in_tile, 64), inv1 = __shfl(inv, qr + 1 + row_in_tile, 64);
 #pragma unroll
-      for (int c = 0; c < 4; ++c)
-        *reinterpret_cast<uint2*>(dst + db * 32 + c * 8) = make_uint2(
-            pack2(o[db][4 * c] * inv, o[db][4 * c + 1] * inv), pack2(o[db][4 * c + 2] * inv, o[db][4 * c + 3] * inv));
-  } else if (wave_active && q < Sq) {
-    const float inv = (kPF16 ? 0.03125f : 1.0f) / l;
-    float* dst = out + ((int64_t)h * Sq + q) * kAttnD + row_in_tile;
-#pragma unroll
-    for (int db = 0; db < kAttnD / 32; ++db)
-#pragma unroll
-      for (int c = 0; c < 4; ++c) {
-        const float4 v4 = make_float4(o[db][4 * c] * inv, o[db][4 * c + 1] * inv, o[db][4 * c + 2] * inv,
-                                      o[db][4 * c + 3] * inv);
-        *reinterpret_cast<float4*>(dst + db * 32 + c * 8) = v4;
+      for (int db = 0; db < kAttnD / 32; ++db) {
+        const float x0 = o[db][v] * inv0, x1 = o[db][v + 1] * inv1;
+        const float got = u2f(__builtin_amdgcn_mov_dpp(f2u(odd ? x0 : x1), 0xB1 /* quad_perm 1 0 3 2 */, 0xF, 0xF, true));
+        __builtin_amdgcn_raw_buffer_store_b32(odd ? pack2(got, x1) : pack2(x0, got), window, lane_to + db * 64, qr * pitch, 0);
       }
+      __builtin_amdgcn_sched_barrier(0);  // (all rows at once would spill)
+    }
+  } else {
+    constexpr int kPitch = kAttnD * 4;
+    const __amdgpu_buffer_rsrc_t window =
+        __builtin_amdgcn_make_buffer_rsrc(out + ((int64_t)h * Sq + qw) * kAttnD, 0, rows * kPitch, 0x00020000);
+    const int lane_to = row_in_tile * kPitch + (lane & 31) * 4;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {
+      const int qr = 8 * (v >> 2) + (v & 3);
+      const float inv_row = __shfl(inv, qr + row_in_tile, 64);
+#pragma unroll
+      for (int db = 0; db < kAttnD / 32; ++db)
+        __builtin_amdgcn_raw_buffer_store_b32(f2u(o[db][v] * inv_row), window, lane_to + db * 128, qr * kPitch, 0);
+      __builtin_amdgcn_sched_barrier(0);
+    }
   }
 }
 
@@ -227,10 +400,13 @@ static hipError_t launch_attn(const uint8_t* Qc, const uint8_t* Qs, bool asym, c
                               hipStream_t s) {
   const int64_t Sqp = round_up(Sq, 32);
   const dim3 grid((unsigned)Hq, (unsigned)((Sqp + kAttnQ - 1) / kAttnQ));
-  hipLaunchKernelGGL((attention_fused_kernel<SK, kAttnD>), grid, dim3(64 * kAttnWaves), 0, s, Qc, Qs, asym ? 1 : 0, Kp,
-                     Vp, out, (int)Sq, (int)Sk, (int)Sqp, (int)round_up(Sk, 64), (int)(Hq / Hkv), scale * 1.4426950408889634f, causal,
-                     merged_bf16);
-  return hipGetLastError();
+  auto go = [&]<bool PAIRS>() {
+    hipLaunchKernelGGL((attention_fused_kernel<SK, kAttnD, PAIRS>), grid, dim3(64 * kAttnWaves), 0, s, Qc, Qs, asym ? 1 : 0,
+                       Kp, Vp, out, (int)Sq, (int)Sk, (int)Sqp, (int)round_up(Sk, 64), (int)(Hq / Hkv),
+                       scale * 1.4426950408889634f, causal, merged_bf16);
+    return hipGetLastError();
+  };
+  return (int64_t)grid.x * grid.y <= kPairsMost ? go.template operator()<true>() : go.template operator()<false>();
 }
 
 template <int kAttnD>

@@ -30,6 +30,13 @@ typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
 // BF16 pairs (exact: at most 6 significant bits, 2^-9 <= 2^8 p <= 2^8, so even the smallest is a normal FP16 number):
 // the scale byte is the upper byte of an FP16, so the FP4 -> FP16 conversion and one packed multiply do it.
 #define AMX_ATTENTION_TILE_PROBS(EMPTY_OK, SACC, SCALE_LOG2, MASKED, KEY0, LIMIT, M, L, PB, ALPHA, P_F16)          \
+  AMX_ATTENTION_TILE_MAX(EMPTY_OK, SACC, SCALE_LOG2, MASKED, KEY0, LIMIT, M, ALPHA)                                \
+  AMX_ATTENTION_TILE_EXP(EMPTY_OK, M, L, ALPHA)                                                                    \
+  uint32_t PB[8];                                                                                                  \
+  AMX_ATTENTION_TILE_CAST(x, pmax, PB, P_F16)
+
+// Its three parts. The scaled scores x, their maximum, the factor of what was accumulated so far.
+#define AMX_ATTENTION_TILE_MAX(EMPTY_OK, SACC, SCALE_LOG2, MASKED, KEY0, LIMIT, M, ALPHA)                          \
     float x[16];                                                                                                   \
     float mx = -__builtin_inff();                                                                                  \
     _Pragma("unroll") for (int v = 0; v < 16; ++v) x[v] = (SACC)[v] * (SCALE_LOG2);                                \
@@ -45,7 +52,10 @@ typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
     const float m_raw = fmaxf(M, mx);                                                                              \
     /* EMPTY_OK: a query that has seen no key yet keeps probabilities 0 and alpha 1 instead of the NaN of -inf - -inf */ \
     const float m_new = (EMPTY_OK) && m_raw == -__builtin_inff() ? 0.f : m_raw;                                    \
-    const float ALPHA = __builtin_amdgcn_exp2f(M - m_new);                                                         \
+    const float ALPHA = __builtin_amdgcn_exp2f(M - m_new);
+
+// The probabilities and their sum.
+#define AMX_ATTENTION_TILE_EXP(EMPTY_OK, M, L, ALPHA)                                                              \
     /* exp is monotonic: the largest probability of the tile is the one of the largest score */                    \
     const float pmax = __builtin_amdgcn_exp2f(mx - m_new);                                                         \
     float psum = 0.f;                                                                                              \
@@ -55,29 +65,31 @@ typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
     }                                                                                                              \
     psum += __shfl_xor(psum, 32, 64);                                                                              \
     L = L * ALPHA + psum;                                                                                          \
-    M = (EMPTY_OK) ? m_raw : m_new;                                                                                \
-    /* cast the 32 probabilities of each query as one group and take the dequantized values as BF16. The quotient  \
-       p / S is taken as p * (1 / S): its error of an ulp or two is that of the hardware exp2 which produced p. */ \
+    M = (EMPTY_OK) ? m_raw : m_new;
+
+// The cast of the 32 probabilities X of each query, of which PMAX is the largest, as one group, dequantized into PB. The
+// quotient p / S is taken as p * (1 / S): its error of an ulp or two is that of the hardware exp2 which produced p.
+#define AMX_ATTENTION_TILE_CAST(X, PMAX, PB, P_F16)                                                                \
+  {                                                                                                                \
     float S, R;                                                                                                    \
     if constexpr (SCALE_KIND == kScaleE5M2 || SCALE_KIND == kScaleE4M3) {                                          \
-      fp8_scale_inexact<SCALE_KIND>(pmax, S, R); /* pmax <= 1: no saturation */                                    \
+      fp8_scale_inexact<SCALE_KIND>(PMAX, S, R); /* at most 1: no saturation */                                    \
     } else {                                                                                                       \
-      (void)encode_scale_sr<SCALE_KIND>(pmax, S, R);                                                               \
+      (void)encode_scale_sr<SCALE_KIND>(PMAX, S, R);                                                               \
     }                                                                                                              \
-    uint32_t PB[8];                                                                                                \
     static_assert(!(P_F16) || SCALE_KIND == kScaleE5M2, "FP16 probabilities: FP8-E5M2 scales");                    \
     const _Float16 s_half_ = (_Float16)S; /* exact: an E5M2 value, subnormals included */                          \
     const f16x2 s_half2_ = {s_half_, s_half_};                                                                     \
     _Pragma("unroll") for (int i = 0; i < 8; ++i) {                                                                \
       if constexpr ((P_F16) && SCALE_KIND == kScaleE5M2) {                                                         \
-        const float z0 = x[2 * i] * R, z1 = x[2 * i + 1] * R;                                                      \
+        const float z0 = (X)[2 * i] * R, z1 = (X)[2 * i + 1] * R;                                                  \
         const uint32_t code = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(f2u(z0), z0, z1, 1.0f, 0);                  \
         const f16x2 e = __builtin_amdgcn_cvt_scalef32_pk_f16_fp4(code, 256.0f, 0);                                 \
         PB[i] = __builtin_bit_cast(uint32_t, e * s_half2_);                                                        \
       } else if constexpr (SCALE_KIND == kScaleE5M2 || SCALE_KIND == kScaleE4M3) {                                 \
         /* the conversion replaces byte 0 of its first operand, the only byte read below: any register will do,    \
            and one that dies here saves the move of a zero */                                                      \
-        const float z0 = x[2 * i] * R, z1 = x[2 * i + 1] * R;                                                      \
+        const float z0 = (X)[2 * i] * R, z1 = (X)[2 * i + 1] * R;                                                  \
         const uint32_t code = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(f2u(z0), z0, z1, 1.0f, 0);                  \
         const f32x2 e = __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(code, 1.0f, 0);                                   \
         /* element * scale has at most 6 significant bits: the truncation to BF16 is exact */                      \
@@ -85,7 +97,8 @@ typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
       } else {                                                                                                     \
         /* a power-of-two scale is applied by the conversions themselves (they read the exponent field of S: the   \
            first divides by it, the second multiplies) */                                                          \
-        const uint32_t code = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(f2u(x[2 * i]), x[2 * i], x[2 * i + 1], S, 0); \
+        const uint32_t code = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(f2u((X)[2 * i]), (X)[2 * i], (X)[2 * i + 1], S, 0); \
         PB[i] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp4(code, S, 0));               \
       }                                                                                                            \
-    }
+    }                                                                                                              \
+  }

@@ -195,3 +195,23 @@ def test_full_size_sampled_rows(Hq, Hkv, S):
     want = attention_ref.fused_attention(qb, kb, vb, D ** -0.5, True, ref.FP8_E5M2, 1, heads=hs, rows=rows)
     got = out[np.ix_(hs, rows)]
     compare(got, want[np.ix_(hs, rows)])
+
+
+@pytest.mark.parametrize("scale_format,asym", FORMATS)
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("Sq,Sk,causal", [(1, 32, True), (33, 96, True), (70, 160, True), (130, 320, False), (150, 192, True)])
+def test_many_workgroups_walk_tile_by_tile(Sq, Sk, causal, d, scale_format, asym):
+    """Beyond 704 workgroups the kernel takes one key tile at a time instead of two (one, odd and even numbers of tiles, ragged
+    queries here): the same arithmetic in the same order, so the same bits as a third of the heads gets in calls of their
+    own, which the tests above compare with the oracle."""
+    heads_, fmt = 720, binding.make_format(scale_format, asym, 32)
+    gen = torch.Generator("cuda").manual_seed(Sq)
+    q, k, v = (torch.randn((n, s, d), generator=gen, device="cuda").to(torch.bfloat16) for n, s in ((heads_, Sq), (heads_ // 4, Sk), (heads_ // 4, Sk)))
+    qkv = (binding.quantize_batched(fmt, q), binding.quantize_batched(fmt, k), binding.quantize_batched(fmt, v, k_axis=1))
+
+    def attend(part):  # of the heads
+        (qc, qs), (kc, ks), (vc, vs) = ([t[part * t.shape[0] // 3:(part + 1) * t.shape[0] // 3].contiguous() for t in pair] for pair in qkv)
+        return binding.attention(fmt, qc, qs, kc, ks, vc, vs, d ** -0.5, causal)
+
+    whole = binding.attention(fmt, *qkv[0], *qkv[1], *qkv[2], d ** -0.5, causal)
+    assert torch.isfinite(whole).all() and torch.equal(whole, torch.cat([attend(0), attend(1), attend(2)]))
