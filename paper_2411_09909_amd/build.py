@@ -1,4 +1,4 @@
-"""Builds libamxfp4.so (HIP kernels + C ABI) for gfx950 with hipcc, in-tree next to this file.
+"""Builds libamxfp4.so (HIP kernels + C ABI) for gfx950 with hipcc, and _calls.so, in-tree next to this file.
 
 Run as `python -m paper_2411_09909_amd.build`. hipcc cross-compiles, so no GPU is needed to build.
 """
@@ -6,12 +6,14 @@ import os
 import re
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libamxfp4.so")
+CALLS = os.path.join(HERE, "_calls.so")
 SOURCES = ["gemm_stream.hip", "gemm_stream_glu.hip", "api.hip", "cast.hip", "gemm_bf16.hip", "gemm_fp4.hip", "gemm_e5m2.hip", "gemm_fp8m.hip", "gemm_fp6m.hip", "layer_ops.hip", "peaks.hip", "attention.hip", "attention_decode.hip", "gemm_skinny.hip"]
 # packed FP32 VALU ops are switched off on purpose (they have given wrong results on these machines)
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++20", "-fPIC", "-Wall", "-Wno-unused-command-line-argument",
@@ -60,9 +62,21 @@ def build(verbose=True):
             raise RuntimeError("hipcc failed on %s" % src)
         if spilling:
             raise RuntimeError("%s: vector registers spill in %s" % (src, ", ".join(spilling)))
+    calls = _start_calls()
     cmd = ["hipcc", "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB] + [r[3] for r in results]
     subprocess.check_call(cmd)
+    if calls.wait():
+        raise RuntimeError("the host compiler failed on calls.cpp")
     return LIB
+
+
+def _start_calls():
+    """Starts the host compiler on the module between torch's tensors and the C ABI (no GPU code in it)."""
+    from torch.utils import cpp_extension
+    lib = os.path.join(os.path.dirname(cpp_extension.__file__), os.pardir, "lib")
+    return subprocess.Popen(["g++", "-O2", "-std=c++17", "-shared", "-fPIC", "-Wall", "-D__HIP_PLATFORM_AMD__", os.path.join(CSRC, "calls.cpp"), "-o", CALLS,
+                             "-I" + sysconfig.get_path("include")] + ["-isystem" + p for p in cpp_extension.include_paths("cuda")]
+                            + ["-L" + os.path.normpath(lib), "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip"])
 
 
 if __name__ == "__main__":
