@@ -84,7 +84,8 @@ __device__ __forceinline__ u32x4 stream_dequant(uint32_t word, uint32_t s_pos, u
 // bytes start on a multiple of four, as their vector loads need); otherwise scale entries are loaded byte by byte.
 // GLU: B's rows are the gate and up rows interleaved in blocks of 32; C is then the BF16 output [M][ldc] of N / 2 columns,
 // bf16(silu(gate) * up). Its sums are the plain product's in the same order wherever both come here in the same shape, which
-// is everywhere but at 17 to 32 rows and N <= 4096 (there the plain form has R = 16, the gated one always R = 32).
+// is everywhere but at 17 to 32 rows with N <= 4096 or 48 columns to a workgroup (there the plain form has R = 16, the gated
+// one always R = 32).
 template <int SCALE_KIND, bool ASYM, int GS_LOG2, int R, int MT, int NT, int WAVES, bool WHOLE, bool GLU>
 __global__ __launch_bounds__(64 * WAVES) void gemm_stream_kernel(
     const uint8_t* A_codes, const uint8_t* A_scales, const uint8_t* B_codes, const uint8_t* B_scales, float* C,
@@ -284,6 +285,13 @@ __global__ __launch_bounds__(64 * WAVES) void gemm_stream_kernel(
   }
 }
 
+// Whether workgroups of 48 columns fill their rounds of 256 compute units at least a tenth better than those of 64.
+inline bool stream_48_columns(int64_t N, int64_t batch) {
+  if (batch != 1 || N <= 8192) return false;
+  auto fill = [](int64_t groups) { return (double)groups / (double)((groups + 255) / 256); };
+  return fill((N + 47) / 48) >= 1.1 * fill((N + 63) / 64);
+}
+
 template <bool GLU>
 static hipError_t stream_launch(int scale_kind, bool asym, int64_t group_size, int64_t M, int64_t N, int64_t K,
                               const uint8_t* A_codes, const uint8_t* A_scales, const uint8_t* B_codes,
@@ -304,9 +312,19 @@ static hipError_t stream_launch(int scale_kind, bool asym, int64_t group_size, i
   // 6.8, 32 x 32 8.0;  N 11008: 32 x 32 13.0, 32 x 64 12.5;  N 28672, K 8192: 44.8, 45.7, the latter in four waves 40.6.
   // 128 rows, N 4096: 32 x 32 13.2, 32 x 64 11.8;  256 rows: 22, 22, 64 x 64 in eight waves 16.7, in four 17.7;  512 rows:
   // 43, 41, 31.6, 27.7, 64 x 128 27.9.)
+  // Up to 32 rows, beyond 8192 columns: workgroups of 48 columns (16-row tiles, three column tiles) where they fill the rounds
+  // of compute units at least a tenth better than those of 64 (stream_48_columns(); K in whole blocks, plain form). Us, 64 / 48
+  // columns: 24 x 11008 x 4096 11.8 / 11.0 (172 workgroups, 230), 20 x 10240 x 8192 18.7 / 16.8, 32 x 22016 x 4096 19.7 / 17.2
+  // (344, 459), 1 x 11008 x 4096 10.3 / 9.0, 16 x 10240 x 8192 16.4 / 14.1, 1 x 22016 x 4096 16.7 / 13.8; NVFP4, 24 x 11008 x
+  // 4096 9.4 / 8.9; but 32 x 28672 x 8192 (448, 598) 39.9 / 45.4, 32 x 13824 x 5120 (216, 288) 14.4 / 20.6. (One workgroup of 112
+  // columns to each unit for 28672: 43.5, too few lines in flight.)
   const int64_t t16 = (N + 15) / 16 * batch, t32 = (N + 31) / 32 * batch, rows32 = (M + 31) / 32;
   auto shape = [&]<int SK, bool ASYM, int GSL>() {
     auto pick = [&]<bool WHOLE>() {
+      if constexpr (!GLU && WHOLE) {
+        if (M <= 16 && stream_48_columns(N, batch)) return run.template operator()<SK, ASYM, GSL, 16, 1, 3, 8, WHOLE>();
+        if (M <= 32 && stream_48_columns(N, batch)) return run.template operator()<SK, ASYM, GSL, 16, 2, 3, 8, WHOLE>();
+      }
       if (M <= 16) {
         if constexpr (!GLU) {
           if (t16 <= 256) return run.template operator()<SK, ASYM, GSL, 16, 1, 1, 8, WHOLE>();

@@ -137,3 +137,11 @@ def test_gated_product(M, width, K, scale, asym, gs):
     assert bool(((out.double() - want).abs() <= limit).all())
     full = pad.float()
     assert bool((full[0] == -7).all() and (full[M + 1] == -7).all() and (full[:, width:] == -7).all())
+
+
+@pytest.mark.parametrize("scale,asym,gs", [(ref.FP8_E5M2, 1, 32), (ref.E8M0_FLOOR, 1, 32), (ref.E8M0_FLOOR, 0, 32), (ref.FP8_E4M3, 0, 16)])
+@pytest.mark.parametrize("M,N,K", [(1, 9001, 256), (16, 12288, 768), (17, 8203, 2304), (32, 16397, 256)])
+def test_48_columns_to_a_workgroup(M, N, K, scale, asym, gs):
+    """Up to 32 rows against columns that fill the compute units better in workgroups of 48 (stream_48_columns() in
+    gemm_stream.h): one and two row tiles, remainders in M and N, fewer K blocks than waves and more."""
+    test_against_the_oracle(M, N, K, scale, asym, gs)
