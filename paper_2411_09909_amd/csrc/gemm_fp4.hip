@@ -66,22 +66,26 @@ struct ScalePackJob {
   const uint8_t* scales;
   uint8_t* packed;
   int64_t R, Rp;
-  int blocks;  // workgroups of this operand per batch entry: (Rp / 128) * ceil(stages / 16)
+  int blocks;  // workgroups of this operand per batch entry: (Rp / 128) * ceil(stages / kPackStages)
 };
 
-// grid: (jobA.blocks + jobB.blocks, 1, batch); block 256. A workgroup re-lays 128 rows x 16 stages: it reads the
-// 128 * SB bytes those stages occupy in each of its rows (whole cache lines, 4 bytes per thread and load), turns them
-// through LDS and writes 16 stages of packed scales, contiguous. SB: bytes per group (1 symmetric, 2 asymmetric).
+// grid: (jobA.blocks + jobB.blocks, 1, batch); block 256. A workgroup re-lays 128 rows x 4 stages: it reads the
+// 32 * SB bytes those stages occupy in each of its rows (4 bytes per thread and load), turns them through LDS and writes
+// 4 stages of packed scales, contiguous. SB: bytes per group (1 symmetric, 2 asymmetric). What bounds it is latency: with
+// 16 stages, whole cache lines, the 1.7 MB of 2048 x 11008 x 4096 were 102 workgroups of 16 loads per thread, 6.8 us; a
+// quarter of that each is 3 us less there and at every size up to 4096 x 28672 x 8192 (a call of 1024 x 4096 x 4096 31.0
+// -> 27.5 us), however often a line is read.
+constexpr int kPackStages = 4;
 template <int SB>
 __global__ __launch_bounds__(256) void scale_pack_kernel(ScalePackJob ja, ScalePackJob jb, int64_t G, int nstages) {
-  constexpr int kRowWords = 16 * 8 * SB / 4;  // 32-bit words of 16 stages of one row
+  constexpr int kRowWords = kPackStages * 8 * SB / 4;  // 32-bit words of the stages of one row
   __shared__ uint32_t turn[kScaleRows][kRowWords + 1];
   const bool second = (int)blockIdx.x >= ja.blocks;
   const ScalePackJob& job = second ? jb : ja;
   const int blk = (int)blockIdx.x - (second ? ja.blocks : 0);
-  const int chunks = (nstages + 15) / 16;
+  const int chunks = (nstages + kPackStages - 1) / kPackStages;
   const int64_t q = blk / chunks, b = blockIdx.z;
-  const int st0 = (blk % chunks) * 16;
+  const int st0 = (blk % chunks) * kPackStages;
   const int64_t row_words = G * SB / 4;  // (scale rows are whole words: G is a multiple of 4)
   const uint32_t* src = reinterpret_cast<const uint32_t*>(job.scales) + b * job.R * row_words;
   for (int idx = threadIdx.x; idx < kScaleRows * kRowWords; idx += 256) {
@@ -93,7 +97,7 @@ __global__ __launch_bounds__(256) void scale_pack_kernel(ScalePackJob ja, ScaleP
   // packed: [q][stage][r 32][i 4][8 * SB bytes]; one 8 * SB-byte entry = 2 * SB words
   constexpr int kEntryWords = 2 * SB, kStageWords = 32 * 4 * kEntryWords;
   uint32_t* dst = reinterpret_cast<uint32_t*>(job.packed) + ((b * (job.Rp / kScaleRows) + q) * nstages + st0) * kStageWords;
-  const int stages_here = nstages - st0 < 16 ? nstages - st0 : 16;
+  const int stages_here = nstages - st0 < kPackStages ? nstages - st0 : kPackStages;
   for (int idx = threadIdx.x; idx < stages_here * kStageWords; idx += 256) {
     const int st = idx / kStageWords, e = (idx % kStageWords) / kEntryWords, w = idx % kEntryWords;
     const int r = e >> 2, i = e & 3;
@@ -449,7 +453,7 @@ static hipError_t launch_fp4(int64_t M, int64_t N, int64_t K, const uint8_t* Ac,
   const int nstages = (int)((K + 255) / 256);
   uint8_t* Asp = reinterpret_cast<uint8_t*>(workspace);
   uint8_t* Bsp = Asp + batch * fp4_packed_scale_bytes(ASYM, M, K);
-  const int chunks = (nstages + 15) / 16;
+  const int chunks = (nstages + kPackStages - 1) / kPackStages;
   const ScalePackJob ja = {As, Asp, M, Mp, (int)(Mp / kScaleRows) * chunks};
   const ScalePackJob jb = {Bs, Bsp, N, Np, (int)(Np / kScaleRows) * chunks};
   hipLaunchKernelGGL((scale_pack_kernel<SB>), dim3((unsigned)(ja.blocks + jb.blocks), 1, (unsigned)batch), dim3(256),
