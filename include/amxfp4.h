@@ -313,7 +313,9 @@ int amxfp4_attention_decode(const amx_format_t* fmt, int64_t q_heads, int64_t kv
  * Measurement aid (not part of the method): arms a pair of caller-owned hipEvent_t (passed as void*) for the NEXT
  * amxfp4_gemm / mxfp4_gemm call made on this host thread. That call records `start` on its stream immediately before
  * and `stop` immediately after the launch of its matrix-multiply kernel (the MFMA main loop, excluding the operand
- * re-layout kernels that precede it), then disarms itself. Pass NULL, NULL to disarm. Returns AMX_OK.
+ * re-layout kernels that precede it), then disarms itself. A product whose weights are expanded and multiplied in pieces
+ * (FP8 scales, an expanded form of 170 MB or more) has several: from before the first to after the last, the expansions of the
+ * later pieces included. Pass NULL, NULL to disarm. Returns AMX_OK.
  */
 int amxfp4_profile_next_gemm(void* start_event, void* stop_event);
 

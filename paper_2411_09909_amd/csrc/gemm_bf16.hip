@@ -546,6 +546,35 @@ int bf16_tile_refined(int choice, int64_t M, int64_t N, int64_t K, int64_t batch
   return best;
 }
 
+// Columns of the product (rows of B) that are expanded and multiplied at a time; N: all of them at once. A panel of B of two
+// thirds of the last-level cache (256 MB) or more does not stay there until it is read: it is written to memory and read back
+// from it. Cut into pieces that go through the same workspace one after the other, it stays. A piece is whole rounds of
+// tiles, so that the pieces take no more rounds than the whole, as many as fit into 144 MB, or else into 280 MB (not for up to four
+// rows of tiles: 800 x 28672 x 8192 483 / 488). Us per call on
+// three sets of buffers in turn, AMXFP4-E5M2, whole / in pieces: 4096 x 28672 x 8192 (448 MB, four pieces) 1437 / 1392, 2048
+// of these rows 870 / 824, 1192 (two pieces of 256 MB) 786 / 634; 1504 x 28672 x 4096 (224 MB) 357 / 343, 3094 rows 694 / 615,
+// 1087 rows 326 / 278; 736 x 22016 x 4096 (172 MB) 216 / 201. Smaller panels stay whole (3000 x 10240 x 8192, 160 MB, 406 / 413;
+// 3618 x 8192 x 8192, 128 MB, 396 / 409), and so do rows of C that are no whole lines, whose stores end the pieces late (2396
+// x 32001 x 4096 675 / 711). Each output's sum is the same.
+int64_t bf16_columns_at_a_time(int tile, int64_t M, int64_t N, int64_t K, int64_t batch) {
+  const int64_t rows = tile == 4 ? 192 : 256, tiles_m = (M + rows - 1) / rows, tiles_n = (N + 255) / 256;
+  const int64_t column_bytes = 256 * round_up(K, kPanelK) * 2;  // of the panel, per column of tiles
+  if (batch != 1 || (tile != 1 && tile != 4) || N % 32 != 0 || tiles_n * column_bytes < (int64_t(170) << 20)) return N;
+  const int64_t rounds = (tiles_m * tiles_n + 255) / 256;
+  for (int64_t most : {int64_t(144) << 20, int64_t(280) << 20}) {
+    if (most > (int64_t(144) << 20) && tiles_m < 5) break;
+    int64_t best = 0;
+    for (int64_t k = 1; k < rounds; ++k) {
+      const int64_t cols = 256 * k / tiles_m;  // columns of tiles in k rounds
+      if (cols >= tiles_n || cols * column_bytes > most) break;
+      const int64_t last = cols == 0 ? 0 : (tiles_n - 1) % cols + 1;
+      if (cols > 0 && (tiles_n - last) / cols * k + (tiles_m * last + 255) / 256 <= rounds) best = cols;
+    }
+    if (best > 0) return best * 256;
+  }
+  return N;
+}
+
 // Estimate of a call that expands both operands, us, up to some 800 rows: B's expansion at the copy rate, and the rounds
 // of tiles at the rate of a lone tile (256 x 256 14 ns per unit of K, 256 x 128 9.3, 64 x 256 6.6 to 8 as they fill the
 // chip) or the chip's, and half of the store of C, c_bytes per element of M x N. Measured / estimated: 512 x 4096 x 4096
@@ -570,15 +599,21 @@ hipError_t launch_gemm_bf16_path(int scale_kind, bool asym, int64_t group_size, 
   if (gs_log2 < 0 || !group_divides(K, group_size) || K % 32 != 0) return hipErrorInvalidValue;
   const int64_t Mp = round_up(M, kPanelRows), Np = round_up(N, kPanelRows), Kp = round_up(K, kPanelK);
   uint16_t* Ap = reinterpret_cast<uint16_t*>(workspace);
-  const uint16_t* Bp = B_panel ? reinterpret_cast<const uint16_t*>(B_panel) : Ap + batch * Mp * Kp;
-  hipError_t e;
-  if (B_panel || (Mp + Np) / 32 > 65535) {  // (a panel the caller expanded once: launch_expand_b_panel; or a grid too tall)
-    e = expand_dispatch(scale_kind, asym, gs_log2, A_codes, A_scales, M, K, Mp, Kp, batch, Ap, s);
-    if (e == hipSuccess && !B_panel)
-      e = expand_dispatch(scale_kind, asym, gs_log2, B_codes, B_scales, N, K, Np, Kp, batch, Ap + batch * Mp * Kp, s);
-  } else {
-    const ExpandJob ja = {A_codes, A_scales, Ap, M, K, Mp, Kp}, jb = {B_codes, B_scales, Ap + batch * Mp * Kp, N, K, Np, Kp};
-    const dim3 grid((unsigned)((Kp + 255) / 256), (unsigned)((Mp + Np) / 32), (unsigned)batch);
+  uint16_t* own_b = Ap + batch * Mp * Kp;
+  hipError_t e = hipSuccess;
+  // Expands A and columns n0 .. n0 + n - 1 of the product (rows of B), either, or neither.
+  auto expand = [&](bool with_a, bool with_b, int64_t n0, int64_t n) {
+    const int64_t Npn = round_up(n, kPanelRows);
+    const uint8_t* bc = B_codes + n0 * (K >> 1);
+    const uint8_t* bs = B_scales + n0 * groups_per_row(K, gs_log2) * (asym ? 2 : 1);
+    if (!with_a || !with_b || (Mp + Npn) / 32 > 65535) {  // one of them, or a grid too tall
+      hipError_t r = hipSuccess;
+      if (with_a) r = expand_dispatch(scale_kind, asym, gs_log2, A_codes, A_scales, M, K, Mp, Kp, batch, Ap, s);
+      if (with_b && r == hipSuccess) r = expand_dispatch(scale_kind, asym, gs_log2, bc, bs, n, K, Npn, Kp, batch, own_b, s);
+      return r;
+    }
+    const ExpandJob ja = {A_codes, A_scales, Ap, M, K, Mp, Kp}, jb = {bc, bs, own_b, n, K, Npn, Kp};
+    const dim3 grid((unsigned)((Kp + 255) / 256), (unsigned)((Mp + Npn) / 32), (unsigned)batch);
     auto go = [&]<int SK>() {
       if (asym)
         hipLaunchKernelGGL((expand_pair_kernel<SK, true>), grid, dim3(256), 0, s, ja, jb, gs_log2);
@@ -586,25 +621,32 @@ hipError_t launch_gemm_bf16_path(int scale_kind, bool asym, int64_t group_size, 
         hipLaunchKernelGGL((expand_pair_kernel<SK, false>), grid, dim3(256), 0, s, ja, jb, gs_log2);
       return hipGetLastError();
     };
-    e = scale_kind == kScaleE5M2 ? go.template operator()<kScaleE5M2>()
-        : scale_kind == kScaleE4M3 ? go.template operator()<kScaleE4M3>() : go.template operator()<kScaleE8M0Floor>();
-  }
-  if (e != hipSuccess) return e;
-  if (timer.start && (e = hipEventRecord(timer.start, s)) != hipSuccess) return e;
-  if (tile == 0) tile = bf16_tile_refined(bf16_tile_choice(M, N, batch), M, N, K, batch, glu);  // (an option overrides it)
-  auto go = [&]<int WM, int WN, int FM, int FN>() {
-    return launch_tiles<WM, WN, FM, FN>(Ap, Bp, C, M, N, Mp, Np, Kp, ldc, batch, A_tensor_pair, B_tensor_pair, glu, s);
+    return scale_kind == kScaleE5M2   ? go.template operator()<kScaleE5M2>()
+           : scale_kind == kScaleE4M3 ? go.template operator()<kScaleE4M3>()
+                                      : go.template operator()<kScaleE8M0Floor>();
   };
-  switch (tile) {
-    case 2: e = go.template operator()<4, 1, 2, 4>(); break;  // 256 x 128
-    case 3: e = go.template operator()<1, 4, 2, 2>(); break;  // 64 x 256
-    case 4: e = go.template operator()<2, 2, 3, 4>(); break;  // 192 x 256
-    case 5: e = go.template operator()<2, 2, 3, 2>(); break;  // 192 x 128
-    case 6: e = go.template operator()<2, 2, 2, 2>(); break;  // 128 x 128
-    case 7: e = go.template operator()<2, 2, 3, 3>(); break;  // 192 x 192
-    default: e = go.template operator()<2, 2, 4, 4>();        // 256 x 256
+  if (tile == 0) tile = bf16_tile_refined(bf16_tile_choice(M, N, batch), M, N, K, batch, glu);  // (an option overrides it)
+  const int64_t columns = B_panel ? N : bf16_columns_at_a_time(tile, M, N, K, batch);
+  for (int64_t n0 = 0; n0 < N; n0 += columns) {
+    const int64_t n = N - n0 < columns ? N - n0 : columns, Npn = columns < N ? round_up(n, kPanelRows) : Np;
+    if ((e = expand(n0 == 0, !B_panel, n0, n)) != hipSuccess) return e;
+    if (n0 == 0 && timer.start && (e = hipEventRecord(timer.start, s)) != hipSuccess) return e;
+    const uint16_t* Bp = B_panel ? reinterpret_cast<const uint16_t*>(B_panel) : own_b;
+    float* Cn = glu ? reinterpret_cast<float*>(reinterpret_cast<uint16_t*>(C) + (n0 >> 1)) : C + n0;
+    auto go = [&]<int WM, int WN, int FM, int FN>() {
+      return launch_tiles<WM, WN, FM, FN>(Ap, Bp, Cn, M, n, Mp, Npn, Kp, ldc, batch, A_tensor_pair, B_tensor_pair, glu, s);
+    };
+    switch (tile) {
+      case 2: e = go.template operator()<4, 1, 2, 4>(); break;  // 256 x 128
+      case 3: e = go.template operator()<1, 4, 2, 2>(); break;  // 64 x 256
+      case 4: e = go.template operator()<2, 2, 3, 4>(); break;  // 192 x 256
+      case 5: e = go.template operator()<2, 2, 3, 2>(); break;  // 192 x 128
+      case 6: e = go.template operator()<2, 2, 2, 2>(); break;  // 128 x 128
+      case 7: e = go.template operator()<2, 2, 3, 3>(); break;  // 192 x 192
+      default: e = go.template operator()<2, 2, 4, 4>();        // 256 x 256
+    }
+    if (e != hipSuccess) return e;
   }
-  if (e != hipSuccess) return e;
   if (timer.stop) e = hipEventRecord(timer.stop, s);
   return e;
 }

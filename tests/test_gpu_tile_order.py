@@ -58,3 +58,22 @@ def test_tiles_between_the_three_large_ones(M, N, K, tile):
     out = torch.full((M, N), float("nan"), device="cuda")
     got = binding.gemm(binding.make_format(ref.FP8_E5M2, 1, 32), ac, as_, bc, bs, out=out, options=binding.gemm_options(few_rows=-1))
     assert torch.equal(got.double(), a @ b.T)
+
+
+@pytest.mark.parametrize("M,N,K", [(700, 28672, 4096), (1290, 24640, 4096)])
+def test_wide_weights_in_pieces(M, N, K):
+    """B's panel goes through the workspace in pieces (the last one shorter): the exact product, and bit for bit what prepared
+    weights give, whose panel is whole; the gated product likewise."""
+    from tests.test_routes import i32, i64, rule
+    at_a_time = rule("_ZN3amx22bf16_columns_at_a_timeEillll", i64, i32, i64, i64, i64, i64)(1, M, N, K, 1)
+    assert at_a_time < N and N % at_a_time != 0
+    ac, as_, a = operand(M, K, 0x3C, 1, 5)
+    bc, bs, b = operand(N, K, 0x3C, 1, 6)
+    fmt, options = binding.make_format(ref.FP8_E5M2, 1, 32), binding.gemm_options(few_rows=-1, tile="256x256")
+    out = torch.full((M, N), float("nan"), device="cuda")
+    got = binding.gemm(fmt, ac, as_, bc, bs, out=out, options=options)
+    for n0 in range(0, N, 4096):
+        assert torch.equal(got[:, n0:n0 + 4096].double(), a @ b[n0:n0 + 4096].T)
+    prepared = binding.prepare_weights(fmt, bc, bs)
+    assert torch.equal(binding.gemm_prepared(fmt, ac, as_, bc, bs, prepared), binding.gemm(fmt, ac, as_, bc, bs))
+    assert torch.equal(binding.gemm_silu_mul(fmt, ac, as_, bc, bs, prepared=prepared), binding.gemm_silu_mul(fmt, ac, as_, bc, bs))
