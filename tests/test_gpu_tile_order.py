@@ -60,7 +60,7 @@ def test_tiles_between_the_three_large_ones(M, N, K, tile):
     assert torch.equal(got.double(), a @ b.T)
 
 
-@pytest.mark.parametrize("M,N,K", [(700, 28672, 4096), (1290, 24640, 4096)])
+@pytest.mark.parametrize("M,N,K", [(1100, 28672, 4096), (1290, 24640, 4096)])
 def test_wide_weights_in_pieces(M, N, K):
     """B's panel goes through the workspace in pieces (the last one shorter): the exact product, and bit for bit what prepared
     weights give, whose panel is whole; the gated product likewise."""
