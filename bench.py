@@ -22,9 +22,9 @@ WORKLOAD = "c3_70b_up_4096x8192x28672"
 PEAK_BF16_TFLOPS = 2500.0   # MI355X dense BF16 MFMA
 PEAK_FP4_TFLOPS = 10100.0   # MI355X dense block-scaled FP4 MFMA (the metric's reference peak)
 PEAK_FP8_TFLOPS = 5000.0    # MI355X dense block-scaled FP8 MFMA
-# HBM bytes per GEMM-kernel launch measured with rocprofv3 --pmc (FETCH_SIZE, WRITE_SIZE), see
+# HBM-side bytes of the GEMM kernel(s) of a call measured with rocprofv3 --pmc (FETCH_SIZE, WRITE_SIZE), see
 # profiles/gemm_bf16_c3_up_counters.md.
-MEASURED_TRAFFIC_BYTES = 3.31e9  # 2.84 GB fetched + 0.47 GB written
+MEASURED_TRAFFIC_BYTES = 1.84e9  # 1.38 GB fetched + 0.46 GB written by the four matrix kernels of a call
 # the GEMM kernels of the block-scaled variants on the headline workload, same counters
 # (profiles/gemm_fp4_c3_up_counters.md, profiles/gemm_fp6m_c3_up_counters.md)
 MEASURED_TRAFFIC_VARIANTS = {"mxfp4_e8m0": 0.749e9 + 0.470e9, "amxfp4_e8m0": 1.138e9 + 0.470e9}
@@ -300,6 +300,8 @@ def main():
             step(ev.pairs[i])
         torch.cuda.synchronize()
         t_total = time.perf_counter() - t0
+        # (weights whose expanded form goes through the workspace in pieces: from the first matrix kernel to the last, with
+        # the expansions of the later pieces between them, some 95 us on the default workload)
         kern_ms = sum(ev.elapsed_ms(i) for i in range(steps)) / steps
         ev.destroy()
         torch.cuda.synchronize()
