@@ -14,7 +14,7 @@ CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libamxfp4.so")
 CALLS = os.path.join(HERE, "_calls.so")
-SOURCES = ["gemm_stream.hip", "gemm_stream_glu.hip", "api.hip", "cast.hip", "gemm_bf16.hip", "gemm_fp4.hip", "gemm_e5m2.hip", "gemm_fp8m.hip", "gemm_fp6m.hip", "layer_ops.hip", "peaks.hip", "attention.hip", "attention_decode.hip", "gemm_skinny.hip"]
+SOURCES = ["gemm_stream.hip", "gemm_stream_glu.hip", "api.hip", "cast.hip", "gemm_bf16.hip", "gemm_fp4.hip", "gemm_e5m2.hip", "gemm_fp8m.hip", "gemm_fp6m.hip", "layer_ops.hip", "peaks.hip", "attention.hip", "attention_64.hip", "attention_decode.hip", "gemm_skinny.hip"]
 # packed FP32 VALU ops are switched off on purpose (they have given wrong results on these machines)
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++20", "-fPIC", "-Wall", "-Wno-unused-command-line-argument",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops", "-Rpass-analysis=kernel-resource-usage"]
@@ -33,6 +33,22 @@ def spilling_kernels(compiler_output):
     return spilling
 
 
+# Kernels that are chosen because so many of their waves fit on a SIMD, with the registers that this leaves each wave.
+REGISTERS = {"attention_fused_64_kernel": 96}  # five waves; the kernel of heads of 128, with three, is a sixth to a third slower
+
+
+def oversized_kernels(compiler_output):
+    """Kernels named in REGISTERS that take more vector registers. A build fails on any: nothing else would show it but time."""
+    name, oversized = "", []
+    for line in compiler_output.splitlines():
+        if "Function Name: " in line:
+            name = line.split("Function Name: ")[1].split()[0]
+        elif "  VGPRs: " in line:
+            taken = int(line.split("  VGPRs: ")[1].split()[0])
+            oversized += ["%s (it takes %d, %d at most)" % (name, taken, most) for k, most in REGISTERS.items() if k in name and taken > most]
+    return oversized
+
+
 def _diagnostics(compiler_output):
     """The output without the resource remarks, the source lines shown under them and the known harmless warning."""
     kept, remark = [], False
@@ -48,7 +64,7 @@ def _compile(src):
     cmd = ["hipcc"] + FLAGS + ["-c", os.path.join(CSRC, src), "-o", obj]
     r = subprocess.run(cmd, capture_output=True, text=True)
     out = r.stdout + r.stderr
-    return src, r.returncode, _diagnostics(out), obj, spilling_kernels(out)
+    return src, r.returncode, _diagnostics(out), obj, spilling_kernels(out) + oversized_kernels(out)
 
 
 def build(verbose=True):

@@ -1,5 +1,6 @@
 // Fused quantized attention: out = softmax(scale * Q_hat . K_hat^T) . V_hat with both products on quantized operands
-// (Sec. 5.1 quantizes Q.K^T and the attention map times V) and the attention map never written to memory: the scores
+// (Sec. 5.1 quantizes Q.K^T and the attention map times V) and the attention map never written to memory, for heads of 128
+// dimensions (the kernel of heads of 64 is in attention_64.hip; the launch of both is here): the scores
 // of one tile of 32 keys become un-normalised probabilities against the running row maximum (online softmax), the
 // tile of probabilities is cast as ONE group per query along the keys (the same element and scale format as the
 // operands; FP32 values go into the cast), multiplied with the V tile, and the row sum divides at the end.
@@ -36,16 +37,16 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 constexpr int64_t kPairsMost = 704;
 constexpr int kAttnWaves = 4;
 constexpr int kAttnQ = 32 * kAttnWaves;     // queries per workgroup
+constexpr int kAttnD = 128;                 // the head dimension
 
-// kAttnD: the head dimension, 128 or 64. A key tile is kAttnD / 16 K fragments (one per 16 of D) and as many V^T
-// fragments (D / 32 row blocks x 2 k-steps), dealt over the waves. All fragments of a product's operand are requested before
-// its first MFMA (two at a time, as the compiler had them, each pair waited out its trip to LDS).
-template <int SCALE_KIND, int kAttnD, bool PAIRS>
+// A key tile is kAttnD / 16 K fragments (one per 16 of D) and as many V^T fragments (D / 32 row blocks x 2 k-steps), dealt
+// over the waves. All fragments of a product's operand are requested before its first MFMA (two at a time, as the compiler had
+// them, each pair waited out its trip to LDS).
+template <int SCALE_KIND, bool PAIRS>
 __global__ __launch_bounds__(64 * kAttnWaves) __attribute__((amdgpu_waves_per_eu(PAIRS ? 2 : 3, PAIRS ? 2 : 3))) void attention_fused_kernel(
     const uint8_t* __restrict__ Q_codes, const uint8_t* __restrict__ Q_scales, int asym, const uint16_t* __restrict__ Kp,
     const uint16_t* __restrict__ Vp, float* __restrict__ out, int Sq, int Sk, int Sqp, int Skv, int kv_group,
     float scale_log2, int causal, int merged_bf16) {
-  static_assert(kAttnD == 128 || kAttnD == 64, "head dimension");
   // FP8-E5M2 scales: the second product runs on FP16 operands. The cast leaves the probabilities as FP16 times 2^8
   // (the scale byte is the upper byte of an FP16: a conversion and a packed multiply per pair instead of a conversion,
   // two multiplies and a permute), V^T comes as an FP16 panel biased by 2^-3, and the 2^5 is taken out with the row
@@ -282,7 +283,7 @@ __global__ __launch_bounds__(64 * kAttnWaves) __attribute__((amdgpu_waves_per_eu
   } else {
     // Three stages of (K tile, V tile): tile t + 2 is requested during tile t, piece by piece, into the stage of t - 1. Past
     // the last tile the loads bring zeros instead of being skipped: a branch around each of them cost 5 %.
-    static_assert(kLoads == 4 || kLoads == 2, "places of the loads in a tile");
+    static_assert(kLoads == 4, "places of the loads in a tile");
 #pragma unroll
     for (int st = 0; st < 2; ++st)
 #pragma unroll
@@ -306,7 +307,7 @@ __global__ __launch_bounds__(64 * kAttnWaves) __attribute__((amdgpu_waves_per_eu
         for (int kb = 0; kb < kAttnKFrags; ++kb) kf[kb] = *reinterpret_cast<const bf16x8*>(cur + kb * kFragBytes + lane_off);
         __builtin_amdgcn_sched_barrier(0);
         load_k(t + 2, to, 0, past);
-        if constexpr (kLoads > 2) load_k(t + 2, to, 1, past);
+        load_k(t + 2, to, 1, past);
 #pragma unroll
         for (int kb = 0; kb < kAttnKFrags; ++kb) s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[kb], qf[kb], s, 0, 0, 0);
         const bool masked = t * 32 + 31 > first_limit;  // some key of the tile is masked for some query
@@ -324,7 +325,7 @@ __global__ __launch_bounds__(64 * kAttnWaves) __attribute__((amdgpu_waves_per_eu
         __builtin_amdgcn_sched_barrier(0);
         uint32_t pb[8];
         AMX_ATTENTION_TILE_CAST(x, pmax, pb, kPF16)
-        if constexpr (kLoads > 2) load_v(t + 2, to + kAttnKFrags * kFragBytes, 1, past);
+        load_v(t + 2, to + kAttnKFrags * kFragBytes, 1, past);
 #pragma unroll
         for (int f = 1; f < kAttnVFrags; f += 2)
           vf[f] = *reinterpret_cast<const u32x4*>(cur + (kAttnKFrags + f) * kFragBytes + lane_off);
@@ -394,14 +395,14 @@ size_t attention_workspace_bytes(int64_t Hq, int64_t Hkv, int64_t Sq, int64_t Sk
   return (size_t)((Hq * round_up(Sq, 32) + Hkv * Sk + Hkv * round_up(Sk, 64)) * head_dim * 2);
 }
 
-template <int SK, int kAttnD>
+template <int SK>
 static hipError_t launch_attn(const uint8_t* Qc, const uint8_t* Qs, bool asym, const uint16_t* Kp, const uint16_t* Vp,
                               float* out, int64_t Hq, int64_t Hkv, int64_t Sq, int64_t Sk, float scale, int causal, int merged_bf16,
                               hipStream_t s) {
   const int64_t Sqp = round_up(Sq, 32);
   const dim3 grid((unsigned)Hq, (unsigned)((Sqp + kAttnQ - 1) / kAttnQ));
   auto go = [&]<bool PAIRS>() {
-    hipLaunchKernelGGL((attention_fused_kernel<SK, kAttnD, PAIRS>), grid, dim3(64 * kAttnWaves), 0, s, Qc, Qs, asym ? 1 : 0,
+    hipLaunchKernelGGL((attention_fused_kernel<SK, PAIRS>), grid, dim3(64 * kAttnWaves), 0, s, Qc, Qs, asym ? 1 : 0,
                        Kp, Vp, out, (int)Sq, (int)Sk, (int)Sqp, (int)round_up(Sk, 64), (int)(Hq / Hkv),
                        scale * 1.4426950408889634f, causal, merged_bf16);
     return hipGetLastError();
@@ -409,42 +410,34 @@ static hipError_t launch_attn(const uint8_t* Qc, const uint8_t* Qs, bool asym, c
   return (int64_t)grid.x * grid.y <= kPairsMost ? go.template operator()<true>() : go.template operator()<false>();
 }
 
-template <int kAttnD>
-static hipError_t launch_attention_fused_d(int scale_kind, bool asym, int64_t Hq, int64_t Hkv, int64_t Sq, int64_t Sk,
-                                  const uint8_t* Q_codes, const uint8_t* Q_scales, const uint8_t* K_codes,
-                                  const uint8_t* K_scales, const uint8_t* V_codes, const uint8_t* V_scales, float scale,
-                                  int causal, float* out, bool merged_bf16, void* workspace, hipStream_t s,
-                                  const KernelTimer& timer) {
-  uint16_t* Kp = reinterpret_cast<uint16_t*>(workspace);
-  uint16_t* Vp = Kp + Hkv * Sk * kAttnD;
-  // K: rows = tokens, K = head dimension; V^T: rows = head dimension, K = keys, in the accumulator's key order
-  hipError_t e = launch_expand_kv(scale_kind, asym, K_codes, K_scales, Kp, V_codes, V_scales, Vp, Sk, kAttnD, Hkv, s);
-  if (e != hipSuccess) return e;
-  if (timer.start && (e = hipEventRecord(timer.start, s)) != hipSuccess) return e;
-  switch (scale_kind) {
-    case kScaleE5M2: e = launch_attn<kScaleE5M2, kAttnD>(Q_codes, Q_scales, asym, Kp, Vp, out, Hq, Hkv, Sq, Sk, scale, causal, merged_bf16, s); break;
-    case kScaleE4M3: e = launch_attn<kScaleE4M3, kAttnD>(Q_codes, Q_scales, asym, Kp, Vp, out, Hq, Hkv, Sq, Sk, scale, causal, merged_bf16, s); break;
-    case kScaleE8M0Floor: e = launch_attn<kScaleE8M0Floor, kAttnD>(Q_codes, Q_scales, asym, Kp, Vp, out, Hq, Hkv, Sq, Sk, scale, causal, merged_bf16, s); break;
-    case kScaleE8M0Round: e = launch_attn<kScaleE8M0Round, kAttnD>(Q_codes, Q_scales, asym, Kp, Vp, out, Hq, Hkv, Sq, Sk, scale, causal, merged_bf16, s); break;
-    default: return hipErrorInvalidValue;
-  }
-  if (e != hipSuccess) return e;
-  if (timer.stop) e = hipEventRecord(timer.stop, s);
-  return e;
-}
-
 hipError_t launch_attention_fused(int scale_kind, bool asym, int64_t Hq, int64_t Hkv, int64_t Sq, int64_t Sk,
                                   int64_t head_dim, const uint8_t* Q_codes, const uint8_t* Q_scales,
                                   const uint8_t* K_codes, const uint8_t* K_scales, const uint8_t* V_codes,
                                   const uint8_t* V_scales, float scale, int causal, float* out, bool merged_bf16,
                                   void* workspace, hipStream_t s, const KernelTimer& timer) {
-  if (head_dim == 128)
-    return launch_attention_fused_d<128>(scale_kind, asym, Hq, Hkv, Sq, Sk, Q_codes, Q_scales, K_codes, K_scales, V_codes,
-                                         V_scales, scale, causal, out, merged_bf16, workspace, s, timer);
+  if (head_dim != 128 && head_dim != 64) return hipErrorInvalidValue;
+  uint16_t* Kp = reinterpret_cast<uint16_t*>(workspace);
+  uint16_t* Vp = Kp + Hkv * Sk * head_dim;
+  // K: rows = tokens, K = head dimension; V^T: rows = head dimension, K = keys, in the accumulator's key order
+  hipError_t e = launch_expand_kv(scale_kind, asym, K_codes, K_scales, Kp, V_codes, V_scales, Vp, Sk, head_dim, Hkv, s);
+  if (e != hipSuccess) return e;
+  if (timer.start && (e = hipEventRecord(timer.start, s)) != hipSuccess) return e;
+  auto go = [&]<int SK>() {
+    return launch_attn<SK>(Q_codes, Q_scales, asym, Kp, Vp, out, Hq, Hkv, Sq, Sk, scale, causal, merged_bf16, s);
+  };
   if (head_dim == 64)
-    return launch_attention_fused_d<64>(scale_kind, asym, Hq, Hkv, Sq, Sk, Q_codes, Q_scales, K_codes, K_scales, V_codes,
-                                        V_scales, scale, causal, out, merged_bf16, workspace, s, timer);
-  return hipErrorInvalidValue;
+    e = launch_attention_64(scale_kind, asym, Hq, Hkv, Sq, Sk, Q_codes, Q_scales, Kp, Vp, scale, causal, out, merged_bf16, s);
+  else
+    switch (scale_kind) {
+      case kScaleE5M2: e = go.template operator()<kScaleE5M2>(); break;
+      case kScaleE4M3: e = go.template operator()<kScaleE4M3>(); break;
+      case kScaleE8M0Floor: e = go.template operator()<kScaleE8M0Floor>(); break;
+      case kScaleE8M0Round: e = go.template operator()<kScaleE8M0Round>(); break;
+      default: return hipErrorInvalidValue;
+    }
+  if (e != hipSuccess) return e;
+  if (timer.stop) e = hipEventRecord(timer.stop, s);
+  return e;
 }
 
 }  // namespace amx

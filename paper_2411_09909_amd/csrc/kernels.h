@@ -114,6 +114,11 @@ hipError_t launch_attention_fused(int scale_kind, bool asym, int64_t Hq, int64_t
                                   const uint8_t* V_scales, float scale, int causal, float* out, bool merged_bf16,
                                   void* workspace, hipStream_t s, const KernelTimer& timer);
 
+// attention_64.hip: its kernel for heads of 64, on the panels that launch_attention_fused() has had written
+hipError_t launch_attention_64(int scale_kind, bool asym, int64_t Hq, int64_t Hkv, int64_t Sq, int64_t Sk,
+                               const uint8_t* Q_codes, const uint8_t* Q_scales, const uint16_t* K_panel,
+                               const uint16_t* V_panel, float scale, int causal, float* out, bool merged_bf16, hipStream_t s);
+
 // attention_decode.hip: the same attention for few queries ((Hq / Hkv) * Sq <= 32) against many keys, K and V read as
 // packed codes, the key tiles cut into key_splits ranges (workspace: the ranges' partial results)
 bool attention_decode_supported(int64_t Hq, int64_t Hkv, int64_t Sq, int64_t head_dim);

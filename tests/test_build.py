@@ -28,3 +28,15 @@ def test_a_spill_fails_the_build(monkeypatch):
     monkeypatch.setattr(build, "_compile", lambda src: (src, 0, "", src, ["_Z5firstv"] if src == "cast.hip" else []))
     with pytest.raises(RuntimeError, match="cast.hip: vector registers spill in _Z5firstv"):
         build.build(verbose=False)
+
+
+def test_the_attention_of_heads_of_64_keeps_five_waves_to_a_simd(monkeypatch, tmp_path):
+    """Heads of 64 on the kernel of heads of 128 (162 and 243 registers: three and two waves) were a sixth to a third slower."""
+    monkeypatch.setattr(build, "OBJ", str(tmp_path))
+    kernel = "_ZN3amx25attention_fused_64_kernelILi2EEEvPKh"
+    assert build.oversized_kernels(REMARKS.replace("_Z5firstv", kernel) % 0) == [kernel + " (it takes 256, 96 at most)"]
+    assert build.oversized_kernels(REMARKS.replace("_Z5firstv", kernel).replace("256", "96") % 0) == []
+    compiled = build._compile("attention_64.hip")
+    assert compiled[1] == 0 and compiled[4] == []
+    monkeypatch.setattr(build, "REGISTERS", {"attention_fused_64_kernel": 80})
+    assert len(build._compile("attention_64.hip")[4]) == 4  # the kernel of each scale format is there
