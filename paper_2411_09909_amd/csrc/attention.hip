@@ -344,33 +344,37 @@ __global__ __launch_bounds__(64 * kAttnWaves) __attribute__((amdgpu_waves_per_eu
   }
   AMX_WAIT_VMCNT(0);  // nothing may still be writing this workgroup's LDS when it retires
 #undef AMX_ATTN_RESCALE
-#undef AMX_ATTN_BY_ROW
 #undef AMX_ATTN_PV
 
   // out[h][query][d] = O[query][d] / l; register 4c + r of column block db is query 8 c + 4 (lane / 32) + r, d = 32 db +
   // lane % 32.
   // merged_bf16: the same values rounded to BF16 and written token-major, out[query][h * D + d] (the layout the output
-  // projection's cast reads: no head-merge pass over an FP32 copy); two neighbouring lanes swap a value so that the even one
-  // stores two columns of register v's row and the odd one the same two of register v + 1's.
+  // projection's cast reads: no head-merge pass over an FP32 copy); a lane packs the values of registers v and v + 1 and swaps
+  // the pair with its neighbour's, of which the even one stores two columns of register v's row and the odd one the same two of
+  // register v + 1's (swapped before they were rounded, twice the instructions: 0.5 us of a call of 96 tokens).
   // The stores go through a window of the wave's valid rows: rows past Sq fall outside it and are dropped, without a branch
   // around every store.
   if (!wave_active) return;
-  const float inv = (kPF16 ? 0.03125f : 1.0f) / l;
+  // (the reciprocals by row through LDS at once: a lane exchange in front of every row's stores was one trip after the other, 0.8
+  // us of a call of 96 tokens)
+  AMX_ATTN_BY_ROW(inv, (kPF16 ? 0.03125f : 1.0f) / l, 0)
+#undef AMX_ATTN_BY_ROW
   const int rows = Sq - qw < 32 ? Sq - qw : 32;
   if (merged_bf16) {
     const int odd = lane & 1, pitch = nheads * kAttnD * 2;
     const __amdgpu_buffer_rsrc_t window = __builtin_amdgcn_make_buffer_rsrc(
         reinterpret_cast<uint16_t*>(out) + ((int64_t)qw * nheads + h) * kAttnD, 0, (rows - 1) * pitch + kAttnD * 2, 0x00020000);
     const int lane_to = (row_in_tile + odd) * pitch + (lane & 30) * 2;
+    const uint32_t pick = odd ? 0x03020706u : 0x05040100u;  // of (the neighbour's pair, one's own): which halves
 #pragma unroll
     for (int v = 0; v < 16; v += 2) {
       const int qr = 8 * (v >> 2) + (v & 3);
-      const float inv0 = __shfl(inv, qr + row_in_tile, 64), inv1 = __shfl(inv, qr + 1 + row_in_tile, 64);
+      const float inv0 = v & 2 ? inv[v >> 2].z : inv[v >> 2].x, inv1 = v & 2 ? inv[v >> 2].w : inv[v >> 2].y;
 #pragma unroll
       for (int db = 0; db < kAttnD / 32; ++db) {
-        const float x0 = o[db][v] * inv0, x1 = o[db][v + 1] * inv1;
-        const float got = u2f(__builtin_amdgcn_mov_dpp(f2u(odd ? x0 : x1), 0xB1 /* quad_perm 1 0 3 2 */, 0xF, 0xF, true));
-        __builtin_amdgcn_raw_buffer_store_b32(odd ? pack2(got, x1) : pack2(x0, got), window, lane_to + db * 64, qr * pitch, 0);
+        const uint32_t own = pack2(o[db][v] * inv0, o[db][v + 1] * inv1);
+        const uint32_t other = __builtin_amdgcn_mov_dpp(own, 0xB1 /* quad_perm 1 0 3 2 */, 0xF, 0xF, true);
+        __builtin_amdgcn_raw_buffer_store_b32(__builtin_amdgcn_perm(other, own, pick), window, lane_to + db * 64, qr * pitch, 0);
       }
       __builtin_amdgcn_sched_barrier(0);  // (all rows at once would spill)
     }
@@ -382,7 +386,7 @@ __global__ __launch_bounds__(64 * kAttnWaves) __attribute__((amdgpu_waves_per_eu
 #pragma unroll
     for (int v = 0; v < 16; ++v) {
       const int qr = 8 * (v >> 2) + (v & 3);
-      const float inv_row = __shfl(inv, qr + row_in_tile, 64);
+      const float inv_row = v & 2 ? (v & 1 ? inv[v >> 2].w : inv[v >> 2].z) : (v & 1 ? inv[v >> 2].y : inv[v >> 2].x);
 #pragma unroll
       for (int db = 0; db < kAttnD / 32; ++db)
         __builtin_amdgcn_raw_buffer_store_b32(f2u(o[db][v] * inv_row), window, lane_to + db * 128, qr * kPitch, 0);

@@ -1,4 +1,7 @@
 """The build refuses kernels whose vector registers spill."""
+import os
+import subprocess
+
 import pytest
 
 from paper_2411_09909_amd import build
@@ -40,3 +43,19 @@ def test_the_attention_of_heads_of_64_keeps_five_waves_to_a_simd(monkeypatch, tm
     assert compiled[1] == 0 and compiled[4] == []
     monkeypatch.setattr(build, "REGISTERS", {"attention_fused_64_kernel": 80})
     assert len(build._compile("attention_64.hip")[4]) == 4  # the kernel of each scale format is there
+
+
+def test_the_attention_stores_its_rows_without_an_exchange_for_each(tmp_path):
+    """The exchanges between lanes left in a kernel are those of a tile's maximum and sum, twice for pairs of tiles: one in front
+    of every row's stores, 32 more, waited out 16 trips in a row."""
+    listing = str(tmp_path / "attention.s")
+    flags = [f for f in build.FLAGS if not f.startswith("-Rpass")]
+    subprocess.run(["hipcc"] + flags + ["--cuda-device-only", "-S", os.path.join(build.CSRC, "attention.hip"), "-o", listing], check=True,
+                   capture_output=True)
+    count, name = {}, None
+    for line in open(listing):
+        if line.startswith("_ZN3amx22attention_fused_kernel"):
+            name = line.split(":")[0]
+        elif "ds_bpermute_b32" in line:
+            count[name] = count.get(name, 0) + 1
+    assert len(count) == 8 and max(count.values()) <= 4
