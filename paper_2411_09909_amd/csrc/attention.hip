@@ -30,11 +30,8 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 // workgroup keeps its waves in the same phase of it, so what hides the chain's latencies is waves of OTHER workgroups on the
 // same SIMD (of one wave, vector instructions and MFMAs add up; of three, an MFMA of 32 cycles is free beside 16 vector
 // instructions): four waves per workgroup and a register budget of a third of the file put three workgroups on a compute
-// unit. A grid that does not fill these is bound by the chain: up to kPairsMost workgroups the kernel walks over pairs of key
-// tiles with half of the register file, so that the latencies are paid once for two tiles. Us per call, AMXFP4-E5M2, causal,
-// before / tile by tile / pairs, 32 / 8 heads: 512 tokens 23.8 / 23.0 / 22.3, 1504 57.4 / 56.3 / 54.9, 2688 (672 workgroups)
-// 99 / 96 / 90, 3008 (768) 117 / 114 / 119, 4064 190 / 180 / 197, 8192 616 / 600 / 628; 64 heads x 1504 (768) 64 / 60 / 64.
-constexpr int64_t kPairsMost = 704;
+// unit. A grid that does not fill these is bound by the chain: there the kernel walks over pairs of key tiles with half of the
+// register file, two workgroups to a compute unit, so that the latencies are paid once for two tiles (pairs_pay()).
 constexpr int kAttnWaves = 4;
 constexpr int kAttnQ = 32 * kAttnWaves;     // queries per workgroup
 constexpr int kAttnD = 128;                 // the head dimension
@@ -399,6 +396,19 @@ size_t attention_workspace_bytes(int64_t Hq, int64_t Hkv, int64_t Sq, int64_t Sk
   return (size_t)((Hq * round_up(Sq, 32) + Hkv * Sk + Hkv * round_up(Sk, 64)) * head_dim * 2);
 }
 
+// Whether pairs of key tiles are the faster walk: up to 704 workgroups of a causal call, whose later query blocks start first
+// and whose short ones fill up what is left, but only while all run at once, 512 of them, where they are of much the same
+// length: without a mask, or with more than an eighth of the keys in front of the first query. Us per call, AMXFP4-E5M2, tile by
+// tile / pairs, 32 / 8 heads, causal: 512 tokens 23.3 / 22.6, 1504 53.5 / 51.3, 2688 (672 workgroups) 93.1 / 87.5, 3008 (768)
+// 114 / 119, 4064 180 / 197; without a mask, 40 / 8 heads x 1920 (600 workgroups) 101 / 118, 64 / 8 x 1344 (704) 77 / 89, up to
+// 512 ratios of 0.95 to 1.01; 513 to 704 workgroups with 1.5 to 4 times the keys 1.08 to 1.25, with 1.25 times 0.95 to 1.12. An
+// odd number of key tiles costs pairs a whole empty one, which up to nine of them is more than they save (96 keys: tile by tile
+// 0.95 to 0.98 of the pairs' time).
+bool pairs_pay(int64_t workgroups, int64_t Sq, int64_t Sk, int causal) {
+  if ((Sk / 32) % 2 == 1 && Sk / 32 <= 9) return false;
+  return workgroups <= (causal && 8 * (Sk - Sq) <= Sk ? 704 : 512);
+}
+
 template <int SK>
 static hipError_t launch_attn(const uint8_t* Qc, const uint8_t* Qs, bool asym, const uint16_t* Kp, const uint16_t* Vp,
                               float* out, int64_t Hq, int64_t Hkv, int64_t Sq, int64_t Sk, float scale, int causal, int merged_bf16,
@@ -411,7 +421,7 @@ static hipError_t launch_attn(const uint8_t* Qc, const uint8_t* Qs, bool asym, c
                        scale * 1.4426950408889634f, causal, merged_bf16);
     return hipGetLastError();
   };
-  return (int64_t)grid.x * grid.y <= kPairsMost ? go.template operator()<true>() : go.template operator()<false>();
+  return pairs_pay((int64_t)grid.x * grid.y, Sq, Sk, causal) ? go.template operator()<true>() : go.template operator()<false>();
 }
 
 hipError_t launch_attention_fused(int scale_kind, bool asym, int64_t Hq, int64_t Hkv, int64_t Sq, int64_t Sk,

@@ -199,10 +199,10 @@ def test_full_size_sampled_rows(Hq, Hkv, S):
 
 @pytest.mark.parametrize("scale_format,asym", FORMATS)
 @pytest.mark.parametrize("d", [64, 128])
-@pytest.mark.parametrize("Sq,Sk,causal", [(1, 32, True), (33, 96, True), (70, 160, True), (130, 320, False), (150, 192, True)])
+@pytest.mark.parametrize("Sq,Sk,causal", [(1, 32, True), (33, 96, True), (70, 160, True), (130, 320, False), (150, 192, True), (100, 352, True), (40, 416, False)])
 def test_many_workgroups_walk_tile_by_tile(Sq, Sk, causal, d, scale_format, asym):
-    """Beyond 704 workgroups the kernel takes one key tile at a time instead of two (one, odd and even numbers of tiles, ragged
-    queries here): the same arithmetic in the same order, so the same bits as a third of the heads gets in calls of their
+    """With many workgroups the kernel takes one key tile at a time instead of two (one, odd and even numbers of tiles, ragged
+    queries here; up to nine tiles two only where their number is even): the same arithmetic in the same order, so the same bits as a third of the heads gets in calls of their
     own, which the tests above compare with the oracle."""
     heads_, fmt = 720, binding.make_format(scale_format, asym, 32)
     gen = torch.Generator("cuda").manual_seed(Sq)

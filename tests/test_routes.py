@@ -146,3 +146,13 @@ def test_beyond_256_rows_the_gated_product_goes_where_the_plain_one_does(scale, 
             for N in (64, 1024, 2048, 5632, 11008, 22016, 28672):
                 for K in (96, 256, 1024, 2048, 4096, 8192, 11008):
                     assert one_launch_gated(scale, asym, M, N, K, group) == one_launch(scale, asym, M, N, K, 1, group)
+
+
+@pytest.mark.parametrize("workgroups,Sq,Sk,causal,pairs", [
+    (672, 2688, 2688, 1, 1), (768, 3072, 3072, 1, 0),                        # 93 / 88 us, 114 / 119
+    (512, 2048, 2048, 0, 1), (600, 1920, 1920, 0, 0), (704, 1344, 1344, 0, 0),  # without a mask: 101 / 118, 77 / 89
+    (640, 2560, 2720, 1, 1), (640, 2560, 3840, 1, 0), (500, 2000, 4000, 1, 1),  # more keys than queries
+    (64, 96, 96, 1, 0), (64, 288, 288, 0, 0), (64, 352, 352, 1, 1), (64, 128, 128, 1, 1)])  # odd numbers of key tiles
+def test_attention_walks_over_pairs_of_key_tiles(workgroups, Sq, Sk, causal, pairs):
+    """Tile by tile / pairs: workgroups of the same length must all run at once, two to a compute unit."""
+    assert rule("_ZN3amx9pairs_payEllli", flag, i64, i64, i64, i32)(workgroups, Sq, Sk, causal) == bool(pairs)
