@@ -506,18 +506,20 @@ int bf16_tile_choice(int64_t M, int64_t N, int64_t batch) {
 
 // The same for a single problem with the shapes between those three: 4: 192 x 256, 5: 192 x 128, 6: 128 x 128, 7: 192 x 192
 // (not gated: gate and up columns alternate in blocks of 32, so a wave's column tiles come in pairs). `choice` stays unless
-// one of them is estimated to be 3 % faster. The estimate, us of the kernel: the rounds of the XCD with the most tiles (32 CUs;
-// the shapes with two workgroups on a CU take less for the second round) at the time of a lone tile per unit of K, which
+// one of them is estimated to be 3 % faster. The estimate, us of the kernel: the rounds of the XCD with the most tiles (32
+// CUs; the shapes with two workgroups on a CU take less for the second round) at the time of a lone tile per unit of K, which
 // grows with the share of the chip that is busy (the clock falls: a lone 256 x 256 tile takes 15 ns per unit of K, a full
 // chip of them 20), or all tiles at the rate the shape reaches on a full chip, and the store of C. Fitted to 280 sizes of
 // 40 to 4097 rows, mean error 5 %; the smaller shapes in the first rounds only, beyond which the larger tiles' lower traffic
-// decides (954 x 28672 x 4096: 256 x 256 195, 192 x 192 228), and 128 x 128 not for a K below 2048 (813 x 1024 x 1024, the call:
-// 64 x 256 13.9, 128 x 128 14.6). Us per call
-// on three sets of buffers in turn, E5M2 asymmetric, before / with the chosen one: 1504 x 6144 x 4096 86 / 73 (192 x 192: 256
-// tiles instead of 144), 1600 x 10240 x 8192 350 / 278 (the same), 1504 x 4096 x 14336 255 / 223 and 1024 x 5120 x 13824 228 /
-// 207 (192 x 128), 2048 x 11008 x 4096 180 / 165 and 3000 x 4096 x 4096 94 / 87 (192 x 256); 281 x 8192 x 8192 67 / 58 (the
-// kernel; 128 x 128). All shapes add the products of an output in
-// the same order: their bits are the same.
+// decides (954 x 28672 x 4096: 256 x 256 195, 192 x 192 228), and 128 x 128 not for a K below 2048 (813 x 1024 x 1024, the
+// call: 64 x 256 13.9, 128 x 128 14.6). Us per call on three sets of buffers in turn, E5M2 asymmetric, before / with the chosen
+// one: 1504 x 6144 x 4096 86 / 73 (192 x 192: 256 tiles instead of 144), 1563 x 10240 x 8192 364 / 307 (192 x 256), 1504 x 4096
+// x 14336 255 / 223 and 1024 x 5120 x 13824 228 / 207 (192 x 128), 2048 x 11008 x 4096 180 / 165 and 3000 x 4096 x 4096 94 /
+// 87 (192 x 256); 281 x 8192 x 8192 67 / 58 (the kernel; 128 x 128).
+// Where the estimate was wrong over 2660 more sizes (257 to 4096 rows, plain, gated and prepared; before / with the other):
+// 192 x 256 in more rounds than 256 x 256 takes (1148 x 25920 x 2432, gated, prepared, 120 / 140; 2071 x 13824 x 5120, gated,
+// 260 / 281), and in a second round instead of 64 x 256 with a K below 2048 (1311 x 11072 x 1792, gated, 65 / 72; 574 x 24704 x
+// 1792 82 / 87). All shapes add the products of an output in the same order: their bits are the same.
 int bf16_tile_refined(int choice, int64_t M, int64_t N, int64_t K, int64_t batch, bool gated) {
   struct Shape {
     int tile, rows, cols, rounds;    // at most so many rounds
@@ -529,6 +531,7 @@ int bf16_tile_refined(int choice, int64_t M, int64_t N, int64_t K, int64_t batch
       {7, 192, 192, 1, 8.2, 16.4, 0.25, 1530}};
   if (batch != 1 || ((M + 255) / 256) * ((N + 255) / 256) > 3 * 256) return choice;
   double us[8];
+  int64_t rounds[8];
   bool ok[8] = {};
   for (const Shape& s : kShapes) {
     const int tiles_m = (int)((M + s.rows - 1) / s.rows), tiles_n = (int)((N + s.cols - 1) / s.cols);
@@ -537,13 +540,28 @@ int bf16_tile_refined(int choice, int64_t M, int64_t N, int64_t K, int64_t batch
     const double own = per * (1.0 + s.grows * (double)tiles / (256.0 * (double)r)) * 1e-3 * (double)K;
     const double full = (double)(tiles * s.rows * s.cols) * 2e-6 * (double)K / s.rate;
     us[s.tile] = 7.0 + (own > full ? own : full) + 0.6 * 4.0 * (double)(M * N) / 5.1e6;
+    rounds[s.tile] = r;
     ok[s.tile] = r <= s.rounds && !(gated && s.tile == 7) && !(s.tile == 6 && K < 2048);
   }
+  if ((choice == 1 && rounds[4] > rounds[1]) || (choice == 3 && rounds[4] > 1 && K < 2048)) ok[4] = false;
   int best = choice;
   double limit = 0.97 * us[choice];
   for (int t = 4; t <= 7; ++t)
     if (ok[t] && us[t] < limit) best = t, limit = us[t];
   return best;
+}
+
+// The shape of a product that leaves it to the library. 192 x 192 takes the place of 256 x 128 tiles that all run at once only
+// where it was never the slower one: for weights whose panel has just been written (prepared ones come from memory, and the
+// smaller tiles read them once more: 803 x 8192 x 8192 124 / 136, 696 x 10240 x 8192 126 / 138, 1577 x 4096 x 11008 159 / 162),
+// from six rows of 256 on (836 x 8192 x 28672 571 / 584; 752 x 10240 x 8192 184 / 187), with a long K or a tenth fewer of them
+// than of the others (1805 x 4096 x 14336 ratio 0.88, 1611 x 4096 x 11008 0.94, 1583 x 4096 x 4096 0.98; but 2029 x 4096 x 4096
+// 64 / 66, 3503 x 2048 x 2048 35.2 / 35.6).
+int bf16_tile(int64_t M, int64_t N, int64_t K, int64_t batch, bool gated, bool prepared) {
+  const int choice = bf16_tile_choice(M, N, batch), refined = bf16_tile_refined(choice, M, N, K, batch, gated);
+  const int64_t now = ((M + 255) / 256) * ((N + 127) / 128), then = ((M + 191) / 192) * ((N + 191) / 192);
+  if (choice == 2 && refined == 7 && now <= 256 && (prepared || M <= 1280 || (K < 8192 && 10 * then > 9 * now))) return choice;
+  return refined;
 }
 
 // Columns of the product (rows of B) that are expanded and multiplied at a time; N: all of them at once. A panel of B of two
@@ -625,7 +643,7 @@ hipError_t launch_gemm_bf16_path(int scale_kind, bool asym, int64_t group_size, 
            : scale_kind == kScaleE4M3 ? go.template operator()<kScaleE4M3>()
                                       : go.template operator()<kScaleE8M0Floor>();
   };
-  if (tile == 0) tile = bf16_tile_refined(bf16_tile_choice(M, N, batch), M, N, K, batch, glu);  // (an option overrides it)
+  if (tile == 0) tile = bf16_tile(M, N, K, batch, glu, B_panel != nullptr);  // (an option overrides it)
   const int64_t columns = B_panel ? N : bf16_columns_at_a_time(tile, M, N, K, batch);
   for (int64_t n0 = 0; n0 < N; n0 += columns) {
     const int64_t n = N - n0 < columns ? N - n0 : columns, Npn = columns < N ? round_up(n, kPanelRows) : Np;
