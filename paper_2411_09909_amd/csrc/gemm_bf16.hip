@@ -557,10 +557,15 @@ int bf16_tile_refined(int choice, int64_t M, int64_t N, int64_t K, int64_t batch
 // from six rows of 256 on (836 x 8192 x 28672 571 / 584; 752 x 10240 x 8192 184 / 187), with a long K or a tenth fewer of them
 // than of the others (1805 x 4096 x 14336 ratio 0.88, 1611 x 4096 x 11008 0.94, 1583 x 4096 x 4096 0.98; but 2029 x 4096 x 4096
 // 64 / 66, 3503 x 2048 x 2048 35.2 / 35.6).
-int bf16_tile(int64_t M, int64_t N, int64_t K, int64_t batch, bool gated, bool prepared) {
+// whole_lines: every row of C is whole 128-byte lines, or C is BF16. Stores of rows that are not take longer, and in the larger
+// tiles there is less beside them: 192 x 256 then takes the place of 64 x 256 only with a K beyond 4096 (1323 x 11008 x 4096 167
+// / 183, 2570 x 6144 x 4096 170 / 177;  1124 x 13824 x 5120 ratio 0.93), that of 256 x 128 with one beyond 2048 (1349 x 16384 x
+// 2048 144 / 149).
+int bf16_tile(int64_t M, int64_t N, int64_t K, int64_t batch, bool gated, bool prepared, bool whole_lines) {
   const int choice = bf16_tile_choice(M, N, batch), refined = bf16_tile_refined(choice, M, N, K, batch, gated);
   const int64_t now = ((M + 255) / 256) * ((N + 127) / 128), then = ((M + 191) / 192) * ((N + 191) / 192);
   if (choice == 2 && refined == 7 && now <= 256 && (prepared || M <= 1280 || (K < 8192 && 10 * then > 9 * now))) return choice;
+  if (!whole_lines && refined == 4 && ((choice == 3 && K <= 4096) || (choice == 2 && K <= 2048))) return choice;
   return refined;
 }
 
@@ -643,7 +648,8 @@ hipError_t launch_gemm_bf16_path(int scale_kind, bool asym, int64_t group_size, 
            : scale_kind == kScaleE4M3 ? go.template operator()<kScaleE4M3>()
                                       : go.template operator()<kScaleE8M0Floor>();
   };
-  if (tile == 0) tile = bf16_tile(M, N, K, batch, glu, B_panel != nullptr);  // (an option overrides it)
+  const bool whole_lines = glu || ((reinterpret_cast<uintptr_t>(C) | (uint64_t)ldc * 4) & 127) == 0;
+  if (tile == 0) tile = bf16_tile(M, N, K, batch, glu, B_panel != nullptr, whole_lines);  // (an option overrides it)
   const int64_t columns = B_panel ? N : bf16_columns_at_a_time(tile, M, N, K, batch);
   for (int64_t n0 = 0; n0 < N; n0 += columns) {
     const int64_t n = N - n0 < columns ? N - n0 : columns, Npn = columns < N ? round_up(n, kPanelRows) : Np;

@@ -169,4 +169,13 @@ def test_attention_walks_over_pairs_of_key_tiles(workgroups, Sq, Sk, causal, pai
 def test_tile_that_the_bf16_panel_kernel_runs(M, N, K, gated, prepared, tile):
     """1: 256 x 256, 2: 256 x 128, 3: 64 x 256, 4: 192 x 256, 5: 192 x 128, 6: 128 x 128, 7: 192 x 192. The sizes behind each
     line; in brackets what the shape that stays / the other one takes."""
-    assert rule("_ZN3amx9bf16_tileEllllbb", i32, i64, i64, i64, i64, flag, flag)(M, N, K, 1, bool(gated), bool(prepared)) == tile
+    bf16_tile = rule("_ZN3amx9bf16_tileEllllbbb", i32, i64, i64, i64, i64, flag, flag, flag)
+    assert bf16_tile(M, N, K, 1, bool(gated), bool(prepared), True) == tile
+
+
+@pytest.mark.parametrize("M,N,K,whole,ragged", [
+    (1323, 11008, 4096, 4, 3), (2570, 6144, 4096, 4, 3), (1124, 13824, 5120, 4, 4),  # 167 / 183 us, 170 / 177, ratio 0.93
+    (1349, 16384, 2048, 4, 2), (1498, 11008, 4096, 4, 4)])                           # 144 / 149, 0.94 to 1.02
+def test_tile_where_rows_of_c_are_no_whole_lines(M, N, K, whole, ragged):
+    bf16_tile = rule("_ZN3amx9bf16_tileEllllbbb", i32, i64, i64, i64, i64, flag, flag, flag)
+    assert [bf16_tile(M, N, K, 1, False, False, w) for w in (True, False)] == [whole, ragged]
