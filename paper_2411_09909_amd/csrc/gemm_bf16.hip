@@ -571,21 +571,35 @@ int bf16_tile(int64_t M, int64_t N, int64_t K, int64_t batch, bool gated, bool p
 
 // Columns of the product (rows of B) that are expanded and multiplied at a time; N: all of them at once. A panel of B of two
 // thirds of the last-level cache (256 MB) or more does not stay there until it is read: it is written to memory and read back
-// from it. Cut into pieces that go through the same workspace one after the other, it stays. A piece is whole rounds of
-// tiles, so that the pieces take no more rounds than the whole, as many as fit into 144 MB, or else into 280 MB (not for up to four
-// rows of tiles: 800 x 28672 x 8192 483 / 488). Us per call on
-// three sets of buffers in turn, AMXFP4-E5M2, whole / in pieces: 4096 x 28672 x 8192 (448 MB, four pieces) 1437 / 1392, 2048
-// of these rows 870 / 824, 1192 (two pieces of 256 MB) 786 / 634; 1504 x 28672 x 4096 (224 MB) 357 / 343, 3094 rows 694 / 615,
-// 1087 rows 326 / 278; 736 x 22016 x 4096 (172 MB) 216 / 201. Smaller panels stay whole (3000 x 10240 x 8192, 160 MB, 406 / 413;
-// 3618 x 8192 x 8192, 128 MB, 396 / 409), and so do rows of C that are no whole lines, whose stores end the pieces late (2396
-// x 32001 x 4096 675 / 711). Each output's sum is the same.
-int64_t bf16_columns_at_a_time(int tile, int64_t M, int64_t N, int64_t K, int64_t batch) {
+// from it. Cut into pieces that go through the same workspace one after the other, more of it stays. A piece is whole rounds of
+// tiles, so that the pieces take no more rounds than the whole, as many as fit into 144 MB, or else into 280 MB (not for up to
+// four rows of tiles: 800 x 28672 x 8192 483 / 488). whole_lines: every row of C is whole 128-byte lines, or C is BF16. Us per
+// call on three sets of buffers in turn, AMXFP4-E5M2, whole / in pieces: 4096 x 28672 x 8192 (448 MB, three pieces of 128 and one
+// of 64) 1437 / 1392, 2048 of these rows 870 / 824; 1504 x 28672 x 4096 (224 MB) 352 / 326, 3094 rows 693 / 604; 736 x 22016 x
+// 4096 (172 MB) 216 / 201. Five rows of tiles gain most (1192 x 28672 x 8192, pieces of 204, 204 and 40 MB, 783 / 624; 1200 x
+// 28672 x 4096 404 / 321), but by their order: the uncut grid of 5 x 112 is dealt in supertiles, whose every XCD leaves three
+// rows of eight empty, and in equal runs it takes 637 and 328.
+// Every piece ends in a round of stores that nothing overlaps. Whole therefore stay, ratio in pieces / whole over 2846 sizes of
+// 520 to 4096 rows (a row of tiles: 256):
+//   panels up to 200 MB beyond five rows of tiles (22016 x 4096 1.02 to 1.06; up to there 0.89 to 0.95), but for those near it
+//     with a K of 6144 or more (16384 x 6144 0.94 to 1.01, 12288 x 8192 0.92 to 1.00); below 170 MB 0.98 to 1.02
+//   products whose last round has hardly any tiles, which overlaps the one before it unless it is a piece of its own (beyond five
+//     rows of tiles: 26624 x 4096, 10 x 104 tiles, 1.07;  12288 x 8192, 12 x 48, 1.05;  27648 x 5120, 12 x 108, 1.02)
+//   rows of an FP32 C that are no whole lines, whose stores take longer: 28672 x 4096 1.03 to 1.10 at six to twelve rows of tiles,
+//     32000 x 4096 1.00 to 1.08, 32001 x 4096 at four rows 1.02 to 1.04; except, for panels of 200 MB and more, three rows and five
+//     (0.84 to 1.02) and a K of 8192 (14336 x 8192 0.90 to 1.03, 28672 x 8192 0.84 to 1.02)
+// Each output's sum is the same.
+int64_t bf16_columns_at_a_time(int tile, int64_t M, int64_t N, int64_t K, int64_t batch, bool whole_lines) {
   const int64_t rows = tile == 4 ? 192 : 256, tiles_m = (M + rows - 1) / rows, tiles_n = (N + 255) / 256;
   const int64_t column_bytes = 256 * round_up(K, kPanelK) * 2;  // of the panel, per column of tiles
-  if (batch != 1 || (tile != 1 && tile != 4) || N % 32 != 0 || tiles_n * column_bytes < (int64_t(170) << 20)) return N;
+  const int64_t panel = tiles_n * column_bytes, mb = int64_t(1) << 20, large_m = (M + 255) / 256;
+  if (batch != 1 || (tile != 1 && tile != 4) || panel < 170 * mb) return N;
+  if (panel < 200 * mb && large_m > 5 && (panel < 190 * mb || K < 6144)) return N;
+  if (large_m > 5 && (tiles_m * tiles_n - 1) % 256 < 64) return N;
+  if (!whole_lines && (panel < 200 * mb || (large_m > 3 && large_m != 5 && K < 8192))) return N;
   const int64_t rounds = (tiles_m * tiles_n + 255) / 256;
-  for (int64_t most : {int64_t(144) << 20, int64_t(280) << 20}) {
-    if (most > (int64_t(144) << 20) && tiles_m < 5) break;
+  for (int64_t most : {144 * mb, 280 * mb}) {
+    if (most > 144 * mb && tiles_m < 5) break;
     int64_t best = 0;
     for (int64_t k = 1; k < rounds; ++k) {
       const int64_t cols = 256 * k / tiles_m;  // columns of tiles in k rounds
@@ -650,7 +664,7 @@ hipError_t launch_gemm_bf16_path(int scale_kind, bool asym, int64_t group_size, 
   };
   const bool whole_lines = glu || ((reinterpret_cast<uintptr_t>(C) | (uint64_t)ldc * 4) & 127) == 0;
   if (tile == 0) tile = bf16_tile(M, N, K, batch, glu, B_panel != nullptr, whole_lines);  // (an option overrides it)
-  const int64_t columns = B_panel ? N : bf16_columns_at_a_time(tile, M, N, K, batch);
+  const int64_t columns = B_panel ? N : bf16_columns_at_a_time(tile, M, N, K, batch, whole_lines);
   for (int64_t n0 = 0; n0 < N; n0 += columns) {
     const int64_t n = N - n0 < columns ? N - n0 : columns, Npn = columns < N ? round_up(n, kPanelRows) : Np;
     if ((e = expand(n0 == 0, !B_panel, n0, n)) != hipSuccess) return e;

@@ -60,12 +60,12 @@ def test_tiles_between_the_three_large_ones(M, N, K, tile):
     assert torch.equal(got.double(), a @ b.T)
 
 
-@pytest.mark.parametrize("M,N,K", [(1100, 28672, 4096), (1290, 24640, 4096)])
+@pytest.mark.parametrize("M,N,K", [(1100, 28672, 4096), (1290, 26688, 4096)])
 def test_wide_weights_in_pieces(M, N, K):
     """B's panel goes through the workspace in pieces (the last one shorter): the exact product, and bit for bit what prepared
     weights give, whose panel is whole; the gated product likewise."""
-    from tests.test_routes import i32, i64, rule
-    at_a_time = rule("_ZN3amx22bf16_columns_at_a_timeEillll", i64, i32, i64, i64, i64, i64)(1, M, N, K, 1)
+    from tests.test_routes import i32, i64, flag, rule
+    at_a_time = rule("_ZN3amx22bf16_columns_at_a_timeEillllb", i64, i32, i64, i64, i64, i64, flag)(1, M, N, K, 1, True)
     assert at_a_time < N and N % at_a_time != 0
     ac, as_, a = operand(M, K, 0x3C, 1, 5)
     bc, bs, b = operand(N, K, 0x3C, 1, 6)

@@ -179,3 +179,16 @@ def test_tile_that_the_bf16_panel_kernel_runs(M, N, K, gated, prepared, tile):
 def test_tile_where_rows_of_c_are_no_whole_lines(M, N, K, whole, ragged):
     bf16_tile = rule("_ZN3amx9bf16_tileEllllbbb", i32, i64, i64, i64, i64, flag, flag, flag)
     assert [bf16_tile(M, N, K, 1, False, False, w) for w in (True, False)] == [whole, ragged]
+
+
+@pytest.mark.parametrize("M,N,K,lines,cut", [
+    (4096, 28672, 8192, 1, 8192), (1192, 28672, 8192, 1, 13056), (1504, 28672, 4096, 1, 10752),
+    (3000, 10240, 8192, 1, 0),                              # 160 MB: 406 / 413 us
+    (2546, 22016, 4096, 1, 0), (1563, 22016, 4096, 1, 0),   # 172 MB, more than five rows of tiles: 388 / 408, gated 286 / 300
+    (2400, 26624, 4096, 1, 0), (2900, 27648, 5120, 1, 0),   # a last round of hardly any tiles: ratios 1.07, 1.02
+    (2400, 28672, 4096, 0, 0), (1504, 28672, 4096, 0, 0),   # rows of C that are no whole lines: 613 / 642, 426 / 437
+    (973, 32001, 4096, 0, 0), (2048, 28672, 8192, 0, 8192)])  # 341 / 353, 976 / 931
+def test_columns_whose_weights_are_expanded_at_a_time(M, N, K, lines, cut):
+    """Whole / in pieces (0: whole) on tiles of 256 x 256."""
+    at_a_time = rule("_ZN3amx22bf16_columns_at_a_timeEillllb", i64, i32, i64, i64, i64, i64, flag)(1, M, N, K, 1, bool(lines))
+    assert at_a_time == (cut or N)
