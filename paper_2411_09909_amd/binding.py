@@ -123,7 +123,7 @@ def load():
                        ("amxfp4_rmsnorm_quantize", [fp, vp, vp, vp, vp, i64, i64, f32, vp, vp, vp])):
         getattr(L, name).argtypes = args
         getattr(L, name).restype = ctypes.c_int
-    calls.bind(*(ctypes.cast(getattr(L, name), vp).value for name in calls.entries))
+    calls.bind(AmxFormat, *(ctypes.cast(getattr(L, name), vp).value for name in calls.entries))
     _lib, _calls = L, calls
     return L
 

@@ -55,8 +55,11 @@ const at::Tensor* pair(PyObject* o) {
   return t && t->scalar_type() == at::kFloat && t->numel() >= 2 && t->is_contiguous() ? t : nullptr;
 }
 
-// The format, out of its ctypes structure.
+// The format, out of its ctypes structure (the class given to bind(), or one derived from it: other structures and bytes of the
+// same size are no formats).
+PyTypeObject* format_type = nullptr;
 bool format(PyObject* o, amx_format_t& f) {
+  if (!format_type || !PyObject_TypeCheck(o, format_type)) return false;
   Py_buffer view;
   if (PyObject_GetBuffer(o, &view, PyBUF_SIMPLE) != 0) {
     PyErr_Clear();
@@ -228,15 +231,20 @@ PyObject* attention_decode(PyObject*, PyObject* const* args, Py_ssize_t n) try {
   Py_RETURN_NONE;
 }
 
-// bind(address of each of `entries`)
+// bind(class of the formats, address of each of `entries`)
 PyObject* bind(PyObject*, PyObject* const* args, Py_ssize_t n) {
   void* address[kNumEntries];
-  if (n != (Py_ssize_t)kNumEntries) return PyErr_Format(PyExc_TypeError, "bind: %zu addresses", kNumEntries);
+  if (n != (Py_ssize_t)kNumEntries + 1 || !PyType_Check(args[0]))
+    return PyErr_Format(PyExc_TypeError, "bind: a class and %zu addresses", kNumEntries);
   for (size_t i = 0; i < kNumEntries; ++i) {
-    address[i] = PyLong_AsVoidPtr(args[i]);
+    address[i] = PyLong_AsVoidPtr(args[i + 1]);
     if (!address[i]) return PyErr_Occurred() ? nullptr : PyErr_Format(PyExc_ValueError, "bind: %s is null", kEntries[i]);
   }
   memcpy(&entry, address, sizeof(address));
+  Py_INCREF(args[0]);
+  PyTypeObject* before = format_type;
+  format_type = reinterpret_cast<PyTypeObject*>(args[0]);
+  Py_XDECREF(before);
   Py_RETURN_NONE;
 }
 

@@ -1,5 +1,7 @@
 """The native way of the calls that are given all their buffers (csrc/calls.cpp): the same results as the general way, which
 allocates them, on the current stream, and the same refusals."""
+import ctypes
+
 import pytest
 import torch
 
@@ -123,3 +125,21 @@ def test_refusals_stay():
         binding.gemm(FMT, *q, *q, out=out, workspace=ws, a_pair=torch.ones(2, device="cuda"))
     with pytest.raises(binding.AmxError, match="workspace of [0-9]+ bytes needed, 0 given"):
         binding.gemm(FMT, *q, *q, out=out, workspace=ws)
+
+
+@pytest.mark.parametrize("other", [bytes(FMT), binding.gemm_options(e5m2_kernel=32, tile=2, few_rows=1)], ids=["bytes", "options"])
+def test_only_a_format_is_a_format(other):
+    """Four 32-bit numbers, the same bytes as a format's (both of these would be valid ones), are refused like any other type."""
+    assert bytes(other) == bytes(FMT)
+    x = randn(64, 96)
+    q = binding.quantize(FMT, x)
+    ws = torch.empty(1 << 24, dtype=torch.uint8, device="cuda")
+    with pytest.raises(AttributeError):
+        binding.quantize(other, x, **like(q))
+    with pytest.raises(AttributeError):
+        binding.quantize_batched(other, x[None], codes=q[0][None], scales=q[1][None])
+    with pytest.raises((TypeError, ctypes.ArgumentError)):
+        binding.gemm(other, *q, *q, out=torch.empty(64, 64, device="cuda"), workspace=ws)
+    derived = type("Derived", (binding.AmxFormat,), {})(*(getattr(FMT, name) for name, _ in FMT._fields_))
+    out = like(q)
+    assert same(binding.quantize(derived, x, **out), q)
