@@ -7,6 +7,7 @@ the library's kernels. There is no fallback: if the library has not been built, 
 """
 import ctypes
 import os
+import threading
 
 import torch
 
@@ -32,13 +33,19 @@ class AmxError(RuntimeError):
 
 _lib = None
 _calls = None  # the module between torch's tensors and the library, bound to it by load()
+_loading = threading.Lock()
 
 
 def load():
     """Loads the built library (does not compile it) and declares the signatures of include/amxfp4.h."""
-    global _lib, _calls
     if _lib is not None:
         return _lib
+    with _loading:  # (one thread binds the native module)
+        return _load() if _lib is None else _lib
+
+
+def _load():
+    global _lib, _calls
     if not os.path.exists(LIB_PATH):
         raise AmxError("libamxfp4.so is not built: run `python -m paper_2411_09909_amd.build` (needs hipcc)")
     try:
@@ -124,7 +131,8 @@ def load():
         getattr(L, name).argtypes = args
         getattr(L, name).restype = ctypes.c_int
     calls.bind(AmxFormat, *(ctypes.cast(getattr(L, name), vp).value for name in calls.entries))
-    _lib, _calls = L, calls
+    _calls = calls  # first: who finds the library loaded finds the module too
+    _lib = L
     return L
 
 

@@ -3,6 +3,7 @@ rejects bad arguments before anything is launched."""
 import ctypes
 import os
 import re
+import sys
 
 import pytest
 
@@ -271,3 +272,24 @@ def test_attention_rejects_bad_arguments(lib):
     need = lib.amxfp4_attention_workspace_bytes(ctypes.byref(ok), 4, 2, 50, 96, 128)
     assert need == (4 * 64 + 2 * 96 + 2 * 128) * 128 * 2   # Q rows padded to 32, V keys padded to 64
     assert lib.amxfp4_attention_workspace_bytes(ctypes.byref(ok), 4, 2, 50, 96, 32) == 0
+
+
+def test_who_finds_the_library_loaded_finds_the_native_module(lib, monkeypatch):
+    """A second thread may look between any two steps of load(): the library must not be there without the module."""
+    monkeypatch.setattr(binding, "_lib", None)
+    monkeypatch.setattr(binding, "_calls", None)
+    seen = set()
+
+    def each_step(frame, event, arg):
+        frame.f_trace_opcodes = True
+        if frame.f_globals.get("__name__") == binding.__name__:
+            seen.add((binding._lib is not None, binding._calls is not None))
+        return each_step
+
+    before = sys.gettrace()
+    sys.settrace(each_step)
+    try:
+        binding.load()
+    finally:
+        sys.settrace(before)
+    assert (False, False) in seen and (True, True) in seen and (True, False) not in seen
