@@ -3,11 +3,13 @@ torch CUDA tensors. The calls of a serving loop, with all their buffers given, g
 (csrc/calls.cpp: a cast of one row 4.8 -> 3.3 us of host time); it leaves whatever it does not take to the code here.
 
 Only argument marshalling happens here (pointers, sizes, the current HIP stream); every step of the path runs in
-the library's kernels. There is no fallback: if the library has not been built, or no GPU is present, calls raise.
+the library's kernels. There is no fallback: if the library has not been built, or no GPU is present, calls raise. (Without
+the native module, or with one compiled for another torch, all calls go through the code here.)
 """
 import ctypes
 import os
 import threading
+import warnings
 
 import torch
 
@@ -48,10 +50,6 @@ def _load():
     global _lib, _calls
     if not os.path.exists(LIB_PATH):
         raise AmxError("libamxfp4.so is not built: run `python -m paper_2411_09909_amd.build` (needs hipcc)")
-    try:
-        from . import _calls as calls
-    except ImportError as e:
-        raise AmxError("_calls.so is not built for this torch: run `python -m paper_2411_09909_amd.build` (%s)" % e)
     L = ctypes.CDLL(LIB_PATH)
     i64, vp, fp = ctypes.c_int64, ctypes.c_void_p, ctypes.POINTER(AmxFormat)
     L.amxfp4_last_error.restype = ctypes.c_char_p
@@ -130,10 +128,31 @@ def _load():
                        ("amxfp4_rmsnorm_quantize", [fp, vp, vp, vp, vp, i64, i64, f32, vp, vp, vp])):
         getattr(L, name).argtypes = args
         getattr(L, name).restype = ctypes.c_int
-    calls.bind(AmxFormat, *(ctypes.cast(getattr(L, name), vp).value for name in calls.entries))
-    _calls = calls  # first: who finds the library loaded finds the module too
+    _calls = _native_calls(L)  # first: who finds the library loaded finds the module too
     _lib = L
     return L
+
+
+class _GeneralWay:
+    """In the place of the native module where it cannot be used: takes no call."""
+    def __getattr__(self, name):
+        return lambda *args: None
+
+
+def _native_calls(L):
+    """The native module, bound to the library's entry points. It reads torch's tensors where they lie, so it serves only the
+    torch that it was compiled against (the library itself knows nothing of torch)."""
+    try:
+        from . import _calls as calls
+        compiled_for = getattr(calls, "torch_version", "of old")
+        if compiled_for != torch.__version__:
+            raise ImportError("compiled for torch %s, not %s" % (compiled_for, torch.__version__))
+    except ImportError as e:
+        warnings.warn("_calls.so cannot be used, calls go through ctypes; `python -m paper_2411_09909_amd.build` builds it (%s)" % e,
+                      RuntimeWarning, stacklevel=4)
+        return _GeneralWay()
+    calls.bind(AmxFormat, *(ctypes.cast(getattr(L, name), ctypes.c_void_p).value for name in calls.entries))
+    return calls
 
 
 def _check(rc):

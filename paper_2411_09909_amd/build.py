@@ -87,10 +87,13 @@ def build(verbose=True):
 
 
 def _start_calls():
-    """Starts the host compiler on the module between torch's tensors and the C ABI (no GPU code in it)."""
+    """Starts the host compiler on the module between torch's tensors and the C ABI (no GPU code in it), for this torch."""
+    import torch
     from torch.utils import cpp_extension
     lib = os.path.join(os.path.dirname(cpp_extension.__file__), os.pardir, "lib")
-    return subprocess.Popen(["g++", "-O2", "-std=c++17", "-shared", "-fPIC", "-Wall", "-D__HIP_PLATFORM_AMD__", os.path.join(CSRC, "calls.cpp"), "-o", CALLS,
+    return subprocess.Popen(["g++", "-O2", "-std=c++17", "-shared", "-fPIC", "-Wall", "-D__HIP_PLATFORM_AMD__",
+                             "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch.compiled_with_cxx11_abi(),
+                             "-DAMX_TORCH_VERSION=\"%s\"" % torch.__version__, os.path.join(CSRC, "calls.cpp"), "-o", CALLS,
                              "-I" + sysconfig.get_path("include")] + ["-isystem" + p for p in cpp_extension.include_paths("cuda")]
                             + ["-L" + os.path.normpath(lib), "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip"])
 

@@ -260,5 +260,6 @@ PyMODINIT_FUNC PyInit__calls() {
   PyObject* names = m ? PyTuple_New(kNumEntries) : nullptr;
   for (size_t i = 0; names && i < kNumEntries; ++i) PyTuple_SET_ITEM(names, i, PyUnicode_FromString(kEntries[i]));
   if (!names || PyModule_AddObject(m, "entries", names) != 0) return nullptr;
+  if (PyModule_AddStringConstant(m, "torch_version", AMX_TORCH_VERSION) != 0) return nullptr;  // binding.py asks before bind()
   return m;
 }

@@ -6,7 +6,9 @@ import re
 import sys
 
 import pytest
+import torch
 
+import paper_2411_09909_amd
 from paper_2411_09909_amd import binding
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
@@ -293,3 +295,24 @@ def test_who_finds_the_library_loaded_finds_the_native_module(lib, monkeypatch):
     finally:
         sys.settrace(before)
     assert (False, False) in seen and (True, True) in seen and (True, False) not in seen
+
+
+@pytest.mark.parametrize("why", ["missing", "another torch"])
+def test_without_a_usable_native_module_calls_go_the_general_way(lib, monkeypatch, why):
+    """The library has no need of it; a module compiled for another torch would read its tensors by the wrong layout."""
+    calls = binding._calls
+    assert calls.torch_version == torch.__version__
+    monkeypatch.setattr(binding, "_lib", None)
+    monkeypatch.setattr(binding, "_calls", None)
+    if why == "missing":
+        monkeypatch.delattr(paper_2411_09909_amd, "_calls")
+        monkeypatch.setitem(sys.modules, "paper_2411_09909_amd._calls", None)
+    else:
+        monkeypatch.setattr(torch, "__version__", "2.0.0")
+    with pytest.warns(RuntimeWarning, match="_calls.so cannot be used"):
+        assert binding.load().amxfp4_last_error
+    assert binding._calls is not calls
+    assert all(getattr(binding._calls, name)(1, 2) is None for name in ("quantize", "gemm", "attention_decode"))
+    x = torch.zeros(32, 64, dtype=torch.bfloat16)
+    with pytest.raises(binding.AmxError, match="device memory only"):
+        binding.quantize(binding.make_format(), x, codes=torch.zeros(32, 32, dtype=torch.uint8), scales=torch.zeros(32, 4, dtype=torch.uint8))
