@@ -94,10 +94,14 @@ __global__ __launch_bounds__(64 * kAttnWaves) __attribute__((amdgpu_waves_per_eu
   constexpr int kLoads = (kAttnKFrags + kAttnVFrags) / kAttnWaves;  // of a wave and key tile
   constexpr uint32_t kPast = 0x80000000u;
   const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_ptr_t)lds;
+  // (m0 is a reserved register: that the compiler does not keep it across the statement, of which it warns, is what is meant)
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"
   auto load_fragment = [&](const u32x4& window, uint32_t to, uint32_t offset) {
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
-                 :: "s"(to), "v"(lane_off), "s"(window), "s"(offset) : "memory");
+                 :: "s"(to), "v"(lane_off), "s"(window), "s"(offset) : "memory", "m0");
   };
+#pragma clang diagnostic pop
   auto load_k = [&](int tile, uint32_t to, int i, uint32_t past) {  // number i of this wave's; a pair's two tiles are adjacent
     const int f = wave + kAttnWaves * i;
     load_fragment(Kr, to + f * kFragBytes, past | (uint32_t)((tile * kAttnKFrags + f) * kFragBytes));

@@ -1,5 +1,7 @@
 """The build refuses kernels whose vector registers spill."""
+import glob
 import os
+import re
 import subprocess
 
 import pytest
@@ -59,3 +61,10 @@ def test_the_attention_stores_its_rows_without_an_exchange_for_each(tmp_path):
         elif "ds_bpermute_b32" in line:
             count[name] = count.get(name, 0) + 1
     assert len(count) == 8 and max(count.values()) <= 4
+
+
+def test_inline_assembly_names_the_m0_it_writes():
+    """The compiler keeps values in m0 (the address of a direct-to-LDS load, an index): a statement that writes it must say so."""
+    statements = [m.group(0) for f in glob.glob(os.path.join(build.CSRC, "*")) for m in re.finditer(r"asm volatile\([^;]*?\);", open(f).read(), re.S)]
+    writing = [s for s in statements if re.search(r"s_mov_b32 m0", s)]
+    assert writing and all('"m0"' in s.rsplit(":", 1)[1] for s in writing)
