@@ -1,5 +1,5 @@
 """Output bounds: every GEMM kernel of the library, on shapes with partial tiles, writes C[b][i][j] for i < M, j < N and
-nothing else. C is a window of a larger buffer filled with a bit pattern (a NaN payload no kernel produces): leading
+nothing else, and the attention kernels write their output and nothing else. C is a window of a larger buffer filled with a bit pattern (a NaN payload no kernel produces): leading
 dimension ldc > N, guard words in front of the first row and behind the last one. After the call the window must match
 the oracle and every other word must still hold the pattern, bit for bit."""
 import numpy as np
@@ -145,3 +145,64 @@ def gated_window(M, width, K, pad, scale, asym):
     torch.cuda.synchronize()
     assert torch.equal(window[0].contiguous().view(torch.int16), plain.view(torch.int16))
     return a, wg, wu, window
+
+
+@pytest.mark.parametrize("M,N,K,tile", [(1290, 8001, 384, 4), (300, 16001, 128, 5), (257, 8191, 4096, 6), (700, 11001, 128, 7)])
+@pytest.mark.parametrize("pad", [37, 63])
+def test_tiles_that_only_the_rule_picks_write_only_their_window(M, N, K, tile, pad):
+    from tests.test_gpu_tile_order import operand, tile_of
+    assert tile_of(M, N, K, whole_lines=False) == tile
+    ac, as_, a = operand(M, K, 0x3C, 1, 3)
+    bc, bs, b = operand(N, K, 0x3C, 1, 4)
+    buf, window, allowed, pattern = canary_window(1, M, N, pad)
+    binding.gemm(binding.make_format(ref.FP8_E5M2, 1, 32), ac, as_, bc, bs, out=window[0], options=binding.gemm_options(few_rows=-1))
+    assert_padding_untouched(buf, allowed, pattern, "tile %d" % tile)
+    assert torch.equal(window[0].double(), a @ b.T)
+
+
+@pytest.mark.parametrize("M,N,K,pad", [(1100, 28672, 4096, 32), (1100, 28672, 4096, 5), (1290, 26688, 4096, 32)])
+def test_weights_in_pieces_write_only_their_window(M, N, K, pad):
+    """A pitch of whole lines, and of five rows of tiles any."""
+    from tests.test_gpu_tile_order import operand
+    from tests.test_routes import i32, i64, flag, rule
+    assert rule("_ZN3amx22bf16_columns_at_a_timeEillllb", i64, i32, i64, i64, i64, i64, flag)(1, M, N, K, 1, pad % 32 == 0) < N
+    ac, as_, a = operand(M, K, 0x3C, 1, 5)
+    bc, bs, b = operand(N, K, 0x3C, 1, 6)
+    buf, window, allowed, pattern = canary_window(1, M, N, pad)
+    binding.gemm(binding.make_format(ref.FP8_E5M2, 1, 32), ac, as_, bc, bs, out=window[0], options=binding.gemm_options(few_rows=-1, tile="256x256"))
+    assert_padding_untouched(buf, allowed, pattern, "pieces")
+    for n0 in range(0, N, 4096):
+        assert torch.equal(window[0][:, n0:n0 + 4096].double(), a @ b[n0:n0 + 4096].T)
+
+
+@pytest.mark.parametrize("M", [1, 16, 19, 32])
+def test_48_columns_to_a_workgroup_write_only_their_window(M):
+    """(9001 columns: the last workgroup has 25)"""
+    from tests.test_gpu_tile_order import operand
+    ac, as_, a = operand(M, 512, 0x3C, 1, 3)
+    bc, bs, b = operand(9001, 512, 0x3C, 1, 4)
+    buf, window, allowed, pattern = canary_window(1, M, 9001, 37)
+    binding.gemm(binding.make_format(ref.FP8_E5M2, 1, 32), ac, as_, bc, bs, out=window[0])
+    assert_padding_untouched(buf, allowed, pattern, "48 columns")
+    assert torch.equal(window[0].double(), a @ b.T)
+
+
+@pytest.mark.parametrize("merged", [False, True])
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("heads,Sq,Sk", [(3, 1, 64), (4, 33, 96), (8, 130, 320), (3, 161, 352), (720, 70, 160)])
+def test_attention_writes_only_its_output(heads, Sq, Sk, D, merged):
+    """The last rows of a wave's 32 queries lie past Sq: dropped by the window of the stores (heads of 128) or skipped. Guard words
+    in front of the output and behind it; one head at a time gives the same rows, so no head wrote into another's."""
+    fmt, gen = binding.make_format(ref.FP8_E5M2, 1, 32), torch.Generator("cuda").manual_seed(Sq)
+    q, k, v = (torch.randn((n, s, D), generator=gen, device="cuda").to(torch.bfloat16) for n, s in ((heads, Sq), (heads, Sk), (heads, Sk)))
+    ops = [binding.quantize_batched(fmt, q), binding.quantize_batched(fmt, k), binding.quantize_batched(fmt, v, k_axis=1)]
+    dtype, pattern = (torch.bfloat16, 0x7FC5) if merged else (torch.float32, CANARY)
+    buf = torch.full((2 * GUARD + heads * Sq * D,), pattern, dtype=torch.int16 if merged else torch.int32, device="cuda")
+    body = buf[GUARD:GUARD + heads * Sq * D]
+    out = body.view(dtype).view((Sq, heads * D) if merged else (heads, Sq, D))
+    binding.attention(fmt, *ops[0], *ops[1], *ops[2], D ** -0.5, True, out=out, merged=merged)
+    torch.cuda.synchronize()
+    assert (buf[:GUARD] == pattern).all() and (buf[GUARD + heads * Sq * D:] == pattern).all() and (body != pattern).all()
+    for h in {0, 1, heads // 2, heads - 1}:
+        one = binding.attention(fmt, *(t[h:h + 1].contiguous() for pair in ops for t in pair), D ** -0.5, True, merged=merged)
+        assert torch.equal(out.view(Sq, heads, D)[:, h] if merged else out[h], one if merged else one[0])
