@@ -1,16 +1,18 @@
-// The per-tile step of the fused quantized attention that both of its kernels share (attention.hip: many queries, K and
-// V tiles through LDS; attention_decode.hip: few queries, K and V dequantized in registers): the scores of one tile of
-// 32 keys, in the 32x32 accumulator layout of S^T[key, query], become un-normalised probabilities against the running
-// row maximum (online softmax), and the 32 probabilities of each query are cast as ONE group (the operands' element and
-// scale format) and returned dequantized, as the BF16 B operand of the second product.
+// The per-tile step of the fused quantized attention that its kernels share (attention.hip and attention_64.hip: many queries,
+// K and V tiles through LDS, heads of 128 and of 64; attention_decode.hip: few queries, K and V dequantized in registers): the
+// scores of one tile of 32 keys, in the 32x32 accumulator layout of S^T[key, query], become un-normalised probabilities against
+// the running row maximum (online softmax), and the 32 probabilities of each query are cast as ONE group (the operands' element
+// and scale format) and returned dequantized, as an operand of the second product.
 //
 // Accumulator layout: lane l holds column l % 32 (one query) and rows 8c + 4(l / 32) + r (c, r = 0..3) in register
 // 4c + r, so all 32 keys of a query sit in the two lanes l and l ^ 32: the row maximum, the row sum and the group
-// maximum of the cast are 16 in-lane steps and one exchange, and registers 8j .. 8j+7, converted to BF16, are the B
-// operand of k-step j of P^T's product with V^T staged in that key order.
+// maximum of the cast are 16 in-lane steps and one exchange, and registers 8j .. 8j+7, converted to 16 bits, are the operand of
+// k-step j of the second product, with V^T staged in that key order: A of P.V (attention.hip) or B of V^T.P^T (the others).
 //
 // It is a statement macro, not a function: as an inlined function the same arithmetic compiled to a different
-// schedule of the many-queries kernel, 7 % slower (0.735 -> 0.787 ms at 32 / 8 heads x 8192).
+// schedule of the many-queries kernel, 7 % slower (0.735 -> 0.787 ms at 32 / 8 heads x 8192). The walk over pairs of key tiles in
+// attention.hip has the first two parts written out for two tiles at a time; the two must stay the same arithmetic (a test
+// compares their bits).
 #pragma once
 #include "cast_math.h"
 #include "gemm_common.h"

@@ -614,9 +614,10 @@ int64_t bf16_columns_at_a_time(int tile, int64_t M, int64_t N, int64_t K, int64_
 
 // Estimate of a call that expands both operands, us, up to some 800 rows: B's expansion at the copy rate, and the rounds
 // of tiles at the rate of a lone tile (256 x 256 14 ns per unit of K, 256 x 128 9.3, 64 x 256 6.6 to 8 as they fill the
-// chip) or the chip's, and half of the store of C, c_bytes per element of M x N. Measured / estimated: 512 x 4096 x 4096
-// 44 / 44, 512 x 11008 x 4096 66 / 68, 768 x 8192 x 8192 121 / 124, 512 x 13824 x 5120 95 / 102, 512 x 4096 x 11008 106 /
-// 109, 448 x 4544 x 4544 50 / 50.
+// chip) or the chip's, and half of the store of C, c_bytes per element of M x N. It prices the shape of bf16_tile_choice(), not
+// the one between those three that most of these sizes run on. Measured (the same buffers again and again, on that one) /
+// estimated: 512 x 4096 x 4096 42 / 44, 512 x 11008 x 4096 65 / 68, 768 x 8192 x 8192 113 / 124, 512 x 13824 x 5120 92 / 102, 512 x
+// 4096 x 11008 101 / 109, 448 x 4544 x 4544 48 / 50; with weights that come from memory 39, 69, 150, 127, 114 and 47.
 double bf16_path_us(int64_t M, int64_t N, int64_t K, double c_bytes) {
   const int tile = bf16_tile_choice(M, N, 1);
   const int64_t tile_m = tile == 3 ? 64 : 256, tile_n = tile == 2 ? 128 : 256;

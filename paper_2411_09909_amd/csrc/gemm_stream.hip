@@ -78,11 +78,14 @@ static bool batch_few_rows(int64_t M, int64_t N, int64_t K, int64_t batch) {
 //     x 8192 45 / 35;  256 x 5120 x 13824 74 / 70;  256 x 32001 x 4096 99 / 83), always with symmetric scales (256 x 32001 x
 //     4096 73 / 78). Asymmetric power-of-two scales end here (prepared weights beyond 256 rows are their FP6 panel alone);
 //   up to 512 rows, and to 768 rows with a long K or few columns: where the estimate is below that of the panels, B's
-//     expansion included (512 x 4096 x 4096 27 / 44;  512 x 4096 x 11008 63 / 106;  448 x 11008 x 4096 62 / 65, but 512 rows
-//     73 / 66;  640 x 8192 x 8192 110 / 116, but 768 rows 133 / 121;  448 x 4544 x 4544 43 / 50, but 512 rows 58 / 51).
+//     expansion included (512 x 4096 x 4096 27 / 42;  512 x 4096 x 11008 64 / 101;  448 x 11008 x 4096 61 / 64, but 512 rows
+//     73 / 65;  448 x 4544 x 4544 43 / 48, but 512 rows 58 / 48;  with the same buffers again and again 640 x 8192 x 8192 113 /
+//     109, 768 rows 138 / 113, 512 x 13824 x 5120 102 / 92, and on three sets of them in turn, whose weights come from memory,
+//     115 / 148, 137 / 150, 103 / 127: the line lies between the two).
 //     A product on prepared weights comes here with the plain one, whose bits it promises, although it would save the
-//     expansion: that costs it 1 us at 384-512 x 6144 x 4096 and 320-448 x 4544 x 4544 (37 / 36 and 42 / 41, the plain calls
-//     37 / 47 and 42 / 50), and where several rounds are taken (384 x 11008 x 4096: 60 / 45, plain 60 / 64) more.
+//     expansion: that costs it 4 to 6 us at 384-512 x 6144 x 4096 and 320-448 x 4544 x 4544 (37-39 / 31-34 and 42-43 / 37-39, the
+//     plain calls 37-39 / 42-45 and 42-43 / 47-48), and where several rounds are taken (384 x 11008 x 4096: 60 / 39-57, plain 60 /
+//     58-62) more.
 // c_bytes: of the output per element of M x N.
 static bool stream_preferred(int scale_kind, bool asym, int64_t group_size, bool scaled, int64_t M, int64_t N, int64_t K,
                              int64_t batch, double c_bytes) {
