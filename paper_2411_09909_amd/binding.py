@@ -50,6 +50,10 @@ def _load():
     global _lib, _calls
     if not os.path.exists(LIB_PATH):
         raise AmxError("libamxfp4.so is not built: run `python -m paper_2411_09909_amd.build` (needs hipcc)")
+    # The module first: where a shared object with thread-local variables comes after the library, and nobody ever touches them,
+    # every access of the other objects to theirs takes the loader's slow way from then on (torch's and the runtime's among them:
+    # 0.2 to 1 us of each call, a layer of 96 tokens 115 -> 130 us of host time). The library's own are touched by its calls.
+    calls = _import_calls()
     L = ctypes.CDLL(LIB_PATH)
     i64, vp, fp = ctypes.c_int64, ctypes.c_void_p, ctypes.POINTER(AmxFormat)
     L.amxfp4_last_error.restype = ctypes.c_char_p
@@ -128,7 +132,11 @@ def _load():
                        ("amxfp4_rmsnorm_quantize", [fp, vp, vp, vp, vp, i64, i64, f32, vp, vp, vp])):
         getattr(L, name).argtypes = args
         getattr(L, name).restype = ctypes.c_int
-    _calls = _native_calls(L)  # first: who finds the library loaded finds the module too
+    if calls is None:
+        calls = _GeneralWay()
+    else:
+        calls.bind(AmxFormat, *(ctypes.cast(getattr(L, name), vp).value for name in calls.entries))
+    _calls = calls  # first: who finds the library loaded finds the module too
     _lib = L
     return L
 
@@ -139,9 +147,9 @@ class _GeneralWay:
         return lambda *args: None
 
 
-def _native_calls(L):
-    """The native module, bound to the library's entry points. It reads torch's tensors where they lie, so it serves only the
-    torch that it was compiled against (the library itself knows nothing of torch)."""
+def _import_calls():
+    """The native module, not yet bound. It reads torch's tensors where they lie, so it serves only the torch that it was compiled
+    against (the library itself knows nothing of torch)."""
     try:
         from . import _calls as calls
         compiled_for = getattr(calls, "torch_version", "of old")
@@ -150,8 +158,7 @@ def _native_calls(L):
     except ImportError as e:
         warnings.warn("_calls.so cannot be used, calls go through ctypes; `python -m paper_2411_09909_amd.build` builds it (%s)" % e,
                       RuntimeWarning, stacklevel=4)
-        return _GeneralWay()
-    calls.bind(AmxFormat, *(ctypes.cast(getattr(L, name), ctypes.c_void_p).value for name in calls.entries))
+        return None
     return calls
 
 

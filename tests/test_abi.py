@@ -3,6 +3,7 @@ rejects bad arguments before anything is launched."""
 import ctypes
 import os
 import re
+import subprocess
 import sys
 
 import pytest
@@ -316,3 +317,19 @@ def test_without_a_usable_native_module_calls_go_the_general_way(lib, monkeypatc
     x = torch.zeros(32, 64, dtype=torch.bfloat16)
     with pytest.raises(binding.AmxError, match="device memory only"):
         binding.quantize(binding.make_format(), x, codes=torch.zeros(32, 32, dtype=torch.uint8), scales=torch.zeros(32, 4, dtype=torch.uint8))
+
+
+def test_the_native_module_is_loaded_before_the_library(lib):
+    """The other way round each call was 0.2 to 1 us slower for good."""
+    seen = subprocess.run([sys.executable, "-c", """
+import ctypes, sys
+from paper_2411_09909_amd import binding
+real = ctypes.CDLL
+def spy(path, *args, **kw):
+    if path == binding.LIB_PATH:
+        print("module first" if "paper_2411_09909_amd._calls" in sys.modules else "library first")
+    return real(path, *args, **kw)
+ctypes.CDLL = spy
+binding.load()
+"""], cwd=ROOT, capture_output=True, text=True, check=True).stdout
+    assert seen == "module first\n"
