@@ -518,8 +518,8 @@ int bf16_tile_choice(int64_t M, int64_t N, int64_t batch) {
 // 87 (192 x 256); 281 x 8192 x 8192 67 / 58 (the kernel; 128 x 128).
 // Where the estimate was wrong over 2660 more sizes (257 to 4096 rows, plain, gated and prepared; before / with the other):
 // 192 x 256 in more rounds than 256 x 256 takes (1148 x 25920 x 2432, gated, prepared, 120 / 140; 2071 x 13824 x 5120, gated,
-// 260 / 281), and in a second round instead of 64 x 256 with a K below 2048 (1311 x 11072 x 1792, gated, 65 / 72; 574 x 24704 x
-// 1792 82 / 87). All shapes add the products of an output in the same order: their bits are the same.
+// 260 / 281), and instead of 64 x 256 with a K up to 1024 (1408 x 5632 x 1024, gated, 25.1 / 25.7), in a second round up to 2048
+// (1311 x 11072 x 1792, gated, 65 / 72; 574 x 24704 x 1792 82 / 87; a gated layer of 1312 tokens x 11264 x 2048 276 / 280). All shapes add the products of an output in the same order: their bits are the same.
 int bf16_tile_refined(int choice, int64_t M, int64_t N, int64_t K, int64_t batch, bool gated) {
   struct Shape {
     int tile, rows, cols, rounds;    // at most so many rounds
@@ -543,7 +543,7 @@ int bf16_tile_refined(int choice, int64_t M, int64_t N, int64_t K, int64_t batch
     rounds[s.tile] = r;
     ok[s.tile] = r <= s.rounds && !(gated && s.tile == 7) && !(s.tile == 6 && K < 2048);
   }
-  if ((choice == 1 && rounds[4] > rounds[1]) || (choice == 3 && rounds[4] > 1 && K < 2048)) ok[4] = false;
+  if ((choice == 1 && rounds[4] > rounds[1]) || (choice == 3 && K <= (rounds[4] > 1 ? 2048 : 1024))) ok[4] = false;
   int best = choice;
   double limit = 0.97 * us[choice];
   for (int t = 4; t <= 7; ++t)
@@ -552,19 +552,21 @@ int bf16_tile_refined(int choice, int64_t M, int64_t N, int64_t K, int64_t batch
 }
 
 // The shape of a product that leaves it to the library. 192 x 192 takes the place of 256 x 128 tiles that all run at once only
-// where it was never the slower one: for weights whose panel has just been written (prepared ones come from memory, and the
+// where it is the faster one: for weights whose panel has just been written (prepared ones come from memory, and the
 // smaller tiles read them once more: 803 x 8192 x 8192 124 / 136, 696 x 10240 x 8192 126 / 138, 1577 x 4096 x 11008 159 / 162),
-// from six rows of 256 on (836 x 8192 x 28672 571 / 584; 752 x 10240 x 8192 184 / 187), with a long K or a tenth fewer of them
-// than of the others (1805 x 4096 x 14336 ratio 0.88, 1611 x 4096 x 11008 0.94, 1583 x 4096 x 4096 0.98; but 2029 x 4096 x 4096
-// 64 / 66, 3503 x 2048 x 2048 35.2 / 35.6).
+// from six rows of 256 on (836 x 8192 x 28672 571 / 584; 752 x 10240 x 8192 184 / 187), with a K beyond 4096 (1805 x 4096 x 14336
+// ratio 0.88, 1611 x 4096 x 11008 0.94, 1493 x 4544 x 4544 0.98; but 2029 x 4096 x 4096 64 / 66, 1600 x 4096 x 4096 56.5 / 57.2,
+// 3503 x 2048 x 2048 35.2 / 35.6). 192 x 256 does not take that of 256 x 128 in a gated product of up to 768 rows, which are as many
+// in tiles of either height (768 x 22016 x 4096 189 / 196).
 // whole_lines: every row of C is whole 128-byte lines, or C is BF16. Stores of rows that are not take longer, and in the larger
 // tiles there is less beside them: 192 x 256 then takes the place of 64 x 256 only with a K beyond 4096 (1323 x 11008 x 4096 167
 // / 183, 2570 x 6144 x 4096 170 / 177;  1124 x 13824 x 5120 ratio 0.93), that of 256 x 128 with one beyond 2048 (1349 x 16384 x
 // 2048 144 / 149).
 int bf16_tile(int64_t M, int64_t N, int64_t K, int64_t batch, bool gated, bool prepared, bool whole_lines) {
   const int choice = bf16_tile_choice(M, N, batch), refined = bf16_tile_refined(choice, M, N, K, batch, gated);
-  const int64_t now = ((M + 255) / 256) * ((N + 127) / 128), then = ((M + 191) / 192) * ((N + 191) / 192);
-  if (choice == 2 && refined == 7 && now <= 256 && (prepared || M <= 1280 || (K < 8192 && 10 * then > 9 * now))) return choice;
+  const bool one_round = ((M + 255) / 256) * ((N + 127) / 128) <= 256;
+  if (choice == 2 && refined == 7 && one_round && (prepared || M <= 1280 || K <= 4096)) return choice;
+  if (choice == 2 && refined == 4 && gated && !prepared && M <= 768) return choice;
   if (!whole_lines && refined == 4 && ((choice == 3 && K <= 4096) || (choice == 2 && K <= 2048))) return choice;
   return refined;
 }
