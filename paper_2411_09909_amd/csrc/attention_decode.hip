@@ -22,20 +22,11 @@
 // (16 j + 4 h + {0,1,2,3,8,9,10,11}); lane (d, h) picks exactly those eight codes out of the 16 bytes its V^T row has
 // for the tile: two 16-bit pieces of two words, one byte permute.
 #include "../../include/amxfp4.h"
-#include "attention_tile.h"
-#include "dequant_regs.h"
+#include "attention_decode.h"
 #include "gemm_common.h"
 #include "kernels.h"
 
 namespace amx {
-
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-
-// The 16-bit type the operands are dequantized to. FP8-E5M2 scales: FP16 with a bias of 2^-3 (every element * scale / 8
-// lies in [2^-20, 43008] with at most 5 significant bits: an FP16 number, subnormals included; the scale byte is the
-// upper byte of an FP16, so the dequantization is a conversion and one packed multiply); everything else: BF16.
-template <int SCALE_KIND>
-constexpr bool kDecodeF16 = SCALE_KIND == kScaleE5M2;
 
 template <int SCALE_KIND>
 __device__ __forceinline__ f32x16 decode_mfma(u32x4 a, u32x4 b, f32x16 acc) {
@@ -43,29 +34,6 @@ __device__ __forceinline__ f32x16 decode_mfma(u32x4 a, u32x4 b, f32x16 acc) {
     return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, a), __builtin_bit_cast(f16x8, b), acc, 0, 0, 0);
   else
     return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), acc, 0, 0, 0);
-}
-
-// Eight codes (one word) of one group -> eight exact 16-bit floats (element * scale has at most 6 significant bits).
-// FP8-E5M2 scales: FP16, biased (above). Power-of-two scales: the FP4 -> BF16 conversion applies the scale itself (it
-// reads the exponent field of a float). FP8-E4M3 scales: FP32 decode, times the scale of the element's sign class as a
-// float, truncated to BF16.
-template <int SCALE_KIND, bool ASYM>
-__device__ __forceinline__ u32x4 decode_word(uint32_t word, uint32_t byte_pos, uint32_t byte_neg) {
-  u32x4 r;
-  if constexpr (kDecodeF16<SCALE_KIND>) {
-    const uint32_t sp = ((byte_pos << 8) | (byte_pos << 24)) & 0x7F007F00u, sn = ((byte_neg << 8) | (byte_neg << 24)) & 0x7F007F00u;
-    r = u32x4{dequant2_f16<ASYM, 0>(word, sp, sn), dequant2_f16<ASYM, 1>(word, sp, sn),
-              dequant2_f16<ASYM, 2>(word, sp, sn), dequant2_f16<ASYM, 3>(word, sp, sn)};
-  } else if constexpr (SCALE_KIND == kScaleE8M0Floor || SCALE_KIND == kScaleE8M0Round) {
-    const uint32_t sp = byte_pos << 23, sn = byte_neg << 23;
-    r = u32x4{dequant2_pot<ASYM, 0>(word, sp, sn), dequant2_pot<ASYM, 1>(word, sp, sn),
-              dequant2_pot<ASYM, 2>(word, sp, sn), dequant2_pot<ASYM, 3>(word, sp, sn)};
-  } else {
-    const uint32_t sp = f2u(scale_value<SCALE_KIND>(byte_pos)), sn = ASYM ? f2u(scale_value<SCALE_KIND>(byte_neg)) : sp;
-    r = u32x4{dequant2_f32<ASYM, 0>(word, sp, sn), dequant2_f32<ASYM, 1>(word, sp, sn),
-              dequant2_f32<ASYM, 2>(word, sp, sn), dequant2_f32<ASYM, 3>(word, sp, sn)};
-  }
-  return r;
 }
 
 // One row's share of a lane for the first product: the D / 4 bytes of codes of dimensions (D / 2) h .. and the scale
@@ -121,8 +89,6 @@ __device__ __forceinline__ void load_v_piece(const uint8_t* __restrict__ codes, 
   else
     p.scales = scales[g];
 }
-
-constexpr int kDecodeCols = 32;  // query columns of a wave
 
 // grid: (key_splits, kv_heads); block: one wave. part: [kv_heads][32 columns][key_splits][D + 2] floats: the
 // un-normalised O of the column in that range, then its running maximum (log2 units) and its sum; only the columns
@@ -391,16 +357,21 @@ static hipError_t launch_decode(int64_t Hq, int64_t Hkv, int64_t Sq, int64_t Sk,
                                 const uint8_t* Kc, const uint8_t* Ks, const uint8_t* Vc, const uint8_t* Vs, float scale,
                                 int causal, int splits, float* out, float* part, hipStream_t s) {
   const int per = (int)(Hq / Hkv), tiles = (int)(Sk / 32), tiles_per_split = (tiles + splits - 1) / splits;
-  // whole chunks of 8 key tiles, and V^T of one head within the 32-bit offsets of a buffer: V through LDS by chunks
-  if (Sk % 256 == 0 && Sk <= (1 << 24))
-    hipLaunchKernelGGL((attention_decode_kernel<SK, ASYM, D, true>), dim3((unsigned)splits, (unsigned)Hkv), dim3(64), 0, s,
-                       Qc, Qs, Kc, Ks, Vc, Vs, part, (int)Sq, (int)Sk, per, tiles_per_split,
-                       scale * 1.4426950408889634f, causal);
-  else
-    hipLaunchKernelGGL((attention_decode_kernel<SK, ASYM, D, false>), dim3((unsigned)splits, (unsigned)Hkv), dim3(64), 0, s,
-                       Qc, Qs, Kc, Ks, Vc, Vs, part, (int)Sq, (int)Sk, per, tiles_per_split,
-                       scale * 1.4426950408889634f, causal);
-  hipError_t e = hipGetLastError();
+  hipError_t e;
+  if (attention_decode_16_preferred(Hq, Hkv, Sq, tiles_per_split, splits)) {
+    e = launch_attention_decode_16(SK, ASYM, Hq, Hkv, Sq, Sk, D, Qc, Qs, Kc, Ks, Vc, Vs, scale, causal, splits, part, s);
+  } else {
+    // whole chunks of 8 key tiles, and V^T of one head within the 32-bit offsets of a buffer: V through LDS by chunks
+    if (Sk % 256 == 0 && Sk <= (1 << 24))
+      hipLaunchKernelGGL((attention_decode_kernel<SK, ASYM, D, true>), dim3((unsigned)splits, (unsigned)Hkv), dim3(64), 0, s,
+                         Qc, Qs, Kc, Ks, Vc, Vs, part, (int)Sq, (int)Sk, per, tiles_per_split,
+                         scale * 1.4426950408889634f, causal);
+    else
+      hipLaunchKernelGGL((attention_decode_kernel<SK, ASYM, D, false>), dim3((unsigned)splits, (unsigned)Hkv), dim3(64), 0, s,
+                         Qc, Qs, Kc, Ks, Vc, Vs, part, (int)Sq, (int)Sk, per, tiles_per_split,
+                         scale * 1.4426950408889634f, causal);
+    e = hipGetLastError();
+  }
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL((attention_decode_combine_kernel<D>), dim3((unsigned)(per * Sq), (unsigned)Hkv), dim3(64), 0, s, part,
                      out, per, (int)Sq, splits);

@@ -69,7 +69,8 @@ typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
     L = L * ALPHA + psum;                                                                                          \
     M = (EMPTY_OK) ? m_raw : m_new;
 
-// The cast of the 32 probabilities X of each query, of which PMAX is the largest, as one group, dequantized into PB. The
+// The cast of the 32 probabilities X of each query, of which PMAX is the largest, as one group, dequantized into the words of
+// PB (an array: eight where two lanes share a query, four where four lanes do). The
 // quotient p / S is taken as p * (1 / S): its error of an ulp or two is that of the hardware exp2 which produced p.
 #define AMX_ATTENTION_TILE_CAST(X, PMAX, PB, P_F16)                                                                \
   {                                                                                                                \
@@ -82,7 +83,7 @@ typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
     static_assert(!(P_F16) || SCALE_KIND == kScaleE5M2, "FP16 probabilities: FP8-E5M2 scales");                    \
     const _Float16 s_half_ = (_Float16)S; /* exact: an E5M2 value, subnormals included */                          \
     const f16x2 s_half2_ = {s_half_, s_half_};                                                                     \
-    _Pragma("unroll") for (int i = 0; i < 8; ++i) {                                                                \
+    _Pragma("unroll") for (int i = 0; i < (int)(sizeof(PB) / 4); ++i) {                                             \
       if constexpr ((P_F16) && SCALE_KIND == kScaleE5M2) {                                                         \
         const float z0 = (X)[2 * i] * R, z1 = (X)[2 * i + 1] * R;                                                  \
         const uint32_t code = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(f2u(z0), z0, z1, 1.0f, 0);                  \

@@ -55,6 +55,51 @@ def test_decode_matches_the_split_key_oracle(Hq, Hkv, Sq, Sk, causal, splits, D,
     compare(gpu_decode(q, k, v, D ** -0.5, causal, scale_format, asym, splits), want)
 
 
+# 16 columns and fewer take one kernel, 17 to 32 the other; a range is walked in rounds of four tiles, one to a wave
+COLUMN_SHAPES = [
+    (16, 1, 1, 288, True, 1, 128),     # 16 columns; 9 tiles in one range: two rounds and a tile
+    (2, 1, 8, 544, True, 4, 128),      # 17 tiles in ranges of 5, 5, 5, 2; 8 queries: masks inside the last two tiles' columns
+    (17, 1, 1, 544, True, 4, 128),     # 17 columns
+    (4, 1, 5, 1024, True, 3, 128),     # 20 columns, V by chunks, ranges that start inside a chunk
+    (8, 2, 5, 768, False, 2, 64),
+    (8, 2, 5, 320, True, 2, 64),       # V tile by tile
+    (4, 4, 4, 224, True, 7, 64),       # ranges of one tile
+    (3, 1, 4, 416, True, 2, 64),       # ranges of 7 and 6 tiles
+    (5, 1, 3, 32, True, 1, 128),       # one tile in all
+]
+
+
+@pytest.mark.parametrize("scale_format,asym", FORMATS)
+@pytest.mark.parametrize("Hq,Hkv,Sq,Sk,causal,splits,D", COLUMN_SHAPES)
+def test_columns_and_rounds(Hq, Hkv, Sq, Sk, causal, splits, D, scale_format, asym):
+    test_decode_matches_the_split_key_oracle(Hq, Hkv, Sq, Sk, causal, splits, D, scale_format, asym)
+
+
+@pytest.mark.parametrize("scale_format,asym", [(ref.FP8_E5M2, 1), (ref.E8M0_FLOOR, 0)])
+@pytest.mark.parametrize("Sk,splits", [(16384, 32), (16416, 30)])
+def test_two_tiles_to_a_wave_same_bits(Sk, splits, scale_format, asym):
+    """64 key / value heads against 16384 keys and more (ranges of 16 tiles, and of 18 with a short last one) go through the keys eight
+    tiles at a time, eight of the heads alone four at a time: every wave has the same tiles in the same order. The scale bytes
+    also from an address that is only 2-byte aligned."""
+    G_, per, D = 64, 2, 128
+    fmt = binding.make_format(scale_format, asym, 32)
+    gen = torch.Generator(device="cuda").manual_seed(5)
+    rnd = lambda *s: torch.randn(s, generator=gen, device="cuda").to(torch.bfloat16)  # noqa: E731
+    q = binding.quantize_batched(fmt, rnd(G_ * per, 1, D))
+    k, v = binding.quantize_batched(fmt, rnd(G_, Sk, D)), binding.quantize_batched(fmt, rnd(G_, Sk, D), k_axis=1)
+    whole = binding.attention_decode(fmt, *q, *k, *v, D ** -0.5, True, key_splits=splits)
+    for g in (0, 24, 56):
+        part = [t[g * per:(g + 8) * per].contiguous() for t in q] + [t[g:g + 8].contiguous() for t in k + v]
+        few = binding.attention_decode(fmt, *part, D ** -0.5, True, key_splits=splits)
+        assert torch.equal(few, whole[g * per:(g + 8) * per])
+        shifted = torch.empty(part[5].numel() + 2, dtype=torch.uint8, device="cuda")[2:].view(part[5].shape)
+        shifted.copy_(part[5])
+        assert torch.equal(few, binding.attention_decode(fmt, *part[:5], shifted, D ** -0.5, True, key_splits=splits))
+    shifted = torch.empty(v[1].numel() + 2, dtype=torch.uint8, device="cuda")[2:].view(v[1].shape)
+    shifted.copy_(v[1])
+    assert torch.equal(whole, binding.attention_decode(fmt, *q, *k, v[0], shifted, D ** -0.5, True, key_splits=splits))
+
+
 def test_one_range_agrees_with_the_many_queries_kernel():
     """key_splits = 1 is the definition amxfp4_attention implements; the two kernels differ in summation order only."""
     Hq, Hkv, Sq, Sk, D = 8, 2, 8, 384, 128
