@@ -286,62 +286,75 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) void
   if (h == 0) dst[D] = m, dst[D + 1] = l;
 }
 
-// One wave per (kv head, column that holds a query): the exact combination of the ranges, in FP32. The lanes first
-// share out the ranges (maximum, then every range's weight 2^(m_c - m*), 0 for a range in which the query saw no key,
-// and the weighted sum of the l_c), then the head dimensions. It is a chain of memory latencies, so the first 32 ranges'
-// rows (D / 64 floats a lane of each) are requested before anything is known about their weights, and further ones 32 at
-// a time (one sequence x 8192 keys, 64 ranges, the whole call, together with the joined requests of the first tile:
-// 19.2 -> 16.4 us).
-constexpr int kDecodeMaxSplits = 1024;
+// Over all lanes of a wave: rotations within rows of 16 lanes, then the rows (lane exchanges through LDS took as long as the loads).
+template <typename Op>
+__device__ __forceinline__ float over_wave(float v, Op op) {
+  v = op(v, u2f((uint32_t)__builtin_amdgcn_update_dpp(0, (int)f2u(v), 0x128, 0xF, 0xF, false)));  // row_ror:8
+  v = op(v, u2f((uint32_t)__builtin_amdgcn_update_dpp(0, (int)f2u(v), 0x124, 0xF, 0xF, false)));
+  v = op(v, u2f((uint32_t)__builtin_amdgcn_update_dpp(0, (int)f2u(v), 0x122, 0xF, 0xF, false)));
+  v = op(v, u2f((uint32_t)__builtin_amdgcn_update_dpp(0, (int)f2u(v), 0x121, 0xF, 0xF, false)));
+  const auto a = __builtin_amdgcn_permlane16_swap(f2u(v), f2u(v), false, false);
+  v = op(u2f(a[0]), u2f(a[1]));
+  const auto b = __builtin_amdgcn_permlane32_swap(f2u(v), f2u(v), false, false);
+  return op(u2f(b[0]), u2f(b[1]));
+}
+
+// Four waves per (kv head, column that holds a query): the exact combination of the ranges, in FP32. Each wave works out the
+// maximum and the ranges' weights 2^(m_c - m*), a range to a lane (0 for a range in which the query saw no key), and adds up every
+// fourth range's row, a weight read from its lane. It is a chain of memory latencies, so the first 64 ranges' rows (16 to a wave,
+// D / 64 floats a lane of each) are requested before anything is known about their weights, and further ones 64 at a time.
+// As one wave with 32 rows in flight and lane exchanges through LDS: 64 ranges, 32 columns 5.3 -> 2.9 us; the whole call of one
+// sequence x 8192 keys 11.3 -> 9.9, of four (32 ranges) 16.5 -> 15.6, 256 ranges 31.5 -> 19.0.
 template <int D>
-__global__ __launch_bounds__(64) void attention_decode_combine_kernel(const float* __restrict__ part,
-                                                                      float* __restrict__ out, int per, int Sq,
-                                                                      int nsplits) {
+__global__ __launch_bounds__(256) void attention_decode_combine_kernel(const float* __restrict__ part, float* __restrict__ out, int per,
+                                                                       int Sq, int nsplits) {
   typedef float row_t __attribute__((ext_vector_type(D / 64)));
-  constexpr int kInFlight = 32;
-  __shared__ float weight[kDecodeMaxSplits];
-  const int lane = threadIdx.x, col = (int)blockIdx.x, g = (int)blockIdx.y;
+  constexpr int kInFlight = 16;
+  __shared__ float sums[4 * D];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), col = (int)blockIdx.x, g = (int)blockIdx.y;
   const float* base = part + ((int64_t)g * kDecodeCols + col) * nsplits * (D + 2);
   row_t rows[kInFlight];
-  auto request = [&](int c0) {  // (past the last range: the last one again, not used)
+  auto request = [&](int c0) {  // (past the last range: the last one again, with weight 0)
 #pragma unroll
     for (int i = 0; i < kInFlight; ++i)
-      rows[i] = *reinterpret_cast<const row_t*>(base + (int64_t)min(c0 + i, nsplits - 1) * (D + 2) + lane * (D / 64));
+      rows[i] = *reinterpret_cast<const row_t*>(base + (int64_t)min(c0 + wave + 4 * i, nsplits - 1) * (D + 2) + lane * (D / 64));
   };
+  // maximum and sum of range c0 + lane (none: a range without a key)
+  auto range_of = [&](int c0) {
+    const float2 ml = *reinterpret_cast<const float2*>(base + (int64_t)min(c0 + lane, nsplits - 1) * (D + 2) + D);
+    return c0 + lane < nsplits ? ml : make_float2(0.f, 0.f);
+  };
+  float2 ml = range_of(0);
   request(0);
-  float mx = -__builtin_inff();
-  for (int c = lane; c < nsplits; c += 64)
-    if (base[(int64_t)c * (D + 2) + D + 1] > 0.f) mx = fmaxf(mx, base[(int64_t)c * (D + 2) + D]);
-#pragma unroll
-  for (int d = 32; d >= 1; d >>= 1) mx = fmaxf(mx, __shfl_xor(mx, d, 64));
-  float den = 0.f;
-  for (int c = lane; c < nsplits; c += 64) {
-    const float lc = base[(int64_t)c * (D + 2) + D + 1];
-    const float w = lc > 0.f ? __builtin_amdgcn_exp2f(base[(int64_t)c * (D + 2) + D] - mx) : 0.f;
-    weight[c] = w;
-    den += w * lc;
+  float mx = ml.y > 0.f ? ml.x : -__builtin_inff();
+  for (int c0 = 64; c0 < nsplits; c0 += 64) {
+    const float2 more = range_of(c0);
+    if (more.y > 0.f) mx = fmaxf(mx, more.x);
   }
-#pragma unroll
-  for (int d = 32; d >= 1; d >>= 1) den += __shfl_xor(den, d, 64);
-  __syncthreads();
-  const float inv = 1.0f / den;
+  mx = over_wave(mx, [](float a, float b) { return fmaxf(a, b); });
+  float den = 0.f;
   row_t num;
 #pragma unroll
   for (int e = 0; e < D / 64; ++e) num[e] = 0.f;
-  for (int c0 = 0; c0 < nsplits; c0 += kInFlight) {
-    if (c0 != 0) request(c0);
+  for (int c0 = 0; c0 < nsplits; c0 += 64) {
+    if (c0 != 0) {
+      ml = range_of(c0);
+      request(c0);
+    }
+    const float w = ml.y > 0.f ? __builtin_amdgcn_exp2f(ml.x - mx) : 0.f;
+    den += w * ml.y;
 #pragma unroll
     for (int i = 0; i < kInFlight; ++i) {
-      if (c0 + i < nsplits) {
+      const float weight = u2f((uint32_t)__builtin_amdgcn_readlane((int)f2u(w), wave + 4 * i));
 #pragma unroll
-        for (int e = 0; e < D / 64; ++e) num[e] += weight[c0 + i] * rows[i][e];
-      }
+      for (int e = 0; e < D / 64; ++e) num[e] += weight * rows[i][e];
     }
   }
-  row_t* dst = reinterpret_cast<row_t*>(out + (((int64_t)g * per + col / Sq) * Sq + col % Sq) * D);
-#pragma unroll
-  for (int e = 0; e < D / 64; ++e) num[e] *= inv;
-  dst[lane] = num;
+  *reinterpret_cast<row_t*>(sums + wave * D + lane * (D / 64)) = num;
+  const float inv = 1.0f / over_wave(den, [](float a, float b) { return a + b; });
+  __syncthreads();
+  if (tid < D)
+    out[(((int64_t)g * per + col / Sq) * Sq + col % Sq) * D + tid] = ((sums[tid] + sums[D + tid]) + (sums[2 * D + tid] + sums[3 * D + tid])) * inv;
 }
 
 bool attention_decode_supported(int64_t Hq, int64_t Hkv, int64_t Sq, int64_t head_dim) {
@@ -373,7 +386,7 @@ static hipError_t launch_decode(int64_t Hq, int64_t Hkv, int64_t Sq, int64_t Sk,
     e = hipGetLastError();
   }
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((attention_decode_combine_kernel<D>), dim3((unsigned)(per * Sq), (unsigned)Hkv), dim3(64), 0, s, part,
+  hipLaunchKernelGGL((attention_decode_combine_kernel<D>), dim3((unsigned)(per * Sq), (unsigned)Hkv), dim3(256), 0, s, part,
                      out, per, (int)Sq, splits);
   return hipGetLastError();
 }

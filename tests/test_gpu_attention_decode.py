@@ -143,9 +143,9 @@ def test_decoding_shape_at_full_size(scale_format, asym):
     compare(out, want)
 
 
-@pytest.mark.parametrize("splits,D", [(1, 128), (31, 128), (32, 64), (33, 128), (64, 64), (65, 128)])
+@pytest.mark.parametrize("splits,D", [(1, 128), (31, 128), (32, 64), (33, 128), (63, 64), (64, 64), (65, 128), (66, 64)])
 def test_ranges_around_what_the_combination_keeps_in_flight(splits, D):
-    """The combination reads 32 ranges' rows at a time: one range, the last of a batch missing, whole batches, one range
+    """The combination reads 64 ranges' rows at a time: one range, the last of a batch missing, whole batches, one range
     beyond. 66 tiles of keys (no whole V chunks): the last ranges hold fewer tiles, or none."""
     Hq, Hkv, Sq, Sk = 4, 2, 2, 66 * 32
     q, k, v = heads(Hq, Sq, 71, d=D), heads(Hkv, Sk, 72, d=D), heads(Hkv, Sk, 73, d=D)
