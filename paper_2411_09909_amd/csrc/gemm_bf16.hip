@@ -292,10 +292,10 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_bf16_kernel(const uint16_t*
     store_glu_tiles<FM, FN>(acc, stage, reinterpret_cast<uint16_t*>(C) + b * M * ldc, M, N >> 1, ldc,
                             (int64_t)tm * Cfg::kTileM + wm * FM * 32, (int64_t)tn * Cfg::kTileN + wn * FN * 32);
   } else if constexpr (SCALED)
-    store_c_tiles<FM, FN, 0, true>(acc, C + b * M * ldc, M, N, ldc, (int64_t)tm * Cfg::kTileM + wm * FM * 32,
+    store_c_tiles<FM, FN, 0, true>(acc, C + b * M * ldc, M, N, Kp, ldc, (int64_t)tm * Cfg::kTileM + wm * FM * 32,
                                    (int64_t)tn * Cfg::kTileN + wn * FN * 32, alpha_a[0] * alpha_b[0]);
   else
-    store_c_tiles<FM, FN>(acc, C + b * M * ldc, M, N, ldc, (int64_t)tm * Cfg::kTileM + wm * FM * 32,
+    store_c_tiles<FM, FN>(acc, C + b * M * ldc, M, N, Kp, ldc, (int64_t)tm * Cfg::kTileM + wm * FM * 32,
                           (int64_t)tn * Cfg::kTileN + wn * FN * 32);
 }
 

@@ -73,7 +73,7 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));  // accumulator of on
 // 2^SCALE_LOG2 (0, or the power of two that undoes an operand bias) and, with ALPHA, by the run-time factor alpha.
 // row_base / col_base: first row / column of the wave's tiles.
 // Accumulator register v of lane l is row 8*(v/4) + 4*(l/32) + v%4, column l%32 of its tile. Rows >= M and columns
-// >= N (partial tiles) are not written. Non-temporal stores: C is not read again by the kernel.
+// >= N (partial tiles) are not written.
 // Addressing: one raw buffer over the wave's window of C, from its first element to the last valid element of its last
 // valid row. The row of a store is a scalar offset (a compile-time multiple of the row pitch), the column and the lane
 // half's row offset a per-lane offset computed once per column tile, so a store costs one scalar addition; the hardware
@@ -89,7 +89,7 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));  // accumulator of on
 // it took the same 7 us as this form.)
 template <int FM, int FN, int SCALE_LOG2 = 0, bool ALPHA = false>
 __device__ __forceinline__ void store_c_tiles(const f32x16 (&acc)[FM][FN], float* __restrict__ Cb, int64_t M,
-                                              int64_t N, int64_t ldc, int64_t row_base, int64_t col_base,
+                                              int64_t N, int64_t K, int64_t ldc, int64_t row_base, int64_t col_base,
                                               float alpha = 1.0f) {
   const int64_t rows_left = M - row_base, cols_left = N - col_base;  // uniform over the wave
   if (rows_left <= 0 || cols_left <= 0) return;
@@ -100,23 +100,41 @@ __device__ __forceinline__ void store_c_tiles(const f32x16 (&acc)[FM][FN], float
       Cb + row_base * ldc + col_base, 0, (int)((uint32_t)(rows_valid - 1) * pitch + (uint32_t)cols_valid * 4u), 0x00020000);
   // the lane number is taken from the hardware again here rather than kept alive (or spilled) across the main loop
   const int lane = (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
+  uint32_t lane_off[FN];
 #pragma unroll
   for (int j = 0; j < FN; ++j) {
     const int col = j * 32 + (lane & 31);
-    const uint32_t lane_off = col < cols_valid ? (uint32_t)col * 4u + (uint32_t)(4 * (lane >> 5)) * pitch : 0x80000000u;
+    lane_off[j] = col < cols_valid ? (uint32_t)col * 4u + (uint32_t)(4 * (lane >> 5)) * pitch : 0x80000000u;
+  }
+  // A row's column tiles one after the other: where rows are no whole lines, a line is written by two stores, and they meet in L2
+  // only if they are close (column by column, as it was, us / row by row / row by row through the caches: FP4 3000 x 5001 x 4096 76 /
+  // 49 / 41, 4096 x 10001 x 1024 160 / 83 / 75, 4096 x 32001 x 4096 532 / 322 / 354, FP6 4096 x 4545 x 4544 141 / 112 / 104, BF16
+  // panels 4096 x 32001 x 4096 1126 / 917 / 892, 1400 x 50257 x 2048 423 / 319 / 364). Streaming stores except for rows that are not
+  // even half lines, a C below 80 MB and a K up to 4096: the two halves of a line then wait for each other in the caches. With a
+  // deeper K the operands need the caches (panels, 1400 x 2161 x 8192 73.4 / 72.5 / 75.3), and whole lines stream in either order
+  // alike, through the caches they take a tenth longer (4096 x 32000 x 4096 266 / 266 / 309).
+  auto store = [&]<int POLICY>() {
 #pragma unroll
     for (int i = 0; i < FM; ++i) {
 #pragma unroll
       for (int v = 0; v < 16; ++v) {
-        float c = acc[i][j][v];
-        if constexpr (SCALE_LOG2 != 0) c *= (float)(1 << SCALE_LOG2);
-        if constexpr (ALPHA) c *= alpha;
         const uint32_t row_off = (uint32_t)(i * 32 + 8 * (v >> 2) + (v & 3)) * pitch;
-        __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, c), window, (int)lane_off, (int)row_off,
-                                              2 /* non-temporal */);
+#pragma unroll
+        for (int j = 0; j < FN; ++j) {
+          float c = acc[i][j][v];
+          if constexpr (SCALE_LOG2 != 0) c *= (float)(1 << SCALE_LOG2);
+          if constexpr (ALPHA) c *= alpha;
+          __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, c), window, (int)lane_off[j], (int)row_off, POLICY);
+        }
       }
     }
-  }
+  };
+  constexpr int kStreaming = 2, kCached = 0;
+  const bool half_lines = ((reinterpret_cast<uintptr_t>(Cb) | pitch) & 63) == 0;
+  if (half_lines || K > 4096 || (uint64_t)M * pitch >= 80000000u)
+    store.template operator()<kStreaming>();
+  else
+    store.template operator()<kCached>();
 }
 
 // The gated-activation epilogue: the wave's column tiles come in pairs (gate columns, up columns: the B operand's rows

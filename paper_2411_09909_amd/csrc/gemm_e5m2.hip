@@ -292,7 +292,7 @@ __global__ __launch_bounds__(512) void gemm_e5m2_kernel(const uint8_t* __restric
 #undef AMX_RAW_READ
 #undef AMX_ISSUE_RAW
 
-  store_c_tiles<FM, FN, 6 /* 2^6 undoes the operand bias */>(acc, C + b * M * ldc, M, N, ldc, (int64_t)tm * kE5Tile + wm * FM * 32,
+  store_c_tiles<FM, FN, 6 /* 2^6 undoes the operand bias */>(acc, C + b * M * ldc, M, N, K, ldc, (int64_t)tm * kE5Tile + wm * FM * 32,
                         (int64_t)tn * kE5Tile + wn * FN * 32);
 }
 
@@ -566,7 +566,7 @@ __global__ __launch_bounds__(256) void gemm_e5m2_hybrid_kernel(const uint16_t* _
 #undef AMX_ISSUE_RAW
 #undef AMX_ISSUE_A
 
-  store_c_tiles<FM, FN, 6 /* 2^6 undoes the operand bias */>(acc, C + b * M * ldc, M, N, ldc, (int64_t)tm * kE5Tile + wm * FM * 32,
+  store_c_tiles<FM, FN, 6 /* 2^6 undoes the operand bias */>(acc, C + b * M * ldc, M, N, K, ldc, (int64_t)tm * kE5Tile + wm * FM * 32,
                         (int64_t)tn * kE5Tile + wn * FN * 32);
 }
 

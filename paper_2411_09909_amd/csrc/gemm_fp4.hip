@@ -429,7 +429,7 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_fp4_kernel(const uint8_t* _
     store_glu_tiles<FM, FN>(acc, stage, reinterpret_cast<uint16_t*>(C) + b * M * ldc, M, N >> 1, ldc,
                             (int64_t)tm * kTileM + wm * FM * 32, (int64_t)tn * kTileN + wn * FN * 32);
   } else
-    store_c_tiles<FM, FN>(acc, C + b * M * ldc, M, N, ldc, (int64_t)tm * kTileM + wm * FM * 32,
+    store_c_tiles<FM, FN>(acc, C + b * M * ldc, M, N, K, ldc, (int64_t)tm * kTileM + wm * FM * 32,
                           (int64_t)tn * kTileN + wn * FN * 32);
 }
 

@@ -711,7 +711,7 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_fp6m_kernel(const uint8_t* 
     store_glu_tiles<FM, FN>(acc, stage, reinterpret_cast<uint16_t*>(C) + b * M * ldc, M, N >> 1, ldc,
                             (int64_t)tm * (32 * FM * WM) + wm * FM * 32, (int64_t)tn * (32 * FN * WN) + wn * FN * 32);
   } else
-    store_c_tiles<FM, FN>(acc, C + b * M * ldc, M, N, ldc, (int64_t)tm * (32 * FM * WM) + wm * FM * 32,
+    store_c_tiles<FM, FN>(acc, C + b * M * ldc, M, N, (int64_t)nsteps * 64, ldc, (int64_t)tm * (32 * FM * WM) + wm * FM * 32,
                           (int64_t)tn * (32 * FN * WN) + wn * FN * 32);
 }
 

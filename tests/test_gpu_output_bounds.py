@@ -175,6 +175,30 @@ def test_weights_in_pieces_write_only_their_window(M, N, K, pad):
         assert torch.equal(window[0][:, n0:n0 + 4096].double(), a @ b[n0:n0 + 4096].T)
 
 
+@pytest.mark.parametrize("fmt_args", [(ref.E8M0_FLOOR, False), (ref.E8M0_FLOOR, True), (ref.FP8_E5M2, True)])
+@pytest.mark.parametrize("M,N", [(300, 1057), (1100, 18721)])  # C below and above 80 MB, in either case more than one column of tiles
+def test_store_policies_same_bits_and_only_the_window(M, N, fmt_args):
+    """Rows of C that are whole lines, half lines and neither (by the pitch, and by the base's alignment) are stored in different ways,
+    a large C in another way than a small one. The same product through all of them."""
+    K = 256
+    fmt = binding.make_format(*fmt_args, 32)
+    gen = torch.Generator(device="cuda").manual_seed(M)
+    a = binding.quantize(fmt, torch.randn((M, K), generator=gen, device="cuda").to(torch.bfloat16))
+    b = binding.quantize(fmt, torch.randn((N, K), generator=gen, device="cuda").to(torch.bfloat16))
+    options = binding.gemm_options(few_rows=-1)  # (the tiled kernels)
+    base = None
+    for pitch, shift in [((N + 31) // 32 * 32, 0), ((N + 15) // 16 * 16 + 16 * (((N + 15) // 16) % 2 == 0), 0), (N, 0), ((N + 31) // 32 * 32, 3)]:
+        buf = torch.full((GUARD + shift + M * pitch + GUARD,), CANARY, dtype=torch.int32, device="cuda")
+        body = buf[GUARD + shift:GUARD + shift + M * pitch].view(M, pitch)
+        binding.gemm(fmt, *a, *b, out=body.view(torch.float32)[:, :N], options=options)
+        got = body[:, :N].clone()
+        base = got if base is None else base
+        assert torch.equal(got, base), (pitch, shift)
+        body[:, :N] = CANARY
+        assert bool((buf == CANARY).all()), (pitch, shift)
+    assert torch.isfinite(base.view(torch.float32)).all()
+
+
 @pytest.mark.parametrize("M", [1, 16, 19, 32])
 def test_48_columns_to_a_workgroup_write_only_their_window(M):
     """(9001 columns: the last workgroup has 25)"""
