@@ -82,11 +82,18 @@ __device__ __forceinline__ u32x4 stream_dequant(uint32_t word, uint32_t s_pos, u
 
 // grid: (ceil(N / (NT R)), ceil(M / (MT R)), batch); block: WAVES waves. WHOLE: K is a multiple of 256 (so every row's scale
 // bytes start on a multiple of four, as their vector loads need); otherwise scale entries are loaded byte by byte.
+// FEW (R = 16, one row tile; 0: not): at most so many rows of A. A lane's share of a fragment is then a padding row's in most lanes, so
+// the wave's lanes share out the rows there are instead (a word of eight codes each, FEW / 2 times), dequantize them into LDS and read
+// the fragments from there, every lane row l % FEW; the rows of C beyond are not stored. Of a block's 272 vector instructions (16 x 16
+// tiles, asymmetric FP8-E5M2) 136 + 36 are left. Us, one row, all lanes on their own fragments / shared out: 4096 x 14336 10.5 / 8.5,
+// 4096 x 11008 8.9 / 7.4, 11008 x 4096 8.9 / 8.2, 28672 x 8192 33.8 / 31.5, 8192 x 28672 31.5 / 27.1; symmetric 4096 x 14336 7.3 / 6.8;
+// NVFP4 4544 x 4544 7.6 / 6.9. (As well for eight rows: 4 % of 5 to 8 rows' time, and beyond three column tiles one workgroup instead of two
+// to a compute unit. Rows 16 bytes apart instead of swizzled: the same, 28672 x 8192 5 % slower.)
 // GLU: B's rows are the gate and up rows interleaved in blocks of 32; C is then the BF16 output [M][ldc] of N / 2 columns,
 // bf16(silu(gate) * up). Its sums are the plain product's in the same order wherever both come here in the same shape, which
 // is everywhere but at 17 to 32 rows with N <= 4096 or 48 columns to a workgroup (there the plain form has R = 16, the gated
 // one always R = 32).
-template <int SCALE_KIND, bool ASYM, int GS_LOG2, int R, int MT, int NT, int WAVES, bool WHOLE, bool GLU>
+template <int SCALE_KIND, bool ASYM, int GS_LOG2, int R, int MT, int NT, int WAVES, int FEW, bool WHOLE, bool GLU>
 __global__ __launch_bounds__(64 * WAVES) void gemm_stream_kernel(
     const uint8_t* A_codes, const uint8_t* A_scales, const uint8_t* B_codes, const uint8_t* B_scales, float* C,
     int64_t M, int64_t N, int64_t K, int64_t ldc, const float* alpha_a, const float* alpha_b) {
@@ -94,7 +101,13 @@ __global__ __launch_bounds__(64 * WAVES) void gemm_stream_kernel(
   constexpr int kAcc = R * R / 64;  // accumulator registers per tile: 16 or 4
   constexpr int kTiles = MT + NT;   // row tiles of A, then column tiles (rows of B)
   constexpr bool kF16 = SCALE_KIND == kScaleE5M2 || SCALE_KIND == kScaleE4M3;
-  constexpr int kRowBytes = kStreamBlockK / 2, kWaveBytes = kTiles * R * kRowBytes;  // one block of a wave's codes
+  static_assert(FEW == 0 || (R == 16 && MT == 1 && FEW == 4));
+  constexpr int kCodeTiles = FEW ? NT : kTiles;  // tiles whose codes go through LDS as they are
+  // A row of A dequantized: 32 chunks of eight elements. Chunk c of row q lies in slot c ^ ((q & 3) + 4 (c / 16)), so that the reads of
+  // a k-step, chunk 8 piece + s of four rows, fall on banks of their own.
+  constexpr int kFewRowBytes = 2 * kStreamBlockK;
+  constexpr int kRowBytes = kStreamBlockK / 2, kFewBytes = FEW * kFewRowBytes;
+  constexpr int kWaveBytes = kCodeTiles * R * kRowBytes + kFewBytes;  // one block of a wave's codes, its rows of A
   constexpr int kSumBytes = WAVES * MT * NT * kAcc * 64 * 4;
   typedef float acc_t __attribute__((ext_vector_type(kAcc)));
   // the waves' blocks of codes; their sums at the end
@@ -139,11 +152,28 @@ __global__ __launch_bounds__(64 * WAVES) void gemm_stream_kernel(
       for (int v = 0; v < kAcc; ++v) acc[i][j][v] = 0.f;
 
   uint32_t s_next[kTiles][Piece::kScaleWords];  // scale bytes of the block whose codes are on their way
+  uint8_t* const few_lds = mine + kCodeTiles * R * kRowBytes;
+  uint32_t few_word[FEW ? FEW / 2 : 1], few_scales[FEW ? FEW / 2 : 1];  // word lane % 32 of rows lane / 32, lane / 32 + 2, ..
   // Requests block `blk` of all tiles: codes to LDS, scale bytes to s_next. left: elements of the block that exist (256
   // but for a last, shorter block, whose chunks of 32 elements past K read as zero).
   auto request = [&](int blk, [[maybe_unused]] int left) {
+    if constexpr (FEW != 0) {
+      const int word = lane & 31, row = lane >> 5;
+      const bool there = WHOLE || word * 8 < left;
+      const int code_off = there ? row * row_codes + word * 4 : kNowhere;
+      const int scale_at = there ? row * row_scales + ((word * 8) >> GS_LOG2) * (ASYM ? 2 : 1) : kNowhere;
 #pragma unroll
-    for (int t = 0; t < kTiles; ++t) {
+      for (int i = 0; i < FEW / 2; ++i) {
+        few_word[i] = __builtin_amdgcn_raw_buffer_load_b32(ac, code_off, 2 * i * row_codes + blk * kRowBytes, 0);
+        const int so = 2 * i * row_scales + blk * ((kStreamBlockK >> GS_LOG2) * (ASYM ? 2 : 1));
+        if constexpr (ASYM)
+          few_scales[i] = (uint16_t)__builtin_amdgcn_raw_buffer_load_b16(as, scale_at, so, 0);
+        else
+          few_scales[i] = (uint8_t)__builtin_amdgcn_raw_buffer_load_b8(as, scale_at, so, 0);
+      }
+    }
+#pragma unroll
+    for (int t = FEW ? MT : 0; t < kTiles; ++t) {
       const bool is_a = t < MT;
       const int row0 = (is_a ? t : t - MT) * R;
 #pragma unroll
@@ -151,7 +181,7 @@ __global__ __launch_bounds__(64 * WAVES) void gemm_stream_kernel(
         const int chunk = (l & 1) ? chunk_even ^ 4 : chunk_even;
         int off = gather + chunk * 16;
         if constexpr (!WHOLE) off = chunk * 32 < left ? off : kNowhere;
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(is_a ? ac : bc, (lds_ptr_t)(mine + (t * R + 8 * l) * kRowBytes), 16, off,
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(is_a ? ac : bc, (lds_ptr_t)(mine + ((FEW ? t - MT : t) * R + 8 * l) * kRowBytes), 16, off,
                                                  (row0 + 8 * l) * row_codes + blk * kRowBytes, 0, 0);
       }
       const int so = row0 * row_scales + blk * ((kStreamBlockK >> GS_LOG2) * (ASYM ? 2 : 1));
@@ -188,11 +218,20 @@ __global__ __launch_bounds__(64 * WAVES) void gemm_stream_kernel(
     asm volatile("" ::: "memory");
     u32x4 w[kTiles][Piece::kWords / 4];
     uint32_t sc[kTiles][Piece::kScaleWords];
+    if constexpr (FEW != 0) {
 #pragma unroll
-    for (int t = 0; t < kTiles; ++t) {
+      for (int i = 0; i < FEW / 2; ++i) {
+        uint32_t s_pos, s_neg;
+        stream_scales<SCALE_KIND, ASYM>(&few_scales[i], 0, s_pos, s_neg);
+        *reinterpret_cast<u32x4*>(few_lds + (2 * i + (lane >> 5)) * kFewRowBytes + (((lane & 31) ^ (((2 * i + (lane >> 5)) & 3) + 4 * ((lane >> 4) & 1))) << 4)) =
+            stream_dequant<SCALE_KIND, ASYM>(few_word[i], s_pos, s_neg);
+      }
+    }
+#pragma unroll
+    for (int t = FEW ? MT : 0; t < kTiles; ++t) {
 #pragma unroll
       for (int c = 0; c < Piece::kWords / 4; ++c)
-        w[t][c] = *reinterpret_cast<const u32x4*>(mine + t * R * kRowBytes + read_off[c]);
+        w[t][c] = *reinterpret_cast<const u32x4*>(mine + (FEW ? t - MT : t) * R * kRowBytes + read_off[c]);
 #pragma unroll
       for (int i = 0; i < Piece::kScaleWords; ++i) sc[t][i] = s_next[t][i];
     }
@@ -203,13 +242,18 @@ __global__ __launch_bounds__(64 * WAVES) void gemm_stream_kernel(
     for (int e = 0; e < Piece::kEntries; ++e) {
       uint32_t s_pos[kTiles], s_neg[kTiles];
 #pragma unroll
-      for (int t = 0; t < kTiles; ++t) stream_scales<SCALE_KIND, ASYM>(sc[t], e, s_pos[t], s_neg[t]);
+      for (int t = FEW ? MT : 0; t < kTiles; ++t) stream_scales<SCALE_KIND, ASYM>(sc[t], e, s_pos[t], s_neg[t]);
 #pragma unroll
       for (int x = 0; x < Piece::kWordsPerEntry; ++x) {
         const int s = e * Piece::kWordsPerEntry + x;
         u32x4 av[MT];
 #pragma unroll
-        for (int i = 0; i < MT; ++i) av[i] = stream_dequant<SCALE_KIND, ASYM>(w[i][s >> 2][s & 3], s_pos[i], s_neg[i]);
+        for (int i = 0; i < MT; ++i) {
+          if constexpr (FEW != 0)
+            av[i] = *reinterpret_cast<const u32x4*>(few_lds + (r % FEW) * kFewRowBytes + ((8 * piece + (s ^ ((r & 3) + 4 * (piece >> 1)))) << 4));
+          else
+            av[i] = stream_dequant<SCALE_KIND, ASYM>(w[i][s >> 2][s & 3], s_pos[i], s_neg[i]);
+        }
 #pragma unroll
         for (int j = 0; j < NT; ++j) {
           const u32x4 bv = stream_dequant<SCALE_KIND, ASYM>(w[MT + j][s >> 2][s & 3], s_pos[MT + j], s_neg[MT + j]);
@@ -300,11 +344,16 @@ static hipError_t stream_launch(int scale_kind, bool asym, int64_t group_size, i
   if ((group_size != 32 && group_size != 16) || K % 32 != 0) return hipErrorInvalidValue;
   hipError_t e = hipSuccess;
   if (timer.start && (e = hipEventRecord(timer.start, s)) != hipSuccess) return e;
-  auto run = [&]<int SK, bool ASYM, int GSL, int R, int MT, int NT, int WAVES, bool WHOLE>() {
-    hipLaunchKernelGGL((gemm_stream_kernel<SK, ASYM, GSL, R, MT, NT, WAVES, WHOLE, GLU>),
+  auto run_few = [&]<int SK, bool ASYM, int GSL, int R, int MT, int NT, int WAVES, bool WHOLE, int FEW>() {
+    hipLaunchKernelGGL((gemm_stream_kernel<SK, ASYM, GSL, R, MT, NT, WAVES, FEW, WHOLE, GLU>),
                        dim3((unsigned)((N + NT * R - 1) / (NT * R)), (unsigned)((M + MT * R - 1) / (MT * R)), (unsigned)batch),
                        dim3(64 * WAVES), 0, s, A_codes, A_scales, B_codes, B_scales, C, M, N, K, ldc, A_tensor_pair, B_tensor_pair);
     return hipGetLastError();
+  };
+  auto run = [&]<int SK, bool ASYM, int GSL, int R, int MT, int NT, int WAVES, bool WHOLE>() {
+    if constexpr (R == 16 && MT == 1 && (ASYM || SK != kScaleE8M0Floor))  // (symmetric power-of-two scales: nothing gained)
+      if (M <= 4) return run_few.template operator()<SK, ASYM, GSL, R, MT, NT, WAVES, WHOLE, 4>();
+    return run_few.template operator()<SK, ASYM, GSL, R, MT, NT, WAVES, WHOLE, 0>();
   };
   // The smallest tiles that still give the 256 compute units one workgroup of eight waves each; beyond that tiles of 64 x
   // 64 in workgroups of four waves, two to a compute unit. (AMXFP4-E5M2, us by tile: 16 rows, N 4096, K 4096: 16 x 16 4.8,

@@ -145,3 +145,29 @@ def test_48_columns_to_a_workgroup(M, N, K, scale, asym, gs):
     """Up to 32 rows against columns that fill the compute units better in workgroups of 48 (stream_48_columns() in
     gemm_stream.h): one and two row tiles, remainders in M and N, fewer K blocks than waves and more."""
     test_against_the_oracle(M, N, K, scale, asym, gs)
+
+
+@pytest.mark.parametrize("scale,asym,gs", FORMATS)
+@pytest.mark.parametrize("N,K", [(17, 32), (300, 544), (4100, 2304), (8200, 256), (8193, 2272), (11008, 512), (16400, 288)])
+def test_one_to_four_rows_same_bits_as_more(N, K, scale, asym, gs):
+    """Up to four rows the lanes share out A's rows; from five rows on each dequantizes its own. The same values in the same order: the
+    rows of a product of nine rows, bit for bit, for random codes and scale bytes (the sign bit of an FP8 one among them, which is
+    ignored)."""
+    gen = torch.Generator(device="cuda").manual_seed(N + K)
+    bytes_ = lambda *s, lo=0, hi=256: torch.randint(lo, hi, s, generator=gen, device="cuda", dtype=torch.uint8)  # noqa: E731
+    # scale bytes whose products stay finite: E5M2 and E4M3 below NaN / infinity, E8M0 around 2^0
+    lo, hi = {ref.FP8_E5M2: (0, 0x7C), ref.FP8_E4M3: (0, 0x7F), ref.E8M0_FLOOR: (100, 150), ref.E8M0_ROUND: (100, 150)}[scale]
+    pair = (2,) if asym else ()
+    fmt = binding.make_format(scale, asym, gs)
+    ac, as_, bc, bs = bytes_(9, K // 2), bytes_(9, K // gs, *pair, lo=lo, hi=hi), bytes_(N, K // 2), bytes_(N, K // gs, *pair, lo=lo, hi=hi)
+    if scale in (ref.FP8_E5M2, ref.FP8_E4M3):
+        as_ |= bytes_(*as_.shape) & 0x80
+    more = binding.gemm(fmt, ac, as_, bc, bs)
+    assert torch.isfinite(more).all()
+    for m in (1, 2, 3, 4):
+        few = binding.gemm(fmt, ac[:m].contiguous(), as_[:m].contiguous(), bc, bs)
+        assert torch.equal(few.view(torch.int32), more[:m].view(torch.int32)), m
+    if N % 64 == 0:
+        glu = [binding.gemm_silu_mul(fmt, ac[:m].contiguous(), as_[:m].contiguous(), bc, bs) for m in (1, 4, 9)]
+        for g in glu:
+            assert torch.equal(g.view(torch.int16), glu[2][:g.shape[0]].view(torch.int16))
