@@ -26,6 +26,36 @@ static double stream_us(bool asym, int64_t group_size, int64_t M, int64_t N, int
   return tail * (3.5 + per_4096 * (double)K / 4096.0) + c_bytes * (double)M * (double)N / 5.1e6;
 }
 
+// More than 256 rows of FP8-scaled operands on this kernel although the estimates above, made for weights that stay in the
+// caches, say the panels: the panels' tiles then wait for memory (a 4096 x 14336 product takes 155 us at 320 as at 768 rows,
+// and 30 more for the expansion), this kernel reads a quarter of the bytes. Measured on three sets of buffers in turn, 2945
+// sizes of 257 to 1700 rows, N 1000 to 33000, K 1024 to 28672; us on the panels / here / the panels with prepared weights:
+// E5M2 symmetric 768 x 8192 x 8192 149 / 99 / 106; asymmetric 149 / 135 / 105; NVFP4 320 x 8192 x 28672 466 / 167, 640 x
+// 28672 x 8192 461 / 311, 1024 x 8192 x 8192 178 / 136.
+// Up to 768 rows: a product on prepared weights goes where the plain one goes, and beyond 768 rows it reads nothing but the
+// prepared form. For the same reason the estimate here has to be 8 % below that of the panels without the expansion, 12 % up
+// to a K of 4096 (547 x 8960 x 3072, symmetric, prepared, 32 / 36), 15 % for a K below 2048 (757 x 6496 x 1536 26 / 28;
+// below 1024 none: 550 x 13952 x 512 20 / 26), 25 % for one that is no multiple of 256.
+// Tensor-wise scales have no prepared form: their line is against the whole call, they come here up to 1500 rows, by 18 %
+// from 1025 on (at 8 %: 1343 x 6144 x 4096 71 / 81), and alone against 2^27 weight elements or more, there up to 1024 rows
+// (1500 x 28672 x 8192 645 / 770). Beyond 1500 rows the panels (1683 x 9184 x 28672 793 / 881).
+static bool beats_panels(bool asym, int64_t group_size, bool scaled, int64_t M, int64_t N, int64_t K) {
+  if (M <= 256 || M > (scaled ? 1500 : 768) || K < 1024) return false;
+  if (N * K >= (int64_t(1) << 27) && (!scaled || M > 1024)) return false;
+  const int64_t rows32 = (M + 31) / 32, t32 = (N + 31) / 32, t64 = (N + 63) / 64, groups = (M + 63) / 64 * t64;
+  const double k = (double)K, rounds = (double)((groups + 255) / 256);
+  double here = 1.03 * stream_us(asym, group_size, M, N, K, 4.0);
+  if (K % kStreamBlockK == 0 && rounds > 1.0 && rows32 * t32 > 256 && rows32 * t64 > 256) {
+    const double small_groups = group_size == 16 ? (asym ? 1.13 : 1.05) : 1.0, many = rounds > 8.0 ? 1.05 : 1.0;
+    here = 3.5 + (asym ? 10.9 : 7.9) * rounds * small_groups * many * k / 4096.0 + 4.0 * (double)(M * N) / 5.1e6;
+  }
+  // (the estimate of the panels is of weights in the caches too; from K 4608 on it falls short, by a quarter from 13824 on)
+  const double cold = K <= 4608 ? 1.0 : K >= 13824 ? 1.25 : 1.0 + 0.25 * (k - 4608.0) / 9216.0;
+  const double expansion = scaled ? 0.0 : 0.51e-6 * (double)(N * K);
+  const double margin = K % kStreamBlockK != 0 ? 0.75 : M > 1024 ? 0.82 : K < 2048 ? 0.85 : K <= 4096 ? 0.88 : 0.92;
+  return here <= margin * cold * (bf16_path_us(M, N, K, 4.0) - expansion);
+}
+
 // Symmetric power-of-two scales of 32-groups, more than 64 rows: whether the FP4 kernel is the fastest of the three that
 // could take them. Besides the output it takes 11 us + 5 ns K, from K 2048 on 12.8 + 4.2 ns K, while its 256 x 256 tiles
 // fit the compute units once (512 x 11008 x 1024 20 us, 1024 x 4096 x 2048 23, x 4096 31.6, output included); this kernel
@@ -75,8 +105,10 @@ static bool batch_few_rows(int64_t M, int64_t N, int64_t K, int64_t batch) {
 //   single problems from there on, symmetric power-of-two scales: where the estimates above say so
 //   the other formats up to 256 rows, against weights below 2^27 elements: where the estimates of this and of the few-rows
 //     kernel, which shares the dequantized A, say so (256 x 4096 x 4096 17 / 50;  256 x 11008 x 4096 40 / 79;  but 96 x 10240
-//     x 8192 45 / 35;  256 x 5120 x 13824 74 / 70;  256 x 32001 x 4096 99 / 83), always with symmetric scales (256 x 32001 x
-//     4096 73 / 78). Asymmetric power-of-two scales end here (prepared weights beyond 256 rows are their FP6 panel alone);
+//     x 8192 45 / 35;  256 x 5120 x 13824 74 / 70;  256 x 32001 x 4096 99 / 83), always with symmetric scales, from 128 rows
+//     on whatever the weights (256 x 32001 x 4096 73 / 78;  256 x 8192 x 28672 114 / 142, 160 x 28672 x 8192 102 / 110;  but
+//     90 x 8960 x 28672 94 / 72). Asymmetric power-of-two scales end here (prepared weights beyond 256 rows are their FP6
+//     panel alone);
 //   up to 512 rows, and to 768 rows with a long K or few columns: where the estimate is below that of the panels, B's
 //     expansion included (512 x 4096 x 4096 27 / 42;  512 x 4096 x 11008 64 / 101;  448 x 11008 x 4096 61 / 64, but 512 rows
 //     73 / 65;  448 x 4544 x 4544 43 / 48, but 512 rows 58 / 48;  with the same buffers again and again 640 x 8192 x 8192 113 /
@@ -97,7 +129,8 @@ static bool stream_preferred(int scale_kind, bool asym, int64_t group_size, bool
   if (batch != 1) return false;
   const bool pot = group_size == 32 && pot_scales(scale_kind);
   if (pot && !asym) return !fp4_path_supported(M, N, K) ? M <= 256 : !fp4_beats_stream(M, N, K, c_bytes);
-  if (N * K >= (int64_t(1) << 27) && (group_size == 32 || M > 256)) return false;
+  if (!pot && beats_panels(asym, group_size, scaled, M, N, K)) return true;
+  if (N * K >= (int64_t(1) << 27) && (M > 256 || (group_size == 32 && (asym || M < 128)))) return false;
   if (M <= 256 && few_rows) return !asym || stream_us(asym, group_size, M, N, K, c_bytes) <= skinny_path_us(M, N, K);
   if (pot) return M <= 256;
   if (M > 768 || (M > 512 && K < 8192 && (M + 63) / 64 * ((N + 63) / 64) > 512)) return false;

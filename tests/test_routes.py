@@ -130,6 +130,19 @@ def test_routes_of_65_to_768_rows(scale, asym, M, N, K, here):
     assert one_launch(scale, asym, M, N, K) == bool(here)
 
 
+@pytest.mark.parametrize("scale,asym,group,scaled,M,N,K,here", [
+    (E5, 0, 32, 0, 768, 8192, 8192, 1), (E5, 0, 32, 0, 769, 8192, 8192, 0),           # 149 / 99; prepared weights alone
+    (E5, 0, 32, 0, 700, 4096, 14336, 1), (E5, 1, 32, 0, 700, 4096, 14336, 1),
+    (E4, 0, 16, 1, 320, 8192, 28672, 1), (E4, 0, 16, 1, 640, 28672, 8192, 1),         # 466 / 167, 461 / 311
+    (E4, 0, 16, 1, 1500, 28672, 8192, 0), (E4, 0, 16, 1, 1343, 6144, 4096, 0),        # 645 / 770, 71 / 81
+    (E4, 0, 16, 1, 550, 13952, 512, 0), (E5, 0, 32, 0, 547, 8960, 3072, 0),           # 20 / 26; prepared 32 / 36
+    (E5, 0, 32, 0, 400, 28672, 8192, 0), (E5, 0, 32, 0, 160, 28672, 8192, 1), (E5, 0, 32, 0, 90, 8960, 28672, 0),  # 110 / 102, 72 / 94
+    (E4, 0, 16, 1, 1500, 1024, 14336, 1), (E4, 0, 16, 1, 1501, 1024, 14336, 0)])
+def test_routes_of_weights_that_come_from_memory(scale, asym, group, scaled, M, N, K, here):
+    """us on the panels / on this kernel, three sets of buffers in turn."""
+    assert one_launch(scale, asym, M, N, K, 1, group, bool(scaled)) == bool(here)
+
+
 @pytest.mark.parametrize("scale,asym,M,N,K,here", [(E5, 1, 256, 28672, 8192, 1), (E5, 1, 257, 28672, 8192, 0),
                                                    (FLOOR, 1, 256, 22016, 4096, 0), (FLOOR, 1, 128, 22016, 4096, 1),
                                                    (FLOOR, 0, 800, 11008, 1024, 0)])
