@@ -16,8 +16,10 @@
 //   - the element quotient x / S is formed correctly rounded away from FP32 midpoints and exactly when representable,
 //     which keeps it on the right side of every E2M1 boundary (see quotient()), and rounded to E2M1 by the hardware
 //     conversion v_cvt_scalef32_pk_fp4_f32.
-// Strided cast (groups down a column, for V in P.V): one lane per (row, group), the same arithmetic.
+// Strided cast (groups down a column, for V in P.V): one lane per (row, group), the same arithmetic, results through LDS.
 // Whole-row groups (group size -1, as in the code example of Appendix B): one thread block per row, two sweeps.
+#include <type_traits>
+
 #include "cast_core.h"
 #include "device_formats.h"
 
@@ -204,53 +206,83 @@ __global__ __launch_bounds__(256) void quantize_row_kernel(const uint16_t* __res
   }
 }
 
-// Groups run down a column: element (r, k) = x[r + k * k_stride]. One lane owns one (row, group) of GS elements;
-// consecutive lanes own consecutive rows, so each of the GS loads of a wave reads 128 contiguous bytes.
-// grid: (K / GS groups, ceil(rows / 256), batch).
+// Groups run down a column: element (r, k) = x[r + k * k_stride]. A wave casts 64 rows of one group, a lane one row of
+// it, so that each of its GS loads reads 128 contiguous bytes; a workgroup is the 2^waves_log2 waves of groups that
+// follow each other. What bounds it is memory: the groups of a row that lie next to each other are in one workgroup
+// and go out through LDS, so that codes are written in runs of up to 128 bytes and not 16 at a time from several
+// dies, and workgroups that follow each other take the next rows, which read what follows in memory, not 32 rows
+// further down the same few channels. BF16 elements are cast in pairs as in the contiguous cast. us, one wave's 16
+// bytes at a time, workgroups of 256 rows / this: 4096 x 8192 39.9 / 18.5 (reading and writing it once takes 16.7 at
+// the rate of a copy), in NVFP4's groups of 16 46.9 / 19.2, of 64 31.5 / 18.7; kernel alone: 4096 x 2048 9.3 / 5.6,
+// 1024 x 4096 6.2 / 3.7, 32 heads of 128 x 4032 14.3 / 9.0, 128 x 8192 3.5 / 2.7.
+// grid: (ceil(rows / 64), ceil(groups / 2^waves_log2), batch).
+constexpr int strided_piece_bytes(int GS) { return GS == 16 ? 8 : 16; }
+constexpr int kStridedLineElements = 256;  // most elements of a row per workgroup: 128 bytes of codes
+
 template <int SCALE_KIND, bool ASYM, bool TENSOR_SCALED, int GS>
-__global__ __launch_bounds__(256) void quantize_strided_kernel(const uint16_t* __restrict__ x, int64_t rows, int64_t K,
+__global__ __launch_bounds__(512) void quantize_strided_kernel(const uint16_t* __restrict__ x, int64_t rows, int64_t K,
                                                                int64_t k_stride, int64_t batch_stride,
                                                                const float* __restrict__ tensor_pair,
                                                                uint8_t* __restrict__ codes,
-                                                               uint8_t* __restrict__ scales) {
+                                                               uint8_t* __restrict__ scales, int waves_log2) {
+  constexpr int kPiece = strided_piece_bytes(GS), kPieces = GS / 2 / kPiece, kPad = 16;
+  using piece_t = std::conditional_t<kPiece == 8, uint2, uint4>;
+  using scale_t = std::conditional_t<ASYM, uint16_t, uint8_t>;
+  __shared__ __attribute__((aligned(16))) uint8_t lds_codes[64 * (kStridedLineElements / 2 + kPad)];
+  __shared__ scale_t lds_scales[512];
   const int64_t G = K / GS;
-  x += (int64_t)blockIdx.z * batch_stride;
-  codes += (int64_t)blockIdx.z * rows * (K >> 1);
-  scales += (int64_t)blockIdx.z * rows * G * (ASYM ? 2 : 1);
-  const int64_t r = (int64_t)blockIdx.y * 256 + threadIdx.x;
-  const int64_t g = blockIdx.x;
-  if (r >= rows) return;
-  const uint16_t* p = x + r + g * GS * k_stride;
-  float rt = 1.0f;
-  if constexpr (TENSOR_SCALED) rt = tensor_pair[1];
-  float y[GS];
+  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), lane = (int)threadIdx.x & 63;
+  const int pitch = ((GS / 2) << waves_log2) + kPad;
+  const int64_t r0 = (int64_t)blockIdx.x * 64, g0 = (int64_t)blockIdx.y << waves_log2, r = r0 + lane, g = g0 + wave;
+  if (r < rows && g < G) {
+    const uint16_t* p = x + (int64_t)blockIdx.z * batch_stride + g * GS * k_stride + r;
+    uint32_t d[GS / 2], code[GS / 8], sb_p, sb_n;
 #pragma unroll
-  for (int i = 0; i < GS; ++i) {
-    y[i] = u2f((uint32_t)p[i * k_stride] << 16);
-    if constexpr (TENSOR_SCALED) y[i] *= rt;
-  }
-  uint32_t amax_p, amax_n;
-  class_extrema<ASYM>(y, amax_p, amax_n);
-  float s_pos, r_pos, s_neg, r_neg;
-  const uint32_t sb_p = encode_scale_sr<SCALE_KIND>(u2f(amax_p), s_pos, r_pos);
-  uint32_t sb_n = sb_p;
-  s_neg = s_pos, r_neg = r_pos;
-  if constexpr (ASYM) sb_n = encode_scale_sr<SCALE_KIND>(u2f(amax_n), s_neg, r_neg);
-  uint32_t* out = reinterpret_cast<uint32_t*>(codes + r * (K >> 1) + g * (GS / 2));
+    for (int i = 0; i < GS / 2; ++i) d[i] = p[2 * i * k_stride] | ((uint32_t)p[(2 * i + 1) * k_stride] << 16);
+    if constexpr (TENSOR_SCALED) {
+      const float rt = tensor_pair[1];
+      float y[GS];
 #pragma unroll
-  for (int t = 0; t < GS / 16; ++t) {
-    const float lo[8] = {y[16 * t], y[16 * t + 1], y[16 * t + 2], y[16 * t + 3],
-                         y[16 * t + 4], y[16 * t + 5], y[16 * t + 6], y[16 * t + 7]};
-    const float hi[8] = {y[16 * t + 8], y[16 * t + 9], y[16 * t + 10], y[16 * t + 11],
-                         y[16 * t + 12], y[16 * t + 13], y[16 * t + 14], y[16 * t + 15]};
-    *reinterpret_cast<uint2*>(out + 2 * t) =
-        make_uint2(encode8<SCALE_KIND, ASYM>(lo, s_pos, r_pos, s_neg, r_neg),
-                   encode8<SCALE_KIND, ASYM>(hi, s_pos, r_pos, s_neg, r_neg));
+      for (int i = 0; i < GS / 2; ++i) y[2 * i] = u2f(d[i] << 16) * rt, y[2 * i + 1] = u2f(d[i] & 0xFFFF0000u) * rt;
+      uint32_t amax_p, amax_n;
+      class_extrema<ASYM>(y, amax_p, amax_n);
+      float s_pos, r_pos, s_neg, r_neg;
+      sb_p = encode_scale_sr<SCALE_KIND>(u2f(amax_p), s_pos, r_pos);
+      sb_n = sb_p, s_neg = s_pos, r_neg = r_pos;
+      if constexpr (ASYM) sb_n = encode_scale_sr<SCALE_KIND>(u2f(amax_n), s_neg, r_neg);
+#pragma unroll
+      for (int t = 0; t < GS / 8; ++t) {
+        const float y8[8] = {y[8 * t], y[8 * t + 1], y[8 * t + 2], y[8 * t + 3],
+                             y[8 * t + 4], y[8 * t + 5], y[8 * t + 6], y[8 * t + 7]};
+        code[t] = encode8<SCALE_KIND, ASYM>(y8, s_pos, r_pos, s_neg, r_neg);
+      }
+    } else {
+      cast_words_bf16<SCALE_KIND, ASYM, GS>(d, 0, code, sb_p, sb_n);
+    }
+    piece_t* out = reinterpret_cast<piece_t*>(lds_codes + lane * pitch + wave * (GS / 2));
+#pragma unroll
+    for (int t = 0; t < kPieces; ++t) {
+      if constexpr (kPiece == 8)
+        out[t] = make_uint2(code[2 * t], code[2 * t + 1]);
+      else
+        out[t] = make_uint4(code[4 * t], code[4 * t + 1], code[4 * t + 2], code[4 * t + 3]);
+    }
+    lds_scales[(lane << waves_log2) + wave] = (scale_t)(ASYM ? sb_p | (sb_n << 8) : sb_p);
   }
-  if constexpr (ASYM)
-    *reinterpret_cast<uint16_t*>(scales + (r * G + g) * 2) = (uint16_t)(sb_p | (sb_n << 8));
-  else
-    scales[r * G + g] = (uint8_t)sb_p;
+  __syncthreads();
+  codes += (int64_t)blockIdx.z * rows * (K >> 1) + g0 * (GS / 2);
+  scales += (int64_t)blockIdx.z * rows * G * sizeof(scale_t);
+#pragma unroll
+  for (int t = 0; t < kPieces; ++t) {
+    const int i = t * (64 << waves_log2) + (int)threadIdx.x;
+    const int row = i / kPieces >> waves_log2, c = i & ((kPieces << waves_log2) - 1);
+    if (r0 + row < rows && g0 + c / kPieces < G)
+      *reinterpret_cast<piece_t*>(codes + (r0 + row) * (K >> 1) + c * kPiece) =
+          *reinterpret_cast<const piece_t*>(lds_codes + row * pitch + c * kPiece);
+  }
+  const int row = (int)threadIdx.x >> waves_log2, c = (int)threadIdx.x & ((1 << waves_log2) - 1);
+  if (r0 + row < rows && g0 + c < G)
+    reinterpret_cast<scale_t*>(scales)[(r0 + row) * G + g0 + c] = lds_scales[threadIdx.x];
 }
 
 // Tensor-wise scale (Sec. 5.3, double scaling): the largest magnitude of a BF16 tensor, then
@@ -473,13 +505,19 @@ template <int SK, bool ASYM, int GS>
 static hipError_t launch_qs(const uint16_t* x, int64_t rows, int64_t K, int64_t k_stride, int64_t batch,
                             int64_t batch_stride, const float* tensor_pair, uint8_t* codes, uint8_t* scales,
                             hipStream_t s) {
-  const dim3 grid((unsigned)(K / GS), (unsigned)((rows + 255) / 256), (unsigned)batch);
+  const int64_t row_blocks = (rows + 63) / 64, G = K / GS;
+  // Runs of 128 bytes of codes (64 in groups of 16), shorter ones while there are fewer workgroups than three quarters
+  // of the compute units (kernel, us, one group to a workgroup / the run this picks: 4096 x 2048 6.9 / 5.6, 32 x 128 x
+  // 4032 14.3 / 9.0; twice as many workgroups / this: 8 x 128 x 1536 3.3 / 2.8; half as many / this: 4096 x 512 3.2 / 2.8).
+  int wl = GS == 128 ? 1 : GS == 64 ? 2 : 3;
+  while (wl > 0 && row_blocks * ((G + (1 << wl) - 1) >> wl) * batch < 192) --wl;
+  const dim3 grid((unsigned)row_blocks, (unsigned)((G + (1 << wl) - 1) >> wl), (unsigned)batch);
   if (tensor_pair)
-    hipLaunchKernelGGL((quantize_strided_kernel<SK, ASYM, true, GS>), grid, dim3(256), 0, s, x, rows, K, k_stride,
-                       batch_stride, tensor_pair, codes, scales);
+    hipLaunchKernelGGL((quantize_strided_kernel<SK, ASYM, true, GS>), grid, dim3(64 << wl), 0, s, x, rows, K, k_stride,
+                       batch_stride, tensor_pair, codes, scales, wl);
   else
-    hipLaunchKernelGGL((quantize_strided_kernel<SK, ASYM, false, GS>), grid, dim3(256), 0, s, x, rows, K, k_stride,
-                       batch_stride, tensor_pair, codes, scales);
+    hipLaunchKernelGGL((quantize_strided_kernel<SK, ASYM, false, GS>), grid, dim3(64 << wl), 0, s, x, rows, K, k_stride,
+                       batch_stride, tensor_pair, codes, scales, wl);
   return hipGetLastError();
 }
 

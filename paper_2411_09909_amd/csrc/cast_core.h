@@ -1,6 +1,6 @@
 // The cast of BF16 elements held in registers (Appendix B Algorithm 1 with the sign-dependent scale pair of Sec. 4.2
 // Eq. 1): shared by the cast kernels and by kernels that cast what they have just computed. A lane holds N / 2 words
-// of two BF16 each (N = 8 or 16 consecutive elements of one row); the 2^lanes_log2 neighbouring lanes of a wave hold
+// of two BF16 each (N = 8, 16 .. consecutive elements of one row); the 2^lanes_log2 neighbouring lanes of a wave hold
 // one group. The arithmetic and why it decides as exact arithmetic does: the BF16 section of cast_math.h.
 #pragma once
 #include "cast_math.h"
@@ -79,23 +79,25 @@ __device__ __forceinline__ uint32_t encode8_bf16(const uint32_t (&d)[4], float r
 template <int SCALE_KIND, bool ASYM, int N>
 __device__ __forceinline__ void cast_words_bf16(const uint32_t (&d)[N / 2], int lanes_log2, uint32_t (&code)[N / 8],
                                                 uint32_t& sb_p, uint32_t& sb_n) {
-  static_assert(N == 8 || N == 16, "8 or 16 elements per lane");
+  static_assert(N % 8 == 0, "whole words of codes");
   uint32_t m;
   if constexpr (ASYM) {
     const uint32_t f = 0x80008000u;
     uint32_t p = pk_max_i16(pk_max_i16(d[0], d[1]), pk_max_i16(d[2], d[3]));
     uint32_t n = pk_max_i16(pk_max_i16(d[0] ^ f, d[1] ^ f), pk_max_i16(d[2] ^ f, d[3] ^ f));
-    if constexpr (N == 16) {
-      p = pk_max_i16(p, pk_max_i16(pk_max_i16(d[4], d[5]), pk_max_i16(d[6], d[7])));
-      n = pk_max_i16(n, pk_max_i16(pk_max_i16(d[4] ^ f, d[5] ^ f), pk_max_i16(d[6] ^ f, d[7] ^ f)));
+#pragma unroll
+    for (int t = 4; t < N / 2; t += 4) {
+      p = pk_max_i16(p, pk_max_i16(pk_max_i16(d[t], d[t + 1]), pk_max_i16(d[t + 2], d[t + 3])));
+      n = pk_max_i16(n, pk_max_i16(pk_max_i16(d[t] ^ f, d[t + 1] ^ f), pk_max_i16(d[t + 2] ^ f, d[t + 3] ^ f)));
     }
     const uint32_t pl = pk_max_i16(p, p >> 16), nh = pk_max_i16(n, n << 16);
     m = pk_max_i16((pl & 0xFFFFu) | (nh & 0xFFFF0000u), 0u);
   } else {
     const uint32_t k = 0x7FFF7FFFu;
     uint32_t a = pk_max_i16(pk_max_i16(d[0] & k, d[1] & k), pk_max_i16(d[2] & k, d[3] & k));
-    if constexpr (N == 16)
-      a = pk_max_i16(a, pk_max_i16(pk_max_i16(d[4] & k, d[5] & k), pk_max_i16(d[6] & k, d[7] & k)));
+#pragma unroll
+    for (int t = 4; t < N / 2; t += 4)
+      a = pk_max_i16(a, pk_max_i16(pk_max_i16(d[t] & k, d[t + 1] & k), pk_max_i16(d[t + 2] & k, d[t + 3] & k)));
     m = pk_max_i16(a, a >> 16) & 0xFFFFu;
   }
   m = group_max_pk16(m, lanes_log2);

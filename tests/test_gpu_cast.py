@@ -111,6 +111,19 @@ def test_row_stride_and_strided_axis(scale, asym):
     assert np.array_equal(gc, rc) and np.array_equal(gs, rs)
 
 
+@pytest.mark.parametrize("scale,asym,gs", [(ref.FP8_E5M2, 1, 32), (ref.E8M0_FLOOR, 0, 32), (ref.FP8_E4M3, 0, 16),
+                                           (ref.FP8_E4M3, 1, 16), (ref.FP8_E5M2, 1, 64), (ref.FP8_E5M2, 0, 128)])
+@pytest.mark.parametrize("rows,groups", [(2, 2), (63, 3), (64, 8), (65, 9), (130, 17), (1000, 140), (960, 136)])
+def test_strided_cast_at_the_edges_of_its_workgroups(rows, groups, scale, asym, gs):
+    """64 rows x up to 8 groups per workgroup, fewer groups where that leaves compute units idle: partial ones of both
+    kinds, exactly the oracle's bytes."""
+    K = gs * groups + (gs if gs == 16 and groups % 2 else 0)
+    v = synth.activations(K, rows, seed=rows + groups, n_outlier=2, outlier_gain=30.0)
+    gc, gsc = G.gpu_quantize(v, scale, asym, k_axis=0, group_size=gs)
+    rc, rs = ref.quantize(v, gs, scale, asym, k_axis=0)
+    assert np.array_equal(gc, rc) and np.array_equal(gsc, rs)
+
+
 @pytest.mark.parametrize("scale,asym", [(ref.FP8_E5M2, 1), (ref.E8M0_FLOOR, 0)])
 def test_batched_cast_equals_the_oracle_per_operand(scale, asym):
     """Several operands in one launch (the heads of an attention layer): along the rows (Q, K), down the columns (V),
