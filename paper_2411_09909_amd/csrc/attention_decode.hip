@@ -5,7 +5,8 @@
 //   - K and V are read as they are stored, packed codes and scale bytes, and dequantized in registers to exact 16-bit
 //     floats (no BF16 panels in a workspace: a quarter of the bytes, and no expansion pass in front);
 //   - the query heads that share a key / value head, and their few queries, are the 32 columns of ONE wave
-//     (q_heads / kv_heads * Sq <= 32), so every K and V byte is read by one wave only;
+//     (q_heads / kv_heads * Sq <= 32), so every K and V byte is read by one wave only. Up to 16 columns
+//     attention_decode_16.hip takes the call (the rule and its times are there), with the same combination;
 //   - the keys are the parallelism: the key tiles are cut into `key_splits` contiguous ranges, one wave per (key / value
 //     head, range), no barriers (LDS only as a wave's own staging space for V); each wave leaves its un-normalised
 //     result, running maximum and sum in the workspace and a second kernel combines the ranges exactly:

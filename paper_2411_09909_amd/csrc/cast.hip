@@ -231,6 +231,8 @@ __global__ __launch_bounds__(512) void quantize_strided_kernel(const uint16_t* _
   __shared__ __attribute__((aligned(16))) uint8_t lds_codes[64 * (kStridedLineElements / 2 + kPad)];
   __shared__ scale_t lds_scales[512];
   const int64_t G = K / GS;
+  codes += (int64_t)blockIdx.z * rows * (K >> 1);
+  scales += (int64_t)blockIdx.z * rows * G * sizeof(scale_t);
   const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), lane = (int)threadIdx.x & 63;
   const int pitch = ((GS / 2) << waves_log2) + kPad;
   const int64_t r0 = (int64_t)blockIdx.x * 64, g0 = (int64_t)blockIdx.y << waves_log2, r = r0 + lane, g = g0 + wave;
@@ -259,19 +261,27 @@ __global__ __launch_bounds__(512) void quantize_strided_kernel(const uint16_t* _
     } else {
       cast_words_bf16<SCALE_KIND, ASYM, GS>(d, 0, code, sb_p, sb_n);
     }
-    piece_t* out = reinterpret_cast<piece_t*>(lds_codes + lane * pitch + wave * (GS / 2));
+    const scale_t scale = (scale_t)(ASYM ? sb_p | (sb_n << 8) : sb_p);
+    auto put = [&](piece_t* out) {
 #pragma unroll
-    for (int t = 0; t < kPieces; ++t) {
-      if constexpr (kPiece == 8)
-        out[t] = make_uint2(code[2 * t], code[2 * t + 1]);
-      else
-        out[t] = make_uint4(code[4 * t], code[4 * t + 1], code[4 * t + 2], code[4 * t + 3]);
+      for (int t = 0; t < kPieces; ++t) {
+        if constexpr (kPiece == 8)
+          out[t] = make_uint2(code[2 * t], code[2 * t + 1]);
+        else
+          out[t] = make_uint4(code[4 * t], code[4 * t + 1], code[4 * t + 2], code[4 * t + 3]);
+      }
+    };
+    if (waves_log2 == 0) {  // nothing to put together (through LDS, 32 x 1024 in MXFP4 2.08 us instead of 2.00)
+      put(reinterpret_cast<piece_t*>(codes + r * (K >> 1) + g * (GS / 2)));
+      reinterpret_cast<scale_t*>(scales)[r * G + g] = scale;
+    } else {
+      put(reinterpret_cast<piece_t*>(lds_codes + lane * pitch + wave * (GS / 2)));
+      lds_scales[(lane << waves_log2) + wave] = scale;
     }
-    lds_scales[(lane << waves_log2) + wave] = (scale_t)(ASYM ? sb_p | (sb_n << 8) : sb_p);
   }
+  if (waves_log2 == 0) return;
   __syncthreads();
-  codes += (int64_t)blockIdx.z * rows * (K >> 1) + g0 * (GS / 2);
-  scales += (int64_t)blockIdx.z * rows * G * sizeof(scale_t);
+  codes += g0 * (GS / 2);
 #pragma unroll
   for (int t = 0; t < kPieces; ++t) {
     const int i = t * (64 << waves_log2) + (int)threadIdx.x;

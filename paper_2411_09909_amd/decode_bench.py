@@ -64,7 +64,7 @@ def _run(args, splits_wanted):
         ms = timed(lambda: binding.attention_decode(fmt, *ops, scale, True, key_splits=splits, out=out, workspace=ws),
                    args.steps)
         res["decode"][str(splits)] = {"us": round(ms * 1e3, 1), "cache_GB_per_s": round(cache_bytes / (ms * 1e-3) / 1e9, 1),
-                                      "waves": G * splits}
+                                      "ranges": G * splits}
     ws = torch.empty(binding.attention_workspace_bytes(fmt, H, G, Sq, Sk, D), dtype=torch.uint8, device=dev)
     ms = timed(lambda: binding.attention(fmt, *ops, scale, True, out=out, workspace=ws), args.steps)
     res["many_queries_kernel_us"] = round(ms * 1e3, 1)
