@@ -561,7 +561,8 @@ int bf16_tile_refined(int choice, int64_t M, int64_t N, int64_t K, int64_t batch
 // whole_lines: every row of C is whole 128-byte lines, or C is BF16. Stores of rows that are not take longer, and in the larger
 // tiles there is less beside them: 192 x 256 then takes the place of 64 x 256 only with a K beyond 4096 (1323 x 11008 x 4096 167
 // / 183, 2570 x 6144 x 4096 170 / 177;  1124 x 13824 x 5120 ratio 0.93), that of 256 x 128 with one beyond 2048 (1349 x 16384 x
-// 2048 144 / 149).
+// 2048 144 / 149). (These figures are from before such rows were stored row by row and through the caches; on both sides of
+// the lines for them, here and below, 10 of 145 sizes then differed by more than 3 %, in either direction.)
 int bf16_tile(int64_t M, int64_t N, int64_t K, int64_t batch, bool gated, bool prepared, bool whole_lines) {
   const int choice = bf16_tile_choice(M, N, batch), refined = bf16_tile_refined(choice, M, N, K, batch, gated);
   const bool one_round = ((M + 255) / 256) * ((N + 127) / 128) <= 256;
