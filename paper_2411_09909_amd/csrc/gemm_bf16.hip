@@ -149,7 +149,7 @@ __global__ __launch_bounds__(256) void expand_pair_kernel(ExpandJob ja, ExpandJo
 // (Sec. 5.3, double scaling), read from device memory after the main loop.
 // GLU: the gated-activation epilogue of store_glu_tiles() instead of the FP32 store: C is then the BF16 output
 // [M][ldc] with N / 2 columns.
-template <int WM, int WN, int FM, int FN, bool SCALED, bool GLU = false>
+template <int WM, int WN, int FM, int FN, bool SCALED, bool GLU = false, StoreWay WAY = kStoreRows>
 __global__ __launch_bounds__(64 * WM * WN) void gemm_bf16_kernel(const uint16_t* __restrict__ Ap,
                                                                  const uint16_t* __restrict__ Bp, float* __restrict__ C,
                                                                  int64_t M, int64_t N, int64_t Mp, int64_t Np,
@@ -292,11 +292,11 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_bf16_kernel(const uint16_t*
     store_glu_tiles<FM, FN>(acc, stage, reinterpret_cast<uint16_t*>(C) + b * M * ldc, M, N >> 1, ldc,
                             (int64_t)tm * Cfg::kTileM + wm * FM * 32, (int64_t)tn * Cfg::kTileN + wn * FN * 32);
   } else if constexpr (SCALED)
-    store_c_tiles<FM, FN, 0, true>(acc, C + b * M * ldc, M, N, Kp, ldc, (int64_t)tm * Cfg::kTileM + wm * FM * 32,
-                                   (int64_t)tn * Cfg::kTileN + wn * FN * 32, alpha_a[0] * alpha_b[0]);
+    store_c_tiles<FM, FN, WAY, 0, true>(acc, C + b * M * ldc, M, N, ldc, (int64_t)tm * Cfg::kTileM + wm * FM * 32,
+                                        (int64_t)tn * Cfg::kTileN + wn * FN * 32, alpha_a[0] * alpha_b[0]);
   else
-    store_c_tiles<FM, FN>(acc, C + b * M * ldc, M, N, Kp, ldc, (int64_t)tm * Cfg::kTileM + wm * FM * 32,
-                          (int64_t)tn * Cfg::kTileN + wn * FN * 32);
+    store_c_tiles<FM, FN, WAY>(acc, C + b * M * ldc, M, N, ldc, (int64_t)tm * Cfg::kTileM + wm * FM * 32,
+                                         (int64_t)tn * Cfg::kTileN + wn * FN * 32);
 }
 
 template <int SK, bool ASYM, bool F16 = false>
@@ -457,6 +457,26 @@ static int64_t largest_share(int tiles_m, int tiles_n, int tile_rows, int tile_c
   return super_m == 0 ? grid / 8 : supertile_share(tiles_m, tiles_n).most;
 }
 
+// Row by row, the column tiles of a row one after the other: where rows are no whole lines, a line is written by two stores, and they
+// meet in L2 only if they are close. Streaming, except for rows that are not even half lines, a C below 80 MB and a K up to 4096: the two
+// halves of a line then wait for each other in the caches; with a deeper K the operands need those (panels, 1400 x 2161 x 8192 73.4 /
+// 72.5 / 75.3). us, column by column / row by row / row by row through the caches: FP4 3000 x 5001 x 4096 76 / 49 / 41, 4096 x 10001 x
+// 1024 160 / 83 / 75, 4096 x 32001 x 4096 532 / 297 / 354, FP6 4096 x 4545 x 4544 141 / 109 / 104, BF16 panels 4096 x 32001 x 4096 1126 /
+// 917 / 892, 1400 x 50257 x 2048 423 / 319 / 364. The 80 MB are of one problem of a batch: its problems are written one after
+// the other (FP4 64 x 512 x 1001 x 256 116 / 57 / 39, 32 x 1000 x 2001 x 512, 256 MB in all, 222 / 102 / 95, panels 32 x 512 x
+// 4097 x 128 238 / 116 / 97).
+// Whole lines, too, are stored faster row by row (FP4 4096 x 4096 x 512 23.8 / 22.3, 2048 x 11008 x 4096 68.3 / 67.2, 4096 x 32000 x
+// 4096 273 / 269, panels 4096 x 11008 x 512 77.0 / 75.6; through the caches they take a tenth longer), but not at a pitch of 8192,
+// 16384 or 32768 elements, where the rows of a tile lie on few memory channels: FP4 2048 x 8192 x 512 24.0 / 30.1, 4096 x 8192 x
+// 4096 83 / 91, 4096 x 16384 x 512 77 / 81, 4096 x 32768 x 512 158 / 169, panels 2048 x 8192 x 1024 49.6 / 53.5, half lines at such a
+// pitch FP4 4096 x 8192 x 1024 53 / 66 (but 3000 x 16384 x 2048 86.3 / 85.4; at 4096 elements 26.6 / 25.4 for 3000 x 4096 x 2048, at 24576
+// 55.2 / 50.6 for 2048 x 24576 x 512; not even half lines 119 / 86).
+StoreWay store_way(const float* C, int64_t M, int64_t K, int64_t pitch) {
+  const bool half_lines = ((reinterpret_cast<uintptr_t>(C) | (uintptr_t)pitch) & 63) == 0;
+  if (half_lines && pitch >= 32768 && (pitch & (pitch - 1)) == 0) return kStoreColumns;
+  return half_lines || K > 4096 || M * pitch >= 80000000 ? kStoreRows : kStoreRowsCached;
+}
+
 template <int WM, int WN, int FM, int FN>
 static hipError_t launch_tiles(const uint16_t* Ap, const uint16_t* Bp, float* C, int64_t M, int64_t N, int64_t Mp,
                                int64_t Np, int64_t Kp, int64_t ldc, int64_t batch, const float* alpha_a,
@@ -473,11 +493,15 @@ static hipError_t launch_tiles(const uint16_t* Ap, const uint16_t* Bp, float* C,
     else
       return hipErrorInvalidValue;
   } else if (alpha_a && alpha_b)
-    hipLaunchKernelGGL((gemm_bf16_kernel<WM, WN, FM, FN, true>), dim3(grid, 1, (unsigned)batch), dim3(Cfg::kThreads), 0,
-                       s, Ap, Bp, C, M, N, Mp, Np, Kp, ldc, tiles_m, tiles_n, super_m, alpha_a, alpha_b);
+    in_store_way(C, M, Kp, ldc, [&]<StoreWay WAY>() {
+      hipLaunchKernelGGL((gemm_bf16_kernel<WM, WN, FM, FN, true, false, WAY>), dim3(grid, 1, (unsigned)batch), dim3(Cfg::kThreads), 0, s,
+                         Ap, Bp, C, M, N, Mp, Np, Kp, ldc, tiles_m, tiles_n, super_m, alpha_a, alpha_b);
+    });
   else
-    hipLaunchKernelGGL((gemm_bf16_kernel<WM, WN, FM, FN, false>), dim3(grid, 1, (unsigned)batch), dim3(Cfg::kThreads),
-                       0, s, Ap, Bp, C, M, N, Mp, Np, Kp, ldc, tiles_m, tiles_n, super_m, alpha_a, alpha_b);
+    in_store_way(C, M, Kp, ldc, [&]<StoreWay WAY>() {
+      hipLaunchKernelGGL((gemm_bf16_kernel<WM, WN, FM, FN, false, false, WAY>), dim3(grid, 1, (unsigned)batch), dim3(Cfg::kThreads), 0, s,
+                         Ap, Bp, C, M, N, Mp, Np, Kp, ldc, tiles_m, tiles_n, super_m, alpha_a, alpha_b);
+    });
   return hipGetLastError();
 }
 

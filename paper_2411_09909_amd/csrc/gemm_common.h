@@ -69,6 +69,23 @@ typedef __attribute__((address_space(3))) void* lds_ptr_t;
 
 typedef float f32x16 __attribute__((ext_vector_type(16)));  // accumulator of one 32x32 MFMA tile
 
+// In which order, and under which cache policy, a wave stores its tiles. A template parameter of the kernels: three epilogues in one
+// kernel read all accumulators out before the branch (FP6 4096 x 4545 x 4544 113 us, this 109; panels 1400 x 32001 x 2048 207, 198;
+// FP4 2048 x 11008 x 4096 70.5, 69.2).
+enum StoreWay : int { kStoreRows, kStoreRowsCached, kStoreColumns };
+// C: of the whole call; pitch: bytes between its rows. (gemm_bf16.hip)
+StoreWay store_way(const float* C, int64_t M, int64_t K, int64_t pitch);
+
+// Launches the kernel built for the way of the call: launch.operator()<WAY>().
+template <typename Launch>
+void in_store_way(const float* C, int64_t M, int64_t K, int64_t ldc, const Launch& launch) {
+  switch (store_way(C, M, K, ldc * 4)) {
+    case kStoreColumns: return launch.template operator()<kStoreColumns>();
+    case kStoreRows: return launch.template operator()<kStoreRows>();
+    default: return launch.template operator()<kStoreRowsCached>();
+  }
+}
+
 // Stores a wave's FM x FN accumulator tiles of 32x32 into C (row-major, leading dimension ldc), multiplied by
 // 2^SCALE_LOG2 (0, or the power of two that undoes an operand bias) and, with ALPHA, by the run-time factor alpha.
 // row_base / col_base: first row / column of the wave's tiles.
@@ -87,9 +104,9 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));  // accumulator of on
 // store then covers 32 rows x 32 bytes instead of two whole 128-byte lines and the tile took 36 us; with the tiles
 // turned through LDS so that a lane stores 16 bytes of a whole row (64 store instructions per wave instead of 256)
 // it took the same 7 us as this form.)
-template <int FM, int FN, int SCALE_LOG2 = 0, bool ALPHA = false>
+template <int FM, int FN, StoreWay WAY, int SCALE_LOG2 = 0, bool ALPHA = false>
 __device__ __forceinline__ void store_c_tiles(const f32x16 (&acc)[FM][FN], float* __restrict__ Cb, int64_t M,
-                                              int64_t N, int64_t K, int64_t ldc, int64_t row_base, int64_t col_base,
+                                              int64_t N, int64_t ldc, int64_t row_base, int64_t col_base,
                                               float alpha = 1.0f) {
   const int64_t rows_left = M - row_base, cols_left = N - col_base;  // uniform over the wave
   if (rows_left <= 0 || cols_left <= 0) return;
@@ -106,35 +123,29 @@ __device__ __forceinline__ void store_c_tiles(const f32x16 (&acc)[FM][FN], float
     const int col = j * 32 + (lane & 31);
     lane_off[j] = col < cols_valid ? (uint32_t)col * 4u + (uint32_t)(4 * (lane >> 5)) * pitch : 0x80000000u;
   }
-  // A row's column tiles one after the other: where rows are no whole lines, a line is written by two stores, and they meet in L2
-  // only if they are close (column by column, as it was, us / row by row / row by row through the caches: FP4 3000 x 5001 x 4096 76 /
-  // 49 / 41, 4096 x 10001 x 1024 160 / 83 / 75, 4096 x 32001 x 4096 532 / 322 / 354, FP6 4096 x 4545 x 4544 141 / 112 / 104, BF16
-  // panels 4096 x 32001 x 4096 1126 / 917 / 892, 1400 x 50257 x 2048 423 / 319 / 364). Streaming stores except for rows that are not
-  // even half lines, a C below 80 MB and a K up to 4096: the two halves of a line then wait for each other in the caches. With a
-  // deeper K the operands need the caches (panels, 1400 x 2161 x 8192 73.4 / 72.5 / 75.3), and whole lines stream in either order
-  // alike, through the caches they take a tenth longer (4096 x 32000 x 4096 266 / 266 / 309).
-  auto store = [&]<int POLICY>() {
-#pragma unroll
-    for (int i = 0; i < FM; ++i) {
-#pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        const uint32_t row_off = (uint32_t)(i * 32 + 8 * (v >> 2) + (v & 3)) * pitch;
-#pragma unroll
-        for (int j = 0; j < FN; ++j) {
-          float c = acc[i][j][v];
-          if constexpr (SCALE_LOG2 != 0) c *= (float)(1 << SCALE_LOG2);
-          if constexpr (ALPHA) c *= alpha;
-          __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, c), window, (int)lane_off[j], (int)row_off, POLICY);
-        }
-      }
-    }
+  auto store = [&](int i, int j, int v) {
+    float c = acc[i][j][v];
+    if constexpr (SCALE_LOG2 != 0) c *= (float)(1 << SCALE_LOG2);
+    if constexpr (ALPHA) c *= alpha;
+    const uint32_t row_off = (uint32_t)(i * 32 + 8 * (v >> 2) + (v & 3)) * pitch;
+    __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, c), window, (int)lane_off[j], (int)row_off,
+                                          WAY == kStoreRowsCached ? 0 : 2 /* non-temporal */);
   };
-  constexpr int kStreaming = 2, kCached = 0;
-  const bool half_lines = ((reinterpret_cast<uintptr_t>(Cb) | pitch) & 63) == 0;
-  if (half_lines || K > 4096 || (uint64_t)M * pitch >= 80000000u)
-    store.template operator()<kStreaming>();
-  else
-    store.template operator()<kCached>();
+  if constexpr (WAY == kStoreColumns) {
+#pragma unroll
+    for (int j = 0; j < FN; ++j)
+#pragma unroll
+      for (int i = 0; i < FM; ++i)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) store(i, j, v);
+  } else {
+#pragma unroll
+    for (int i = 0; i < FM; ++i)
+#pragma unroll
+      for (int v = 0; v < 16; ++v)
+#pragma unroll
+        for (int j = 0; j < FN; ++j) store(i, j, v);
+  }
 }
 
 // The gated-activation epilogue: the wave's column tiles come in pairs (gate columns, up columns: the B operand's rows

@@ -69,7 +69,7 @@ __device__ __forceinline__ uint4 expand_scale1(const uint32_t (&r)[4], uint32_t 
   return make_uint4(o[0], o[1], o[2], o[3]);
 }
 
-template <bool ASYM>
+template <bool ASYM, StoreWay WAY>
 __global__ __launch_bounds__(512) void gemm_e5m2_kernel(const uint8_t* __restrict__ Ac, const uint8_t* __restrict__ As,
                                                         const uint8_t* __restrict__ Bc, const uint8_t* __restrict__ Bs,
                                                         float* __restrict__ C, int64_t M, int64_t N, int64_t K,
@@ -292,7 +292,7 @@ __global__ __launch_bounds__(512) void gemm_e5m2_kernel(const uint8_t* __restric
 #undef AMX_RAW_READ
 #undef AMX_ISSUE_RAW
 
-  store_c_tiles<FM, FN, 6 /* 2^6 undoes the operand bias */>(acc, C + b * M * ldc, M, N, K, ldc, (int64_t)tm * kE5Tile + wm * FM * 32,
+  store_c_tiles<FM, FN, WAY, 6 /* 2^6 undoes the operand bias */>(acc, C + b * M * ldc, M, N, ldc, (int64_t)tm * kE5Tile + wm * FM * 32,
                         (int64_t)tn * kE5Tile + wn * FN * 32);
 }
 
@@ -309,12 +309,12 @@ hipError_t launch_gemm_e5m2_fused(bool asym, int64_t M, int64_t N, int64_t K, co
   const dim3 grid(supertile_grid(tiles_m, tiles_n, kE5Tile, kE5Tile, batch, super_m), 1, (unsigned)batch);
   hipError_t e;
   if (timer.start && (e = hipEventRecord(timer.start, s)) != hipSuccess) return e;
-  if (asym)
-    hipLaunchKernelGGL((gemm_e5m2_kernel<true>), grid, dim3(512), 0, s, A_codes, A_scales, B_codes, B_scales, C, M, N,
-                       K, ldc, tiles_m, tiles_n, super_m);
-  else
-    hipLaunchKernelGGL((gemm_e5m2_kernel<false>), grid, dim3(512), 0, s, A_codes, A_scales, B_codes, B_scales, C, M, N,
-                       K, ldc, tiles_m, tiles_n, super_m);
+  in_store_way(C, M, K, ldc, [&]<StoreWay WAY>() {
+    if (asym)
+      hipLaunchKernelGGL((gemm_e5m2_kernel<true, WAY>), grid, dim3(512), 0, s, A_codes, A_scales, B_codes, B_scales, C, M, N, K, ldc, tiles_m, tiles_n, super_m);
+    else
+      hipLaunchKernelGGL((gemm_e5m2_kernel<false, WAY>), grid, dim3(512), 0, s, A_codes, A_scales, B_codes, B_scales, C, M, N, K, ldc, tiles_m, tiles_n, super_m);
+  });
   if ((e = hipGetLastError()) != hipSuccess) return e;
   if (timer.stop) e = hipEventRecord(timer.stop, s);
   return e;
@@ -333,7 +333,7 @@ hipError_t launch_gemm_e5m2_fused(bool asym, int64_t M, int64_t N, int64_t K, co
 // ring two steps ahead, B fragments of the whole slice already in registers), reads the B fragments of slice q+1 into
 // the other register set, expands slice q+2 (raw data in registers) into the fragment buffer that slice q's fragments
 // came from, reads the raw data of slice q+3 into registers, and issues the A loads of slice q+3.
-template <bool ASYM>
+template <bool ASYM, StoreWay WAY>
 __global__ __launch_bounds__(256) void gemm_e5m2_hybrid_kernel(const uint16_t* __restrict__ Ap,
                                                                const uint8_t* __restrict__ Bc,
                                                                const uint8_t* __restrict__ Bs, float* __restrict__ C,
@@ -566,7 +566,7 @@ __global__ __launch_bounds__(256) void gemm_e5m2_hybrid_kernel(const uint16_t* _
 #undef AMX_ISSUE_RAW
 #undef AMX_ISSUE_A
 
-  store_c_tiles<FM, FN, 6 /* 2^6 undoes the operand bias */>(acc, C + b * M * ldc, M, N, K, ldc, (int64_t)tm * kE5Tile + wm * FM * 32,
+  store_c_tiles<FM, FN, WAY, 6 /* 2^6 undoes the operand bias */>(acc, C + b * M * ldc, M, N, ldc, (int64_t)tm * kE5Tile + wm * FM * 32,
                         (int64_t)tn * kE5Tile + wn * FN * 32);
 }
 
@@ -595,12 +595,12 @@ hipError_t launch_gemm_e5m2_hybrid(bool asym, int64_t M, int64_t N, int64_t K, c
   int super_m;
   const dim3 grid(supertile_grid(tiles_m, tiles_n, kE5Tile, kE5Tile, batch, super_m), 1, (unsigned)batch);
   if (timer.start && (e = hipEventRecord(timer.start, s)) != hipSuccess) return e;
-  if (asym)
-    hipLaunchKernelGGL((gemm_e5m2_hybrid_kernel<true>), grid, dim3(256), 0, s, Ap, B_codes, B_scales, C, M, N, Mp, K,
-                       ldc, tiles_m, tiles_n, super_m);
-  else
-    hipLaunchKernelGGL((gemm_e5m2_hybrid_kernel<false>), grid, dim3(256), 0, s, Ap, B_codes, B_scales, C, M, N, Mp, K,
-                       ldc, tiles_m, tiles_n, super_m);
+  in_store_way(C, M, K, ldc, [&]<StoreWay WAY>() {
+    if (asym)
+      hipLaunchKernelGGL((gemm_e5m2_hybrid_kernel<true, WAY>), grid, dim3(256), 0, s, Ap, B_codes, B_scales, C, M, N, Mp, K, ldc, tiles_m, tiles_n, super_m);
+    else
+      hipLaunchKernelGGL((gemm_e5m2_hybrid_kernel<false, WAY>), grid, dim3(256), 0, s, Ap, B_codes, B_scales, C, M, N, Mp, K, ldc, tiles_m, tiles_n, super_m);
+  });
   if ((e = hipGetLastError()) != hipSuccess) return e;
   if (timer.stop) e = hipEventRecord(timer.stop, s);
   return e;

@@ -113,7 +113,7 @@ __global__ __launch_bounds__(256) void scale_pack_kernel(ScalePackJob ja, ScaleP
 // its last fragments of the current buffer and the next stage has landed; the two steps after it read ahead into the
 // next buffer.
 // GLU: the gated-activation epilogue of store_glu_tiles() (gemm_common.h); C is then the BF16 output [M][ldc].
-template <int WM, int WN, int FM, int FN, bool ASYM, bool GLU = false>
+template <int WM, int WN, int FM, int FN, bool ASYM, bool GLU = false, StoreWay WAY = kStoreRows>
 __global__ __launch_bounds__(64 * WM * WN) void gemm_fp4_kernel(const uint8_t* __restrict__ Ac,
                                                                 const uint8_t* __restrict__ Asp,
                                                                 const uint8_t* __restrict__ Bc,
@@ -429,8 +429,8 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_fp4_kernel(const uint8_t* _
     store_glu_tiles<FM, FN>(acc, stage, reinterpret_cast<uint16_t*>(C) + b * M * ldc, M, N >> 1, ldc,
                             (int64_t)tm * kTileM + wm * FM * 32, (int64_t)tn * kTileN + wn * FN * 32);
   } else
-    store_c_tiles<FM, FN>(acc, C + b * M * ldc, M, N, K, ldc, (int64_t)tm * kTileM + wm * FM * 32,
-                          (int64_t)tn * kTileN + wn * FN * 32);
+    store_c_tiles<FM, FN, WAY>(acc, C + b * M * ldc, M, N, ldc, (int64_t)tm * kTileM + wm * FM * 32,
+                                         (int64_t)tn * kTileN + wn * FN * 32);
 }
 
 bool fp4_path_supported(int64_t M, int64_t N, int64_t K) {
@@ -465,8 +465,10 @@ static hipError_t launch_fp4(int64_t M, int64_t N, int64_t K, const uint8_t* Ac,
     hipLaunchKernelGGL((gemm_fp4_kernel<2, 2, 4, 4, ASYM, true>), dim3(grid, 1, (unsigned)batch), dim3(Cfg::kThreads),
                        0, s, Ac, Asp, Bc, Bsp, C, M, N, K, ldc, tiles_m, tiles_n, super_m);
   else
-    hipLaunchKernelGGL((gemm_fp4_kernel<2, 2, 4, 4, ASYM>), dim3(grid, 1, (unsigned)batch), dim3(Cfg::kThreads), 0, s,
-                       Ac, Asp, Bc, Bsp, C, M, N, K, ldc, tiles_m, tiles_n, super_m);
+    in_store_way(C, M, K, ldc, [&]<StoreWay WAY>() {
+      hipLaunchKernelGGL((gemm_fp4_kernel<2, 2, 4, 4, ASYM, false, WAY>), dim3(grid, 1, (unsigned)batch), dim3(Cfg::kThreads), 0, s, Ac,
+                         Asp, Bc, Bsp, C, M, N, K, ldc, tiles_m, tiles_n, super_m);
+    });
   if ((e = hipGetLastError()) != hipSuccess) return e;
   if (timer.stop) e = hipEventRecord(timer.stop, s);
   return e;

@@ -465,7 +465,7 @@ static hipError_t launch_fp6_merge(const Fp6MergeJob& ja, const Fp6MergeJob& jb,
 // GLU: the gated-activation epilogue of store_glu_tiles() (gemm_common.h); C is then the BF16 output [M][ldc].
 // PREP: B comes from a prepared panel (B's own blocks, independent of A): b_steps K steps per row block, and the plan
 // holds, behind the step count, the table of B blocks of the lengthened K; Bsc is this call's gathered anchor array.
-template <int WM, int WN, int FM, int FN, bool GLU = false, bool PREP = false>
+template <int WM, int WN, int FM, int FN, bool GLU = false, bool PREP = false, StoreWay WAY = kStoreRows>
 __global__ __launch_bounds__(64 * WM * WN) void gemm_fp6m_kernel(const uint8_t* __restrict__ Ap,
                                                                  const uint8_t* __restrict__ Asc,
                                                                  const uint8_t* __restrict__ Bp,
@@ -711,8 +711,8 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_fp6m_kernel(const uint8_t* 
     store_glu_tiles<FM, FN>(acc, stage, reinterpret_cast<uint16_t*>(C) + b * M * ldc, M, N >> 1, ldc,
                             (int64_t)tm * (32 * FM * WM) + wm * FM * 32, (int64_t)tn * (32 * FN * WN) + wn * FN * 32);
   } else
-    store_c_tiles<FM, FN>(acc, C + b * M * ldc, M, N, (int64_t)nsteps * 64, ldc, (int64_t)tm * (32 * FM * WM) + wm * FM * 32,
-                          (int64_t)tn * (32 * FN * WN) + wn * FN * 32);
+    store_c_tiles<FM, FN, WAY>(acc, C + b * M * ldc, M, N, ldc,
+                               (int64_t)tm * (32 * FM * WM) + wm * FM * 32, (int64_t)tn * (32 * FN * WN) + wn * FN * 32);
 }
 
 bool fp6m_path_supported(int64_t M, int64_t N, int64_t K) {
@@ -751,9 +751,11 @@ hipError_t launch_gemm_fp6m_path(int64_t M, int64_t N, int64_t K, const uint8_t*
                        Ap, Asc, Bp, Bsc, plan, plan_stride, steps_offset, C, M, N, Mp, Np, steps_cap, ldc, tiles_m,
                        tiles_n, super_m, 0, (int64_t)0);
   else
-    hipLaunchKernelGGL((gemm_fp6m_kernel<2, 2, 4, 4>), dim3(grid, 1, (unsigned)batch), dim3(Cfg::kThreads), 0, s, Ap,
-                       Asc, Bp, Bsc, plan, plan_stride, steps_offset, C, M, N, Mp, Np, steps_cap, ldc, tiles_m, tiles_n,
-                       super_m, 0, (int64_t)0);
+    in_store_way(C, M, K, ldc, [&]<StoreWay WAY>() {
+      hipLaunchKernelGGL((gemm_fp6m_kernel<2, 2, 4, 4, false, false, WAY>), dim3(grid, 1, (unsigned)batch), dim3(Cfg::kThreads), 0, s, Ap,
+                         Asc, Bp, Bsc, plan, plan_stride, steps_offset, C, M, N, Mp, Np, steps_cap, ldc, tiles_m, tiles_n, super_m, 0,
+                         (int64_t)0);
+    });
   if ((e = hipGetLastError()) != hipSuccess) return e;
   if (timer.stop) e = hipEventRecord(timer.stop, s);
   return e;
@@ -813,9 +815,10 @@ hipError_t launch_gemm_fp6m_prepared(int64_t M, int64_t N, int64_t K, const uint
                        Bsc, plan, plan_stride, steps_offset, C, M, N, Mp, Np, steps_cap, ldc, tiles_m, tiles_n, super_m,
                        b_cap, table_offset);
   else
-    hipLaunchKernelGGL((gemm_fp6m_kernel<2, 2, 4, 4, false, true>), dim3(grid, 1, 1), dim3(Cfg::kThreads), 0, s, Ap, Asc, Bp,
-                       Bsc, plan, plan_stride, steps_offset, C, M, N, Mp, Np, steps_cap, ldc, tiles_m, tiles_n, super_m,
-                       b_cap, table_offset);
+    in_store_way(C, M, K, ldc, [&]<StoreWay WAY>() {
+      hipLaunchKernelGGL((gemm_fp6m_kernel<2, 2, 4, 4, false, true, WAY>), dim3(grid, 1, 1), dim3(Cfg::kThreads), 0, s, Ap, Asc, Bp, Bsc,
+                         plan, plan_stride, steps_offset, C, M, N, Mp, Np, steps_cap, ldc, tiles_m, tiles_n, super_m, b_cap, table_offset);
+    });
   if ((e = hipGetLastError()) != hipSuccess) return e;
   if (timer.stop) e = hipEventRecord(timer.stop, s);
   return e;

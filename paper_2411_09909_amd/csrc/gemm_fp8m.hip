@@ -92,7 +92,7 @@ __global__ __launch_bounds__(256) void merge_kernel(const uint8_t* __restrict__ 
 }
 
 // GLU: the gated-activation epilogue of store_glu_tiles() (gemm_common.h); C is then the BF16 output [M][ldc].
-template <int WM, int WN, int FM, int FN, bool GLU = false>
+template <int WM, int WN, int FM, int FN, bool GLU = false, StoreWay WAY = kStoreRows>
 __global__ __launch_bounds__(64 * WM * WN) void gemm_fp8m_kernel(const uint8_t* __restrict__ Ap,
                                                                  const uint8_t* __restrict__ Asc,
                                                                  const uint8_t* __restrict__ Bp,
@@ -260,7 +260,7 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_fp8m_kernel(const uint8_t* 
     store_glu_tiles<FM, FN>(acc, stage, reinterpret_cast<uint16_t*>(C) + b * M * ldc, M, N >> 1, ldc,
                             (int64_t)tm * Cfg::kTileM + wm * FM * 32, (int64_t)tn * Cfg::kTileN + wn * FN * 32);
   } else
-    store_c_tiles<FM, FN>(acc, C + b * M * ldc, M, N, Kp, ldc, (int64_t)tm * Cfg::kTileM + wm * FM * 32,
+    store_c_tiles<FM, FN, WAY>(acc, C + b * M * ldc, M, N, ldc, (int64_t)tm * Cfg::kTileM + wm * FM * 32,
                           (int64_t)tn * Cfg::kTileN + wn * FN * 32);
 }
 
@@ -287,8 +287,10 @@ hipError_t launch_gemm_fp8m_path(int64_t M, int64_t N, int64_t K, const uint8_t*
     hipLaunchKernelGGL((gemm_fp8m_kernel<2, 2, 4, 4, true>), dim3(grid, 1, (unsigned)batch), dim3(Cfg::kThreads), 0, s,
                        Ap, Asc, Bp, Bsc, C, M, N, Mp, Np, Kp, ldc, tiles_m, tiles_n, super_m);
   else
-    hipLaunchKernelGGL((gemm_fp8m_kernel<2, 2, 4, 4>), dim3(grid, 1, (unsigned)batch), dim3(Cfg::kThreads), 0, s, Ap,
-                       Asc, Bp, Bsc, C, M, N, Mp, Np, Kp, ldc, tiles_m, tiles_n, super_m);
+    in_store_way(C, M, K, ldc, [&]<StoreWay WAY>() {
+      hipLaunchKernelGGL((gemm_fp8m_kernel<2, 2, 4, 4, false, WAY>), dim3(grid, 1, (unsigned)batch), dim3(Cfg::kThreads), 0, s, Ap, Asc, Bp,
+                         Bsc, C, M, N, Mp, Np, Kp, ldc, tiles_m, tiles_n, super_m);
+    });
   if ((e = hipGetLastError()) != hipSuccess) return e;
   if (timer.stop) e = hipEventRecord(timer.stop, s);
   return e;

@@ -48,6 +48,20 @@ def test_order_in_a_batch_and_of_small_tiles(tiles_m, tiles_n, rows, batch, runs
     assert (tile_order(tiles_m, tiles_n, rows, 256, batch)[1] == 0) == bool(runs)
 
 
+ROWS, ROWS_CACHED, COLUMNS = 0, 1, 2
+
+
+@pytest.mark.parametrize("M,ldc,K,way,base", [
+    (2048, 11008, 4096, ROWS, 0), (1504, 4096, 14336, ROWS, 0), (4096, 4096, 512, ROWS, 0),        # whole lines: 68.3 / 67.2 row by row
+    (2048, 8192, 512, COLUMNS, 0), (4096, 16384, 1024, COLUMNS, 0), (64, 32768, 128, COLUMNS, 64),  # 24.0 / 30.1; half lines 53 / 66
+    (2048, 24576, 512, ROWS, 0), (2048, 8192, 1024, ROWS_CACHED, 4), (4096, 8208, 1024, ROWS, 0),   # 55.2 / 50.6; 119 / 86
+    (3000, 5001, 4096, ROWS_CACHED, 0), (4096, 32001, 4096, ROWS, 0), (4096, 4545, 4544, ROWS, 0)])
+def test_order_and_policy_of_the_stores(M, ldc, K, way, base):
+    """us column by column / row by row (rows that are not even half lines: through the caches below 80 MB of C and up to K 4096)"""
+    store_way = rule("_ZN3amx9store_wayEPKflll", i32, ctypes.c_void_p, i64, i64, i64)
+    assert store_way(1 << 20 | base, M, K, 4 * ldc) == way
+
+
 def test_grid_has_a_workgroup_for_every_tile():
     for tiles_m in range(1, 40):
         for tiles_n in range(1, 70):
