@@ -315,7 +315,7 @@ __global__ __launch_bounds__(256) void attention_decode_combine_kernel(const flo
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), col = (int)blockIdx.x, g = (int)blockIdx.y;
   const float* base = part + ((int64_t)g * kDecodeCols + col) * nsplits * (D + 2);
   row_t rows[kInFlight];
-  auto request = [&](int c0) {  // (past the last range: the last one again, with weight 0)
+  auto request = [&](int c0) {  // (past the last range: the last one again, not used)
 #pragma unroll
     for (int i = 0; i < kInFlight; ++i)
       rows[i] = *reinterpret_cast<const row_t*>(base + (int64_t)min(c0 + wave + 4 * i, nsplits - 1) * (D + 2) + lane * (D / 64));
@@ -347,8 +347,9 @@ __global__ __launch_bounds__(256) void attention_decode_combine_kernel(const flo
 #pragma unroll
     for (int i = 0; i < kInFlight; ++i) {
       const float weight = u2f((uint32_t)__builtin_amdgcn_readlane((int)f2u(w), wave + 4 * i));
+      const bool there = c0 + wave + 4 * i < nsplits;  // (a weight of 0 would make NaN of an infinity in the last range's row)
 #pragma unroll
-      for (int e = 0; e < D / 64; ++e) num[e] += weight * rows[i][e];
+      for (int e = 0; e < D / 64; ++e) num[e] += weight * (there ? rows[i][e] : 0.f);
     }
   }
   *reinterpret_cast<row_t*>(sums + wave * D + lane * (D / 64)) = num;

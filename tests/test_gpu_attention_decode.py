@@ -153,6 +153,28 @@ def test_ranges_around_what_the_combination_keeps_in_flight(splits, D):
     compare(gpu_decode(q, k, v, D ** -0.5, True, ref.FP8_E5M2, 1, splits), want)
 
 
+@pytest.mark.parametrize("Hq,D", [(2, 128), (20, 128), (2, 64)])  # either kernel in front of the combination
+@pytest.mark.parametrize("splits", [1, 5, 63, 64, 66])
+def test_an_infinite_partial_result_stays_infinite(splits, Hq, D):
+    """The rounded power-of-two scale of 3.3e38 is 2^126 and the element 4: an infinite element of V, here of the last range. Equal
+    scores (zero keys), so that every query has a part of it: that output is infinite, not NaN, and the others are what they are without."""
+    Sk = 66 * 32
+    fmt = binding.make_format(ref.E8M0_ROUND, 0, 32)
+    q, v = heads(Hq, 1, 81, d=D), heads(1, Sk, 83, d=D)
+    dev = lambda x: G.to_dev_bf16(x)  # noqa: E731
+    qc, qs = binding.quantize_batched(fmt, dev(q).view(Hq, 1, D))
+    kc, ks = binding.quantize_batched(fmt, torch.zeros((1, Sk, D), dtype=torch.bfloat16, device="cuda"))
+    v = dev(v).view(1, Sk, D)
+    huge = v.clone()
+    huge[0, Sk - 1, 5] = 3.3e38
+    out = [binding.attention_decode(fmt, qc, qs, kc, ks, *binding.quantize_batched(fmt, x, k_axis=1), D ** -0.5, True, key_splits=splits)
+           for x in (v, huge)]
+    assert torch.isfinite(out[0]).all()
+    assert bool((out[1][..., 5] == float("inf")).all())
+    out[1][..., 5] = out[0][..., 5]
+    assert torch.equal(out[0], out[1])
+
+
 def test_invalid_arguments():
     fmt = binding.make_format(ref.FP8_E5M2, 1, 32)
     z = lambda *s: torch.zeros(s, dtype=torch.uint8, device="cuda")  # noqa: E731
