@@ -511,16 +511,25 @@ hipError_t launch_quantize_contig(int scale_kind, bool asym, int64_t group_size,
   });
 }
 
+// Groups of a row, as a power of two, that a workgroup of the strided cast takes, a wave each: runs of 128 bytes of codes (64 in groups
+// of 16), shorter ones while there are fewer workgroups than three quarters of the compute units (kernel, us, one group to a workgroup /
+// the run this picks: 4096 x 2048 6.9 / 5.6, 32 x 128 x 4032 14.3 / 9.0; twice as many workgroups / this: 8 x 128 x 1536 3.3 / 2.8; half
+// as many / this: 4096 x 512 3.2 / 2.8), and no waves for groups that a short K does not have (10^6 x 32 29.1 / 15.3, 4096 heads of 128 x 32
+// 16.0 / 8.9; eight groups to a workgroup / this). Beyond some 10^5 rows rows of an odd number of wide groups, whose last ones are
+// workgroups that run much later, take longer than with all groups of some rows one after the other (10^6 x 9 groups of 128 705 / 616).
+int strided_waves_log2(int group_size, int64_t rows, int64_t groups, int64_t batch) {
+  int wl = group_size == 128 ? 1 : group_size == 64 ? 2 : 3;
+  while (wl > 0 && groups <= (int64_t(1) << (wl - 1))) --wl;
+  while (wl > 0 && (rows + 63) / 64 * ((groups + (1 << wl) - 1) >> wl) * batch < 192) --wl;
+  return wl;
+}
+
 template <int SK, bool ASYM, int GS>
 static hipError_t launch_qs(const uint16_t* x, int64_t rows, int64_t K, int64_t k_stride, int64_t batch,
                             int64_t batch_stride, const float* tensor_pair, uint8_t* codes, uint8_t* scales,
                             hipStream_t s) {
   const int64_t row_blocks = (rows + 63) / 64, G = K / GS;
-  // Runs of 128 bytes of codes (64 in groups of 16), shorter ones while there are fewer workgroups than three quarters
-  // of the compute units (kernel, us, one group to a workgroup / the run this picks: 4096 x 2048 6.9 / 5.6, 32 x 128 x
-  // 4032 14.3 / 9.0; twice as many workgroups / this: 8 x 128 x 1536 3.3 / 2.8; half as many / this: 4096 x 512 3.2 / 2.8).
-  int wl = GS == 128 ? 1 : GS == 64 ? 2 : 3;
-  while (wl > 0 && row_blocks * ((G + (1 << wl) - 1) >> wl) * batch < 192) --wl;
+  const int wl = strided_waves_log2(GS, rows, G, batch);
   const dim3 grid((unsigned)row_blocks, (unsigned)((G + (1 << wl) - 1) >> wl), (unsigned)batch);
   if (tensor_pair)
     hipLaunchKernelGGL((quantize_strided_kernel<SK, ASYM, true, GS>), grid, dim3(64 << wl), 0, s, x, rows, K, k_stride,

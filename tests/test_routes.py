@@ -48,6 +48,16 @@ def test_order_in_a_batch_and_of_small_tiles(tiles_m, tiles_n, rows, batch, runs
     assert (tile_order(tiles_m, tiles_n, rows, 256, batch)[1] == 0) == bool(runs)
 
 
+@pytest.mark.parametrize("group,rows,groups,batch,log2", [
+    (32, 4096, 256, 1, 3), (16, 4096, 512, 1, 3), (64, 4096, 128, 1, 2), (128, 4096, 64, 1, 1), (32, 128, 126, 32, 3),
+    (32, 32, 32, 1, 0), (32, 4096, 16, 1, 2), (32, 128, 48, 8, 2),                                     # few workgroups
+    (32, 1000000, 1, 1, 0), (32, 128, 1, 4096, 0), (32, 1000000, 2, 1, 1), (16, 1000000, 3, 1, 2),     # 29.1 / 15.3, 16.0 / 8.9
+    (32, 65536, 5, 1, 3), (128, 1000000, 1, 1, 0), (64, 1000000, 1, 1, 0), (64, 1000000, 2, 1, 1)])
+def test_groups_to_a_workgroup_of_the_strided_cast(group, rows, groups, batch, log2):
+    """No more waves than there are groups (us with eight to a workgroup / as many as there are)."""
+    assert rule("_ZN3amx18strided_waves_log2Eilll", i32, i32, i64, i64, i64)(group, rows, groups, batch) == log2
+
+
 ROWS, ROWS_CACHED, COLUMNS = 0, 1, 2
 
 
