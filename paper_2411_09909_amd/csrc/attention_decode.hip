@@ -300,25 +300,27 @@ __device__ __forceinline__ float over_wave(float v, Op op) {
   return op(u2f(b[0]), u2f(b[1]));
 }
 
-// Four waves per (kv head, column that holds a query): the exact combination of the ranges, in FP32. Each wave works out the
+// W waves per (kv head, column that holds a query): the exact combination of the ranges, in FP32. Each wave works out the
 // maximum and the ranges' weights 2^(m_c - m*), a range to a lane (0 for a range in which the query saw no key), and adds up every
-// fourth range's row, a weight read from its lane. It is a chain of memory latencies, so the first 64 ranges' rows (16 to a wave,
-// D / 64 floats a lane of each) are requested before anything is known about their weights, and further ones 64 at a time.
-// As one wave with 32 rows in flight and lane exchanges through LDS: 64 ranges, 32 columns 5.3 -> 2.9 us; the whole call of one
-// sequence x 8192 keys 11.3 -> 9.9, of four (32 ranges) 16.5 -> 15.6, 256 ranges 31.5 -> 19.0.
-template <int D>
-__global__ __launch_bounds__(256) void attention_decode_combine_kernel(const float* __restrict__ part, float* __restrict__ out, int per,
-                                                                       int Sq, int nsplits) {
+// W-th range's row, a weight read from its lane. It is a chain of memory latencies, so the first W F ranges' rows (F to a wave,
+// D / 64 floats a lane of each) are requested before anything is known about their weights, and with four waves further ones 64 at a time.
+// Four waves of 16, as one wave with 32 rows in flight and lane exchanges through LDS / this: 64 ranges, 32 columns 5.3 -> 2.9 us; the
+// whole call of one sequence x 8192 keys 11.3 -> 9.9, of four (32 ranges) 16.5 -> 15.6, 256 ranges 31.5 -> 19.0. Up to 16 ranges one
+// wave has them all: with thousands of columns four are waves for nothing (the whole call, us, one wave and exchanges / four waves / this:
+// 256 heads of 32 columns, 4 ranges 26.1 / 31.8 / 19.2; 192 of 16, 16 ranges 31.2 / 26.8 / 24.7; 8 of 4, 4 ranges 11.3 / 6.5 / 6.2).
+template <int D, int W, int F>
+__global__ __launch_bounds__(64 * W) void attention_decode_combine_kernel(const float* __restrict__ part, float* __restrict__ out, int per,
+                                                                          int Sq, int nsplits) {
   typedef float row_t __attribute__((ext_vector_type(D / 64)));
-  constexpr int kInFlight = 16;
-  __shared__ float sums[4 * D];
+  static_assert(W * F <= 64);  // (nsplits <= F unless W F = 64)
+  __shared__ float sums[W * D];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), col = (int)blockIdx.x, g = (int)blockIdx.y;
   const float* base = part + ((int64_t)g * kDecodeCols + col) * nsplits * (D + 2);
-  row_t rows[kInFlight];
+  row_t rows[F];
   auto request = [&](int c0) {  // (past the last range: the last one again, not used)
 #pragma unroll
-    for (int i = 0; i < kInFlight; ++i)
-      rows[i] = *reinterpret_cast<const row_t*>(base + (int64_t)min(c0 + wave + 4 * i, nsplits - 1) * (D + 2) + lane * (D / 64));
+    for (int i = 0; i < F; ++i)
+      rows[i] = *reinterpret_cast<const row_t*>(base + (int64_t)min(c0 + wave + W * i, nsplits - 1) * (D + 2) + lane * (D / 64));
   };
   // maximum and sum of range c0 + lane (none: a range without a key)
   auto range_of = [&](int c0) {
@@ -345,18 +347,22 @@ __global__ __launch_bounds__(256) void attention_decode_combine_kernel(const flo
     const float w = ml.y > 0.f ? __builtin_amdgcn_exp2f(ml.x - mx) : 0.f;
     den += w * ml.y;
 #pragma unroll
-    for (int i = 0; i < kInFlight; ++i) {
-      const float weight = u2f((uint32_t)__builtin_amdgcn_readlane((int)f2u(w), wave + 4 * i));
-      const bool there = c0 + wave + 4 * i < nsplits;  // (a weight of 0 would make NaN of an infinity in the last range's row)
+    for (int i = 0; i < F; ++i) {
+      const float weight = u2f((uint32_t)__builtin_amdgcn_readlane((int)f2u(w), wave + W * i));
+      const bool there = c0 + wave + W * i < nsplits;  // (a weight of 0 would make NaN of an infinity in the last range's row)
 #pragma unroll
       for (int e = 0; e < D / 64; ++e) num[e] += weight * (there ? rows[i][e] : 0.f);
     }
   }
-  *reinterpret_cast<row_t*>(sums + wave * D + lane * (D / 64)) = num;
   const float inv = 1.0f / over_wave(den, [](float a, float b) { return a + b; });
-  __syncthreads();
-  if (tid < D)
-    out[(((int64_t)g * per + col / Sq) * Sq + col % Sq) * D + tid] = ((sums[tid] + sums[D + tid]) + (sums[2 * D + tid] + sums[3 * D + tid])) * inv;
+  float* dst = out + (((int64_t)g * per + col / Sq) * Sq + col % Sq) * D;
+  if constexpr (W == 1) {
+    *reinterpret_cast<row_t*>(dst + lane * (D / 64)) = num * inv;
+  } else {
+    *reinterpret_cast<row_t*>(sums + wave * D + lane * (D / 64)) = num;
+    __syncthreads();
+    if (tid < D) dst[tid] = ((sums[tid] + sums[D + tid]) + (sums[2 * D + tid] + sums[3 * D + tid])) * inv;
+  }
 }
 
 bool attention_decode_supported(int64_t Hq, int64_t Hkv, int64_t Sq, int64_t head_dim) {
@@ -388,8 +394,16 @@ static hipError_t launch_decode(int64_t Hq, int64_t Hkv, int64_t Sq, int64_t Sk,
     e = hipGetLastError();
   }
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((attention_decode_combine_kernel<D>), dim3((unsigned)(per * Sq), (unsigned)Hkv), dim3(256), 0, s, part,
-                     out, per, (int)Sq, splits);
+  auto combine = [&]<int W, int F>() {
+    hipLaunchKernelGGL((attention_decode_combine_kernel<D, W, F>), dim3((unsigned)(per * Sq), (unsigned)Hkv), dim3(64 * W), 0, s, part, out,
+                       per, (int)Sq, splits);
+  };
+  if (splits <= 4)
+    combine.template operator()<1, 4>();
+  else if (splits <= 16)
+    combine.template operator()<1, 16>();
+  else
+    combine.template operator()<4, 16>();
   return hipGetLastError();
 }
 

@@ -143,7 +143,8 @@ def test_decoding_shape_at_full_size(scale_format, asym):
     compare(out, want)
 
 
-@pytest.mark.parametrize("splits,D", [(1, 128), (31, 128), (32, 64), (33, 128), (63, 64), (64, 64), (65, 128), (66, 64)])
+@pytest.mark.parametrize("splits,D", [(1, 128), (3, 64), (4, 128), (5, 128), (15, 64), (16, 128), (17, 64), (31, 128), (32, 64),
+                                      (33, 128), (63, 64), (64, 64), (65, 128), (66, 64)])
 def test_ranges_around_what_the_combination_keeps_in_flight(splits, D):
     """The combination reads 64 ranges' rows at a time: one range, the last of a batch missing, whole batches, one range
     beyond. 66 tiles of keys (no whole V chunks): the last ranges hold fewer tiles, or none."""
@@ -154,7 +155,7 @@ def test_ranges_around_what_the_combination_keeps_in_flight(splits, D):
 
 
 @pytest.mark.parametrize("Hq,D", [(2, 128), (20, 128), (2, 64)])  # either kernel in front of the combination
-@pytest.mark.parametrize("splits", [1, 5, 63, 64, 66])
+@pytest.mark.parametrize("splits", [1, 3, 5, 33, 63, 64, 66])
 def test_an_infinite_partial_result_stays_infinite(splits, Hq, D):
     """The rounded power-of-two scale of 3.3e38 is 2^126 and the element 4: an infinite element of V, here of the last range. Equal
     scores (zero keys), so that every query has a part of it: that output is infinite, not NaN, and the others are what they are without."""
