@@ -379,7 +379,7 @@ static hipError_t launch_decode(int64_t Hq, int64_t Hkv, int64_t Sq, int64_t Sk,
                                 int causal, int splits, float* out, float* part, hipStream_t s) {
   const int per = (int)(Hq / Hkv), tiles = (int)(Sk / 32), tiles_per_split = (tiles + splits - 1) / splits;
   hipError_t e;
-  if (attention_decode_16_preferred(Hq, Hkv, Sq, tiles_per_split, splits)) {
+  if (attention_decode_16_preferred(Hq, Hkv, Sq, D, tiles_per_split, splits)) {
     e = launch_attention_decode_16(SK, ASYM, Hq, Hkv, Sq, Sk, D, Qc, Qs, Kc, Ks, Vc, Vs, scale, causal, splits, part, s);
   } else {
     // whole chunks of 8 key tiles, and V^T of one head within the 32-bit offsets of a buffer: V through LDS by chunks

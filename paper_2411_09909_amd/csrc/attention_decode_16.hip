@@ -360,10 +360,19 @@ static hipError_t launch_16(int per, int64_t Hkv, int64_t Sq, int64_t Sk, const 
   return wide_or_not.template operator()<4, 1>();
 }
 
-// Ranges of a single tile leave three of the four waves idle: 32768 of them 162 us on the other kernel, 177 on this one; 2048 of them 32.8
-// and 31.5; 16384 ranges of two tiles 99.9 and 99.1.
-bool attention_decode_16_preferred(int64_t Hq, int64_t Hkv, int64_t Sq, int tiles_per_split, int key_splits) {
-  return (Hq / Hkv) * Sq <= 16 && (tiles_per_split > 1 || Hkv * key_splits < 4096);
+// Ranges of a single tile leave three of the four waves idle, those of two or three some; the more ranges, the more that costs, most with
+// heads of 64, whose tiles are half the work. Ratios of the whole call, this kernel / the other, over 5900 sizes:
+//   one tile: 1.03 to 1.18 on average from one range to 65536, heads of 64 to 1.45 (8192 heads, 1024 groups x 32 keys, heads of 64, 15.7 /
+//     9.8 us; 288 heads and groups x 96, heads of 128, three ranges, OCP MXFP4 8.4 / 5.7 with the new combination). Some are below 1, to 0.82: heads of 128, 1024 to 8192 ranges of whole chunks of eight
+//     tiles (128 heads, 16 x 2048 keys, 64 ranges, two queries 13.3 / 15.8)
+//   two tiles: heads of 64 0.92 below 512 ranges, 1.03 to 1.19 from there on (4096 heads, 1024 x 1024, 16 ranges 56.8 / 46.1); of 128 0.84 to 0.97
+//   three: heads of 64 beyond 16384 ranges 1.02 to 1.06 up to four columns (816 heads, 408 x 7424, 78 ranges 122 / 110), 0.84 beyond; else 0.70 to 0.95
+//   four and more: 0.3 to 0.93
+bool attention_decode_16_preferred(int64_t Hq, int64_t Hkv, int64_t Sq, int64_t head_dim, int tiles_per_split, int key_splits) {
+  const int64_t columns = (Hq / Hkv) * Sq, ranges = Hkv * key_splits;
+  if (columns > 16 || tiles_per_split == 1) return false;
+  if (head_dim == 128 || tiles_per_split > 3) return true;
+  return tiles_per_split == 2 ? ranges < 512 : ranges < 16384 || columns > 4;
 }
 
 hipError_t launch_attention_decode_16(int scale_kind, bool asym, int64_t Hq, int64_t Hkv, int64_t Sq, int64_t Sk, int64_t head_dim,

@@ -123,7 +123,7 @@ hipError_t launch_attention_64(int scale_kind, bool asym, int64_t Hq, int64_t Hk
 // packed codes, the key tiles cut into key_splits ranges (workspace: the ranges' partial results)
 bool attention_decode_supported(int64_t Hq, int64_t Hkv, int64_t Sq, int64_t head_dim);
 // attention_decode_16.hip: its kernel for at most 16 queries per key / value head, without the combination of the ranges
-bool attention_decode_16_preferred(int64_t Hq, int64_t Hkv, int64_t Sq, int tiles_per_split, int key_splits);
+bool attention_decode_16_preferred(int64_t Hq, int64_t Hkv, int64_t Sq, int64_t head_dim, int tiles_per_split, int key_splits);
 hipError_t launch_attention_decode_16(int scale_kind, bool asym, int64_t Hq, int64_t Hkv, int64_t Sq, int64_t Sk, int64_t head_dim,
                                       const uint8_t* Q_codes, const uint8_t* Q_scales, const uint8_t* K_codes, const uint8_t* K_scales,
                                       const uint8_t* V_codes, const uint8_t* V_scales, float scale, int causal, int key_splits,

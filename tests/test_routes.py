@@ -58,6 +58,17 @@ def test_groups_to_a_workgroup_of_the_strided_cast(group, rows, groups, batch, l
     assert rule("_ZN3amx18strided_waves_log2Eilll", i32, i32, i64, i64, i64)(group, rows, groups, batch) == log2
 
 
+@pytest.mark.parametrize("Hq,Hkv,Sq,D,tiles,splits,here", [
+    (32, 8, 1, 128, 1, 4, 0), (8192, 1024, 1, 64, 1, 1, 0), (128, 16, 2, 128, 1, 64, 0),                  # one tile: 15.7 / 9.8 us, but 13.3 / 15.8
+    (32, 8, 1, 64, 2, 63, 1), (32, 8, 1, 64, 2, 64, 0), (4096, 1024, 1, 64, 2, 16, 0), (32, 8, 1, 128, 2, 64, 1),   # two: 56.8 / 46.1
+    (816, 408, 1, 64, 3, 78, 0), (64, 8, 1, 64, 3, 2048, 1), (816, 408, 1, 64, 3, 40, 1), (816, 408, 1, 64, 4, 78, 1),  # three: 122 / 110
+    (816, 408, 1, 128, 3, 78, 1), (34, 2, 1, 128, 8, 64, 0)])
+def test_decode_attention_of_short_ranges(Hq, Hkv, Sq, D, tiles, splits, here):
+    """The kernel of 16 columns and four waves to a range / the other one."""
+    f = rule("_ZN3amx29attention_decode_16_preferredEllllii", flag, i64, i64, i64, i64, i32, i32)
+    assert f(Hq, Hkv, Sq, D, tiles, splits) == bool(here)
+
+
 ROWS, ROWS_CACHED, COLUMNS = 0, 1, 2
 
 
