@@ -18,6 +18,7 @@
 //     conversion v_cvt_scalef32_pk_fp4_f32.
 // Strided cast (groups down a column, for V in P.V): one lane per (row, group), the same arithmetic, results through LDS.
 // Whole-row groups (group size -1, as in the code example of Appendix B): one thread block per row, two sweeps.
+#include <algorithm>
 #include <type_traits>
 
 #include "cast_core.h"
@@ -207,35 +208,36 @@ __global__ __launch_bounds__(256) void quantize_row_kernel(const uint16_t* __res
 }
 
 // Groups run down a column: element (r, k) = x[r + k * k_stride]. A wave casts 64 rows of one group, a lane one row of
-// it, so that each of its GS loads reads 128 contiguous bytes; a workgroup is the 2^waves_log2 waves of groups that
-// follow each other. What bounds it is memory: the groups of a row that lie next to each other are in one workgroup
-// and go out through LDS, so that codes are written in runs of up to 128 bytes and not 16 at a time from several
-// dies, and workgroups that follow each other take the next rows, which read what follows in memory, not 32 rows
-// further down the same few channels. BF16 elements are cast in pairs as in the contiguous cast. us, one wave's 16
+// it, so that each of its GS loads reads 128 contiguous bytes; a workgroup is 2^groups_log2 groups that follow each other,
+// of 64 * 2^rows_log2 rows, eight waves at most. What bounds it is memory: the groups of a row that lie next to each other
+// are in one workgroup and go out through LDS, so that codes are written in runs of up to 128 bytes and not 16 at a time
+// from several dies, and workgroups that follow each other take the next rows, which read what follows in memory, not 32
+// rows further down the same few channels. BF16 elements are cast in pairs as in the contiguous cast. us, one wave's 16
 // bytes at a time, workgroups of 256 rows / this: 4096 x 8192 39.9 / 18.5 (reading and writing it once takes 16.7 at
 // the rate of a copy), in NVFP4's groups of 16 46.9 / 19.2, of 64 31.5 / 18.7; kernel alone: 4096 x 2048 9.3 / 5.6,
 // 1024 x 4096 6.2 / 3.7, 32 heads of 128 x 4032 14.3 / 9.0, 128 x 8192 3.5 / 2.7.
-// grid: (ceil(rows / 64), ceil(groups / 2^waves_log2), batch).
+// grid: (ceil(rows / (64 * 2^rows_log2)), ceil(groups / 2^groups_log2), batch).
 constexpr int strided_piece_bytes(int GS) { return GS == 16 ? 8 : 16; }
-constexpr int kStridedLineElements = 256;  // most elements of a row per workgroup: 128 bytes of codes
 
 template <int SCALE_KIND, bool ASYM, bool TENSOR_SCALED, int GS>
 __global__ __launch_bounds__(512) void quantize_strided_kernel(const uint16_t* __restrict__ x, int64_t rows, int64_t K,
                                                                int64_t k_stride, int64_t batch_stride,
                                                                const float* __restrict__ tensor_pair,
                                                                uint8_t* __restrict__ codes,
-                                                               uint8_t* __restrict__ scales, int waves_log2) {
+                                                               uint8_t* __restrict__ scales, int groups_log2, int rows_log2) {
   constexpr int kPiece = strided_piece_bytes(GS), kPieces = GS / 2 / kPiece, kPad = 16;
   using piece_t = std::conditional_t<kPiece == 8, uint2, uint4>;
   using scale_t = std::conditional_t<ASYM, uint16_t, uint8_t>;
-  __shared__ __attribute__((aligned(16))) uint8_t lds_codes[64 * (kStridedLineElements / 2 + kPad)];
+  constexpr int kLine = GS == 16 ? 64 : 128;  // longest run of codes; the rows below: of one such workgroup, of one of 2 groups x 128
+  __shared__ __attribute__((aligned(16))) uint8_t lds_codes[std::max(64 * (kLine + kPad), 128 * (GS + kPad))];
   __shared__ scale_t lds_scales[512];
   const int64_t G = K / GS;
   codes += (int64_t)blockIdx.z * rows * (K >> 1);
   scales += (int64_t)blockIdx.z * rows * G * sizeof(scale_t);
   const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), lane = (int)threadIdx.x & 63;
-  const int pitch = ((GS / 2) << waves_log2) + kPad;
-  const int64_t r0 = (int64_t)blockIdx.x * 64, g0 = (int64_t)blockIdx.y << waves_log2, r = r0 + lane, g = g0 + wave;
+  const int pitch = ((GS / 2) << groups_log2) + kPad;
+  const int group = wave & ((1 << groups_log2) - 1), row_in = (wave >> groups_log2) * 64 + lane;
+  const int64_t r0 = (int64_t)blockIdx.x * 64 << rows_log2, g0 = (int64_t)blockIdx.y << groups_log2, r = r0 + row_in, g = g0 + group;
   if (r < rows && g < G) {
     const uint16_t* p = x + (int64_t)blockIdx.z * batch_stride + g * GS * k_stride + r;
     uint32_t d[GS / 2], code[GS / 8], sb_p, sb_n;
@@ -271,26 +273,26 @@ __global__ __launch_bounds__(512) void quantize_strided_kernel(const uint16_t* _
           out[t] = make_uint4(code[4 * t], code[4 * t + 1], code[4 * t + 2], code[4 * t + 3]);
       }
     };
-    if (waves_log2 == 0) {  // nothing to put together (through LDS, 32 x 1024 in MXFP4 2.08 us instead of 2.00)
+    if (groups_log2 == 0) {  // nothing to put together (through LDS, 32 x 1024 in MXFP4 2.08 us instead of 2.00)
       put(reinterpret_cast<piece_t*>(codes + r * (K >> 1) + g * (GS / 2)));
       reinterpret_cast<scale_t*>(scales)[r * G + g] = scale;
     } else {
-      put(reinterpret_cast<piece_t*>(lds_codes + lane * pitch + wave * (GS / 2)));
-      lds_scales[(lane << waves_log2) + wave] = scale;
+      put(reinterpret_cast<piece_t*>(lds_codes + row_in * pitch + group * (GS / 2)));
+      lds_scales[(row_in << groups_log2) + group] = scale;
     }
   }
-  if (waves_log2 == 0) return;
+  if (groups_log2 == 0) return;
   __syncthreads();
   codes += g0 * (GS / 2);
 #pragma unroll
   for (int t = 0; t < kPieces; ++t) {
-    const int i = t * (64 << waves_log2) + (int)threadIdx.x;
-    const int row = i / kPieces >> waves_log2, c = i & ((kPieces << waves_log2) - 1);
+    const int i = t * (64 << (groups_log2 + rows_log2)) + (int)threadIdx.x;
+    const int row = i / kPieces >> groups_log2, c = i & ((kPieces << groups_log2) - 1);
     if (r0 + row < rows && g0 + c / kPieces < G)
       *reinterpret_cast<piece_t*>(codes + (r0 + row) * (K >> 1) + c * kPiece) =
           *reinterpret_cast<const piece_t*>(lds_codes + row * pitch + c * kPiece);
   }
-  const int row = (int)threadIdx.x >> waves_log2, c = (int)threadIdx.x & ((1 << waves_log2) - 1);
+  const int row = (int)threadIdx.x >> groups_log2, c = (int)threadIdx.x & ((1 << groups_log2) - 1);
   if (r0 + row < rows && g0 + c < G)
     reinterpret_cast<scale_t*>(scales)[(r0 + row) * G + g0 + c] = lds_scales[threadIdx.x];
 }
@@ -524,19 +526,37 @@ int strided_waves_log2(int group_size, int64_t rows, int64_t groups, int64_t bat
   return wl;
 }
 
+// Times 64 rows, as a power of two, that it takes besides: four waves in all where the groups alone are fewer, of one or two groups of a
+// row always, of more while each compute unit has two such workgroups, or half of them one where the steps along K are no whole lines:
+// neighbouring waves of rows then share the lines between them (which two groups of 64 and twice the rows are the better for than four
+// groups). us, one wave of rows / this: 32 heads of 12086 x 32 9.5 / 5.4, 512 of 752 x 32 8.4 / 5.1; groups of 64, 512 heads of 227 x
+// 512 43.1 / 35.8, 53557 x 1024 37.7 / 33.7; but whole lines and few workgroups (at least 128 / 512 of them): groups of 128, 128 x 81920
+// 8.3 / 6.5, NVFP4 128 x 3040 2.5 / 2.2. What lies on neither side: steps that are no whole lines in groups of 128 (512 heads of 218 x 384
+// 29.2, where workgroups of 256 rows of a group took 22.2), and few rows of it (64 of 18 x 1536 5.8, 4.7).
+int strided_rows_log2(int groups_log2, int64_t rows, int64_t groups, int64_t batch, bool whole_lines) {
+  int rl = groups_log2 < 2 ? 2 - groups_log2 : 0;
+  while (rl > 0 && rows <= (32 << rl)) --rl;
+  if (groups <= 2 && groups_log2 == 0) return rl;
+  const int64_t least = whole_lines ? 512 : 128;
+  while (rl > 0 && ((rows + (64 << rl) - 1) >> (6 + rl)) * ((groups + (1 << groups_log2) - 1) >> groups_log2) * batch < least) --rl;
+  return rl;
+}
+
 template <int SK, bool ASYM, int GS>
 static hipError_t launch_qs(const uint16_t* x, int64_t rows, int64_t K, int64_t k_stride, int64_t batch,
                             int64_t batch_stride, const float* tensor_pair, uint8_t* codes, uint8_t* scales,
                             hipStream_t s) {
-  const int64_t row_blocks = (rows + 63) / 64, G = K / GS;
-  const int wl = strided_waves_log2(GS, rows, G, batch);
-  const dim3 grid((unsigned)row_blocks, (unsigned)((G + (1 << wl) - 1) >> wl), (unsigned)batch);
+  const int64_t G = K / GS;
+  const bool whole_lines = k_stride % 64 == 0;  // (of the elements that a step along K is)
+  int wl = strided_waves_log2(GS, rows, G, batch), rl = strided_rows_log2(wl, rows, G, batch, whole_lines);
+  if (GS == 64 && wl == 2 && !whole_lines && strided_rows_log2(1, rows, G, batch, false) == 1) wl = 1, rl = 1;
+  const dim3 grid((unsigned)((rows + (64 << rl) - 1) >> (6 + rl)), (unsigned)((G + (1 << wl) - 1) >> wl), (unsigned)batch);
   if (tensor_pair)
-    hipLaunchKernelGGL((quantize_strided_kernel<SK, ASYM, true, GS>), grid, dim3(64 << wl), 0, s, x, rows, K, k_stride,
-                       batch_stride, tensor_pair, codes, scales, wl);
+    hipLaunchKernelGGL((quantize_strided_kernel<SK, ASYM, true, GS>), grid, dim3(64 << (wl + rl)), 0, s, x, rows, K, k_stride,
+                       batch_stride, tensor_pair, codes, scales, wl, rl);
   else
-    hipLaunchKernelGGL((quantize_strided_kernel<SK, ASYM, false, GS>), grid, dim3(64 << wl), 0, s, x, rows, K, k_stride,
-                       batch_stride, tensor_pair, codes, scales, wl);
+    hipLaunchKernelGGL((quantize_strided_kernel<SK, ASYM, false, GS>), grid, dim3(64 << (wl + rl)), 0, s, x, rows, K, k_stride,
+                       batch_stride, tensor_pair, codes, scales, wl, rl);
   return hipGetLastError();
 }
 

@@ -124,6 +124,54 @@ def test_strided_cast_at_the_edges_of_its_workgroups(rows, groups, scale, asym, 
     assert np.array_equal(gc, rc) and np.array_equal(gsc, rs)
 
 
+@pytest.mark.parametrize("scale,asym,gs", [(ref.FP8_E5M2, 1, 32), (ref.E8M0_FLOOR, 0, 32), (ref.FP8_E4M3, 0, 16), (ref.FP8_E5M2, 1, 64),
+                                           (ref.FP8_E5M2, 0, 128)])
+@pytest.mark.parametrize("rows,groups,batch", [(65, 1, 3), (129, 2, 2), (257, 1, 40), (130, 2, 300), (300, 5, 100), (128, 2, 600)])
+def test_strided_cast_of_a_short_k(rows, groups, batch, scale, asym, gs):
+    """Up to five groups: a workgroup takes 64, 128 or 256 rows of one group or of two (in groups of 64 also where the steps along K
+    are no whole lines); partial ones, exactly the oracle's bytes, nothing written behind them."""
+    K = gs * groups * (2 if gs == 16 else 1)
+    v = synth.activations(batch * K, rows, seed=rows + groups, n_outlier=2, outlier_gain=30.0)
+    rc, rs = ref.quantize(np.ascontiguousarray(v.reshape(batch, K, rows).transpose(0, 2, 1)).reshape(batch * rows, K), gs, scale, asym)
+    fmt = binding.make_format(scale, asym, gs)
+    c = torch.full((rc.size + 256,), 0xA5, dtype=torch.uint8, device="cuda")
+    s = torch.full((rs.size + 256,), 0xA5, dtype=torch.uint8, device="cuda")
+    pair = (2,) if asym else ()
+    binding.quantize_batched(fmt, G.to_dev_bf16(v).view(batch, K, rows), k_axis=1, codes=c[:rc.size].view(batch, rows, K // 2),
+                             scales=s[:rs.size].view(batch, rows, K // gs, *pair))
+    assert np.array_equal(c[:rc.size].cpu().numpy(), rc.ravel()) and np.array_equal(s[:rs.size].cpu().numpy(), rs.ravel())
+    assert (c[rc.size:] == 0xA5).all() and (s[rs.size:] == 0xA5).all()
+
+
+@pytest.mark.parametrize("gs", [16, 32, 64, 128])
+@pytest.mark.parametrize("scale,asym", FORMATS + [(ref.FP8_E4M3, 1), (ref.FP8_E4M3, 0)])
+def test_strided_cast_of_every_bf16_value(scale, asym, gs):
+    """Every BF16 pattern beside group maxima that give each scale mantissa, a tiny and a subnormal scale, and as the maximum itself:
+    the oracle's bytes for the finite ones, and for all of them, infinities and NaN too, those of the contiguous cast."""
+    bits = np.arange(0, 0x10000, dtype=np.uint32).astype(np.uint16)
+    groups = []
+    for amax in (6.0, 7.5, 9.0, 10.5, 0.046875, 3.0e-5, 1.0e-6, 1536.0, None):
+        n = -(-bits.size // (gs - 2))
+        x = np.zeros((n, gs), np.uint16)
+        x[:, 2:] = np.resize(bits, n * (gs - 2)).reshape(n, gs - 2)
+        if amax is not None:
+            top = synth.f32_to_bf16_bits(np.array([amax], np.float32))[0]
+            x[:, 2:][(x[:, 2:] & 0x7FFF) > top] = 0
+            x[:, 0], x[:, 1] = top, top | 0x8000
+        groups.append(x)
+    x = np.concatenate(groups)
+    x = x[:x.shape[0] // 2 * 2].reshape(-1, 2 * gs)  # (two groups to a row: whole 32s of every size)
+    fmt = binding.make_format(scale, asym, gs)
+    xd = G.to_dev_bf16(x)
+    c, s = binding.quantize(fmt, xd.T.contiguous(), k_axis=0)
+    rc, rs = binding.quantize(fmt, xd)
+    assert torch.equal(c, rc) and torch.equal(s, rs)
+    finite = ((x & 0x7F80) != 0x7F80).all(axis=1)
+    oc, os_ = ref.quantize(np.ascontiguousarray(x[finite]), gs, scale, asym)
+    keep = torch.from_numpy(finite).cuda()
+    assert np.array_equal(c[keep].cpu().numpy(), oc) and np.array_equal(s[keep].cpu().numpy(), os_)
+
+
 @pytest.mark.parametrize("scale,asym", [(ref.FP8_E5M2, 1), (ref.E8M0_FLOOR, 0)])
 def test_batched_cast_equals_the_oracle_per_operand(scale, asym):
     """Several operands in one launch (the heads of an attention layer): along the rows (Q, K), down the columns (V),

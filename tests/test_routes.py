@@ -58,6 +58,16 @@ def test_groups_to_a_workgroup_of_the_strided_cast(group, rows, groups, batch, l
     assert rule("_ZN3amx18strided_waves_log2Eilll", i32, i32, i64, i64, i64)(group, rows, groups, batch) == log2
 
 
+@pytest.mark.parametrize("groups_log2,rows,groups,batch,lines,log2", [
+    (0, 12086, 1, 32, 0, 2), (0, 752, 1, 512, 0, 2), (0, 128, 2, 1, 1, 1), (0, 64, 1, 512, 1, 0), (0, 334, 1, 1, 0, 2),  # 9.5 / 5.9 us, 8.4 / 5.2
+    (0, 2300, 8, 1, 0, 1), (0, 1782, 8, 1, 0, 0), (0, 128, 190, 1, 1, 0), (1, 8163, 2, 64, 0, 1), (1, 130, 2, 300, 0, 1),
+    (1, 128, 2, 300, 1, 0), (1, 128, 2, 512, 1, 1), (3, 4096, 256, 1, 1, 0)])
+def test_rows_to_a_workgroup_of_the_strided_cast(groups_log2, rows, groups, batch, lines, log2):
+    """Four waves to a workgroup where the groups are fewer, unless that leaves compute units idle (one wave / four)."""
+    rows_log2 = rule("_ZN3amx17strided_rows_log2Eilllb", i32, i32, i64, i64, i64, flag)
+    assert rows_log2(groups_log2, rows, groups, batch, bool(lines)) == log2
+
+
 @pytest.mark.parametrize("Hq,Hkv,Sq,D,tiles,splits,here", [
     (32, 8, 1, 128, 1, 4, 0), (8192, 1024, 1, 64, 1, 1, 0), (128, 16, 2, 128, 1, 64, 0),                  # one tile: 15.7 / 9.8 us, but 13.3 / 15.8
     (32, 8, 1, 64, 2, 63, 1), (32, 8, 1, 64, 2, 64, 0), (4096, 1024, 1, 64, 2, 16, 0), (32, 8, 1, 128, 2, 64, 1),   # two: 56.8 / 46.1
