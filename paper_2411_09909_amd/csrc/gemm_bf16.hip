@@ -544,7 +544,13 @@ int bf16_tile_choice(int64_t M, int64_t N, int64_t batch) {
 // 192 x 256 in more rounds than 256 x 256 takes (1148 x 25920 x 2432, gated, prepared, 120 / 140; 2071 x 13824 x 5120, gated,
 // 260 / 281), and instead of 64 x 256 with a K up to 1024 (1408 x 5632 x 1024, gated, 25.1 / 25.7), in a second round up to 2048
 // (1311 x 11072 x 1792, gated, 65 / 72; 574 x 24704 x 1792 82 / 87; a gated layer of 1312 tokens x 11264 x 2048 276 / 280). All shapes add the products of an output in the same order: their bits are the same.
-int bf16_tile_refined(int choice, int64_t M, int64_t N, int64_t K, int64_t batch, bool gated) {
+struct TileEstimates {
+  double us[8];
+  int64_t rounds[8];
+  bool ok[8];
+};
+
+static TileEstimates tile_estimates(int64_t M, int64_t N, int64_t K, bool gated) {
   struct Shape {
     int tile, rows, cols, rounds;    // at most so many rounds
     double lone, pair, grows, rate;  // ns per unit of K: one round, two; slower by this share on a full chip; TFLOP/s
@@ -553,25 +559,28 @@ int bf16_tile_refined(int choice, int64_t M, int64_t N, int64_t K, int64_t batch
       {1, 256, 256, 0, 14.4, 28.8, 0.30, 1500}, {2, 256, 128, 0, 7.6, 15.2, 0.23, 1330}, {3, 64, 256, 0, 6.1, 11.0, 0.23, 1080},
       {4, 192, 256, 3, 10.7, 21.4, 0.26, 1440}, {5, 192, 128, 1, 6.4, 12.5, 0.21, 1500}, {6, 128, 128, 1, 5.4, 9.0, 0.24, 1370},
       {7, 192, 192, 1, 8.2, 16.4, 0.25, 1530}};
-  if (batch != 1 || ((M + 255) / 256) * ((N + 255) / 256) > 3 * 256) return choice;
-  double us[8];
-  int64_t rounds[8];
-  bool ok[8] = {};
+  TileEstimates e = {};
   for (const Shape& s : kShapes) {
     const int tiles_m = (int)((M + s.rows - 1) / s.rows), tiles_n = (int)((N + s.cols - 1) / s.cols);
     const int64_t r = (largest_share(tiles_m, tiles_n, s.rows, s.cols) + 31) / 32, tiles = (int64_t)tiles_m * tiles_n;
     const double per = (double)(r / 2) * s.pair + (double)(r % 2) * s.lone;
     const double own = per * (1.0 + s.grows * (double)tiles / (256.0 * (double)r)) * 1e-3 * (double)K;
     const double full = (double)(tiles * s.rows * s.cols) * 2e-6 * (double)K / s.rate;
-    us[s.tile] = 7.0 + (own > full ? own : full) + 0.6 * 4.0 * (double)(M * N) / 5.1e6;
-    rounds[s.tile] = r;
-    ok[s.tile] = r <= s.rounds && !(gated && s.tile == 7) && !(s.tile == 6 && K < 2048);
+    e.us[s.tile] = 7.0 + (own > full ? own : full) + 0.6 * 4.0 * (double)(M * N) / 5.1e6;
+    e.rounds[s.tile] = r;
+    e.ok[s.tile] = r <= s.rounds && !(gated && s.tile == 7) && !(s.tile == 6 && K < 2048);
   }
-  if ((choice == 1 && rounds[4] > rounds[1]) || (choice == 3 && K <= (rounds[4] > 1 ? 2048 : 1024))) ok[4] = false;
+  return e;
+}
+
+int bf16_tile_refined(int choice, int64_t M, int64_t N, int64_t K, int64_t batch, bool gated) {
+  if (batch != 1 || ((M + 255) / 256) * ((N + 255) / 256) > 3 * 256) return choice;
+  TileEstimates e = tile_estimates(M, N, K, gated);
+  if ((choice == 1 && e.rounds[4] > e.rounds[1]) || (choice == 3 && K <= (e.rounds[4] > 1 ? 2048 : 1024))) e.ok[4] = false;
   int best = choice;
-  double limit = 0.97 * us[choice];
+  double limit = 0.97 * e.us[choice];
   for (int t = 4; t <= 7; ++t)
-    if (ok[t] && us[t] < limit) best = t, limit = us[t];
+    if (e.ok[t] && e.us[t] < limit) best = t, limit = e.us[t];
   return best;
 }
 
@@ -639,7 +648,13 @@ int64_t bf16_columns_at_a_time(int tile, int64_t M, int64_t N, int64_t K, int64_
   return N;
 }
 
-// Estimate of a call that expands both operands, us, up to some 800 rows: B's expansion at the copy rate, and the rounds
+// Estimate of the kernel on prepared weights that stay in the caches, us: the estimate above of the tile that it runs.
+double bf16_prepared_us(int64_t M, int64_t N, int64_t K) {
+  return tile_estimates(M, N, K, false).us[bf16_tile(M, N, K, 1, false, true, N % 32 == 0)];
+}
+
+// Estimate of a call that expands both operands, us, for up to some 800 rows (with what beats_panels() in gemm_stream.hip adds to it, up to
+// 1500): B's expansion at the copy rate, and the rounds
 // of tiles at the rate of a lone tile (256 x 256 14 ns per unit of K, 256 x 128 9.3, 64 x 256 6.6 to 8 as they fill the
 // chip) or the chip's, and half of the store of C, c_bytes per element of M x N. It prices the shape of bf16_tile_choice(), not
 // the one between those three that most of these sizes run on. Measured (the same buffers again and again, on that one) /

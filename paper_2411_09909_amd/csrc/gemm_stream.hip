@@ -30,7 +30,7 @@ static double stream_us(bool asym, int64_t group_size, int64_t M, int64_t N, int
 // caches, say the panels: the panels' tiles then wait for memory (a 4096 x 14336 product takes 155 us at 320 as at 768 rows,
 // and 30 more for the expansion), this kernel reads a quarter of the bytes. Measured on three sets of buffers in turn, 2945
 // sizes of 257 to 1700 rows, N 1000 to 33000, K 1024 to 28672; us on the panels / here / the panels with prepared weights:
-// E5M2 symmetric 768 x 8192 x 8192 149 / 99 / 106; asymmetric 149 / 135 / 105; NVFP4 320 x 8192 x 28672 466 / 167, 640 x
+// E5M2 symmetric 768 x 8192 x 8192 149 / 99 / 106; asymmetric 149 / 135 / 105, which therefore stays on the panels; NVFP4 320 x 8192 x 28672 466 / 167, 640 x
 // 28672 x 8192 461 / 311, 1024 x 8192 x 8192 178 / 136.
 // Up to 768 rows: a product on prepared weights goes where the plain one goes, and beyond 768 rows it reads nothing but the
 // prepared form. For the same reason the estimate here has to be 8 % below that of the panels without the expansion, 12 % up
@@ -39,6 +39,13 @@ static double stream_us(bool asym, int64_t group_size, int64_t M, int64_t N, int
 // Tensor-wise scales have no prepared form: their line is against the whole call, they come here up to 1500 rows, by 18 %
 // from 1025 on (at 8 %: 1343 x 6144 x 4096 71 / 81), and alone against 2^27 weight elements or more, there up to 1024 rows
 // (1500 x 28672 x 8192 645 / 770). Beyond 1500 rows the panels (1683 x 9184 x 28672 793 / 881).
+// Nor may weights that stay in the caches lose (3400 calls whose route these lines had moved, the same buffers again and again, us
+// before / here): no product without tensor-wise scales comes here whose estimate is above that of its prepared form on the tile that
+// it runs (symmetric, prepared, 548 x 11008 x 4096 51 / 61, 576 x 11296 x 6400 71 / 94, 525 x 17792 x 6144 94 / 131; of 56 such sizes the least 1.12
+// times, although the plain call gains a tenth there; of 154 that stay the slowest 1.03 times, 0.74 on average), and beyond 768 rows
+// the estimate has to be 7 % below that of the panels as they are in the caches (NVFP4 1344 x 4096 x 14336 163 / 176, 973 x 8192 x 8192
+// 139 / 148, 1138 x 5120 x 13824 167 / 178; from memory those gained 2 to 5 %). What is left: single sizes of a K that is no multiple of
+// 256 (NVFP4 953 x 8544 x 5888 102 / 117), and symmetric, prepared, 200 to 256 rows of such a K (206 x 24128 x 9888 158 / 169, plain half).
 static bool beats_panels(bool asym, int64_t group_size, bool scaled, int64_t M, int64_t N, int64_t K) {
   if (M <= 256 || M > (scaled ? 1500 : 768) || K < 1024) return false;
   if (N * K >= (int64_t(1) << 27) && (!scaled || M > 1024)) return false;
@@ -51,9 +58,9 @@ static bool beats_panels(bool asym, int64_t group_size, bool scaled, int64_t M, 
   }
   // (the estimate of the panels is of weights in the caches too; from K 4608 on it falls short, by a quarter from 13824 on)
   const double cold = K <= 4608 ? 1.0 : K >= 13824 ? 1.25 : 1.0 + 0.25 * (k - 4608.0) / 9216.0;
-  const double expansion = scaled ? 0.0 : 0.51e-6 * (double)(N * K);
+  const double expansion = scaled ? 0.0 : 0.51e-6 * (double)(N * K), panels = bf16_path_us(M, N, K, 4.0) - expansion;
   const double margin = K % kStreamBlockK != 0 ? 0.75 : M > 1024 ? 0.82 : K < 2048 ? 0.85 : K <= 4096 ? 0.88 : 0.92;
-  return here <= margin * cold * (bf16_path_us(M, N, K, 4.0) - expansion);
+  return here <= margin * cold * panels && (scaled ? M <= 768 || here <= 0.93 * panels : here <= bf16_prepared_us(M, N, K));
 }
 
 // Symmetric power-of-two scales of 32-groups, more than 64 rows: whether the FP4 kernel is the fastest of the three that

@@ -64,6 +64,7 @@ hipError_t launch_gemm_bf16_path(int scale_kind, bool asym, int64_t group_size, 
 // B's panel alone, expanded once for weights that stay (bf16_panel_bytes(N, K) bytes); passed as B_panel above, the
 // call then expands only A and its workspace is bf16_panel_bytes(M, K) per batch entry.
 size_t bf16_panel_bytes(int64_t rows, int64_t K);
+double bf16_prepared_us(int64_t M, int64_t N, int64_t K);  // of the kernel alone, on the tile that it runs
 double bf16_path_us(int64_t M, int64_t N, int64_t K, double c_bytes);  // estimate of the call, both operands expanded
 hipError_t launch_expand_b_panel(int scale_kind, bool asym, int64_t group_size, int64_t N, int64_t K,
                                  const uint8_t* B_codes, const uint8_t* B_scales, void* panel, hipStream_t s);

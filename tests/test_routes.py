@@ -188,6 +188,15 @@ def test_routes_of_weights_that_come_from_memory(scale, asym, group, scaled, M, 
     assert one_launch(scale, asym, M, N, K, 1, group, bool(scaled)) == bool(here)
 
 
+@pytest.mark.parametrize("scale,asym,group,scaled,M,N,K,here", [
+    (E5, 0, 32, 0, 548, 11008, 4096, 0), (E5, 0, 32, 0, 576, 11296, 6400, 0), (E5, 0, 32, 0, 525, 17792, 6144, 0),  # prepared 51 / 61, 71 / 94, 94 / 131
+    (E4, 0, 16, 1, 1344, 4096, 14336, 0), (E4, 0, 16, 1, 973, 8192, 8192, 0), (E4, 0, 16, 1, 1138, 5120, 13824, 0),  # 161 / 171, 139 / 148, 167 / 178
+    (E5, 0, 32, 0, 548, 4096, 4096, 1), (E5, 0, 32, 0, 700, 8192, 8192, 1), (E4, 0, 16, 1, 901, 4096, 4096, 1), (E4, 0, 16, 1, 1200, 1024, 14336, 1)])
+def test_routes_of_weights_that_stay_in_the_caches(scale, asym, group, scaled, M, N, K, here):
+    """us on the panels / on this kernel, the same buffers again and again."""
+    assert one_launch(scale, asym, M, N, K, 1, group, bool(scaled)) == bool(here)
+
+
 @pytest.mark.parametrize("scale,asym,M,N,K,here", [(E5, 1, 256, 28672, 8192, 1), (E5, 1, 257, 28672, 8192, 0),
                                                    (FLOOR, 1, 256, 22016, 4096, 0), (FLOOR, 1, 128, 22016, 4096, 1),
                                                    (FLOOR, 0, 800, 11008, 1024, 0)])
