@@ -8,15 +8,17 @@
 //     product need nothing of the other tiles; then the waves exchange the tiles' maxima through LDS, and each knows the running
 //     maximum that its tile's probabilities are cast against. Each wave accumulates its tiles' share of the output against its own last
 //     maximum; the shares are added at the end, times 2^(m_wave - m_range), as ranges are;
-//   - products are 16 x 16 x 32: half the scores, exponentials and casts per tile, half the accumulators (32), so four waves per SIMD
-//     (125 to 128 registers; as four waves with 32 columns, or with two rounds' requests in flight, they spill or gain nothing);
+//   - products are 16 x 16 x 32: half the scores, exponentials and casts per tile, half the accumulators (32 with heads of 128), so four
+//     waves per SIMD (121 to 128 registers with heads of 128, 85 to 89 with heads of 64; as four waves with 32 columns, or with two rounds'
+//     requests in flight, they spill or gain nothing);
 //   - V of a round goes through registers into LDS (two buffers, one barrier a round); V and K of the next round are requested before
 //     this round's second product;
 //   - neighbouring ranges run on one XCD.
-// The whole call (this kernel and the combination), us, the other kernel / this one, cache in codes, 32 / 8 heads of 128, three caches in
-// turn: AMXFP4 4 sequences x 8192 keys 23.0 / 16.5, 1 x 8192 16.2 / 11.3, 16 x 8192 61 / 46 (3.3 TB/s), 1 x 16384 22.0 / 14.5;
-// OCP MXFP4 16 x 8192 46 / 38; 32 / 32 heads of 64, 9 x 2048 25.6 / 21.0. With two waves to a range: 24.3, 14.0, 81; with eight: 18.1,
-// 12.4, 52. Ranges dealt to the XCDs in turn: 19.4, 12.8, 48 (an eighth of each line of V's scale bytes used per fetch).
+// The whole call (this kernel and the combination), us, before this kernel and the combination by four waves / now, cache in codes, 32 / 8
+// heads of 128, three caches in turn: AMXFP4 4 sequences x 8192 keys 23.1 / 15.8, 1 x 8192 16.3 / 8.5, 16 x 8192
+// 61 / 45 (3.3 TB/s), 1 x 16384 22.3 / 11.8; OCP MXFP4 16 x 8192 47 / 38; 32 / 32 heads of 64, 9 x 2048 25.8 / 20.6. Of these, with the
+// combination by one wave: 16.5, 11.3, 46, 14.5, 38, 21.0; and so with two waves to a range: 24.3, 14.0, 81; with eight: 18.1, 12.4, 52;
+// ranges dealt to the XCDs in turn: 19.4, 12.8, 48 (an eighth of each line of V's scale bytes used per fetch).
 //
 // Layouts in registers. First product, S^T[key, query] = K_tile . Q^T: lane l of the A operand holds row l % 16 and 8 head dimensions
 // of quarter l / 16; k-step s multiplies word s of the quarter's D / 4 contiguous dimensions, for K and Q alike. Row i of block kb
@@ -351,10 +353,12 @@ static hipError_t launch_16(int per, int64_t Hkv, int64_t Sq, int64_t Sk, const 
         return go.template operator()<W, T, false>();
     return go.template operator()<W, T, true>();
   };
-  // Two tiles to a wave and round (whole lines of V, but no request in flight during the second product) where heads of 128 stream
-  // more keys and values than the last-level cache keeps between uses: 16 x 8192 keys 48.9 / 45.9 us, OCP MXFP4 43.2 / 38.5, 16 x
-  // 16384 88.7 / 83.3 (one tile / two); 4 x 8192 (ranges of 8 tiles) 16.5 / 16.6, 9 x 2048 with 32 / 32 heads (of 4) 30.4 / 37.7, heads of
-  // 64, 5 x 16352 21.8 / 23.9.
+  // Two tiles to a wave and round (whole lines of V, but no request in flight during the second product): heads of 128 from 2^20 keys of all
+  // heads on (136 to 144 MB), in ranges of 16 tiles and more, for keys and values that come from memory. Two tiles / one, 2163 sizes, three
+  // caches in turn, symmetric scales: 1.07 to 1.09 at 2^19 keys, 1.00 at 2^19.5, 0.97 at 2^20, 0.95 from 2^21 on (OCP MXFP4 16 x 8192 keys, 8
+  // heads, 38.2 / 42.1 us); asymmetric ones, whose dequantization takes longer: 1.07, 1.04, 1.03 (but 16 x 8192 45.4 / 47.4),
+  // 1.00. The same cache again and again, which up to 256 MB need not come from memory, 1.06 to 1.09 at 2^20, 1.00 beyond 2^21. Shorter ranges
+  // 1.05 to 1.00 up to 2^20. Heads of 64, 5 x 16352 keys, one tile 21.8, two 23.9 us.
   if constexpr (D == 128)
     if (tiles_per_split >= 16 && Hkv * Sk >= (int64_t(1) << 20)) return wide_or_not.template operator()<4, 2>();
   return wide_or_not.template operator()<4, 1>();
