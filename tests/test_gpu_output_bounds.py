@@ -199,6 +199,38 @@ def test_store_policies_same_bits_and_only_the_window(M, N, fmt_args):
     assert torch.isfinite(base.view(torch.float32)).all()
 
 
+@pytest.mark.parametrize("M,N,K,batch,scaled,fmt_args", [
+    (300, 1057, 4352, 1, False, (ref.E8M0_FLOOR, False, 32)), (300, 1057, 4352, 1, False, (ref.FP8_E5M2, True, 32)),  # a deep K: streaming
+    (300, 1057, 4352, 1, False, (ref.E8M0_FLOOR, True, 32)),
+    (300, 1057, 256, 3, False, (ref.E8M0_FLOOR, False, 32)), (300, 1057, 256, 3, False, (ref.FP8_E5M2, True, 32)),
+    (300, 1057, 256, 3, False, (ref.E8M0_FLOOR, True, 32)),
+    (1501, 1057, 256, 1, True, (ref.FP8_E4M3, False, 16)), (1501, 1057, 4352, 1, True, (ref.FP8_E4M3, True, 16))])
+def test_store_policies_of_a_deep_k_a_batch_and_tensor_scales(M, N, K, batch, scaled, fmt_args):
+    """Whole lines, half lines, neither, and rows at a pitch of 8192 elements (stored column by column): the same bits, only the window."""
+    fmt = binding.make_format(*fmt_args)
+    gen = torch.Generator(device="cuda").manual_seed(K + batch)
+    x, w = (torch.randn((batch, r, K), generator=gen, device="cuda").to(torch.bfloat16) for r in (M, N))
+    if scaled:
+        pairs = [binding.tensor_scale(t[0]) for t in (x, w)]
+        ops = [u for t, p in zip((x, w), pairs) for u in binding.quantize(fmt, t[0], tensor_pair=p)]
+        how = {"a_pair": pairs[0], "b_pair": pairs[1]}
+    else:
+        ops = [u if batch > 1 else u[0] for t in (x, w) for u in binding.quantize_batched(fmt, t)]
+        how = {"options": binding.gemm_options(few_rows=-1)}  # (the tiled kernels)
+    base = None
+    for pitch, shift in [(1088, 0), (1072, 0), (N, 0), (1088, 3), (8192, 0), (8192, 16)]:
+        buf = torch.full((GUARD + shift + batch * M * pitch + GUARD,), CANARY, dtype=torch.int32, device="cuda")
+        body = buf[GUARD + shift:GUARD + shift + batch * M * pitch].view(batch, M, pitch)
+        out = body.view(torch.float32)[:, :, :N]
+        binding.gemm(fmt, *ops, out=out if batch > 1 else out[0], **how)
+        got = body[:, :, :N].clone()
+        base = got if base is None else base
+        assert torch.equal(got, base), (pitch, shift)
+        body[:, :, :N] = CANARY
+        assert bool((buf == CANARY).all()), (pitch, shift)
+    assert torch.isfinite(base.view(torch.float32)).all()
+
+
 @pytest.mark.parametrize("M", [1, 16, 19, 32])
 def test_48_columns_to_a_workgroup_write_only_their_window(M):
     """(9001 columns: the last workgroup has 25)"""

@@ -91,9 +91,10 @@ def test_fp4_kernel_for_few_rows_against_large_weights():
     assert binding.gemm_workspace_bytes(fmt, M, N, K) >= binding.gemm_workspace_bytes(fmt, M, N, K, options=few)
 
 
-@pytest.mark.parametrize("M,N,K,asym", [(1, 300, 1024, 0), (24, 4100, 512, 1), (64, 130, 4512, 0), (200, 300, 1056, 1)])
+@pytest.mark.parametrize("M,N,K,asym", [(1, 300, 1024, 0), (24, 4100, 512, 1), (64, 130, 4512, 0), (200, 300, 1056, 1), (1000, 1000, 1024, 0),
+                                        (1100, 520, 2048, 1), (1400, 1001, 1024, 0)])
 def test_tensor_scaled(M, N, K, asym):
-    """Double scaling on the few-rows shapes: the product of the dequantized operands times the two tensor-wise scales."""
+    """Double scaling on the few-rows shapes, and of the many rows that come here with it alone: the product of the dequantized operands times the two tensor-wise scales."""
     fmt = binding.make_format(ref.FP8_E4M3, asym, 16)
     x = G.to_dev_bf16(synth.activations(M, K, seed=M, n_outlier=1, outlier_gain=60.0))
     w = G.to_dev_bf16(synth.weights(N, K, seed=N))
@@ -148,7 +149,7 @@ def test_48_columns_to_a_workgroup(M, N, K, scale, asym, gs):
 
 
 @pytest.mark.parametrize("scale,asym,gs", FORMATS)
-@pytest.mark.parametrize("N,K", [(17, 32), (300, 544), (4100, 2304), (8200, 256), (8193, 2272), (11008, 512), (16400, 288)])
+@pytest.mark.parametrize("N,K", [(17, 32), (300, 544), (4100, 2304), (8200, 256), (8193, 2272), (11008, 512), (16400, 288), (320, 544), (64, 2272)])
 def test_one_to_four_rows_same_bits_as_more(N, K, scale, asym, gs):
     """Up to four rows the lanes share out A's rows; from five rows on each dequantizes its own. The same values in the same order: the
     rows of a product of nine rows, bit for bit, for random codes and scale bytes (the sign bit of an FP8 one among them, which is
@@ -171,3 +172,15 @@ def test_one_to_four_rows_same_bits_as_more(N, K, scale, asym, gs):
         glu = [binding.gemm_silu_mul(fmt, ac[:m].contiguous(), as_[:m].contiguous(), bc, bs) for m in (1, 4, 9)]
         for g in glu:
             assert torch.equal(g.view(torch.int16), glu[2][:g.shape[0]].view(torch.int16))
+
+
+@pytest.mark.parametrize("scale,asym,gs", [(ref.FP8_E5M2, 1, 32), (ref.E8M0_FLOOR, 0, 32), (ref.FP8_E4M3, 0, 16)])
+@pytest.mark.parametrize("M", [1, 4, 5])
+@pytest.mark.parametrize("N,K", [(300, 544), (4100, 512)])
+def test_a_batch_of_few_rows_same_bits_as_single_products(M, N, K, scale, asym, gs):
+    fmt, gen = binding.make_format(scale, asym, gs), torch.Generator(device="cuda").manual_seed(M + N)
+    a, b = (binding.quantize_batched(fmt, torch.randn((3, r, K), generator=gen, device="cuda").to(torch.bfloat16)) for r in (M, N))
+    C = binding.gemm(fmt, *a, *b)
+    for i in range(3):
+        one = binding.gemm(fmt, *(t[i].clone() for t in a + b))  # (a slice of its own alignment would be refused)
+        assert torch.equal(C[i].view(torch.int32), one.view(torch.int32))
