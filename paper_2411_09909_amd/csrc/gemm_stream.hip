@@ -44,8 +44,9 @@ static double stream_us(bool asym, int64_t group_size, int64_t M, int64_t N, int
 // it runs (symmetric, prepared, 548 x 11008 x 4096 51 / 61, 576 x 11296 x 6400 71 / 94, 525 x 17792 x 6144 94 / 131; of 56 such sizes the least 1.12
 // times, although the plain call gains a tenth there; of 154 that stay the slowest 1.03 times, 0.74 on average), and beyond 768 rows
 // the estimate has to be 7 % below that of the panels as they are in the caches (NVFP4 1344 x 4096 x 14336 163 / 176, 973 x 8192 x 8192
-// 139 / 148, 1138 x 5120 x 13824 167 / 178; from memory those gained 2 to 5 %). What is left: single sizes of a K that is no multiple of
-// 256 (NVFP4 953 x 8544 x 5888 102 / 117), and symmetric, prepared, 200 to 256 rows of such a K (206 x 24128 x 9888 158 / 169, plain half).
+// 139 / 148, 1138 x 5120 x 13824 167 / 178; from memory those gained 2 to 5 %). What is left, of 4530: single sizes
+// (NVFP4 953 x 8544 x 5888 102 / 117), and below 257 rows, where this rule has no say, symmetric, prepared, 200 rows and more of a K
+// that is no multiple of 256 (206 x 24128 x 9888 158 / 169; the plain call takes half the time there).
 static bool beats_panels(bool asym, int64_t group_size, bool scaled, int64_t M, int64_t N, int64_t K) {
   if (M <= 256 || M > (scaled ? 1500 : 768) || K < 1024) return false;
   if (N * K >= (int64_t(1) << 27) && (!scaled || M > 1024)) return false;
