@@ -531,8 +531,7 @@ int strided_waves_log2(int group_size, int64_t rows, int64_t groups, int64_t bat
 // neighbouring waves of rows then share the lines between them (which two groups of 64 and twice the rows are the better for than four
 // groups). us, one wave of rows / this: 32 heads of 12086 x 32 9.5 / 5.4, 512 of 752 x 32 8.4 / 5.1; groups of 64, 512 heads of 227 x
 // 512 43.1 / 35.8, 53557 x 1024 37.7 / 33.7; but whole lines and few workgroups (at least 128 / 512 of them): groups of 128, 128 x 81920
-// 8.3 / 6.5, NVFP4 128 x 3040 2.5 / 2.2. What lies on neither side: steps that are no whole lines in groups of 128 (512 heads of 218 x 384
-// 29.2, where workgroups of 256 rows of a group took 22.2), and few rows of it (64 of 18 x 1536 5.8, 4.7).
+// 8.3 / 6.5, NVFP4 128 x 3040 2.5 / 2.2.
 int strided_rows_log2(int groups_log2, int64_t rows, int64_t groups, int64_t batch, bool whole_lines) {
   int rl = groups_log2 < 2 ? 2 - groups_log2 : 0;
   while (rl > 0 && rows <= (32 << rl)) --rl;
@@ -540,6 +539,17 @@ int strided_rows_log2(int groups_log2, int64_t rows, int64_t groups, int64_t bat
   const int64_t least = whole_lines ? 512 : 128;
   while (rl > 0 && ((rows + (64 << rl) - 1) >> (6 + rl)) * ((groups + (1 << groups_log2) - 1) >> groups_log2) * batch < least) --rl;
   return rl;
+}
+
+// Whether groups of 128 whose steps along K are no whole lines go one to a workgroup, with up to four times 64 rows, where two would fit:
+// few rows then share the lines of a step between fewer workgroups. Time over that of two groups and 64 rows, 300 calls of 20000 to 6
+// 10^7 elements: up to 64 rows 0.69 to 0.99 (1.1 for a few of under 400 workgroups), 129 to 256 rows 0.73 to 1.08, 0.90 on average; more
+// rows 0.96 below 768 workgroups of two groups, 0.94 to 1.27 from there on; 65 to 128 rows, two blocks of 64 either way, 0.94 to 1.23.
+// us, workgroups of 256 rows of a group / two groups / this: 64 heads of 18 x 1536 7.2 / 8.3 / 5.7, 16 of 161 x 3200 11.4 / 11.3 / 9.5, 8964
+// x 896 9.5 / 10.6 / 8.3 (asymmetric). Against workgroups of 256 rows the 300 are 0.85 on average, 19 slower by more than 3 %, by 9 % at most (16
+// heads of 396 x 7552 32.4 / 35.1, symmetric); with two groups always 0.89, 49, 21 %.
+bool strided_one_wide_group(int64_t rows, int64_t groups, int64_t batch) {
+  return rows <= 64 || (rows > 128 && (rows <= 256 || (rows + 63) / 64 * ((groups + 1) / 2) * batch < 768));
 }
 
 template <int SK, bool ASYM, int GS>
@@ -550,6 +560,7 @@ static hipError_t launch_qs(const uint16_t* x, int64_t rows, int64_t K, int64_t 
   const bool whole_lines = k_stride % 64 == 0;  // (of the elements that a step along K is)
   int wl = strided_waves_log2(GS, rows, G, batch), rl = strided_rows_log2(wl, rows, G, batch, whole_lines);
   if (GS == 64 && wl == 2 && !whole_lines && strided_rows_log2(1, rows, G, batch, false) == 1) wl = 1, rl = 1;
+  if (GS == 128 && wl == 1 && !whole_lines && strided_one_wide_group(rows, G, batch)) wl = 0, rl = strided_rows_log2(0, rows, G, batch, false);
   const dim3 grid((unsigned)((rows + (64 << rl) - 1) >> (6 + rl)), (unsigned)((G + (1 << wl) - 1) >> wl), (unsigned)batch);
   if (tensor_pair)
     hipLaunchKernelGGL((quantize_strided_kernel<SK, ASYM, true, GS>), grid, dim3(64 << (wl + rl)), 0, s, x, rows, K, k_stride,

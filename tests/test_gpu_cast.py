@@ -126,10 +126,11 @@ def test_strided_cast_at_the_edges_of_its_workgroups(rows, groups, scale, asym, 
 
 @pytest.mark.parametrize("scale,asym,gs", [(ref.FP8_E5M2, 1, 32), (ref.E8M0_FLOOR, 0, 32), (ref.FP8_E4M3, 0, 16), (ref.FP8_E5M2, 1, 64),
                                            (ref.FP8_E5M2, 0, 128)])
-@pytest.mark.parametrize("rows,groups,batch", [(65, 1, 3), (129, 2, 2), (257, 1, 40), (130, 2, 300), (300, 5, 100), (128, 2, 600)])
+@pytest.mark.parametrize("rows,groups,batch", [(65, 1, 3), (129, 2, 2), (257, 1, 40), (130, 2, 300), (300, 5, 100), (128, 2, 600),
+                                                (18, 12, 64), (161, 25, 16), (2003, 7, 3)])
 def test_strided_cast_of_a_short_k(rows, groups, batch, scale, asym, gs):
     """Up to five groups: a workgroup takes 64, 128 or 256 rows of one group or of two (in groups of 64 also where the steps along K
-    are no whole lines); partial ones, exactly the oracle's bytes, nothing written behind them."""
+    are no whole lines, and there any number of groups of 128); partial ones, exactly the oracle's bytes, nothing written behind them."""
     K = gs * groups * (2 if gs == 16 else 1)
     v = synth.activations(batch * K, rows, seed=rows + groups, n_outlier=2, outlier_gain=30.0)
     rc, rs = ref.quantize(np.ascontiguousarray(v.reshape(batch, K, rows).transpose(0, 2, 1)).reshape(batch * rows, K), gs, scale, asym)

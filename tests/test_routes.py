@@ -68,6 +68,14 @@ def test_rows_to_a_workgroup_of_the_strided_cast(groups_log2, rows, groups, batc
     assert rows_log2(groups_log2, rows, groups, batch, bool(lines)) == log2
 
 
+@pytest.mark.parametrize("rows,groups,batch,one", [
+    (18, 12, 64, 1), (64, 3, 512, 1), (65, 12, 64, 0), (128, 32, 32, 0), (129, 24, 32, 1), (256, 3, 512, 1),  # 8.3 / 5.7 us; 7.1 / 8.6; 15.8 / 13.8
+    (257, 3, 70, 1), (257, 3, 77, 0), (8964, 7, 1, 1), (14169, 28, 1, 0)])                                    # 10.6 / 8.3; 35 / 38
+def test_wide_groups_of_the_strided_cast(rows, groups, batch, one):
+    """Steps along K that are no whole lines, groups of 128: two of them to a workgroup / one, of up to 256 rows."""
+    assert rule("_ZN3amx22strided_one_wide_groupElll", flag, i64, i64, i64)(rows, groups, batch) == bool(one)
+
+
 @pytest.mark.parametrize("Hq,Hkv,Sq,D,tiles,splits,here", [
     (32, 8, 1, 128, 1, 4, 0), (8192, 1024, 1, 64, 1, 1, 0), (128, 16, 2, 128, 1, 64, 0),                  # one tile: 15.7 / 9.8 us, but 13.3 / 15.8
     (32, 8, 1, 64, 2, 63, 1), (32, 8, 1, 64, 2, 64, 0), (4096, 1024, 1, 64, 2, 16, 0), (32, 8, 1, 128, 2, 64, 1),   # two: 56.8 / 46.1
